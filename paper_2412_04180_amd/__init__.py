@@ -25,7 +25,7 @@ EXPORTS = ["skim_create", "skim_destroy", "skim_last_error", "skim_workspace_byt
            "skim_profile_enable", "skim_profile_last", "skim_validate_enable",
            "skim_error_table", "skim_error_table_lfull", "skim_cluster_rows", "skim_select_allocated", "skim_greedy_allocate", "skim_greedy_allocate_device",
            "skim_dp_allocate_scratch_bytes", "skim_dp_allocate", "skim_kmeans_optimal_scratch_bytes", "skim_kmeans_optimal",
-           "skim_packed_words", "skim_codebook_entries", "skim_pack", "skim_pack_static", "skim_layer_loss", "skim_scale_step", "skim_train_scale", "skim_unpack", "skim_dequant_matvec", "skim_dequant_matvec_f32", "skim_hessian_from_activations"]
+           "skim_packed_words", "skim_codebook_entries", "skim_pack", "skim_pack_static", "skim_layer_loss", "skim_scale_step", "skim_train_scale", "skim_unpack", "skim_dequant_matvec", "skim_dequant_matvec_f32", "skim_hessian_workspace_bytes", "skim_hessian_from_activations"]
 
 
 class SkimError(RuntimeError):
@@ -85,6 +85,8 @@ def load_library():
         lib.skim_pack_static.argtypes = [vp, vp, vp, i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, vp]
         lib.skim_layer_loss.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, vp, vp, vp]
         lib.skim_scale_step.argtypes = [vp, vp, vp, vp, i64, i64, i64, vp, vp, vp, vp, i64, C.POINTER(AdamOpts), vp, vp]
+        lib.skim_hessian_workspace_bytes.argtypes = [vp, i64, i64]
+        lib.skim_hessian_workspace_bytes.restype = C.c_size_t
         lib.skim_hessian_from_activations.argtypes = [vp, vp, i64, i64, vp]
         lib.skim_unpack.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp]
         lib.skim_dequant_matvec.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp, vp]
@@ -167,7 +169,9 @@ class Context:
         return int(self.lib.skim_workspace_bytes(n, m))
 
     def ensure_workspace(self, n, m):
-        need = self.workspace_bytes(n, m)
+        self._ensure_bytes(self.workspace_bytes(n, m))
+
+    def _ensure_bytes(self, need):
         if self._ws is None or self._ws.numel() < need:
             # allocated on the context's stream: torch's allocator then ties the lifetime of the old block to
             # the work already queued on that stream
@@ -361,6 +365,7 @@ class Context:
         N, m = X_bf16.shape
         assert X_bf16.is_contiguous() and X_bf16.element_size() == 2
         H = out if out is not None else self.empty((m, m), self.torch.float32)
+        self._ensure_bytes(int(self.lib.skim_hessian_workspace_bytes(self.h, N, m)))
         self._check(self.lib.skim_hessian_from_activations(self.h, _dp(X_bf16), N, m, _dp(H)))
         return H
 
