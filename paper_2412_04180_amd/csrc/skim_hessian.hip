@@ -13,7 +13,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v lds_short4v;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
@@ -21,7 +20,9 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 constexpr int XT = 256;                    // output tile (rows and columns of H = columns of X)
 constexpr int XK = 32;                     // activations per stage
 constexpr int X_BUFS = 4;                  // stages in LDS: one in use, three on their way
-constexpr int X_THREADS = 512;
+constexpr int X_WAVES = 8, X_WC = X_WAVES / 2, X_BY = 8 / X_WC;   // wavefronts: 2 x X_WC, each 4 x X_BY blocks of 32 x 32
+constexpr int X_THREADS = 64 * X_WAVES;
+constexpr int X_LOADS = (XK * XT * 4) / (1024 * X_WAVES);   // 1 KB loads of a wavefront per stage
 constexpr int X_PANEL_BYTES = XK * XT * 2; // one operand panel of a stage, activation-major: 16 KB
 constexpr int X_STAGE_BYTES = 2 * X_PANEL_BYTES;
 constexpr size_t X_LDS_BYTES = (size_t)X_BUFS * X_STAGE_BYTES;
@@ -72,13 +73,21 @@ __device__ __forceinline__ bf16x8 operand(uint32_t addr, int off) {
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// 8 wavefronts, two per SIMD, of 128 x 64 each (12 operand reads for 8 MFMAs; 4 wavefronts of 128 x 128 would read a
+// third less, but their 256 accumulators and two operand sets spill: 4.3 ms).  Four stages of 32 activations in LDS (128
+// KB): the loads of stage s + 4 go out as soon as everybody has read stage s, i.e. three and a half stages ahead; the
+// operands of the next half stage are read between the MFMAs of this one, so the barrier in the middle costs little.
+// Bound: the power the matrix cores draw.  131072 x 4096 (1.18 PFLOP/s executed): MFMAs busy 76 % of the cycles, at 1.4 GHz
+// instead of 2.4; no bank conflicts; 4.3 GB read past L2 of 1.07 GB.  1.90 ms; with one workgroup per tile on 136 of the
+// 256 CUs, X staged through registers and transposed there: 3.60.  16384 x 2048: 85 us, of which the partial tiles (66 MB
+// written, read again by xtx_finish_kernel) take about 30; the 128 x 128 full-product kernel this replaces: 485.
 // DIRECT: the partial sums are added up in H itself (every tile is one workgroup's), not in slots.
 template <bool DIRECT>
-__global__ void __launch_bounds__(X_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(X_THREADS) __attribute__((amdgpu_waves_per_eu(X_WAVES / 4, X_WAVES / 4)))
 xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *H, int nt, XtxPlan plan, float4 *slots) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 2, wc = wave & 3;
+    const int wr = wave / X_WC, wc = wave % X_WC;
     const int l32 = lane & 31, lhi = lane >> 5;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem;
     const int swave = __builtin_amdgcn_readfirstlane(wave);
@@ -87,15 +96,15 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
     // bytes of either), straight from memory into LDS.  LDS row of an activation: its 256 values in 16-byte units,
     // unit u of the panel at place u ^ 4 (activation % 4): the transposing reads below take four activations
     // at once, which would share their banks otherwise.
-    const int srow = 8 * (wave & 3) + lhi;
-    uint32_t voff_row[4];
-    int unit[4];
+    const int srow = 2 * X_LOADS * (wave % X_WC) + lhi;
+    uint32_t voff_row[X_LOADS];
+    int unit[X_LOADS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < X_LOADS; ++i) {
         unit[i] = l32 ^ (((2 * i + lhi) & 3) << 2);
         voff_row[i] = (uint32_t)((long long)(srow + 2 * i) * m * 2);
     }
-    const uint32_t stage_dst = lds0 + (uint32_t)((swave >> 2) * X_PANEL_BYTES + (swave & 3) * 8 * 2 * XT);
+    const uint32_t stage_dst = lds0 + (uint32_t)((swave / X_WC) * X_PANEL_BYTES + (swave % X_WC) * 2 * X_LOADS * 2 * XT);
 
     // Operand reads (ds_read_b64_tr_b16): 16 lanes read 4 activations x 16 columns, 8 bytes each, and get 4
     // activations of one column each.  A lane's operand is column lane % 32 of a 32-column block, 8 activations.
@@ -105,11 +114,11 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
         const int u = (4 * (block ^ (i16 >> 2))) + 2 * (g & 1) + ((i16 & 3) >> 1);
         return (uint32_t)(rrow * 2 * XT + u * 16 + (i16 & 1) * 8);
     };
-    uint32_t ra[4], rb[2];
+    uint32_t ra[4], rb[X_BY];
 #pragma unroll
     for (int x = 0; x < 4; ++x) ra[x] = lds0 + read_addr(4 * wr + x);
 #pragma unroll
-    for (int y = 0; y < 2; ++y) rb[y] = lds0 + X_PANEL_BYTES + read_addr(2 * wc + y);
+    for (int y = 0; y < X_BY; ++y) rb[y] = lds0 + X_PANEL_BYTES + read_addr(X_BY * wc + y);
 
     const double inv = 1.0 / (double)N;
     const int nstage = (int)((N + XK - 1) / XK);
@@ -128,91 +137,118 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
             tile_of(plan.tile0[p] + t, nt, bi, bj);
             const int s0 = (int)((long long)nstage * part / split), s1 = (int)((long long)nstage * (part + 1) / split);
             const long long i0 = (long long)bi * XT, j0 = (long long)bj * XT;
-            const long long sc0 = swave >= 4 ? j0 : i0;
-            uint32_t voff[4];
+            const long long sc0 = swave >= X_WC ? j0 : i0;
+            uint32_t voff[X_LOADS];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < X_LOADS; ++i) {
                 // a column group past the matrix reads zeros (out of the buffer's range); one that the matrix ends in
                 // reads on into the next row: those columns only reach entries that are never stored
                 const long long c = sc0 + 8 * unit[i];
                 voff[i] = c < m ? voff_row[i] + (uint32_t)(c * 2) : 0x80000000u;
             }
+            // the stage that is requested next: its first activation, and the bytes from there to the end of the part (a stage
+            // past it is requested like any other, to keep the count of loads in flight, but reads nothing: zeros arrive)
+            const uint64_t stage_bytes = (uint64_t)XK * (uint64_t)m * 2;
+            uint64_t base = (uint64_t)(uintptr_t)X + (uint64_t)s0 * stage_bytes;
+            long long left = min(N, (long long)s1 * XK) * m * 2 - (long long)((uint64_t)s0 * stage_bytes);
             auto issue = [&](int st) {
-                const long long k0 = (long long)st * XK;
-                const long long left = (N - k0) * m * 2;
-                const uint64_t base = (uint64_t)(uintptr_t)(X + (k0 < N ? k0 : 0) * m);
                 int4v rs;
                 rs.x = (int)(uint32_t)base;
                 rs.y = (int)((uint32_t)(base >> 32) & 0xFFFFu);
-                rs.z = (int)(left <= 0 ? 0ll : (left < 0x7FFFFFFFll ? left : 0x7FFFFFFFll));
+                rs.z = (int)max(min(left, 0x7FFFFFFFll), 0ll);
                 rs.w = 0x00020000;
                 const uint32_t dst = stage_dst + (uint32_t)(st & (X_BUFS - 1)) * X_STAGE_BYTES;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < X_LOADS; ++i)
                     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst + i * 2 * 2 * XT),
                                  "v"(voff[i]), "s"(rs)
                                  : "memory", "m0");
+                base += stage_bytes;
+                left -= (long long)stage_bytes;
             };
-            floatx16 acc[4][2];
+            floatx16 acc[4][X_BY];
 #pragma unroll
             for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int y = 0; y < 2; ++y)
+                for (int y = 0; y < X_BY; ++y)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the piece before is done with the LDS
-            issue(s0);
-            issue(s0 + 1);
-            issue(s0 + 2);
+            // (the piece before is done with the LDS)
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < X_BUFS; ++i) issue(s0 + i);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * X_LOADS) : "memory");
+            bf16x8 a0[4], b0[X_BY], a1[4], b1[X_BY];
+            auto read_ops = [&](int st, int ks, bf16x8 (&a)[4], bf16x8 (&b)[X_BY]) {
+                const uint32_t sb = (uint32_t)(st & (X_BUFS - 1)) * X_STAGE_BYTES;
+#pragma unroll
+                for (int y = 0; y < X_BY; ++y) b[y] = operand(rb[y] + sb, ks * 16 * 2 * XT);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) a[x] = operand(ra[x] + sb, ks * 16 * 2 * XT);
+            };
+            auto multiply = [&](const bf16x8 (&a)[4], const bf16x8 (&b)[X_BY]) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int y = 0; y < X_BY; ++y)
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+            };
+            read_ops(s0, 0, a0, b0);
             bool first = true;
             for (int c0 = s0; c0 < s1; c0 += X_CHUNK) {
                 const int c1 = min(c0 + X_CHUNK, s1);
                 for (int st = c0; st < c1; ++st) {
-                    // this stage's loads have landed (those of the two stages after it may be in flight), and everybody is
-                    // done with the stage before, whose place the new loads take
-                    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                    issue(st + 3);
-                    const uint32_t sb = (uint32_t)(st & (X_BUFS - 1)) * X_STAGE_BYTES;
-#pragma unroll
-                    for (int ks = 0; ks < XK / 16; ++ks) {
-                        bf16x8 a[4], b[2];
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) a[x] = operand(ra[x] + sb, ks * 16 * 2 * XT);
-#pragma unroll
-                        for (int y = 0; y < 2; ++y) b[y] = operand(rb[y] + sb, ks * 16 * 2 * XT);
-#pragma unroll
-                        for (int x = 0; x < 4; ++x)
-#pragma unroll
-                            for (int y = 0; y < 2; ++y)
-                                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+                    read_ops(st, 1, a1, b1);
+                    multiply(a0, b0);
+                    #pragma unroll
+                    for (int q = 0; q < 4 + X_BY; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                     }
+                    __builtin_amdgcn_sched_group_barrier(0x008, 4 * X_BY - 4 - X_BY, 0);
+                    // the loads of the next stage have landed (those of the two after it may be in flight), and everybody has
+                    // read all of this stage, whose place the new loads take
+                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * X_LOADS) : "memory");
+                    issue(st + X_BUFS);
+                    read_ops(st + 1, 0, a0, b0);
+                    multiply(a1, b1);
+                    #pragma unroll
+                    for (int q = 0; q < 4 + X_BY; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x008, 4 * X_BY - 4 - X_BY, 0);
                 }
                 // the chunk's sums go to memory.  Accumulator element e of a 32 x 32 tile: row = 8*(e/4) + 4*(lane/32)
                 // + e%4, column = lane%32.
                 if constexpr (!DIRECT) {
                     // partial tile: wavefront by wavefront, its accumulators' quarters as 16 bytes per lane
-                    const __amdgpu_buffer_rsrc_t sr = __builtin_amdgcn_make_buffer_rsrc(
-                        (void *)(slots + ((size_t)(plan.slot0[p] + v) * 8 + swave) * (8 * 4 * 64)), 0, 8 * 4 * 64 * 16, 0x00020000);
+                    constexpr int XY = 4 * X_BY;
+                    // (not through buffer stores with a scalar offset: their first data register may not be overwritten by the
+                    // very next instruction on this chip, and the compiler does not know)
+                    floatx4 *sp = (floatx4 *)slots + ((size_t)(plan.slot0[p] + v) * X_WAVES + swave) * (XY * 4 * 64) + lane;
+                    floatx4 o[2][4];      // what is there already, one accumulator block ahead
+                    auto old = [&](int xy) {
+                        if (first) return;
 #pragma unroll
-                    for (int xy = 0; xy < 8; ++xy) {
-                        floatx4 o[4];
+                        for (int q = 0; q < 4; ++q) o[xy & 1][q] = sp[(xy * 4 + q) * 64];
+                    };
+                    old(0);
+#pragma unroll
+                    for (int xy = 0; xy < XY; ++xy) {
+                        if (xy + 1 < XY) old(xy + 1);
+                        const floatx16 &c = acc[xy / X_BY][xy % X_BY];
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const floatx16 &c = acc[xy >> 1][xy & 1];
-                            o[q] = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
-                        }
-                        if (!first) {
+                            floatx4 t;
 #pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                o[q] += __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(sr, lane * 16, (xy * 4 + q) * 1024, 0));
+                            for (int e = 0; e < 4; ++e) t[e] = c[4 * q + e] + (first ? 0.f : o[xy & 1][q][e]);
+                            sp[(xy * 4 + q) * 64] = t;
                         }
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, o[q]), sr, lane * 16, (xy * 4 + q) * 1024, 0);
                     }
                 } else {
                     const double scale = c1 == s1 ? inv : 1.0;
-                    const long long ib = i0 + wr * 128 + 4 * lhi, jb = j0 + wc * 64 + l32;
+                    const long long ib = i0 + wr * 128 + 4 * lhi, jb = j0 + wc * 32 * X_BY + l32;
                     float *hp = H + ib * m + jb;
                     long long mm = m;
                     int rlim = (int)min(m - ib, 4096ll), clim = (int)min(m - jb, 4096ll);
@@ -221,7 +257,7 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
 #pragma unroll
                         for (int x = 0; x < 4; ++x)
 #pragma unroll
-                            for (int y = 0; y < 2; ++y) {
+                            for (int y = 0; y < X_BY; ++y) {
                                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                                 for (int e = 0; e < 16; ++e) {
@@ -239,12 +275,14 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
 #pragma unroll
                 for (int x = 0; x < 4; ++x)
 #pragma unroll
-                    for (int y = 0; y < 2; ++y)
+                    for (int y = 0; y < X_BY; ++y)
 #pragma unroll
                         for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
             }
         }
     }
+    // no load may still be on its way into the LDS when the workgroup gives it back
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // The partial tiles of a split tile added up, and every tile off the diagonal mirrored.  One wavefront per 32 x 32 block.
@@ -259,14 +297,15 @@ __global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, 
     int bi, bj;
     tile_of(tile, nt, bi, bj);
     const int split = slots ? plan.split[p] : 0;           // 0: the sums are in H already
-    const int ow = blk >> 3, xy = blk & 7;                  // the wavefront of xtx_big_kernel that owned the block, and which of its 8
-    const long long ib = (long long)bi * XT + (ow >> 2) * 128 + (xy >> 1) * 32, jb = (long long)bj * XT + (ow & 3) * 64 + (xy & 1) * 32;
+    constexpr int XY = 4 * X_BY;
+    const int ow = blk / XY, xy = blk % XY;                 // the wavefront of xtx_big_kernel that owned the block, and which of its blocks
+    const long long ib = (long long)bi * XT + (ow / X_WC) * 128 + (xy / X_BY) * 32, jb = (long long)bj * XT + (ow % X_WC) * 32 * X_BY + (xy % X_BY) * 32;
     if (ib < m && jb < m) {
         const int rlim = (int)min(m - ib, 32ll), clim = (int)min(m - jb, 32ll);
         float v[16];
         if (split > 0) {
             const double inv = 1.0 / (double)N;
-            const float4 *sp = slots + ((size_t)(plan.slot0[p] + tile - plan.tile0[p]) * 8 + ow) * (8 * 4 * 64) + xy * 256 + lane;
+            const float4 *sp = slots + ((size_t)(plan.slot0[p] + tile - plan.tile0[p]) * X_WAVES + ow) * (XY * 4 * 64) + xy * 256 + lane;
             const size_t step = (size_t)plan.ntile[p] * (8 * 8 * 4 * 64);       // from one part's slot to the next
             double s[16];
 #pragma unroll
@@ -311,7 +350,7 @@ __global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, 
 // Estimated length of the plan for `rem` tiles in stages, and the plan itself: whole rounds of one workgroup per tile
 // while there are as many tiles as workgroups; what is left either in one phase (every tile in floor(G / rem) parts)
 // or first as many tiles as ceil(G / rem) parts each fill the chip with, then the rest likewise.
-constexpr int X_PHASE_COST = 24;      // what starting a phase and writing its partial tiles costs, in stages
+constexpr int X_PHASE_COST = 24;      // what starting a phase and writing its partial tiles costs, in stages of 0.8 us (256 KB per workgroup)
 long long plan_rest(int rem, int G, int nstage, int maxsplit, int depth, int *nts, int *sps, int &n) {
     n = 0;
     if (rem == 0) return 0;

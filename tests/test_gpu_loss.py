@@ -205,3 +205,31 @@ def test_hessian_from_activations_matches_oracle(ctx, N, m):
     scale = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
     assert np.all(np.abs(got - ref) <= RTOL * scale), f"max scaled diff {(np.abs(got - ref) / scale).max():.3e}"
     assert torch.equal(H, H.T.contiguous())
+
+
+@pytest.mark.parametrize("N,m,workspace", [
+    (31, 2, "full"), (257, 514, "full"), (4100, 1030, "full"),      # widths that no 16-byte load divides; a short last stage
+    (520, 5890, "full"),                     # more tiles than workgroups: one round of whole tiles, then split ones
+    (16500, 300, "full"), (16500, 300, "one slot per tile"), (16500, 300, "none")])   # split; three chunks added up in a slot; in H
+def test_hessian_plans_match_oracle(gpu_lib, N, m, workspace):
+    """The ways the activations of a tile are shared out, against the float64 definition (bound as in
+    test_hessian_from_activations_matches_oracle)."""
+    X = np.concatenate(list(skim_synth.make_x(3, N, m)))
+    ref = oracle.hessian_from_activations(X).astype(np.float64)
+    Xb = torch.from_numpy(X).cuda().to(torch.bfloat16)
+    c = gpu_lib.Context(0)
+    H = torch.full((m, m), float("nan"), device="cuda")
+    if workspace == "full":
+        c.hessian_from_activations(Xb, out=H)
+    else:
+        tiles = ((m + 255) // 256) * ((m + 255) // 256 + 1) // 2
+        ws = torch.empty(tiles * 65536, device="cuda")
+        if workspace != "none":
+            c._check(c.lib.skim_set_workspace(c.h, ws.data_ptr(), ws.numel() * 4))
+        c._check(c.lib.skim_hessian_from_activations(c.h, Xb.data_ptr(), N, m, H.data_ptr()))
+    torch.cuda.synchronize()
+    got = H.cpu().numpy().astype(np.float64)
+    scale = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+    assert np.all(np.abs(got - ref) <= RTOL * scale), f"max scaled diff {(np.abs(got - ref) / scale).max():.3e}"
+    assert torch.equal(H, H.T.contiguous())
+    c.close()
