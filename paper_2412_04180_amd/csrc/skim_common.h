@@ -70,8 +70,12 @@ static inline int skim_block_offset(int bmin, int b) {  // start of block b insi
 skim_status skim_pack_static_setup(skim_ctx *ctx);
 
 // skim_layer_loss with the per-row losses written at a stride (row i at row_loss[i * row_stride]).  kept (may be
-// NULL): kept_n centroids per row at kept + i * kept_stride, used for clusters whose members carry no mass.
+// NULL): kept_n centroids per row at kept + i * kept_stride, used for clusters whose members carry no mass.  loss may be
+// NULL.  h_ready: the pieces of H are where the last such call with the same n, m left them in the workspace.
 skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *S, const float *alpha, const float *H,
                                     int64_t n, int64_t m, int64_t ld, const uint8_t *labels, double *loss,
                                     double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
-                                    int kept_n);
+                                    int kept_n, bool h_ready);
+
+// Bytes of the partial tiles a scale step on an n x m layer uses on a device with num_cu compute units.
+size_t skim_dwh_slot_bytes(int64_t n, int64_t m, int num_cu);

@@ -127,20 +127,21 @@ extern "C" const char *skim_last_error(const skim_ctx *ctx) { return ctx ? ctx->
 extern "C" size_t skim_workspace_bytes(int64_t n, int64_t m) {
     if (n < 0 || m < 0) return 0;
     const size_t N = (size_t)n, M = (size_t)m;
-    const size_t ntile = (M + 127) / 128, nstrip = (N + 7) / 8;
+    const size_t ti = (N + 255) / 256, tj = (M + 255) / 256, nstrip = (N + 7) / 8;
     size_t b = 0;
-    b += 3 * N * M * sizeof(uint16_t) + N * M * sizeof(float);   // scale step: dW (as three bfloat16 pieces per value, or as float32) and P
+    b += 3 * N * M * sizeof(uint16_t) + N * M * sizeof(float);   // scale step: dW (as three bfloat16 pieces per value) and P
     b += 3 * M * M * sizeof(uint16_t);   // the pieces of H
     b += 2 * N * 16 * sizeof(double);    // centroids and masses from fixed labels
-    b += ntile * N * sizeof(double);     // per-tile row sums of the loss
-    b += nstrip * M * sizeof(double);    // per-strip column sums of the gradient
+    b += (ti * tj + 256) * 256 * sizeof(double) + N * sizeof(double);   // row sums of the loss, piece by piece (256 pieces beyond one per tile) and in all
+    b += nstrip * (M + 1) * sizeof(double);    // per-strip column sums of the gradient and shares of the loss
+    b += skim_dwh_slot_bytes(n, m, 256);   // partial tiles of P where the tiles are split to fill the chip
     b += N * 30 * sizeof(double);        // centroid scratch of skim_error_table when the caller wants none
     b += N * (14 * M + 8192);            // clustering: sorted keys (8 B per weight), per-chunk sums and Lloyd state between the kernels
     if (M > 16384) b += N * 8 * M + N * 8 + 256;   // rows sorted in two halves: the unmerged keys, a mass flag per half
     b += N * sizeof(int) + 1024;         // pack: row positions and group table
     b += N * 4 * sizeof(double) + 1024;  // L-full error table: S-diag errors and the loss scalar at the tail
     b += N * (16 * sizeof(float) + sizeof(double)) + 1024;   // scale training: thresholds and errors of the re-clustering
-    return b + 16 * 256;                 // alignment slack (every piece is 256-byte aligned)
+    return b + 20 * 256;                 // alignment slack (every piece is 256-byte aligned)
 }
 
 extern "C" skim_status skim_set_workspace(skim_ctx *ctx, void *dev_ptr, size_t bytes) {

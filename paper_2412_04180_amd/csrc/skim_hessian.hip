@@ -4,20 +4,16 @@
 // accumulation over chunks of at most 8192 activations.  Only the 256 x 256 tiles on and above the
 // diagonal are computed; where there are fewer of them than compute units the activations of a tile are
 // split over several workgroups, whose partial tiles a second kernel adds up (float64) and mirrors.
-#include "skim_common.h"
+#include "skim_tiles.h"
 
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef int int4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v lds_short4v;
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
-constexpr int XT = 256;                    // output tile (rows and columns of H = columns of X)
+constexpr int XT = TILE;                   // output tile (rows and columns of H = columns of X)
 constexpr int XK = 32;                     // activations per stage
 constexpr int X_BUFS = 4;                  // stages in LDS: one in use, three on their way
 constexpr int X_WAVES = 8, X_WC = X_WAVES / 2, X_BY = 8 / X_WC;   // wavefronts: 2 x X_WC, each 4 x X_BY blocks of 32 x 32
@@ -28,16 +24,7 @@ constexpr int X_STAGE_BYTES = 2 * X_PANEL_BYTES;
 constexpr size_t X_LDS_BYTES = (size_t)X_BUFS * X_STAGE_BYTES;
 constexpr int X_CHUNK = 8192 / XK;         // stages summed in float32 registers before they are added to memory
 constexpr int X_MIN_STAGES = 8;            // no workgroup gets a shorter share of the activations than this
-constexpr int X_MAX_PHASES = 6;
-constexpr size_t X_SLOT_BYTES = (size_t)XT * XT * sizeof(float);
-
-// How the tiles are shared out: phase p takes tiles tile0 .. tile0 + ntile - 1 and cuts the activations of each into
-// `split` equal parts; part q of tile t is one piece of work with a partial tile ("slot") of its own, number
-// slot0 + q * ntile + (t - tile0).
-struct XtxPlan {
-    int nph;
-    int tile0[X_MAX_PHASES], ntile[X_MAX_PHASES], split[X_MAX_PHASES], slot0[X_MAX_PHASES];
-};
+constexpr int X_PHASE_COST = 24;           // a phase and its partial tiles, in stages of 0.8 us (256 KB per workgroup)
 
 // Tile number -> (bi, bj), bi <= bj: bands of 8 tile rows; inside a band column by column, first the columns the
 // diagonal cuts short.  Consecutive tiles share operand panels (32 of them cover about 8 x 4 tiles: 12 panels).
@@ -84,7 +71,7 @@ __device__ __forceinline__ bf16x8 operand(uint32_t addr, int off) {
 // DIRECT: the partial sums are added up in H itself (every tile is one workgroup's), not in slots.
 template <bool DIRECT>
 __global__ void __launch_bounds__(X_THREADS) __attribute__((amdgpu_waves_per_eu(X_WAVES / 4, X_WAVES / 4)))
-xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *H, int nt, XtxPlan plan, float4 *slots) {
+xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *H, int nt, TilePlan plan, float4 *slots) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave / X_WC, wc = wave % X_WC;
@@ -122,13 +109,8 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
 
     const double inv = 1.0 / (double)N;
     const int nstage = (int)((N + XK - 1) / XK);
-    // Workgroups of one XCD (ids equal modulo 8) take neighbouring pieces of work
     const int G = gridDim.x;
-    int me;
-    {
-        const int q8 = G >> 3, r8 = G & 7, xcd = blockIdx.x & 7;
-        me = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
-    }
+    const int me = xcd_order(blockIdx.x, G);
     for (int p = 0; p < plan.nph; ++p) {
         const int ntile = plan.ntile[p], split = plan.split[p];
         for (int v = me; v < ntile * split; v += G) {
@@ -149,22 +131,14 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
             // the stage that is requested next: its first activation, and the bytes from there to the end of the part (a stage
             // past it is requested like any other, to keep the count of loads in flight, but reads nothing: zeros arrive)
             const uint64_t stage_bytes = (uint64_t)XK * (uint64_t)m * 2;
-            uint64_t base = (uint64_t)(uintptr_t)X + (uint64_t)s0 * stage_bytes;
-            long long left = min(N, (long long)s1 * XK) * m * 2 - (long long)((uint64_t)s0 * stage_bytes);
+            LdsSource src{(uint64_t)(uintptr_t)X + (uint64_t)s0 * stage_bytes,
+                          min(N, (long long)s1 * XK) * m * 2 - (long long)((uint64_t)s0 * stage_bytes)};
             auto issue = [&](int st) {
-                int4v rs;
-                rs.x = (int)(uint32_t)base;
-                rs.y = (int)((uint32_t)(base >> 32) & 0xFFFFu);
-                rs.z = (int)max(min(left, 0x7FFFFFFFll), 0ll);
-                rs.w = 0x00020000;
+                const int4v rs = src.rsrc();
                 const uint32_t dst = stage_dst + (uint32_t)(st & (X_BUFS - 1)) * X_STAGE_BYTES;
 #pragma unroll
-                for (int i = 0; i < X_LOADS; ++i)
-                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst + i * 2 * 2 * XT),
-                                 "v"(voff[i]), "s"(rs)
-                                 : "memory", "m0");
-                base += stage_bytes;
-                left -= (long long)stage_bytes;
+                for (int i = 0; i < X_LOADS; ++i) copy_to_lds(dst + i * 2 * 2 * XT, voff[i], rs);
+                src.advance(stage_bytes);
             };
             floatx16 acc[4][X_BY];
 #pragma unroll
@@ -286,7 +260,7 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
 }
 
 // The partial tiles of a split tile added up, and every tile off the diagonal mirrored.  One wavefront per 32 x 32 block.
-__global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, long long m, int nt, XtxPlan plan,
+__global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, long long m, int nt, TilePlan plan,
                                                          const float4 *__restrict__ slots) {
     __shared__ float tr[4][32][33];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -347,72 +321,14 @@ __global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, 
     }
 }
 
-// Estimated length of the plan for `rem` tiles in stages, and the plan itself: whole rounds of one workgroup per tile
-// while there are as many tiles as workgroups; what is left either in one phase (every tile in floor(G / rem) parts)
-// or first as many tiles as ceil(G / rem) parts each fill the chip with, then the rest likewise.
-constexpr int X_PHASE_COST = 24;      // what starting a phase and writing its partial tiles costs, in stages of 0.8 us (256 KB per workgroup)
-long long plan_rest(int rem, int G, int nstage, int maxsplit, int depth, int *nts, int *sps, int &n) {
-    n = 0;
-    if (rem == 0) return 0;
-    const int one = rem >= G ? 1 : (G / rem < maxsplit ? G / rem : maxsplit);
-    if (rem >= G) {
-        const int whole = rem - rem % G;
-        nts[0] = whole;
-        sps[0] = 1;
-        int k = 0;
-        const long long c = (long long)(whole / G) * nstage + X_PHASE_COST +
-                            (depth > 1 ? plan_rest(rem - whole, G, nstage, maxsplit, depth - 1, nts + 1, sps + 1, k) : 0);
-        if (depth <= 1) nts[0] = rem;      // (all of it then: one more round, partly filled)
-        n = 1 + k;
-        return c;
-    }
-    const long long cost_one = (nstage + one - 1) / one + X_PHASE_COST;
-    const int more = (G + rem - 1) / rem;
-    if (depth > 1 && more <= maxsplit && more > one) {
-        int nts2[X_MAX_PHASES], sps2[X_MAX_PHASES], k = 0;
-        const int take = G / more;
-        const long long c = (nstage + more - 1) / more + X_PHASE_COST +
-                            plan_rest(rem - take, G, nstage, maxsplit, depth - 1, nts2, sps2, k);
-        if (c < cost_one) {
-            nts[0] = take;
-            sps[0] = more;
-            for (int i = 0; i < k; ++i) {
-                nts[1 + i] = nts2[i];
-                sps[1 + i] = sps2[i];
-            }
-            n = 1 + k;
-            return c;
-        }
-    }
-    nts[0] = rem;
-    sps[0] = one;
-    n = 1;
-    return cost_one;
-}
-
-// The plan for G workgroups (whole: no tile is split); returns the number of partial tiles.
-long long make_plan(XtxPlan &plan, int G, int64_t N, int64_t m, bool whole) {
-    const long long nt = (m + XT - 1) / XT, tiles = nt * (nt + 1) / 2;
-    const int nstage = (int)((N + XK - 1) / XK);
-    const int maxsplit = !whole && nstage / X_MIN_STAGES > 1 ? nstage / X_MIN_STAGES : 1;
-    plan = XtxPlan{};
-    plan_rest((int)tiles, G, nstage, maxsplit, whole ? 1 : 4, plan.ntile, plan.split, plan.nph);
-    long long t = 0, slots = 0;
-    for (int p = 0; p < plan.nph; ++p) {
-        plan.tile0[p] = (int)t;
-        t += plan.ntile[p];
-        plan.slot0[p] = (int)slots;
-        slots += (long long)plan.ntile[p] * plan.split[p];
-    }
-    return slots;
-}
-
 }  // namespace
 
 extern "C" size_t skim_hessian_workspace_bytes(const skim_ctx *ctx, int64_t N, int64_t m) {
     if (!ctx || N < 1 || m < 1 || m > 0x7fffffff) return 0;
-    XtxPlan plan;
-    return (size_t)make_plan(plan, ctx->num_cu, N, m, false) * X_SLOT_BYTES;
+    TilePlan plan;
+    const int64_t nt = (m + XT - 1) / XT;
+    return (size_t)skim_make_plan(plan, ctx->num_cu, nt * (nt + 1) / 2, (int)((N + XK - 1) / XK), X_MIN_STAGES, X_PHASE_COST, false) *
+           TILE_SLOT_BYTES;
 }
 
 extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m,
@@ -431,12 +347,14 @@ extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16
     const int nt = (int)((m + XT - 1) / XT);
     const int G = ctx->num_cu;
     // Without a workspace that holds the partial tiles the splits are given up, then the slots altogether
-    XtxPlan plan;
+    TilePlan plan;
     const long long tiles = (long long)nt * (nt + 1) / 2;
+    const int nstage = (int)((N + XK - 1) / XK);
     bool direct = true;
     for (int whole = 0; whole < 2 && direct; ++whole)
-        direct = !ctx->ws || (size_t)make_plan(plan, G, N, m, whole != 0) * X_SLOT_BYTES > ctx->ws_bytes;
-    if (direct) (void)make_plan(plan, G, N, m, true);
+        direct = !ctx->ws || (size_t)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, whole != 0) * TILE_SLOT_BYTES >
+                                 ctx->ws_bytes;
+    if (direct) (void)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, true);
     long long grid = 0;
     for (int p = 0; p < plan.nph; ++p) {
         const long long items = (long long)plan.ntile[p] * plan.split[p];

@@ -69,10 +69,9 @@ extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, con
         SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
     const int nb = bmax - bmin + 1;
     // the tail of the workspace holds what must survive the calls below (they carve from its start)
-    const size_t tail_bytes = (((size_t)n * nb * sizeof(double) + 255) & ~(size_t)255) + 256;
+    const size_t tail_bytes = (((size_t)n * nb * sizeof(double) + 255) & ~(size_t)255);
     char *tail = (char *)ctx->ws + ((ctx->ws_bytes - tail_bytes) & ~(size_t)255);
-    double *loss_scalar = (double *)tail;
-    double *sdiag = E_sdiag ? E_sdiag : (double *)(tail + 256);
+    double *sdiag = E_sdiag ? E_sdiag : (double *)tail;
     if ((st = skim_error_table(ctx, W, S, alpha, n, m, ld, bmin, bmax, iters, sdiag, centroids_all, upper_all)) != SKIM_OK)
         return st;
     const int stride = (2 << bmax) - (1 << bmin);
@@ -82,8 +81,8 @@ extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, con
         SKIM_HIP(ctx, hipGetLastError());
         // a cluster whose members carry no sensitivity mass keeps the centroid the clustering left it with
         // (the value the packed codebook holds), not the 0 a weighted mean over no mass would give
-        if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels_work, loss_scalar, E_full + (b - bmin),
-                                          nb, centroids_all + ((1 << b) - (1 << bmin)), stride, 1 << b)) != SKIM_OK)
+        if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels_work, nullptr, E_full + (b - bmin),
+                                          nb, centroids_all + ((1 << b) - (1 << bmin)), stride, 1 << b, b > bmin)) != SKIM_OK)
             return st;
     }
     return SKIM_OK;

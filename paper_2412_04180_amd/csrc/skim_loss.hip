@@ -5,20 +5,20 @@
 //   c_ik  = sum_{j in k} s~_ij w~_ij / sum_{j in k} s~_ij      (calc_centroids(W*alpha^-1, L))
 //   dW_ij = w_ij - alpha_j c_{i,L_ij}                           (W - replace(c, L) * alpha)
 //   P     = dW H            matrix cores, float32 accumulation (the path's one dense contraction): bf16 MFMA on
-//                           three-piece splits of the float32 operands (dwh_gemm3_kernel), or fp32 MFMA (dwh_gemm_kernel)
+//                           three-piece splits of the float32 operands; where only the loss is wanted, half of it
 //   loss  = sum_ij P_ij dW_ij                                   float64 reduction
 //   dloss/dalpha_l = -2 sum_i [ P_il c_{i,L_il}
 //                    + Q_{i,L_il} s_il (w_il - 2 alpha_l c_{i,L_il}) / D_{i,L_il} ],
 //   Q_ik = sum_{j in k} P_ij alpha_j,  D_ik = sum_{j in k} s~_ij  (gradient through the centroids).
-#include "skim_common.h"
+#include "skim_tiles.h"
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-// Pieces of a float32 value for the contraction on the bf16 matrix cores (see dwh_gemm3_kernel)
+// Pieces of a float32 value for the contraction on the bf16 matrix cores (see dwh_kernel)
 __device__ __forceinline__ uint32_t bf16_rn(float f) {      // finite f
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
@@ -32,15 +32,14 @@ __device__ __forceinline__ void split3(float x, uint32_t &p1, uint32_t &p2, uint
     r -= bf16_f32(p2);                // exact; at most 8 significant bits are left
     p3 = bf16_rn(r);
 }
+// Layout of a split matrix ("planes"): for every block of 16 k, row after row, [piece 1 (16) | piece 2 (16) | piece 3 (16)]
+// as 96 contiguous bytes: the rows of a tile for one 16-k step are one contiguous region of memory.
+constexpr int GK = 16;
 __device__ __forceinline__ size_t plane_index(long long row, long long rows, long long k) {
-    return ((size_t)(k >> 5) * (size_t)rows + (size_t)row) * 96 + (size_t)(k & 31);     // piece p at + 32 p
+    return ((size_t)(k >> 4) * (size_t)rows + (size_t)row) * 48 + (size_t)(k & 15);     // piece p at + 16 p
 }
 
-
 constexpr int PREP_THREADS = 256;
-constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int A_STRIDE = BM + 4;   // k-major A tile, padded against bank conflicts of the transposing store
-constexpr int GEMM_THREADS = 256;
 constexpr int STRIP = 8;           // rows per workgroup in the gradient kernel
 
 __device__ __forceinline__ double block_sum_256(double x, double *scratch /* >= 4 doubles */) {
@@ -66,12 +65,12 @@ __device__ __forceinline__ double bin_total(const double (*bins)[16], int k) {
 }
 
 // Per row: weighted cluster sums with fixed labels -> centroids c (n x 16 float64),
-// masses Den (n x 16 float64), and the row of dW (float32, or its three bfloat16 pieces when dWp is given).
+// masses Den (n x 16 float64), and the row of dW as three bfloat16 pieces per value.
 // kept (optional): per row, at kept + row * kept_stride, the centroid a cluster keeps when its members carry no
 // sensitivity mass (what the clustering that produced the labels left there); without it such a centroid is 0.
 __global__ void __launch_bounds__(PREP_THREADS) row_prep_kernel(const float *W, const float *S, const float *alpha,
                                                                 long long m, long long ld, const uint8_t *labels,
-                                                                double *cent, double *Den, float *dW, uint16_t *dWp,
+                                                                double *cent, double *Den, uint16_t *dWp,
                                                                 const double *kept, long long kept_stride, int kept_n,
                                                                 bool vec4) {
     __shared__ double binD[BIN_SETS][16], binN[BIN_SETS][16];
@@ -118,8 +117,7 @@ __global__ void __launch_bounds__(PREP_THREADS) row_prep_kernel(const float *W, 
         Den[row * 16 + tid] = d;
     }
     __syncthreads();
-    // dW as float32 for dwh_gemm_kernel, or as three bfloat16 pieces per value for dwh_gemm3_kernel
-    if (vec4 && dWp) {
+    if (vec4) {
         for (long long j = 4ll * tid; j < m; j += 4 * PREP_THREADS) {
             const float4 w4 = *(const float4 *)(Wr + j);
             const float4 a4 = alpha ? *(const float4 *)(alpha + j) : make_float4(1.f, 1.f, 1.f, 1.f);
@@ -131,319 +129,366 @@ __global__ void __launch_bounds__(PREP_THREADS) row_prep_kernel(const float *W, 
                 const float d = (float)((double)wv[e] - (double)av[e] * csh[(l4 >> (8 * e)) & 15u]);
                 split3(d, pc[0][e], pc[1][e], pc[2][e]);
             }
-            uint16_t *o = dWp + plane_index(row, nrows, j);   // four neighbouring k stay inside one block of 32
+            uint16_t *o = dWp + plane_index(row, nrows, j);   // four neighbouring k stay inside one block of 16
 #pragma unroll
             for (int q = 0; q < 3; ++q)
-                *(uint2 *)(o + 32 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
+                *(uint2 *)(o + 16 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
         }
         return;
     }
     for (long long j = tid; j < m; j += PREP_THREADS) {
         const double a = alpha ? (double)alpha[j] : 1.0;
         const float d = (float)((double)Wr[j] - a * csh[Lr[j] & 15]);
-        if (dWp) {
-            uint32_t p1, p2, p3;
-            split3(d, p1, p2, p3);
-            uint16_t *o = dWp + plane_index(row, nrows, j);
-            o[0] = (uint16_t)p1;
-            o[32] = (uint16_t)p2;
-            o[64] = (uint16_t)p3;
-        } else {
-            dW[row * m + j] = d;
-        }
+        uint32_t p1, p2, p3;
+        split3(d, p1, p2, p3);
+        uint16_t *o = dWp + plane_index(row, nrows, j);
+        o[0] = (uint16_t)p1;
+        o[16] = (uint16_t)p2;
+        o[32] = (uint16_t)p3;
     }
 }
 
-// P = dW * H on fp32 MFMA (v_mfma_f32_32x32x2_f32), 128 x 128 output tile per
-// workgroup, four wavefronts in a 2 x 2 arrangement of 64 x 64 sub-tiles.  Four workgroups
-// per compute unit (register budget 128 per lane): the 1024 tiles of a 4096 x 4096 layer are
-// then resident at once instead of leaving a quarter of them for a thin second round.
-// Epilogue: optional store of P and, per output row, sum_j P_ij dW_ij over the
-// tile's columns in float64 -> partial[tile_col][row].
-template <bool STORE_P>
-__global__ void __launch_bounds__(GEMM_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) dwh_gemm_kernel(const float *__restrict__ A, const float *__restrict__ H,
-                                                                int n, int m, float *__restrict__ P,
-                                                                double *__restrict__ partial) {
-    __shared__ float As[2][BK][A_STRIDE];
-    __shared__ float Bs[2][BK][BN];
-    __shared__ double rsum[2][BM];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int row0 = blockIdx.y * BM, col0 = blockIdx.x * BN;
-    const int l32 = lane & 31, lhi = lane >> 5;
-
-    // global -> register staging: A tile 128 x 16 (two float4 per thread), B tile 16 x 128 (two float4)
-    const int a_r = tid >> 2, a_k = (tid & 3) * 4;     // rows a_r and a_r + 64
-    const int b_k = tid >> 5, b_c = (tid & 31) * 4;    // k rows b_k and b_k + 8
-    float4 ra[2], rb[2];
-    auto load_tiles = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = row0 + a_r + 64 * i;
-            ra[i] = (r < n) ? *(const float4 *)(A + (long long)r * m + k0 + a_k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            const int c = col0 + b_c;
-            const float *src = H + (long long)(k0 + b_k + 8 * i) * m + c;
-            if (c + 3 < m) {
-                rb[i] = *(const float4 *)src;
-            } else {
-                rb[i].x = (c + 0 < m) ? src[0] : 0.f;
-                rb[i].y = (c + 1 < m) ? src[1] : 0.f;
-                rb[i].z = (c + 2 < m) ? src[2] : 0.f;
-                rb[i].w = 0.f;
-            }
-        }
-    };
-    auto store_tiles = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = a_r + 64 * i;
-            As[buf][a_k + 0][r] = ra[i].x;
-            As[buf][a_k + 1][r] = ra[i].y;
-            As[buf][a_k + 2][r] = ra[i].z;
-            As[buf][a_k + 3][r] = ra[i].w;
-            *(float4 *)&Bs[buf][b_k + 8 * i][b_c] = rb[i];
-        }
-    };
-
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    const int nk = m / BK;
-    load_tiles(0);
-    store_tiles(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_tiles((kt + 1) * BK);
-#pragma unroll
-        for (int kp = 0; kp < BK / 2; ++kp) {
-            const int k = 2 * kp + lhi;
-            const float a0 = As[buf][k][wr * 64 + l32];
-            const float a1 = As[buf][k][wr * 64 + 32 + l32];
-            const float b0 = Bs[buf][k][wc * 64 + l32];
-            const float b1 = Bs[buf][k][wc * 64 + 32 + l32];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        if (kt + 1 < nk) store_tiles(buf ^ 1);
-        __syncthreads();
-    }
-
-    // epilogue.  Accumulator element e of a 32 x 32 tile: row = 8*(e/4) + 4*(lane/32) + e%4, column = lane%32.
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int rl = wr * 64 + i * 32 + 8 * (e >> 2) + 4 * lhi + (e & 3);
-            const int r = row0 + rl;
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = col0 + wc * 64 + j * 32 + l32;
-                if (r < n && c < m) {
-                    const float p = acc[i][j][e];
-                    if (STORE_P) P[(long long)r * m + c] = p;
-                    t += (double)p * (double)A[(long long)r * m + c];
-                }
-            }
-            // sum over the 32 lanes that share this row
-            for (int o = 16; o >= 1; o >>= 1) t += __shfl_xor(t, o, 64);
-            if (l32 == 0) rsum[wc][rl] = t;
-        }
-    }
-    __syncthreads();
-    if (tid < BM && row0 + tid < n) partial[(long long)blockIdx.x * n + row0 + tid] = rsum[0][tid] + rsum[1][tid];
-}
-
-// ---- the same contraction on the bf16 matrix cores -----------------------------------------------------------
+// ---- the contraction on the bf16 matrix cores ------------------------------------------------------------------
 // A float32 value is the exact sum of three bfloat16 values (8 + 8 + 8 significant bits, each piece the rounding of
 // what the pieces before it leave), so x y = sum over the nine products of pieces, each exact in float32.  The six
 // products with piece indices i + j <= 4 carry everything down to 2^-24 of |x y| -- the size of float32's own
 // rounding -- and v_mfma_f32_32x32x16_bf16 does one of them for 16 k in half the time v_mfma_f32_32x32x2_f32
 // needs for 2 k: 6 x 32 clocks against 512 per 16 k.  Accumulation is float32 in the matrix core either way.
-// Layout of a split matrix ("planes"): for every block of 32 k, row after row, [piece 1 (32) | piece 2 (32) |
-// piece 3 (32)] as 192 contiguous bytes: the rows of a tile for one 32-k step are one contiguous region of memory
-// (64 lanes of a load instruction read 1024 consecutive bytes; with the blocks of a row side by side instead, an
-// instruction read 192 bytes of each of six rows and the kernel sat at the rate the memory system serves that).
-// H (m x m float32, symmetric, m % 32 == 0) -> its planes, row j of the planes = row j of H = column j of H.
-__global__ void __launch_bounds__(256) split_rows_kernel(const float *__restrict__ H, long long rows, long long m,
-                                                         uint16_t *__restrict__ Hp) {
+// H (m x m float32, symmetric, m % 16 == 0) -> its planes, row j of the planes = row j of H = column j of H.
+// lower: only the columns up to the end of the 256-column block that holds j (all that the loss needs).
+__global__ void __launch_bounds__(256) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, bool lower) {
     const long long g = (long long)blockIdx.x * 256 + threadIdx.x;     // 8 consecutive k of one row
     const long long per_row = m >> 3;
-    if (g >= rows * per_row) return;
+    if (g >= m * per_row) return;
     const long long j = g / per_row, k = (g - j * per_row) << 3;
+    if (lower && k >= ((j | (TILE - 1)) + 1)) return;
     const float4 a = *(const float4 *)(H + j * m + k), b = *(const float4 *)(H + j * m + k + 4);
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     uint32_t p[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
-    uint16_t *dst = Hp + plane_index(j, rows, k);
+    uint16_t *dst = Hp + plane_index(j, m, k);
 #pragma unroll
     for (int q = 0; q < 3; ++q)
-        *(uint4 *)(dst + 32 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
+        *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
                                               p[q][6] | (p[q][7] << 16));
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-constexpr int G3_BM = 256, G3_BN = 128, G3_BK = 32, G3_THREADS = 512;
-constexpr int G3_PITCH = 104;                  // bfloat16 per LDS row: 3 pieces x 32 k + 8 of padding = 208 bytes
-constexpr int G3_ROWS = G3_BM + G3_BN;         // the dW rows of the tile, then the H rows
-constexpr int G3_CHUNKS = G3_ROWS * 12 / G3_THREADS;      // 16-byte pieces a thread stages per step: 9
-constexpr size_t G3_LDS_BYTES = 2 * (size_t)G3_ROWS * G3_PITCH * sizeof(uint16_t);   // double-buffered: 159744
+typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8;
+constexpr int G_THREADS = 512;                     // 8 wavefronts, two per SIMD: 2 x 4, each 128 x 64 of the 256 x 256 tile
+constexpr int G_BUFS = 3;
+constexpr uint32_t G_PANEL_BYTES = TILE * 96;      // one operand of one 16-k stage: 24 KB
+constexpr uint32_t G_STAGE_BYTES = 2 * G_PANEL_BYTES;
+constexpr size_t G_LDS_BYTES = (size_t)G_BUFS * G_STAGE_BYTES;      // 147456
+constexpr int G_LOADS = G_STAGE_BYTES / (1024 * (G_THREADS / 64));  // 1 KB copies of a wavefront per stage: 6
+constexpr int G_MIN_STAGES = 16;
+constexpr int G_PHASE_COST = 20;                   // a phase of split tiles with its partial tiles, in stages
 
-// P = dW H from the planes of dW (n rows) and of H (m rows; H symmetric: its row j stands in for its column j).
-// 256 x 128 output tile, 8 wavefronts (two per SIMD) of 64 x 64; 32 k per step, LDS double-buffered, the next
-// step's rows staged through registers while this step's MFMAs run.  Epilogue as in dwh_gemm_kernel, with dW
-// put together again from its pieces (exactly).
-template <bool STORE_P>
-__global__ void __launch_bounds__(G3_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-dwh_gemm3_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, int n, int m, float *__restrict__ P,
-                 double *__restrict__ partial) {
-    extern __shared__ __align__(16) unsigned char g3_smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int l32 = lane & 31, lhi = lane >> 5;
-    const int row0 = blockIdx.y * G3_BM, col0 = blockIdx.x * G3_BN;
-
-    // staging: piece c = tid + 512 q of the 384 x 12 pieces of a step; consecutive lanes read consecutive 16 bytes
-    const uint16_t *src[G3_CHUNKS];
-    uint32_t dst[G3_CHUNKS];          // byte offset inside one LDS buffer
-    bool ok[G3_CHUNKS];
+// What a lane needs to know about the LDS.  A panel is copied as it lies in memory (96 bytes per row: six 16-byte units,
+// unit 2 p + h = piece p, k 8 h .. 8 h + 7), except that the units of the rows with bit 3 set are rotated by one: any 16
+// rows then read one unit from 64 different banks.
+struct DwhLane {
+    uint32_t voff[G_LOADS];      // source of its copies inside the panel
+    uint32_t dst;                // their first kilobyte (the same in the whole wavefront)
+    uint32_t ra[3], rb[3];       // operand addresses of the three pieces, A block x at + x * 3072, B block y likewise
+    int swave, wr, wc, l32, lhi;
+    __device__ __forceinline__ DwhLane(uint32_t lds0, int tid) {
+        const int lane = tid & 63, wave = tid >> 6;
+        swave = __builtin_amdgcn_readfirstlane(wave);
+        wr = wave >> 2;
+        wc = wave & 3;
+        l32 = lane & 31;
+        lhi = lane >> 5;
 #pragma unroll
-    for (int q = 0; q < G3_CHUNKS; ++q) {
-        const int c = tid + G3_THREADS * q;
-        const int trow = c / 12, part = c - 12 * trow;
-        const bool isa = trow < G3_BM;
-        const long long grow = isa ? (long long)row0 + trow : (long long)col0 + (trow - G3_BM);
-        ok[q] = grow < (isa ? (long long)n : (long long)m);
-        src[q] = (isa ? Ap : Hp) + (size_t)(ok[q] ? grow : 0) * 96 + 8 * part;
-        dst[q] = (uint32_t)(trow * G3_PITCH + 8 * part) * 2u;
-    }
-    // (pieces 0 .. 3071 of a step are rows of dW, the rest rows of H: q < 6 is all dW, q = 6 .. 8 all H)
-    static_assert(6 * G3_THREADS == G3_BM * 12, "the dW rows of a step end on a whole pass of the workgroup");
-    const size_t step_a = (size_t)n * 96, step_h = (size_t)m * 96;      // from one 32-k block to the next
-    uint4 sg[G3_CHUNKS];
-    auto load_step = [&](int kt) {
-#pragma unroll
-        for (int q = 0; q < G3_CHUNKS; ++q) {
-            const uint4 v = *(const uint4 *)(src[q] + (size_t)kt * (q < 6 ? step_a : step_h));
-            sg[q] = ok[q] ? v : make_uint4(0u, 0u, 0u, 0u);
+        for (int i = 0; i < G_LOADS; ++i) {
+            const int c = ((wave & 3) * G_LOADS + i) * 64 + lane;
+            const int row = c / 6, pos = c - 6 * row;
+            const int unit = (pos + 6 - ((row >> 3) & 1)) % 6;
+            voff[i] = (uint32_t)(row * 96 + unit * 16);
         }
-    };
-    auto store_step = [&](int buf, int q0, int q1) {
-        unsigned char *base = g3_smem + (size_t)buf * (G3_ROWS * G3_PITCH * 2);
+        dst = lds0 + (uint32_t)(swave >> 2) * G_PANEL_BYTES + (uint32_t)(swave & 3) * (G_LOADS * 1024);
 #pragma unroll
-        for (int q = 0; q < G3_CHUNKS; ++q)
-            if (q >= q0 && q < q1) *(uint4 *)(base + dst[q]) = sg[q];
-    };
+        for (int p = 0; p < 3; ++p) {
+            const uint32_t u = (uint32_t)((2 * p + lhi + ((l32 >> 3) & 1)) % 6) * 16;
+            ra[p] = lds0 + (uint32_t)(wr * 128 + l32) * 96 + u;
+            rb[p] = lds0 + G_PANEL_BYTES + (uint32_t)(wc * 64 + l32) * 96 + u;
+        }
+    }
+};
 
-    floatx16 acc[2][2];
+// acc = (rows row0 .. of dW) (rows col0 .. of H)^T over the 16-k stages [s0, s1), from the planes; with HALVED the sums are
+// doubled ahead of stage sdouble.  Rows past the end of either matrix carry values of other rows or zeros.
+// 16 k are 48 MFMAs and 18 operand reads per wavefront.  The operands of the next quarter of a stage are read between the
+// MFMAs of this one; the barrier stands ahead of the last quarter: past it the next stage is complete in LDS and this
+// one's place is free for the stage after the next two.
+template <bool HALVED>
+__device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhLane &L, const uint16_t *Ap, long long n,
+                                               const uint16_t *Hp, long long m, long long row0, long long col0, int s0, int s1,
+                                               int sdouble) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+    const bool isb = L.swave >= 4;
+    const long long step = (isb ? m : n) * 96, skip = (isb ? col0 : row0) * 96;
+    LdsSource src{(uint64_t)(uintptr_t)(isb ? Hp : Ap) + (uint64_t)((long long)s0 * step + skip), (long long)(s1 - s0) * step - skip};
+    auto issue = [&](uint32_t buf) {
+        const int4v rs = src.rsrc();
+#pragma unroll
+        for (int i = 0; i < G_LOADS; ++i) copy_to_lds(L.dst + buf + i * 1024, L.voff[i], rs);
+        src.advance((uint64_t)step);
+    };
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the LDS is free
+    issue(0);
+    issue(G_STAGE_BYTES);
+    issue(2 * G_STAGE_BYTES);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * G_LOADS) : "memory");
+    bf16x8_t a[2][3], b[2][2][3];
+    auto read_a = [&](int set, uint32_t buf, int x) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a[set][p] = *(lds_bf16x8 *)(L.ra[p] + buf + x * 3072);
+    };
+    auto read_b = [&](int set, uint32_t buf) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[set][y][p] = *(lds_bf16x8 *)(L.rb[p] + buf + y * 3072);
+    };
+    auto multiply = [&](int x, int as, int bs) {     // smallest products first
+        constexpr int PA[6] = {2, 1, 0, 0, 1, 0}, PB[6] = {0, 1, 2, 1, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[as][PA[q]], b[bs][y][PB[q]], acc[x][y], 0, 0, 0);
+    };
+    uint32_t cur = 0;
+    read_b(0, cur);
+    read_a(0, cur, 0);
+    auto stage = [&](auto par, int st) {
+        constexpr int BS = decltype(par)::value;
+        if (HALVED && st == sdouble) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[x][y][e] += acc[x][y][e];
+        }
+        const uint32_t nxt = cur == 2 * G_STAGE_BYTES ? 0 : cur + G_STAGE_BYTES;
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            read_a((x + 1) & 1, cur, x + 1);
+            multiply(x, x & 1, BS);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // an MFMA, the three reads, the other MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 11, 0);
+        }
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G_LOADS) : "memory");
+        issue(cur);
+        read_b(BS ^ 1, nxt);
+        read_a(0, nxt, 0);
+        multiply(3, 1, BS);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+        cur = nxt;
+    };
+    for (int st = s0;;) {
+        stage(std::integral_constant<int, 0>{}, st);
+        if (++st >= s1) break;
+        stage(std::integral_constant<int, 1>{}, st);
+        if (++st >= s1) break;
+    }
+}
 
-    const int nk = m / G3_BK;
-    load_step(0);
-    store_step(0, 0, G3_CHUNKS);
-    load_step(nk > 1 ? 1 : 0);
-    __syncthreads();
-    // operand of a lane: 8 consecutive k (16 ks + 8 (lane / 32) ..) of piece p of row (lane % 32) of a 32-row block
-    const uint32_t a_off = (uint32_t)((wr * 64 + l32) * G3_PITCH + 8 * lhi) * 2u;
-    const uint32_t b_off = (uint32_t)((G3_BM + wc * 64 + l32) * G3_PITCH + 8 * lhi) * 2u;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        const unsigned char *tb = g3_smem + (size_t)buf * (G3_ROWS * G3_PITCH * 2);
+// P = dW H, tile by tile as the plan says: a whole tile goes straight into P, a part of a split one into its slot.
+__global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, long long n, long long m, int tj, TilePlan plan,
+           float *__restrict__ P, floatx4 *__restrict__ slots) {
+    extern __shared__ __align__(16) unsigned char g_smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid);
+    const int nk = (int)(m / GK);
+    const int G = gridDim.x, me = xcd_order(blockIdx.x, G);
+    for (int p = 0; p < plan.nph; ++p) {
+        const int ntile = plan.ntile[p], split = plan.split[p];
+        for (int v = me; v < ntile * split; v += G) {
+            const int part = v / ntile, t = plan.tile0[p] + v - part * ntile;
+            const int ti = t / tj;
+            const long long row0 = (long long)ti * TILE, col0 = (long long)(t - ti * tj) * TILE;
+            const int s0 = (int)((long long)nk * part / split), s1 = (int)((long long)nk * (part + 1) / split);
+            floatx16 acc[4][2];
+            dwh_accumulate<false>(acc, L, Ap, n, Hp, m, row0, col0, s0, s1, -1);
+            // accumulator element e of a 32 x 32 block: row = 8*(e/4) + 4*(lane/32) + e%4, column = lane%32
+            if (split > 1) {
+                floatx4 *sp = slots + ((size_t)(plan.slot0[p] + v) * 8 + wave) * (8 * 4 * 64) + lane;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8_t a[3][2], b[3][2];
+                for (int xy = 0; xy < 8; ++xy)
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
+                    for (int q = 0; q < 4; ++q) {
+                        const floatx16 &c = acc[xy >> 1][xy & 1];
+                        sp[(xy * 4 + q) * 64] = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+                    }
+            } else {
+                const long long rb = row0 + L.wr * 128 + 4 * L.lhi, cb = col0 + L.wc * 64 + L.l32;
+                float *pp = P + rb * m + cb;
+                long long mm = m;
+                int rlim = (int)min(n - rb, 4096ll), clim = (int)min(m - cb, 4096ll);
+                asm volatile("" : "+v"(pp), "+s"(mm), "+v"(rlim), "+v"(clim));     // the addresses are worked out here, not ahead of the loop
 #pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    a[p][x] = *(const bf16x8_t *)(tb + a_off + (uint32_t)(32 * x * G3_PITCH + 32 * p + 16 * ks) * 2u);
-                    b[p][x] = *(const bf16x8_t *)(tb + b_off + (uint32_t)(32 * x * G3_PITCH + 32 * p + 16 * ks) * 2u);
-                }
+                for (int x = 0; x < 4; ++x)
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
+                    for (int e = 0; e < 16; ++e) {
+                        const int r = x * 32 + 8 * (e >> 2) + (e & 3);
+                        float *q = pp + r * mm;
+                        if (r < rlim) {
+                            if (clim > 0) q[0] = acc[x][0][e];
+                            if (clim > 32) q[32] = acc[x][1][e];
+                        }
+                    }
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no copy into the LDS is left behind
+}
+
+// P of the split tiles: their parts added up.  One wavefront per 32 x 32 block (16 workgroups per tile).
+__global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, long long n, long long m, int tj, TilePlan plan, int ph,
+                                                        const floatx4 *__restrict__ slots) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const int tv = blockIdx.x >> 4, blk = (blockIdx.x & 15) * 4 + wave;
+    const int t = plan.tile0[ph] + tv, ti = t / tj;
+    const int ow = blk >> 3, xy = blk & 7;
+    const long long rb = (long long)ti * TILE + (ow >> 2) * 128 + (xy >> 1) * 32 + 4 * lhi;
+    const long long cb = (long long)(t - ti * tj) * TILE + (ow & 3) * 64 + (xy & 1) * 32 + l32;
+    const floatx4 *sp = slots + ((size_t)(plan.slot0[ph] + tv) * 8 + ow) * (8 * 4 * 64) + xy * 256 + lane;
+    const size_t step = (size_t)plan.ntile[ph] * (8 * 8 * 4 * 64);
+    floatx4 s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = sp[q * 64];
+    for (int k = 1; k < plan.split[ph]; ++k) {
+        sp += step;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += sp[q * 64];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (rb + 8 * q + e < n && cb < m) P[(rb + 8 * q + e) * m + cb] = s[q][e];
+}
+
+// Loss only: dW_i H dW_i^T = sum over the 256-column blocks J of H of [ 2 sum_{K < J} dW_K H_KJ + dW_J H_JJ ] . dW_J, H being
+// symmetric: half the products.  The stages of all tiles -- tile (I, J) has those of the blocks K <= J -- form one line that is
+// cut into equal pieces, one per workgroup; the loss is linear in the sums, so the pieces of a tile need not meet: each
+// multiplies its own sums by dW_J and leaves 256 row sums (float64) behind, at partial[(tile + workgroup) * 256 ..] (tiles
+// and workgroups both count up along the line, so no two pieces share a number).
+struct LossLine {
+    int tj, G, nk;              // column blocks, workgroups, stages of the longest tile
+    long long per_row, total;   // stages of a row of tiles, of all
+    __host__ __device__ __forceinline__ long long before(int j) const { return 8ll * j * (j + 1); }          // of the tiles ahead of J in its row
+    __host__ __device__ __forceinline__ int stages(int j) const { return 16 * (j + 1) < nk ? 16 * (j + 1) : nk; }
+    __host__ __device__ __forceinline__ long long start(int g) const { return total * g / G; }               // first stage of workgroup g
+    __host__ __device__ __forceinline__ int owner(long long stage) const { return (int)(((stage + 1) * G - 1) / total); }
+};
+constexpr int LOSS_MAX_WG = 256;
+inline LossLine loss_line(int64_t n, int64_t m, int num_cu) {
+    LossLine l;
+    l.tj = (int)((m + TILE - 1) / TILE);
+    l.nk = (int)(m / GK);
+    l.per_row = l.before(l.tj - 1) + l.stages(l.tj - 1);
+    l.total = l.per_row * ((n + TILE - 1) / TILE);
+    const long long most = l.total / G_MIN_STAGES > 1 ? l.total / G_MIN_STAGES : 1;
+    l.G = num_cu < LOSS_MAX_WG ? num_cu : LOSS_MAX_WG;
+    if (l.G > most) l.G = (int)most;
+    return l;
+}
+
+__global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, long long n, long long m, LossLine line,
+                double *__restrict__ partial) {
+    extern __shared__ __align__(16) unsigned char g_smem[];
+    const int tid = threadIdx.x;
+    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid);
+    const int g = xcd_order(blockIdx.x, line.G);
+    long long at = line.start(g);
+    const long long end = line.start(g + 1);
+    while (at < end) {
+        const int I = (int)(at / line.per_row);
+        const int in_row = (int)(at - (long long)I * line.per_row);
+        int J = 0;
+        while (J + 1 < line.tj && line.before(J + 1) <= in_row) ++J;
+        const int s0 = in_row - (int)line.before(J);
+        const int s1 = (int)min((long long)line.stages(J), s0 + (end - at));
+        const long long row0 = (long long)I * TILE, col0 = (long long)J * TILE;
+        floatx16 acc[4][2];
+        // (a piece that starts inside the diagonal block is not doubled; one that ends ahead of it is, at the end)
+        dwh_accumulate<true>(acc, L, Ap, n, Hp, m, row0, col0, s0, s1, s0 < 16 * J ? 16 * J : -1);
+        const float twice = s1 <= 16 * J ? 2.0f : 1.0f;
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the tiles in LDS are no longer read or written
+        double *rsum = (double *)g_smem;                                              // [4][256]
+        const long long rb = row0 + L.wr * 128 + 4 * L.lhi, cb = col0 + L.wc * 64 + L.l32;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            double t[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const long long r = rb + x * 32 + 8 * (e >> 2) + (e & 3);
+                t[e] = 0.0;
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
-                    // smallest products first
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][x], b[1][y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][x], b[2][y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][x], b[0][y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][x], b[1][y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][x], b[0][y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][x], b[0][y], acc[x][y], 0, 0, 0);
-                }
-        }
-        // the next step's rows, requested a whole step ago, go to the other buffer (past the end: a repeat, never read)
-        store_step(buf ^ 1, 0, G3_CHUNKS);
-        load_step(min(kt + 2, nk - 1));
-        __syncthreads();
-    }
-
-    // epilogue.  Accumulator element e of a 32 x 32 tile: row = 8*(e/4) + 4*(lane/32) + e%4, column = lane%32.
-    double *rsum = (double *)g3_smem;          // [2][G3_BM]; the tiles are no longer read
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int rl = wr * 64 + i * 32 + 8 * (e >> 2) + 4 * lhi + (e & 3);
-            const int r = row0 + rl;
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int c = col0 + wc * 64 + j * 32 + l32;
-                if (r < n && c < m) {
-                    const float p = acc[i][j][e];
-                    if (STORE_P) P[(long long)r * m + c] = p;
-                    const uint16_t *ap = Ap + plane_index(r, n, c);
-                    const float dw = (bf16_f32(ap[0]) + bf16_f32(ap[32])) + bf16_f32(ap[64]);     // exact
-                    t += (double)p * (double)dw;
+                    const long long c = cb + 32 * y;
+                    if (r < n && c < m) {
+                        const uint16_t *ap = Ap + plane_index(r, n, c);
+                        const float dw = (bf16_f32(ap[0]) + bf16_f32(ap[16])) + bf16_f32(ap[32]);     // exact
+                        t[e] += (double)(acc[x][y][e] * twice) * (double)dw;
+                    }
                 }
             }
-            // sum over the 32 lanes that share this row
-            for (int o = 16; o >= 1; o >>= 1) t += __shfl_xor(t, o, 64);
-            if (l32 == 0) rsum[wc * G3_BM + rl] = t;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                for (int o = 16; o >= 1; o >>= 1) t[e] += __shfl_xor(t[e], o, 64);     // over the 32 lanes that share the row
+                if (L.l32 == 0) rsum[L.wc * TILE + L.wr * 128 + x * 32 + 8 * (e >> 2) + 4 * L.lhi + (e & 3)] = t[e];
+            }
         }
+        __syncthreads();
+        if (tid < TILE)
+            partial[((long long)I * line.tj + J + g) * TILE + tid] = (rsum[tid] + rsum[TILE + tid]) + (rsum[2 * TILE + tid] + rsum[3 * TILE + tid]);
+        at += s1 - s0;
     }
-    __syncthreads();
-    if (tid < G3_BM && row0 + tid < n) partial[(long long)blockIdx.x * n + row0 + tid] = rsum[tid] + rsum[G3_BM + tid];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// row_loss[i] = sum over column tiles (one thread per row, neighbouring threads on neighbouring rows of every
-// tile's partials; four running sums keep four loads in flight), left in partial[i] for the total.
-__global__ void __launch_bounds__(256) loss_rows_kernel(double *partial, int ntile, long long n, double *row_loss,
-                                                        long long row_stride) {
+// row_loss[i] = the pieces of the tiles of its row, in the order of the line; left in rows[i] for the total.
+__global__ void __launch_bounds__(256) loss_rows_kernel(const double *__restrict__ partial, LossLine line, long long n, double *rows,
+                                                        double *row_loss, long long row_stride) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    double r[4] = {0.0, 0.0, 0.0, 0.0};
-    int t = 0;
-    for (; t + 3 < ntile; t += 4) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] += partial[(long long)(t + u) * n + i];
+    const int I = blockIdx.x;
+    const long long first = (long long)I * line.per_row;
+    double tot = 0.0;
+    for (int J = 0; J < line.tj; ++J) {
+        const long long s = first + line.before(J);
+        const int g0 = line.owner(s), g1 = line.owner(s + line.stages(J) - 1);
+        for (int g = g0; g <= g1; ++g) tot += partial[((long long)I * line.tj + J + g) * TILE + threadIdx.x];
     }
-    for (; t < ntile; ++t) r[t & 3] += partial[(long long)t * n + i];
-    const double tot = (r[0] + r[1]) + (r[2] + r[3]);
     if (row_loss) row_loss[i * row_stride] = tot;
-    partial[i] = tot;
+    rows[i] = tot;
 }
 
-// loss = sum_i partial[i] (single workgroup, fixed order).
-__global__ void __launch_bounds__(1024) loss_total_kernel(const double *partial, long long n, double *loss) {
+// loss = sum_i rows[i] (single workgroup, fixed order).
+__global__ void __launch_bounds__(1024) loss_total_kernel(const double *rows, long long n, double *loss) {
     __shared__ double sh[16];
     double acc = 0.0;
-    for (long long i = threadIdx.x; i < n; i += 1024) acc += partial[i];
+    for (long long i = threadIdx.x; i < n; i += 1024) acc += rows[i];
     for (int d = 32; d >= 1; d >>= 1) acc += __shfl_down(acc, d, 64);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -454,19 +499,12 @@ __global__ void __launch_bounds__(1024) loss_total_kernel(const double *partial,
     }
 }
 
-static void launch_loss_finish(hipStream_t stream, double *partial, int ntile, long long n, double *loss, double *row_loss,
-                               long long row_stride) {
-    hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, partial, ntile, n,
-                       row_loss, row_stride);
-    hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(1024), 0, stream, (const double *)partial, n, loss);
-}
-
 // Gradient terms.  One workgroup walks STRIP consecutive rows; per row it forms
 // Q_ik = sum_{j in k} P_ij alpha_j (LDS bins as in row_prep_kernel), then adds each column's term to the
 // thread's private column sums.  A thread owns the columns tid, tid + 256, ...: with REG (m <= 16 * 256)
 // their sums, alpha and the row's P and labels stay in registers, so a row is read from HBM once;
 // otherwise the sums live in gpart and the row is read twice.  gpart[strip][l] is reduced over the strips
-// afterwards.
+// afterwards.  The strip's share of the loss, sum P_ij dW_ij with dW as row_prep_kernel forms it, falls out on the way.
 constexpr int GRAD_NC = 16;
 
 template <bool REG>
@@ -474,7 +512,9 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
                                                                  long long n, long long m, long long ld,
                                                                  const uint8_t *labels, const float *P,
                                                                  const double *cent, const double *Den,
-                                                                 double *gpart, bool vec4) {
+                                                                 double *gpart, double *lossp, bool vec4) {
+    __shared__ double lsum[4];
+    double lacc = 0.0;
     __shared__ double binQ[BIN_SETS][16];
     __shared__ double rsh[16], csh[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -564,12 +604,14 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
                 const double a = (double)al[c], cc = csh[lv[c]];
                 const double term = (double)pv[c] * cc + rsh[lv[c]] * (double)sv[c] * ((double)wv[c] - 2.0 * a * cc);
                 gacc[c] += -2.0 * term;
+                lacc += (double)pv[c] * (double)(float)((double)wv[c] - a * cc);       // (columns past the row: P = 0)
             }
         } else {
             for (long long l = tid; l < m; l += PREP_THREADS) {
                 const int k = Lr[l] & 15;
                 const double a = (double)alpha[l], cc = csh[k];
                 const double term = (double)Pr[l] * cc + rsh[k] * (double)Sr[l] * ((double)Wr[l] - 2.0 * a * cc);
+                lacc += (double)Pr[l] * (double)(float)((double)Wr[l] - a * cc);
                 gp[l] += -2.0 * term;   // the same thread owns column l for every row of the strip
             }
         }
@@ -581,18 +623,34 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
             if (l < m) gp[l] = gacc[c];
         }
     }
+    const double l = block_sum_256(lacc, lsum);
+    if (tid == 0) lossp[blockIdx.x] = l;
 }
 
 // Column sums of the per-strip gradient terms, then the Adam update.  16 columns per workgroup (m / 16 workgroups:
 // one per CU at 4096 columns); the strips are shared out to 64 groups of threads (a column's 64 partial sums are
-// added in a fixed order).
+// added in a fixed order).  One more workgroup adds up the strips' shares of the loss.
 constexpr int ADAM_COLS = 16, ADAM_GROUPS = 64;
 
 __global__ void __launch_bounds__(ADAM_COLS * ADAM_GROUPS) adam_kernel(const double *gpart, int nstrip, long long m,
                                                                       float *alpha, float *am, float *av, float lr,
                                                                       float beta1, float beta2, float eps, float bc1,
-                                                                      float bc2, float *grad_out) {
+                                                                      float bc2, float *grad_out, const double *lossp, double *loss) {
     __shared__ double part[ADAM_GROUPS][ADAM_COLS];
+    if (blockIdx.x == gridDim.x - 1) {
+        double *sh = &part[0][0];
+        double a = 0.0;
+        for (int i = threadIdx.x; i < nstrip; i += ADAM_COLS * ADAM_GROUPS) a += lossp[i];
+        for (int d = 32; d >= 1; d >>= 1) a += __shfl_down(a, d, 64);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double s = 0.0;
+            for (int w = 0; w < ADAM_COLS * ADAM_GROUPS / 64; ++w) s += sh[w];
+            *loss = s;
+        }
+        return;
+    }
     const int c = threadIdx.x % ADAM_COLS, g = threadIdx.x / ADAM_COLS;
     const long long l = (long long)blockIdx.x * ADAM_COLS + c;
     double acc = 0.0;
@@ -615,73 +673,68 @@ __global__ void __launch_bounds__(ADAM_COLS * ADAM_GROUPS) adam_kernel(const dou
 }
 
 struct LossWs {
-    float *dW, *P;
-    uint16_t *dWp, *Hp;      // pieces of dW and of H for dwh_gemm3_kernel (null: the float32 kernel is used)
-    double *cent, *Den, *partial, *gpart;
-    int ntile, nstrip;
+    float *P;
+    uint16_t *dWp, *Hp;      // pieces of dW and of H
+    double *cent, *Den, *partial, *rows, *gpart, *lossp;
+    floatx4 *slots;
+    TilePlan plan;
+    LossLine line;
+    int nstrip, tj;
+    long long tiles;
 };
 
-// The contraction runs on the bf16 matrix cores when the rows split into whole 32-k blocks and are long enough to
-// fill a step pipeline; otherwise on the float32 ones.
-bool use_pieces(int64_t m) { return (m % G3_BK) == 0 && m >= 128; }
-
-skim_status carve(skim_ctx *ctx, int64_t n, int64_t m, bool need_grad, LossWs &w) {
-    skim_ws_cursor cur{(char *)ctx->ws, 0, ctx->ws_bytes};
-    w.ntile = (int)((m + BN - 1) / BN);
-    w.nstrip = (int)((n + STRIP - 1) / STRIP);
-    w.dW = nullptr;
-    w.dWp = w.Hp = nullptr;
-    if (use_pieces(m)) {        // (first in the workspace: skim_train_scale keeps the pieces of H across its steps)
-        w.Hp = (uint16_t *)cur.take((size_t)m * m * 3 * sizeof(uint16_t));
-        w.dWp = (uint16_t *)cur.take((size_t)n * m * 3 * sizeof(uint16_t));
-    } else {
-        w.dW = (float *)cur.take((size_t)n * m * sizeof(float));
+// The plan of dwh_kernel; whole tiles go straight into P, only the parts of split ones have slots.  Returns their number.
+long long dwh_plan(TilePlan &plan, int64_t n, int64_t m, int num_cu) {
+    const long long tiles = (n + TILE - 1) / TILE * ((m + TILE - 1) / TILE);
+    (void)skim_make_plan(plan, num_cu, tiles, (int)(m / GK), G_MIN_STAGES, G_PHASE_COST, false);
+    long long slots = 0;
+    for (int p = 0; p < plan.nph; ++p) {
+        plan.slot0[p] = (int)slots;
+        if (plan.split[p] > 1) slots += (long long)plan.ntile[p] * plan.split[p];
     }
+    return slots;
+}
+
+// grad: what a scale step needs (P and the gradient's partial sums) instead of what the loss needs
+skim_status carve(skim_ctx *ctx, int64_t n, int64_t m, bool grad, LossWs &w) {
+    skim_ws_cursor cur{(char *)ctx->ws, 0, ctx->ws_bytes};
+    w.nstrip = (int)((n + STRIP - 1) / STRIP);
+    w.tj = (int)((m + TILE - 1) / TILE);
+    w.tiles = (n + TILE - 1) / TILE * w.tj;
+    // (H first: skim_train_scale and skim_error_table_lfull keep its pieces across their steps)
+    w.Hp = (uint16_t *)cur.take((size_t)m * m * 3 * sizeof(uint16_t));
+    w.dWp = (uint16_t *)cur.take((size_t)n * m * 3 * sizeof(uint16_t));
     w.cent = (double *)cur.take((size_t)n * 16 * sizeof(double));
     w.Den = (double *)cur.take((size_t)n * 16 * sizeof(double));
-    w.partial = (double *)cur.take((size_t)w.ntile * n * sizeof(double));
-    w.P = nullptr;
-    w.gpart = nullptr;
-    bool ok = (w.dW || (w.dWp && w.Hp)) && w.cent && w.Den && w.partial;
-    if (need_grad) {
+    bool ok = w.dWp && w.Hp && w.cent && w.Den;
+    if (grad) {
         w.P = (float *)cur.take((size_t)n * m * sizeof(float));
         w.gpart = (double *)cur.take((size_t)w.nstrip * m * sizeof(double));
-        ok = ok && w.P && w.gpart;
+        w.lossp = (double *)cur.take((size_t)w.nstrip * sizeof(double));
+        const long long slots = dwh_plan(w.plan, n, m, ctx->num_cu);
+        w.slots = (floatx4 *)cur.take((size_t)slots * TILE_SLOT_BYTES);
+        if (!w.slots) (void)skim_make_plan(w.plan, ctx->num_cu, w.tiles, (int)(m / GK), G_MIN_STAGES, G_PHASE_COST, true);
+        ok = ok && w.P && w.gpart && w.lossp;
+    } else {
+        w.line = loss_line(n, m, ctx->num_cu);
+        w.partial = (double *)cur.take((size_t)(w.tiles + w.line.G) * TILE * sizeof(double));
+        w.rows = (double *)cur.take((size_t)n * sizeof(double));
+        ok = ok && w.partial && w.rows;
     }
     if (!ok) SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
     return SKIM_OK;
 }
 
-// P = dW H (and the per-tile row sums of P o dW) by whichever kernel the workspace was carved for.  h_ready: the
-// pieces of H are already in w.Hp (skim_train_scale splits H once per round of steps).
-skim_status launch_contraction(skim_ctx *ctx, const LossWs &w, const float *H, int64_t n, int64_t m, bool store_p,
-                               bool h_ready) {
-    if (w.dWp) {
-        if (!ctx->gemm3_lds_enabled) {
-            SKIM_HIP(ctx, hipFuncSetAttribute((const void *)dwh_gemm3_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G3_LDS_BYTES));
-            SKIM_HIP(ctx, hipFuncSetAttribute((const void *)dwh_gemm3_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G3_LDS_BYTES));
-            ctx->gemm3_lds_enabled = 1;
-        }
-        if (!h_ready)
-            hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((m * (m / 8) + 255) / 256)), dim3(256), 0, ctx->stream, H,
-                               (long long)m, (long long)m, w.Hp);
-        const dim3 grid((unsigned)((m + G3_BN - 1) / G3_BN), (unsigned)((n + G3_BM - 1) / G3_BM));
-        if (store_p)
-            hipLaunchKernelGGL(dwh_gemm3_kernel<true>, grid, dim3(G3_THREADS), G3_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (int)n,
-                               (int)m, w.P, w.partial);
-        else
-            hipLaunchKernelGGL(dwh_gemm3_kernel<false>, grid, dim3(G3_THREADS), G3_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (int)n,
-                               (int)m, (float *)nullptr, w.partial);
-    } else {
-        const dim3 grid(w.ntile, (unsigned)((n + BM - 1) / BM));
-        if (store_p)
-            hipLaunchKernelGGL(dwh_gemm_kernel<true>, grid, dim3(GEMM_THREADS), 0, ctx->stream, w.dW, H, (int)n, (int)m, w.P,
-                               w.partial);
-        else
-            hipLaunchKernelGGL(dwh_gemm_kernel<false>, grid, dim3(GEMM_THREADS), 0, ctx->stream, w.dW, H, (int)n, (int)m,
-                               (float *)nullptr, w.partial);
-    }
+skim_status enable_lds(skim_ctx *ctx) {
+    if (ctx->gemm3_lds_enabled) return SKIM_OK;
+    SKIM_HIP(ctx, hipFuncSetAttribute((const void *)dwh_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G_LDS_BYTES));
+    SKIM_HIP(ctx, hipFuncSetAttribute((const void *)dwh_loss_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G_LDS_BYTES));
+    ctx->gemm3_lds_enabled = 1;
     return SKIM_OK;
+}
+
+void launch_split(skim_ctx *ctx, const LossWs &w, const float *H, int64_t m, bool lower) {
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((m * (m / 8) + 255) / 256)), dim3(256), 0, ctx->stream, H, (long long)m, w.Hp, lower);
 }
 
 // rows of W and S start 16-byte aligned, alpha is, and the labels of a row start 4-byte aligned (m is a multiple of 16)
@@ -690,36 +743,48 @@ bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t
 }
 
 skim_status check_shape(skim_ctx *ctx, int64_t n, int64_t m, int64_t ld) {
-    if (n < 1 || n > 0x7fffffff || m < BK || m > 0x7fffffff || ld < m || (m % BK) != 0)
-        SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "layer loss needs n >= 1, m a multiple of %d, ld >= m (n=%lld m=%lld ld=%lld)", BK,
+    if (n < 1 || n > 0x7fffffff || m < GK || m > 0x7fffffff || ld < m || (m % GK) != 0)
+        SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "layer loss needs n >= 1, m a multiple of %d, ld >= m (n=%lld m=%lld ld=%lld)", GK,
                   (long long)n, (long long)m, (long long)ld);
     return SKIM_OK;
 }
 
 }  // namespace
 
+size_t skim_dwh_slot_bytes(int64_t n, int64_t m, int num_cu) {
+    if (n < 1 || m < GK || (n + TILE - 1) / TILE * ((m + TILE - 1) / TILE) > 0x7fffffffll) return 0;
+    TilePlan plan;
+    return (size_t)dwh_plan(plan, n, m, num_cu) * TILE_SLOT_BYTES;
+}
+
 extern "C" skim_status skim_layer_loss(skim_ctx *ctx, const float *W, const float *S, const float *alpha,
                                        const float *H, int64_t n, int64_t m, int64_t ld, const uint8_t *labels,
                                        double *loss, double *row_loss) {
-    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, loss, row_loss, 1, nullptr, 0, 0);
+    if (ctx && !loss) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
+    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, loss, row_loss, 1, nullptr, 0, 0, false);
 }
 
 skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *S, const float *alpha, const float *H,
                                     int64_t n, int64_t m, int64_t ld, const uint8_t *labels, double *loss,
                                     double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
-                                    int kept_n) {
+                                    int kept_n, bool h_ready) {
     skim_status st = skim_enter(ctx);
     if (st != SKIM_OK) return st;
-    if (!W || !S || !H || !labels || !loss) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
+    if (!W || !S || !H || !labels) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
     if ((st = check_shape(ctx, n, m, ld)) != SKIM_OK) return st;
     if ((uintptr_t)H & 15) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: H must be 16-byte aligned");
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
     hipLaunchKernelGGL(row_prep_kernel, dim3((unsigned)n), dim3(PREP_THREADS), 0, ctx->stream, W, S, alpha, (long long)m,
-                       (long long)ld, labels, w.cent, w.Den, w.dW, w.dWp, kept, (long long)kept_stride, kept_n,
+                       (long long)ld, labels, w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n,
                        rows_vec4(W, S, alpha, labels, ld));
-    if ((st = launch_contraction(ctx, w, H, n, m, false, false)) != SKIM_OK) return st;
-    launch_loss_finish(ctx->stream, w.partial, w.ntile, (long long)n, loss, row_loss, (long long)row_stride);
+    if ((st = enable_lds(ctx)) != SKIM_OK) return st;
+    if (!h_ready) launch_split(ctx, w, H, m, true);
+    hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
+                       (long long)m, w.line, w.partial);
+    hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
+                       w.line, (long long)n, w.rows, row_loss, (long long)row_stride);
+    if (loss) hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double *)w.rows, (long long)n, loss);
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;
 }
@@ -751,25 +816,36 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     LossWs w;
     if ((st = carve(ctx, n, m, true, w)) != SKIM_OK) return st;
     hipLaunchKernelGGL(row_prep_kernel, dim3((unsigned)n), dim3(PREP_THREADS), 0, ctx->stream, W, S, (const float *)alpha,
-                       (long long)m, (long long)ld, labels, w.cent, w.Den, w.dW, w.dWp, (const double *)nullptr, 0ll, 0,
+                       (long long)m, (long long)ld, labels, w.cent, w.Den, w.dWp, (const double *)nullptr, 0ll, 0,
                        rows_vec4(W, S, alpha, labels, ld));
-    if ((st = launch_contraction(ctx, w, H, n, m, true, h_ready)) != SKIM_OK) return st;
-    launch_loss_finish(ctx->stream, w.partial, w.ntile, (long long)n, loss_before, (double *)nullptr, 1ll);
+    if ((st = enable_lds(ctx)) != SKIM_OK) return st;
+    if (!h_ready) launch_split(ctx, w, H, m, false);
+    {
+        long long grid = 0;
+        for (int p = 0; p < w.plan.nph; ++p) grid = max(grid, (long long)w.plan.ntile[p] * w.plan.split[p]);
+        if (grid > ctx->num_cu) grid = ctx->num_cu;
+        hipLaunchKernelGGL(dwh_kernel, dim3((unsigned)grid), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
+                           (long long)m, w.tj, w.plan, w.P, w.slots);
+        for (int p = 0; p < w.plan.nph; ++p)
+            if (w.plan.split[p] > 1)
+                hipLaunchKernelGGL(dwh_parts_kernel, dim3((unsigned)(w.plan.ntile[p] * 16)), dim3(256), 0, ctx->stream, w.P, (long long)n,
+                                   (long long)m, w.tj, w.plan, p, (const floatx4 *)w.slots);
+    }
     // rows of W, S, P start 16-byte aligned and the labels of a row 4-byte aligned (m is a multiple of 16)
     const bool vec4 = rows_vec4(W, S, alpha, labels, ld) && ((uintptr_t)w.P & 15) == 0;
     if (m <= (int64_t)GRAD_NC * PREP_THREADS)
         hipLaunchKernelGGL(grad_rows_kernel<true>, dim3(w.nstrip), dim3(PREP_THREADS), 0, ctx->stream, W, S,
                            (const float *)alpha, (long long)n, (long long)m, (long long)ld, labels, w.P, w.cent, w.Den,
-                           w.gpart, vec4);
+                           w.gpart, w.lossp, vec4);
     else
         hipLaunchKernelGGL(grad_rows_kernel<false>, dim3(w.nstrip), dim3(PREP_THREADS), 0, ctx->stream, W, S,
                            (const float *)alpha, (long long)n, (long long)m, (long long)ld, labels, w.P, w.cent, w.Den,
-                           w.gpart, false);
+                           w.gpart, w.lossp, false);
     const double lr = (double)opts->lr0 * pow((double)opts->decay, (double)((t - 1) / opts->decay_every));
     const double bc1 = 1.0 - pow((double)opts->beta1, (double)t), bc2 = 1.0 - pow((double)opts->beta2, (double)t);
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((m + ADAM_COLS - 1) / ADAM_COLS)), dim3(ADAM_COLS * ADAM_GROUPS), 0, ctx->stream, w.gpart, w.nstrip,
+    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((m + ADAM_COLS - 1) / ADAM_COLS) + 1u), dim3(ADAM_COLS * ADAM_GROUPS), 0, ctx->stream, w.gpart, w.nstrip,
                        (long long)m, alpha, adam_m, adam_v, (float)lr, opts->beta1, opts->beta2, opts->eps, (float)bc1,
-                       (float)bc2, grad_out);
+                       (float)bc2, grad_out, (const double *)w.lossp, loss_before);
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;
 }
@@ -815,7 +891,8 @@ extern "C" skim_status skim_train_scale(skim_ctx *ctx, const float *W, const flo
     if ((st = check_shape(ctx, n, m, ld)) != SKIM_OK) return st;
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
-    if ((st = skim_layer_loss(ctx, W, S, alpha, H, n, m, ld, labels, loss_trace + slot, nullptr)) != SKIM_OK) return st;
+    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, loss_trace + slot, nullptr, 1, nullptr, 0, 0, steps > 0)) != SKIM_OK)
+        return st;
     SKIM_HIP(ctx, hipMemcpyAsync(centroids, w.cent, (size_t)n * 16 * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
     return SKIM_OK;
 }
