@@ -1,59 +1,9 @@
 // Error pre-recording with the layer-wise error (Alg. 3, pre-recording loop with Err(.) in its L-full
 // form, Sec. 3.4 and the remark under Alg. 1): for every bit width the rows are clustered as
 // in skim_error_table, each weight gets the label of its cluster, and the error of channel i
-// is dW_i H dW_i^T.  Composition of the clustering call, a label kernel and the layer-loss
-// kernels; one contraction dW * H per bit width.
+// is dW_i H dW_i^T.  Composition of the clustering call and the layer-loss kernels, which work the
+// labels out themselves; one contraction dW * H per bit width.
 #include "skim_common.h"
-
-#include <math.h>
-
-namespace {
-
-constexpr int LAB_THREADS = 256;
-
-// labels[i][j] = cluster of w~_ij at bit width b, from the clusters' upper bounds (the largest
-// member of each cluster, -inf for an empty one): the cluster with the smallest bound >= w~.
-__global__ void __launch_bounds__(LAB_THREADS) labels_from_bounds_kernel(const float *W, const float *alpha, long long m,
-                                                                       long long ld, int K, const float *upper_all,
-                                                                       int stride, int block_off, uint8_t *labels) {
-    __shared__ float thr[16];
-    __shared__ int thl[16];
-    const long long row = blockIdx.x;
-    const int tid = threadIdx.x;
-    const float *up_row = upper_all + row * stride + block_off;
-    if (tid < 16) {
-        thr[tid] = INFINITY;
-        thl[tid] = 0;
-    }
-    __syncthreads();
-    if (tid < K) {
-        const float up = up_row[tid];
-        int rank = 0;
-        for (int j = 0; j < K; ++j) {
-            const float uj = up_row[j];
-            rank += (uj < up || (uj == up && j < tid)) ? 1 : 0;
-        }
-        thr[rank] = up;
-        thl[rank] = tid;
-    }
-    __syncthreads();
-    // bounds ascending (empty clusters, -inf, first), +inf beyond the K-th
-    if (tid >= K && tid < 16) thl[tid] = thl[K - 1];
-    __syncthreads();
-    const float *Wr = W + row * ld;
-    uint8_t *Lr = labels + row * m;
-    for (long long j = tid; j < m; j += LAB_THREADS) {
-        const float w = Wr[j];
-        const float wt = alpha ? __fdiv_rn(w, alpha[j]) : w;
-        int pos = (thr[7] < wt) ? 8 : 0;
-        pos += (thr[pos + 3] < wt) ? 4 : 0;
-        pos += (thr[pos + 1] < wt) ? 2 : 0;
-        pos += (thr[pos] < wt) ? 1 : 0;
-        Lr[j] = (uint8_t)thl[pos];
-    }
-}
-
-}  // namespace
 
 extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, const float *S, const float *alpha,
                                               const float *H, int64_t n, int64_t m, int64_t ld, int bmin, int bmax,
@@ -76,13 +26,17 @@ extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, con
         return st;
     const int stride = (2 << bmax) - (1 << bmin);
     for (int b = bmin; b <= bmax; ++b) {
-        hipLaunchKernelGGL(labels_from_bounds_kernel, dim3((unsigned)n), dim3(LAB_THREADS), 0, ctx->stream, W, alpha,
-                           (long long)m, (long long)ld, 1 << b, upper_all, stride, (1 << b) - (1 << bmin), labels_work);
-        SKIM_HIP(ctx, hipGetLastError());
+        const int off = (1 << b) - (1 << bmin);
+        // the labels are those of the clusters' upper bounds; the caller's buffer holds the last bit width's on return
+        skim_label_bounds bounds;
+        bounds.bits = b;
+        bounds.upper = upper_all + off;
+        bounds.upper_stride = stride;
+        bounds.labels_out = b == bmax ? labels_work : nullptr;
         // a cluster whose members carry no sensitivity mass keeps the centroid the clustering left it with
         // (the value the packed codebook holds), not the 0 a weighted mean over no mass would give
-        if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels_work, nullptr, E_full + (b - bmin),
-                                          nb, centroids_all + ((1 << b) - (1 << bmin)), stride, 1 << b, b > bmin)) != SKIM_OK)
+        if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, nullptr, bounds, nullptr, E_full + (b - bmin), nb,
+                                          centroids_all + off, stride, 1 << b, b > bmin)) != SKIM_OK)
             return st;
     }
     return SKIM_OK;

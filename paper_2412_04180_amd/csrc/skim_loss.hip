@@ -32,11 +32,13 @@ __device__ __forceinline__ void split3(float x, uint32_t &p1, uint32_t &p2, uint
     r -= bf16_f32(p2);                // exact; at most 8 significant bits are left
     p3 = bf16_rn(r);
 }
-// Layout of a split matrix ("planes"): for every block of 16 k, row after row, [piece 1 (16) | piece 2 (16) | piece 3 (16)]
-// as 96 contiguous bytes: the rows of a tile for one 16-k step are one contiguous region of memory.
+// Layout of a split matrix ("planes"): groups of 4 rows; a group holds, for every block of 16 k, its 4 rows' [piece 1 (16) |
+// piece 2 (16) | piece 3 (16)], 384 contiguous bytes.  A tile reads whole 128-byte lines for a 16-k step, and the four
+// rows one workgroup writes are one contiguous region of memory.
 constexpr int GK = 16;
-__device__ __forceinline__ size_t plane_index(long long row, long long rows, long long k) {
-    return ((size_t)(k >> 4) * (size_t)rows + (size_t)row) * 48 + (size_t)(k & 15);     // piece p at + 16 p
+__host__ __device__ __forceinline__ size_t plane_rows(long long rows) { return (size_t)(rows + 3) & ~(size_t)3; }      // rows stored
+__device__ __forceinline__ size_t plane_index(long long row, long long k, long long m) {
+    return ((size_t)(row >> 2) * (size_t)(m >> 4) + (size_t)(k >> 4)) * 192 + (size_t)(row & 3) * 48 + (size_t)(k & 15);     // piece p at + 16 p
 }
 
 constexpr int PREP_THREADS = 256;
@@ -64,87 +66,209 @@ __device__ __forceinline__ double bin_total(const double (*bins)[16], int k) {
     return t;
 }
 
+// four neighbouring values, in one load where the caller's rows allow it
+__device__ __forceinline__ float4 load4(const float *p, bool vec) { return vec ? *(const float4 *)p : make_float4(p[0], p[1], p[2], p[3]); }
+__device__ __forceinline__ uint32_t load4(const uint8_t *p, bool vec) {
+    return vec ? *(const uint32_t *)p : (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
+}
+
 // Per row: weighted cluster sums with fixed labels -> centroids c (n x 16 float64),
 // masses Den (n x 16 float64), and the row of dW as three bfloat16 pieces per value.
+// BITS == 0: labels are read.  BITS == 1 .. 4: they are worked out from the clusters' upper bounds (the largest member of each
+// cluster, -inf for an empty one) at upper + row * upper_stride: the cluster with the smallest bound >= w~; labels_out
+// (optional) receives them.
 // kept (optional): per row, at kept + row * kept_stride, the centroid a cluster keeps when its members carry no
 // sensitivity mass (what the clustering that produced the labels left there); without it such a centroid is 0.
-__global__ void __launch_bounds__(PREP_THREADS) row_prep_kernel(const float *W, const float *S, const float *alpha,
-                                                                long long m, long long ld, const uint8_t *labels,
-                                                                double *cent, double *Den, uint16_t *dWp,
-                                                                const double *kept, long long kept_stride, int kept_n,
-                                                                bool vec4) {
-    __shared__ double binD[BIN_SETS][16], binN[BIN_SETS][16];
-    __shared__ double csh[16];
-    const long long row = blockIdx.x, nrows = gridDim.x;
+// A workgroup takes 4 rows (one group of the planes: it writes one contiguous region), four wavefronts each, four columns
+// per lane and step.  KEEP > 0: the row takes at most KEEP steps, and its weights and labels stay in registers between the
+// two passes; 0: longer rows are read twice.  Bound: HBM (9 to 14 bytes read and 6 written per weight):
+// 66 us at 4096 x 4096, 252 MB (54 us at the rate of a copy); one workgroup per row, its pieces in 32-byte scraps: 81.
+// Labels from bounds: 60 to 72 us, instead of 66 and 27 for a kernel that writes them first.
+constexpr int ROWP_WAVES = 16, ROWP_COPIES = 8;      // copies of the bins per wavefront, picked by the lane
+template <int BITS, int KEEP>
+__global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
+                                                                   long long m, long long ld, const uint8_t *labels, const float *upper,
+                                                                   long long upper_stride, uint8_t *labels_out, double *cent, double *Den,
+                                                                   uint16_t *dWp, const double *kept, long long kept_stride, int kept_n,
+                                                                   bool vec4) {
+    constexpr int WAVES = ROWP_WAVES, K = 1 << BITS, NSC = BITS == 4 ? 3 : K - 1;
+    __shared__ double binD[WAVES][ROWP_COPIES][16], binN[WAVES][ROWP_COPIES][16];
+    __shared__ double csh[WAVES][16];
+    __shared__ __align__(16) float thr[WAVES][16];
+    __shared__ int thl[WAVES][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sub = wave & 3;                                       // quarter of the row's steps
+    const bool live = (long long)blockIdx.x * 4 + (wave >> 2) < n;
+    const long long row = live ? (long long)blockIdx.x * 4 + (wave >> 2) : n - 1;
+    const long long mm = live ? m : 0;                              // (a row past the end has no columns)
     const float *Wr = W + row * ld, *Sr = S + row * ld;
-    const uint8_t *Lr = labels + row * m;
-    static_assert(BIN_SETS * 16 == PREP_THREADS, "one bin per thread to clear");
-    (&binD[0][0])[tid] = 0.0;
-    (&binN[0][0])[tid] = 0.0;
-    __syncthreads();
-    double *myD = binD[wave * BIN_COPIES + (lane & (BIN_COPIES - 1))];
-    double *myN = binN[wave * BIN_COPIES + (lane & (BIN_COPIES - 1))];
-    auto add_element = [&](float wt, float st, float a, int l) {
-        if (alpha) {
-            wt = __fdiv_rn(wt, a);
-            st = __fmul_rn(__fmul_rn(st, a), a);
-        }
-        atomicAdd(&myD[l], (double)st);
-        atomicAdd(&myN[l], (double)st * (double)wt);
-    };
-    // vec4: rows start 16-byte aligned (labels 4-byte) and m is a multiple of 4: four neighbouring columns per
-    // thread and step, a quarter of the load instructions
-    if (vec4) {
-        for (long long j = 4ll * tid; j < m; j += 4 * PREP_THREADS) {
-            const float4 w4 = *(const float4 *)(Wr + j), s4 = *(const float4 *)(Sr + j);
-            const float4 a4 = alpha ? *(const float4 *)(alpha + j) : make_float4(1.f, 1.f, 1.f, 1.f);
-            const uint32_t l4 = *(const uint32_t *)(Lr + j);
-            add_element(w4.x, s4.x, a4.x, (int)(l4 & 15u));
-            add_element(w4.y, s4.y, a4.y, (int)((l4 >> 8) & 15u));
-            add_element(w4.z, s4.z, a4.z, (int)((l4 >> 16) & 15u));
-            add_element(w4.w, s4.w, a4.w, (int)((l4 >> 24) & 15u));
-        }
-    } else {
-        for (long long j = tid; j < m; j += PREP_THREADS) add_element(Wr[j], Sr[j], alpha ? alpha[j] : 1.0f, Lr[j] & 15);
-    }
-    __syncthreads();
-    if (tid < 16) {
-        const double d = bin_total(binD, tid), nn = bin_total(binN, tid);
-        const double c = d > 0.0 ? nn / d : ((kept && tid < kept_n) ? kept[row * kept_stride + tid] : 0.0);
-        csh[tid] = c;
-        cent[row * 16 + tid] = c;
-        Den[row * 16 + tid] = d;
-    }
-    __syncthreads();
-    if (vec4) {
-        for (long long j = 4ll * tid; j < m; j += 4 * PREP_THREADS) {
-            const float4 w4 = *(const float4 *)(Wr + j);
-            const float4 a4 = alpha ? *(const float4 *)(alpha + j) : make_float4(1.f, 1.f, 1.f, 1.f);
-            const uint32_t l4 = *(const uint32_t *)(Lr + j);
-            const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
-            uint32_t pc[3][4];
+    const uint8_t *Lr = BITS == 0 ? labels + row * m : nullptr;
+    uint8_t *Lo = BITS > 0 && labels_out ? labels_out + row * m : nullptr;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float d = (float)((double)wv[e] - (double)av[e] * csh[(l4 >> (8 * e)) & 15u]);
-                split3(d, pc[0][e], pc[1][e], pc[2][e]);
+    for (int q = 0; q < ROWP_COPIES / 4; ++q) {
+        (&binD[wave][0][0])[64 * q + lane] = 0.0;
+        (&binN[wave][0][0])[64 * q + lane] = 0.0;
+    }
+    float ts[NSC > 0 ? NSC : 1];
+    if constexpr (BITS > 0) {
+        // bounds ascending (empty clusters, -inf, first; equal ones by cluster), +inf beyond the last
+        if (lane < 16) {
+            const float *up_row = upper + row * upper_stride;
+            const float up = lane < K ? up_row[lane] : INFINITY;
+            int rank = lane;
+            if (lane < K) {
+                rank = 0;
+                for (int j = 0; j < K; ++j) {
+                    const float uj = up_row[j];
+                    rank += (uj < up || (uj == up && j < lane)) ? 1 : 0;
+                }
             }
-            uint16_t *o = dWp + plane_index(row, nrows, j);   // four neighbouring k stay inside one block of 16
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                *(uint2 *)(o + 16 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
+            thr[wave][rank] = up;
+            thl[wave][rank] = lane;
         }
-        return;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < NSC; ++k)
+            ts[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(thr[wave][BITS == 4 ? 4 * k + 3 : k])));
     }
-    for (long long j = tid; j < m; j += PREP_THREADS) {
-        const double a = alpha ? (double)alpha[j] : 1.0;
-        const float d = (float)((double)Wr[j] - a * csh[Lr[j] & 15]);
-        uint32_t p1, p2, p3;
-        split3(d, p1, p2, p3);
-        uint16_t *o = dWp + plane_index(row, nrows, j);
-        o[0] = (uint16_t)p1;
-        o[16] = (uint16_t)p2;
-        o[32] = (uint16_t)p3;
+    auto label_of = [&](float wt) -> int {      // position = number of bounds below the weight
+        int pos = 0;
+        if (BITS == 4) {
+            int q = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) q += (ts[k] < wt) ? 1 : 0;
+            const float4 t4 = *(const float4 *)&thr[wave][4 * q];
+            pos = 4 * q + ((t4.x < wt) ? 1 : 0) + ((t4.y < wt) ? 1 : 0) + ((t4.z < wt) ? 1 : 0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < NSC; ++k) pos += (ts[k] < wt) ? 1 : 0;
+        }
+        return thl[wave][pos];
+    };
+    double *myD = binD[wave][lane & (ROWP_COPIES - 1)], *myN = binN[wave][lane & (ROWP_COPIES - 1)];
+    // two or four clusters: their sums in registers (in the bins most lanes of a wavefront would meet on the same few addresses)
+    constexpr int REGS = BITS == 1 || BITS == 2 ? K : 0;
+    double rd[REGS > 0 ? REGS : 1], rn[REGS > 0 ? REGS : 1];
+#pragma unroll
+    for (int k = 0; k < REGS; ++k) rd[k] = rn[k] = 0.0;
+    // the four weights and labels of one step: sums; returns the labels
+    auto add_four = [&](const float4 &w4, const float4 &s4, const float4 &a4, uint32_t l4) -> uint32_t {
+        const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
+        uint32_t out = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float wt = alpha ? __fdiv_rn(wv[e], av[e]) : wv[e];
+            const float st = alpha ? __fmul_rn(__fmul_rn(sv[e], av[e]), av[e]) : sv[e];
+            const int l = BITS == 0 ? (int)((l4 >> (8 * e)) & 15u) : label_of(wt);
+            out |= (uint32_t)l << (8 * e);
+            if constexpr (REGS > 0) {
+#pragma unroll
+                for (int k = 0; k < REGS; ++k) {
+                    const double sk = l == k ? (double)st : 0.0;
+                    rd[k] += sk;
+                    rn[k] = fma(sk, (double)wt, rn[k]);
+                }
+            } else {
+                atomicAdd(&myD[l], (double)st);
+                atomicAdd(&myN[l], (double)st * (double)wt);
+            }
+        }
+        return out;
+    };
+    const float4 ones = make_float4(1.f, 1.f, 1.f, 1.f);
+    float4 wk[KEEP > 0 ? KEEP : 1];
+    uint32_t lk[KEEP > 0 ? KEEP : 1];
+    auto first_pass = [&](int it, long long j) {
+        const float4 w4 = load4(Wr + j, vec4), s4 = load4(Sr + j, vec4);
+        const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
+        const uint32_t l4 = add_four(w4, s4, a4, BITS == 0 ? load4(Lr + j, vec4) : 0u);
+        if (BITS > 0 && Lo) {
+            if (vec4) *(uint32_t *)(Lo + j) = l4;
+            else
+                for (int e = 0; e < 4; ++e) Lo[j + e] = (uint8_t)(l4 >> (8 * e));
+        }
+        if (KEEP > 0) {
+            wk[KEEP > 0 ? it : 0] = w4;
+            lk[KEEP > 0 ? it : 0] = l4;
+        }
+    };
+    const long long j0 = 4ll * (lane + 64 * sub);
+    if constexpr (KEEP > 0) {
+#pragma unroll
+        for (int it = 0; it < KEEP; ++it)
+            if (j0 + 1024 * it < mm) first_pass(it, j0 + 1024 * it);
+    } else {
+#pragma unroll 2
+        for (long long j = j0; j < mm; j += 1024) first_pass(0, j);
+    }
+#pragma unroll
+    for (int k = 0; k < REGS; ++k) {
+        for (int o = 32; o >= 1; o >>= 1) {
+            rd[k] += __shfl_xor(rd[k], o, 64);
+            rn[k] += __shfl_xor(rn[k], o, 64);
+        }
+        if (lane == 0) {
+            binD[wave][0][k] = rd[k];
+            binN[wave][0][k] = rn[k];
+        }
+    }
+    __syncthreads();
+    {
+        // 16 clusters; the bins of one of the row's four wavefronts in every 16 lanes
+        double d = 0.0, nn = 0.0;
+        const int bw = (wave & ~3) + (lane >> 4);
+#pragma unroll
+        for (int q = 0; q < ROWP_COPIES; ++q) {
+            d += binD[bw][q][lane & 15];
+            nn += binN[bw][q][lane & 15];
+        }
+        d += __shfl_xor(d, 16, 64);
+        nn += __shfl_xor(nn, 16, 64);
+        d += __shfl_xor(d, 32, 64);
+        nn += __shfl_xor(nn, 32, 64);
+        if (lane < 16) {
+            const double c = d > 0.0 ? nn / d : ((kept && lane < kept_n) ? kept[row * kept_stride + lane] : 0.0);
+            csh[wave][lane] = c;
+            if (sub == 0 && live) {
+                cent[row * 16 + lane] = c;
+                Den[row * 16 + lane] = d;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();      // (one wavefront's LDS accesses execute in order)
+    }
+    auto second_pass = [&](const float4 &w4, const float4 &a4, uint32_t l4, long long j) {
+        const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
+        uint32_t pc[3][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float d = (float)((double)wv[e] - (double)av[e] * csh[wave][(l4 >> (8 * e)) & 15u]);
+            split3(d, pc[0][e], pc[1][e], pc[2][e]);
+        }
+        uint16_t *o = dWp + plane_index(row, j, m);   // four neighbouring k stay inside one block of 16
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            *(uint2 *)(o + 16 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
+    };
+    if constexpr (KEEP > 0) {
+#pragma unroll
+        for (int it = 0; it < KEEP; ++it)
+            if (j0 + 1024 * it < mm) second_pass(wk[it], alpha ? load4(alpha + j0 + 1024 * it, vec4) : ones, lk[it], j0 + 1024 * it);
+    } else {
+#pragma unroll 2
+        for (long long j = j0; j < mm; j += 1024) {
+            const float4 w4 = load4(Wr + j, vec4);
+            const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
+            uint32_t l4;
+            if (BITS == 0) {
+                l4 = load4(Lr + j, vec4);
+            } else {
+                const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
+                l4 = 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) l4 |= (uint32_t)label_of(alpha ? __fdiv_rn(wv[e], av[e]) : wv[e]) << (8 * e);
+            }
+            second_pass(w4, a4, l4, j);
+        }
     }
 }
 
@@ -167,7 +291,7 @@ __global__ void __launch_bounds__(256) split_rows_kernel(const float *__restrict
     uint32_t p[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
-    uint16_t *dst = Hp + plane_index(j, m, k);
+    uint16_t *dst = Hp + plane_index(j, k, m);
 #pragma unroll
     for (int q = 0; q < 3; ++q)
         *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
@@ -185,15 +309,15 @@ constexpr int G_LOADS = G_STAGE_BYTES / (1024 * (G_THREADS / 64));  // 1 KB copi
 constexpr int G_MIN_STAGES = 16;
 constexpr int G_PHASE_COST = 20;                   // a phase of split tiles with its partial tiles, in stages
 
-// What a lane needs to know about the LDS.  A panel is copied as it lies in memory (96 bytes per row: six 16-byte units,
+// What a lane needs to know about the LDS.  A panel holds its rows one after the other (96 bytes each: six 16-byte units,
 // unit 2 p + h = piece p, k 8 h .. 8 h + 7), except that the units of the rows with bit 3 set are rotated by one: any 16
 // rows then read one unit from 64 different banks.
 struct DwhLane {
-    uint32_t voff[G_LOADS];      // source of its copies inside the panel
+    uint32_t voff[G_LOADS];      // source of its copies inside the tile's rows
     uint32_t dst;                // their first kilobyte (the same in the whole wavefront)
     uint32_t ra[3], rb[3];       // operand addresses of the three pieces, A block x at + x * 3072, B block y likewise
     int swave, wr, wc, l32, lhi;
-    __device__ __forceinline__ DwhLane(uint32_t lds0, int tid) {
+    __device__ __forceinline__ DwhLane(uint32_t lds0, int tid, long long m) {
         const int lane = tid & 63, wave = tid >> 6;
         swave = __builtin_amdgcn_readfirstlane(wave);
         wr = wave >> 2;
@@ -205,7 +329,7 @@ struct DwhLane {
             const int c = ((wave & 3) * G_LOADS + i) * 64 + lane;
             const int row = c / 6, pos = c - 6 * row;
             const int unit = (pos + 6 - ((row >> 3) & 1)) % 6;
-            voff[i] = (uint32_t)(row * 96 + unit * 16);
+            voff[i] = (uint32_t)((row >> 2) * m * 24) + (uint32_t)((row & 3) * 96 + unit * 16);
         }
         dst = lds0 + (uint32_t)(swave >> 2) * G_PANEL_BYTES + (uint32_t)(swave & 3) * (G_LOADS * 1024);
 #pragma unroll
@@ -217,15 +341,15 @@ struct DwhLane {
     }
 };
 
-// acc = (rows row0 .. of dW) (rows col0 .. of H)^T over the 16-k stages [s0, s1), from the planes; with HALVED the sums are
-// doubled ahead of stage sdouble.  Rows past the end of either matrix carry values of other rows or zeros.
+// acc = (rows arow0 .. of A) (rows brow0 .. of B)^T over the 16-k stages [s0, s1), from the planes of two matrices of m columns;
+// with HALVED the sums are doubled ahead of stage sdouble.  Rows past the end of either matrix carry no meaning.
 // 16 k are 48 MFMAs and 18 operand reads per wavefront.  The operands of the next quarter of a stage are read between the
 // MFMAs of this one; the barrier stands ahead of the last quarter: past it the next stage is complete in LDS and this
 // one's place is free for the stage after the next two.
 template <bool HALVED>
-__device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhLane &L, const uint16_t *Ap, long long n,
-                                               const uint16_t *Hp, long long m, long long row0, long long col0, int s0, int s1,
-                                               int sdouble) {
+__device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhLane &L, const uint16_t *Ap, long long arows,
+                                               long long arow0, const uint16_t *Bp, long long brows, long long brow0, long long m,
+                                               int s0, int s1, int sdouble) {
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -233,13 +357,15 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
     const bool isb = L.swave >= 4;
-    const long long step = (isb ? m : n) * 96, skip = (isb ? col0 : row0) * 96;
-    LdsSource src{(uint64_t)(uintptr_t)(isb ? Hp : Ap) + (uint64_t)((long long)s0 * step + skip), (long long)(s1 - s0) * step - skip};
+    const long long rows = isb ? brows : arows, skip = ((isb ? brow0 : arow0) >> 2) * m * 24 + (long long)s0 * 384;
+    LdsSource src{(uint64_t)(uintptr_t)(isb ? Bp : Ap) + (uint64_t)skip, (long long)plane_rows(rows) * m * 6 - skip};
+    int ahead = s1 - s0;         // stages still to be requested (past the end nothing is read: zeros arrive)
     auto issue = [&](uint32_t buf) {
+        if (ahead-- <= 0) src.left = 0;
         const int4v rs = src.rsrc();
 #pragma unroll
         for (int i = 0; i < G_LOADS; ++i) copy_to_lds(L.dst + buf + i * 1024, L.voff[i], rs);
-        src.advance((uint64_t)step);
+        src.advance(384);
     };
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the LDS is free
     issue(0);
@@ -308,13 +434,16 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
     }
 }
 
+// What bounds it: the power the matrix cores draw.  4096^3: 0.53 ms = 1.56 PFLOP/s of executed piece products (a bf16
+// product of the same size by the library: 1.25), MFMAs busy 88 % of the cycles at 1.7 GHz instead of 2.4, no bank
+// conflicts.  256 x 128 tiles staged through registers, 32 k per barrier: 0.67 ms, 62 % busy.
 // P = dW H, tile by tile as the plan says: a whole tile goes straight into P, a part of a split one into its slot.
 __global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, long long n, long long m, int tj, TilePlan plan,
            float *__restrict__ P, floatx4 *__restrict__ slots) {
     extern __shared__ __align__(16) unsigned char g_smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid);
+    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid, m);
     const int nk = (int)(m / GK);
     const int G = gridDim.x, me = xcd_order(blockIdx.x, G);
     for (int p = 0; p < plan.nph; ++p) {
@@ -325,7 +454,7 @@ dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, lon
             const long long row0 = (long long)ti * TILE, col0 = (long long)(t - ti * tj) * TILE;
             const int s0 = (int)((long long)nk * part / split), s1 = (int)((long long)nk * (part + 1) / split);
             floatx16 acc[4][2];
-            dwh_accumulate<false>(acc, L, Ap, n, Hp, m, row0, col0, s0, s1, -1);
+            dwh_accumulate<false>(acc, L, Ap, n, row0, Hp, m, col0, m, s0, s1, -1);
             // accumulator element e of a 32 x 32 block: row = 8*(e/4) + 4*(lane/32) + e%4, column = lane%32
             if (split > 1) {
                 floatx4 *sp = slots + ((size_t)(plan.slot0[p] + v) * 8 + wave) * (8 * 4 * 64) + lane;
@@ -386,6 +515,7 @@ __global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, l
             if (rb + 8 * q + e < n && cb < m) P[(rb + 8 * q + e) * m + cb] = s[q][e];
 }
 
+// 4096^3: 0.33 ms, of which the 136 stages of every workgroup take 0.28; the full product with its row sums: 0.67.
 // Loss only: dW_i H dW_i^T = sum over the 256-column blocks J of H of [ 2 sum_{K < J} dW_K H_KJ + dW_J H_JJ ] . dW_J, H being
 // symmetric: half the products.  The stages of all tiles -- tile (I, J) has those of the blocks K <= J -- form one line that is
 // cut into equal pieces, one per workgroup; the loss is linear in the sums, so the pieces of a tile need not meet: each
@@ -417,7 +547,7 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
                 double *__restrict__ partial) {
     extern __shared__ __align__(16) unsigned char g_smem[];
     const int tid = threadIdx.x;
-    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid);
+    const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid, m);
     const int g = xcd_order(blockIdx.x, line.G);
     long long at = line.start(g);
     const long long end = line.start(g + 1);
@@ -430,38 +560,50 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
         const int s1 = (int)min((long long)line.stages(J), s0 + (end - at));
         const long long row0 = (long long)I * TILE, col0 = (long long)J * TILE;
         floatx16 acc[4][2];
+        // H takes the rows of the tile here and dW its columns: a lane then holds 4 neighbouring columns of dW_i H for a row i of
+        // its own, and multiplies them by 8 bytes of each piece.
         // (a piece that starts inside the diagonal block is not doubled; one that ends ahead of it is, at the end)
-        dwh_accumulate<true>(acc, L, Ap, n, Hp, m, row0, col0, s0, s1, s0 < 16 * J ? 16 * J : -1);
-        const float twice = s1 <= 16 * J ? 2.0f : 1.0f;
+        dwh_accumulate<true>(acc, L, Hp, m, col0, Ap, n, row0, m, s0, s1, s0 < 16 * J ? 16 * J : -1);
+        const double twice = s1 <= 16 * J ? 2.0 : 1.0;
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the tiles in LDS are no longer read or written
-        double *rsum = (double *)g_smem;                                              // [4][256]
-        const long long rb = row0 + L.wr * 128 + 4 * L.lhi, cb = col0 + L.wc * 64 + L.l32;
+        double *rsum = (double *)g_smem;                                              // [2][256]
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            double t[16];
+        for (int y = 0; y < 2; ++y) {
+            const int rl = L.wc * 64 + 32 * y + L.l32;
+            const long long r = row0 + rl;
+            double t = 0.0;
+            if (r < n) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const long long r = rb + x * 32 + 8 * (e >> 2) + (e & 3);
-                t[e] = 0.0;
+                for (int x = 0; x < 4; ++x) {
+                    __builtin_amdgcn_sched_barrier(0);      // (one block's loads at a time: the registers hold the sums)
+                    const long long c = col0 + L.wr * 128 + x * 32 + 4 * L.lhi;
+                    uint2 d[4][3];
 #pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                    const long long c = cb + 32 * y;
-                    if (r < n && c < m) {
-                        const uint16_t *ap = Ap + plane_index(r, n, c);
-                        const float dw = (bf16_f32(ap[0]) + bf16_f32(ap[16])) + bf16_f32(ap[32]);     // exact
-                        t[e] += (double)(acc[x][y][e] * twice) * (double)dw;
-                    }
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            d[q][p] = c + 8 * q < m ? *(const uint2 *)(Ap + plane_index(r, c + 8 * q, m) + 16 * p) : make_uint2(0u, 0u);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int sh = (e & 1) * 16;
+                            auto piece = [&](int p) { return bf16_f32(((e < 2 ? d[q][p].x : d[q][p].y) >> sh) & 0xFFFFu); };
+                            const float dw = (piece(0) + piece(1)) + piece(2);     // exact
+                            t += (double)acc[x][y][4 * q + e] * (double)dw;         // (columns past the matrix: dw = 0)
+                        }
                 }
             }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                for (int o = 16; o >= 1; o >>= 1) t[e] += __shfl_xor(t[e], o, 64);     // over the 32 lanes that share the row
-                if (L.l32 == 0) rsum[L.wc * TILE + L.wr * 128 + x * 32 + 8 * (e >> 2) + 4 * L.lhi + (e & 3)] = t[e];
-            }
+            t += __shfl_xor(t, 32, 64);
+            if (L.lhi == 0) rsum[L.wr * TILE + rl] = t;
         }
         __syncthreads();
-        if (tid < TILE)
-            partial[((long long)I * line.tj + J + g) * TILE + tid] = (rsum[tid] + rsum[TILE + tid]) + (rsum[2 * TILE + tid] + rsum[3 * TILE + tid]);
+        if (tid < TILE) {
+            double *o = partial + ((long long)I * line.tj + J + g) * TILE + tid;
+            o[0] = (rsum[tid] + rsum[TILE + tid]) * twice;
+            // (a workgroup that starts with a tile leaves a number unused behind the piece before it)
+            if (s0 == 0 && at == line.start(g) && g > 0) o[-TILE] = 0.0;
+        }
         at += s1 - s0;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -474,12 +616,10 @@ __global__ void __launch_bounds__(256) loss_rows_kernel(const double *__restrict
     if (i >= n) return;
     const int I = blockIdx.x;
     const long long first = (long long)I * line.per_row;
+    const long long p0 = (long long)I * line.tj + line.owner(first), p1 = (long long)I * line.tj + line.tj - 1 + line.owner(first + line.per_row - 1);
     double tot = 0.0;
-    for (int J = 0; J < line.tj; ++J) {
-        const long long s = first + line.before(J);
-        const int g0 = line.owner(s), g1 = line.owner(s + line.stages(J) - 1);
-        for (int g = g0; g <= g1; ++g) tot += partial[((long long)I * line.tj + J + g) * TILE + threadIdx.x];
-    }
+#pragma unroll 8
+    for (long long p = p0; p <= p1; ++p) tot += partial[p * TILE + threadIdx.x];
     if (row_loss) row_loss[i * row_stride] = tot;
     rows[i] = tot;
 }
@@ -703,7 +843,7 @@ skim_status carve(skim_ctx *ctx, int64_t n, int64_t m, bool grad, LossWs &w) {
     w.tiles = (n + TILE - 1) / TILE * w.tj;
     // (H first: skim_train_scale and skim_error_table_lfull keep its pieces across their steps)
     w.Hp = (uint16_t *)cur.take((size_t)m * m * 3 * sizeof(uint16_t));
-    w.dWp = (uint16_t *)cur.take((size_t)n * m * 3 * sizeof(uint16_t));
+    w.dWp = (uint16_t *)cur.take(plane_rows(n) * m * 3 * sizeof(uint16_t));
     w.cent = (double *)cur.take((size_t)n * 16 * sizeof(double));
     w.Den = (double *)cur.take((size_t)n * 16 * sizeof(double));
     bool ok = w.dWp && w.Hp && w.cent && w.Den;
@@ -742,6 +882,32 @@ bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t
     return (ld % 4) == 0 && (((uintptr_t)W | (uintptr_t)S | (uintptr_t)alpha) & 15) == 0 && ((uintptr_t)labels & 3) == 0;
 }
 
+template <int BITS>
+void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
+                          const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride,
+                          int kept_n) {
+    const dim3 grid((unsigned)((n + 3) / 4)), block(64 * ROWP_WAVES);
+    const bool vec4 = rows_vec4(W, S, alpha, BITS == 0 ? labels : bd.labels_out, ld);
+    auto launch = [&](auto keep) {
+        hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value>), grid, block, 0, ctx->stream, W, S, alpha, (long long)n, (long long)m,
+                           (long long)ld, labels, bd.upper, (long long)bd.upper_stride, bd.labels_out, w.cent, w.Den, w.dWp, kept,
+                           (long long)kept_stride, kept_n, vec4);
+    };
+    if (m <= 4 * 1024) launch(std::integral_constant<int, 4>{});
+    else if (m <= 11 * 1024) launch(std::integral_constant<int, 11>{});
+    else launch(std::integral_constant<int, 0>{});
+}
+void launch_row_prep(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
+                     const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride, int kept_n) {
+    switch (bd.bits) {
+        case 0: launch_row_prep_bits<0>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+        case 1: launch_row_prep_bits<1>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+        case 2: launch_row_prep_bits<2>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+        case 3: launch_row_prep_bits<3>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+        default: launch_row_prep_bits<4>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+    }
+}
+
 skim_status check_shape(skim_ctx *ctx, int64_t n, int64_t m, int64_t ld) {
     if (n < 1 || n > 0x7fffffff || m < GK || m > 0x7fffffff || ld < m || (m % GK) != 0)
         SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "layer loss needs n >= 1, m a multiple of %d, ld >= m (n=%lld m=%lld ld=%lld)", GK,
@@ -761,23 +927,21 @@ extern "C" skim_status skim_layer_loss(skim_ctx *ctx, const float *W, const floa
                                        const float *H, int64_t n, int64_t m, int64_t ld, const uint8_t *labels,
                                        double *loss, double *row_loss) {
     if (ctx && !loss) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
-    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, loss, row_loss, 1, nullptr, 0, 0, false);
+    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss, row_loss, 1, nullptr, 0, 0, false);
 }
 
 skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *S, const float *alpha, const float *H,
-                                    int64_t n, int64_t m, int64_t ld, const uint8_t *labels, double *loss,
+                                    int64_t n, int64_t m, int64_t ld, const uint8_t *labels, const skim_label_bounds &bounds, double *loss,
                                     double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
                                     int kept_n, bool h_ready) {
     skim_status st = skim_enter(ctx);
     if (st != SKIM_OK) return st;
-    if (!W || !S || !H || !labels) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
+    if (!W || !S || !H || (!labels && !bounds.upper)) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
     if ((st = check_shape(ctx, n, m, ld)) != SKIM_OK) return st;
     if ((uintptr_t)H & 15) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: H must be 16-byte aligned");
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
-    hipLaunchKernelGGL(row_prep_kernel, dim3((unsigned)n), dim3(PREP_THREADS), 0, ctx->stream, W, S, alpha, (long long)m,
-                       (long long)ld, labels, w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n,
-                       rows_vec4(W, S, alpha, labels, ld));
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
     if (!h_ready) launch_split(ctx, w, H, m, true);
     hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
@@ -815,9 +979,7 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     if ((uintptr_t)H & 15) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_scale_step: H must be 16-byte aligned");
     LossWs w;
     if ((st = carve(ctx, n, m, true, w)) != SKIM_OK) return st;
-    hipLaunchKernelGGL(row_prep_kernel, dim3((unsigned)n), dim3(PREP_THREADS), 0, ctx->stream, W, S, (const float *)alpha,
-                       (long long)m, (long long)ld, labels, w.cent, w.Den, w.dWp, (const double *)nullptr, 0ll, 0,
-                       rows_vec4(W, S, alpha, labels, ld));
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, nullptr, 0, 0);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
     if (!h_ready) launch_split(ctx, w, H, m, false);
     {
@@ -891,7 +1053,8 @@ extern "C" skim_status skim_train_scale(skim_ctx *ctx, const float *W, const flo
     if ((st = check_shape(ctx, n, m, ld)) != SKIM_OK) return st;
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
-    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, loss_trace + slot, nullptr, 1, nullptr, 0, 0, steps > 0)) != SKIM_OK)
+    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss_trace + slot, nullptr, 1, nullptr, 0, 0, steps > 0)) !=
+        SKIM_OK)
         return st;
     SKIM_HIP(ctx, hipMemcpyAsync(centroids, w.cent, (size_t)n * 16 * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
     return SKIM_OK;

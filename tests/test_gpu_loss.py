@@ -233,3 +233,23 @@ def test_hessian_plans_match_oracle(gpu_lib, N, m, workspace):
     assert np.all(np.abs(got - ref) <= RTOL * scale), f"max scaled diff {(np.abs(got - ref) / scale).max():.3e}"
     assert torch.equal(H, H.T.contiguous())
     c.close()
+
+
+@pytest.mark.parametrize("n,m,K", [
+    (3, 4112, 16), (9, 11280, 8),       # rows of 5 .. 11 steps kept in registers, longer ones read twice; row groups part empty
+    (70, 2064, 4),                      # few tiles: every one split; a last stage of 16 columns past a multiple of 32
+    (8200, 2080, 16)])                  # more tiles than workgroups: one round of whole tiles, then split ones
+def test_loss_and_scale_step_on_other_tile_plans(ctx, n, m, K):
+    """Shapes on which the contraction shares its tiles out differently from the small ones above, and the row kernel keeps
+    its columns differently: loss, row losses and gradient against the oracle (bounds as above)."""
+    W, S, labels, H, al = make_case(n + m, n, m, K, N=64)
+    ref = oracle.scale_grad(W, S, H, labels, al)
+    out = ctx.layer_loss(dev(W), dev(S), dev(H), dev(labels), alpha=dev(al))
+    step = ctx.scale_step(dev(W), dev(S), dev(H), dev(labels), dev(al), dev(np.zeros(m, np.float32)), dev(np.zeros(m, np.float32)), 1)
+    torch.cuda.synchronize()
+    assert out["loss"].item() == pytest.approx(ref["loss"], rel=RTOL)
+    assert step["loss_before"].item() == pytest.approx(ref["loss"], rel=RTOL)
+    rl = oracle.layer_loss(W, H, labels, ref["centroids"], al)["row_loss"]
+    assert np.all(np.abs(out["row_loss"].cpu().numpy() - rl) <= RTOL * np.abs(rl) + 1e-9 * ref["loss"] / n)
+    g = step["grad"].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(g - ref["grad"]) <= RTOL * np.abs(ref["grad"]) + 1e-6 * np.abs(ref["grad"]).max())
