@@ -1309,11 +1309,17 @@ struct LevelMap {
     int n[8];        // entries per level
     int roff[8];     // byte offset of the second-moment sums of level >= 2 inside the row's LDS block
     int w16_off, ppd_off, ppn_off, bytes;   // first weights; running sums of s and of s*w (n[1] + 1 double2 each)
+    int n2, t1_off, t2_off;                 // search tree over the first weights: every 8th, every 64th (n2 of them)
 };
 __host__ __device__ inline LevelMap level_map(int n1u) {
     LevelMap L;
     L.w16_off = 0;
-    int o = (n1u * 4 + 15) & ~15;
+    int o = ((n1u + 7) & ~7) * 4;
+    L.n2 = (n1u + 63) >> 6;
+    L.t1_off = o;
+    o += L.n2 * 32;
+    L.t2_off = o;
+    o += ((L.n2 + 3) & ~3) * 4;
     L.n[0] = n1u;
     int lv = 0, n = n1u;
     do {
@@ -1448,13 +1454,17 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         if (hh >= nhalf) break;
         const long long rr = 2ll * blockIdx.x + hh;
         unsigned char *blkw = smem + (size_t)hh * LM.bytes;
-        float *w16w = (float *)(blkw + LM.w16_off);
+        float *w16w = (float *)(blkw + LM.w16_off), *t1w = (float *)(blkw + LM.t1_off), *t2w = (float *)(blkw + LM.t2_off);
         const float *gw = prm.w16 + rr * prm.n1;
+        // (the weights and both levels of the tree over them are filled up with +inf, which counts as above everything)
+        auto put_w16 = [&](int j, float w) {
+            const float x = j < n1u ? w : INFINITY;
+            if (j < ((n1u + 7) & ~7)) w16w[j] = x;
+            if ((j & 7) == 0 && j < 64 * LM.n2) t1w[j >> 3] = x;
+            if ((j & 63) == 0 && j < 64 * ((LM.n2 + 3) & ~3)) t2w[j >> 6] = x;
+        };
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int j = u * ITER_THREADS + lane;
-            if (j < n1u) w16w[j] = t8[hh][u];
-        }
+        for (int u = 0; u < 8; ++u) put_w16(u * ITER_THREADS + lane, t8[hh][u]);
         for (int j0 = 8 * ITER_THREADS; j0 < n1u; j0 += 8 * ITER_THREADS) {
             float t[8];
 #pragma unroll
@@ -1463,43 +1473,46 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 t[u] = (j < n1u) ? gw[j] : 0.0f;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = j0 + u * ITER_THREADS + lane;
-                if (j < n1u) w16w[j] = t[u];
-            }
+            for (int u = 0; u < 8; ++u) put_w16(j0 + u * ITER_THREADS + lane, t[u]);
         }
         // running sums ahead of every group of 4 chunks, pp[ng] = row total.  A lane takes `per` consecutive
         // groups; one double-double scan over the lanes per quantity.
         {
             double2 *ppd = (double2 *)(blkw + LM.ppd_off), *ppn = (double2 *)(blkw + LM.ppn_off);
-            double2 md = make_double2(0.0, 0.0), mn = make_double2(0.0, 0.0);
+            auto scan = [&](auto cnt) {
+                constexpr int N = decltype(cnt)::value;
+                double2 md = make_double2(0.0, 0.0), mn = make_double2(0.0, 0.0);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                md = dd_add(md, make_double2(qv[hh][k].x, 0.0));
-                mn = dd_add(mn, make_double2(qv[hh][k].y, 0.0));
-            }
-            const double2 id = dd_wave_scan_incl(md), in = dd_wave_scan_incl(mn);
-            // sums of the lanes below: the inclusive sums shifted up by one lane
-            double2 rd = make_double2(lane_below(id.x), lane_below(id.y));
-            double2 rn = make_double2(lane_below(in.x), lane_below(in.y));
-            if (lane == 0) {
-                rd = make_double2(0.0, 0.0);
-                rn = make_double2(0.0, 0.0);
-            }
+                for (int k = 0; k < N; ++k) {
+                    md = dd_add(md, make_double2(qv[hh][k].x, 0.0));
+                    mn = dd_add(mn, make_double2(qv[hh][k].y, 0.0));
+                }
+                const double2 id = dd_wave_scan_incl(md), in = dd_wave_scan_incl(mn);
+                // sums of the lanes below: the inclusive sums shifted up by one lane
+                double2 rd = make_double2(lane_below(id.x), lane_below(id.y));
+                double2 rn = make_double2(lane_below(in.x), lane_below(in.y));
+                if (lane == 0) {
+                    rd = make_double2(0.0, 0.0);
+                    rn = make_double2(0.0, 0.0);
+                }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int q = lane * per + k;
-                if (k < per && q < ng) {
-                    ppd[q] = rd;
-                    ppn[q] = rn;
-                    rd = dd_add(rd, make_double2(qv[hh][k].x, 0.0));
-                    rn = dd_add(rn, make_double2(qv[hh][k].y, 0.0));
-                    if (q == ng - 1) {
-                        ppd[ng] = rd;
-                        ppn[ng] = rn;
+                for (int k = 0; k < N; ++k) {
+                    const int q = lane * per + k;
+                    if (k < per && q < ng) {
+                        ppd[q] = rd;
+                        ppn[q] = rn;
+                        rd = dd_add(rd, make_double2(qv[hh][k].x, 0.0));
+                        rn = dd_add(rn, make_double2(qv[hh][k].y, 0.0));
+                        if (q == ng - 1) {
+                            ppd[ng] = rd;
+                            ppn[ng] = rn;
+                        }
                     }
                 }
-            }
+            };
+            if (per == 1) scan(std::integral_constant<int, 1>{});
+            else if (per <= 3) scan(std::integral_constant<int, 3>{});
+            else scan(std::integral_constant<int, 8>{});
         }
         // second moments: level 2 from the groups' sums in global memory
         if (LM.nlev > 2) {
@@ -1598,8 +1611,13 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 }
             }
             const int r0 = chunk * 16;
+            const u64x2_a8 *kv = (const u64x2_a8 *)(keys + r0);       // (a last chunk's keys past the row are not used below)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) el[j] = (r0 + j < m) ? keys[r0 + j] : NEUTRAL_KEY;
+            for (int j = 0; j < 8; ++j) {
+                const u64x2 t2 = kv[j];
+                el[2 * j] = t2.x;
+                el[2 * j + 1] = t2.y;
+            }
             int found = min(r0 + 15, m - 1);
             bool hit = false;
 #pragma unroll
@@ -1633,9 +1651,11 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     if (__ballot(on && !wstart_ok) != 0) {
         if (on && !wstart_ok) wstart = elem_w(keys[r]);
     }
+    // largest magnitude of the row
+    const double wabs = on ? (double)fmaxf(fabsf(elem_w(keys[0])), fabsf(elem_w(keys[m - 1]))) : 0.0;
     double v = on ? (double)wstart : 0.0;
     int idx = p;
-    int Bcur = 0, Bold = -1, idxold = -1, cold = 0;
+    int Bcur = 0, Bold = -1, idxold = -1;
     double Dk = 0.0, Nk = 0.0;       // sums of this lane's cluster under the last assignment it took part in
     bool emptyk = false;             // ... in which it owned nothing (its value repeated the one below)
     bool done = !on;
@@ -1644,6 +1664,11 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     // ranks, inside the same 16 keys, and then the lane asks the memory system for nothing
     u64 el[16];
     int cl_held = -2;
+    // so do the sums over the whole chunks between the boundary chunks [a0_held, b0_held)
+    int a0_held = 0, b0_held = 0;
+    double midD = 0.0, midN = 0.0;
+    const float4 *w16q = (const float4 *)w16, *t1q = (const float4 *)(blk + LM.t1_off), *t2q = (const float4 *)(blk + LM.t2_off);
+    const int n2q = (LM.n2 + 3) >> 2;
     for (int it = 0; it < prm.iters; ++it) {
         if (__ballot(!done) == 0) break;
         const bool live = !done;     // this lane's bit width still iterates
@@ -1699,52 +1724,47 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         };
         auto nearer_lo = [&](float xf) -> bool { return nearer_raw(xf) != tie_lo; };
 
-        // ---- chunk of the boundary: cnt = number of chunks whose first key is nearer to the lower
-        // centroid (a prefix of the chunks); invariant lo <= cnt <= hi -----------------------------
-        const int rlo = lane_below(r);
-        int lo = 0, hi = 0, mode = 0, step = 1;
-        if (it == 0) {
-            // the starting centroids are the keys at ranks r: the boundary lies in (r_{p-1}, r_p]
-            if (searching) {
-                lo = (rlo >> 4) + 1;
-                hi = (r + 15) >> 4;
+        // The threshold in single precision: of all floats, those below u are nearer to the lower centroid, the others are
+        // not.  t, the float nearest to the midpoint, is asked the exact question; every other float is at least a quarter of a
+        // float spacing from the midpoint, far more than the rounding of the question -- unless the midpoint nearly cancels
+        // or the centroids nearly coincide (against the row's largest weight): such a boundary (`hard`) is found with the
+        // exact question itself.
+        const double mid = 0.5 * (vlo + v);
+        const float t = __fadd_rn((float)mid, 0.0f);
+        const int tb = __float_as_int(t);
+        const float u = nearer_lo(t) ? __int_as_float(tb >= 0 ? tb + 1 : tb - 1) : t;
+        const bool hard = searching && !(fabs(mid) > 0x1p-24 * fmax(fabs(v), fabs(vlo)) && v - vlo > 0x1p-30 * wabs);
+        const bool anyhard = __ballot(hard) != 0;
+
+        // ---- chunk of the boundary: lo = number of chunks whose first key is nearer to the lower centroid (a prefix of
+        // the chunks): three levels of a search tree, 8 first weights per node (one trip to the LDS each)
+        int lo = 0;
+        {
+            int c2 = 0;
+            for (int q = 0; q < n2q; ++q) {
+                const float4 x = t2q[q];
+                c2 += (x.x < u ? 1 : 0) + (x.y < u ? 1 : 0) + (x.z < u ? 1 : 0) + (x.w < u ? 1 : 0);
             }
-        } else {
-            // two probes next to the previous answer; a miss gallops away from it
-            const int ia = min(max(cold - 1, 0), n1u - 1), ib = min(cold, n1u - 1);
-            const bool ta = nearer_lo(w16[ia]), tb = nearer_lo(w16[ib]);
-            if (searching) {
-                lo = 0;
-                hi = n1u;
-                bool below = false;
-                if (cold >= 1) {
-                    if (ta) lo = cold; else { hi = cold - 1; mode = 1; below = true; }
-                }
-                if (!below && cold < n1u) {
-                    if (tb) { lo = cold + 1; mode = 2; } else hi = cold;
-                }
-            }
+            const int b1 = max(c2 - 1, 0);
+            auto node = [&](const float4 *p) -> int {
+                const float4 x = p[0], y = p[1];
+                return (x.x < u ? 1 : 0) + (x.y < u ? 1 : 0) + (x.z < u ? 1 : 0) + (x.w < u ? 1 : 0) + (y.x < u ? 1 : 0) +
+                       (y.y < u ? 1 : 0) + (y.z < u ? 1 : 0) + (y.w < u ? 1 : 0);
+            };
+            const int b0 = 8 * b1 + max(node(t1q + 2 * b1) - 1, 0);
+            lo = 8 * b0 + node(w16q + 2 * b0);
         }
-        for (;;) {
-            const int len = hi - lo;
-            if (__ballot(len > 0) == 0) break;
-            int mid;
-            if (mode == 1) mid = max(lo, hi - step);
-            else if (mode == 2) mid = min(hi - 1, lo + step - 1);
-            else mid = lo + (len >> 1);
-            mid = min(max(mid, 0), n1u - 1);
-            const bool t = nearer_lo(w16[mid]);
-            if (len > 0) {
-                if (t) {
-                    lo = mid + 1;
-                    if (mode == 2) step <<= 2; else mode = 0;
-                } else {
-                    hi = mid;
-                    if (mode == 1) step <<= 2; else mode = 0;
+        if (__builtin_expect(anyhard, 0)) {
+            int l2 = 0, h2 = hard ? n1u : 0;
+            while (__ballot(l2 < h2) != 0) {
+                const int md = min((l2 + h2) >> 1, n1u - 1);
+                const bool nl = nearer_lo(w16[md]);
+                if (l2 < h2) {
+                    if (nl) l2 = md + 1; else h2 = md;
                 }
             }
+            if (hard) lo = l2;
         }
-        if (searching) cold = lo;
         int cl = searching ? lo - 1 : -1;          // chunk that holds the boundary (-1: boundary at rank 0)
         // what the cluster below sees of this position: its chunk, boundary and the sums of the
         // keys of that chunk below the boundary; a position that repeats the value below it owns
@@ -1780,32 +1800,49 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             }
             cl_held = cl_want;
         }
-        const int la0 = min(b0, (a0 + 3) & ~3), rb0 = max(la0, b0 & ~3);
-        // (with two wavefronts per SIMD the pieces are requested here, ahead of the work on the keys; with three
-        // there are no registers to park them in, and a third wavefront to wait behind)
-        double2 pc[6];
-        auto load_pieces = [&]() {
+        // the whole chunks in between: up to 3 + 3 chunk sums (requested with the keys), the whole groups of 4 chunks as the
+        // difference of the running sums in LDS
+        const bool resum = summing && (a0 != a0_held || b0 != b0_held);
+        if (__ballot(resum) != 0) {
+            const int la0 = min(b0, (a0 + 3) & ~3), rb0 = max(la0, b0 & ~3);
+            double2 pc[6];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                pc[k] = (a0 + k < la0) ? L1[a0 + k] : make_double2(0.0, 0.0);
-                pc[3 + k] = (rb0 + k < b0) ? L1[rb0 + k] : make_double2(0.0, 0.0);
+                pc[k] = (resum && a0 + k < la0) ? L1[a0 + k] : make_double2(0.0, 0.0);
+                pc[3 + k] = (resum && rb0 + k < b0) ? L1[rb0 + k] : make_double2(0.0, 0.0);
             }
-        };
-        if (WAVES <= 2) load_pieces();
+            int ga = la0 >> 2, gb = rb0 >> 2;
+            if (la0 >= rb0) { ga = 0; gb = 0; }
+            const double2 da = ppd[ga], db = ppd[gb], na = ppn[ga], nb = ppn[gb];
+            double sD = dd_diff(db, da), sN = dd_diff(nb, na);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                sD += pc[k].x;
+                sN += pc[k].y;
+            }
+            if (resum) {
+                midD = sD;
+                midN = sN;
+                a0_held = a0;
+                b0_held = b0;
+            }
+        }
 
-        int tc = 0;         // (counted with the raw comparison and turned round once for the lanes that flip it)
-        if (RAGGED) {
-            const int nvalid = m - rbase;   // keys past the end of the row are not this row's
+        // rank inside the chunk
+        const int nvalid = RAGGED ? m - rbase : 16;
+        if (RAGGED && reload) {     // keys past the end of the row are not this row's: above every threshold, without mass
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                if (j >= nvalid) el[j] = NEUTRAL_KEY;
-                tc += (j < nvalid && nearer_raw(elem_w(el[j]))) ? 1 : 0;
-            }
-            if (tie_lo) tc = min(max(nvalid, 0), 16) - tc;
-        } else {
+            for (int j = 0; j < 16; ++j)
+                if (j >= m - cl_want * 16) el[j] = (u64)0x7F7FFFFFu << 32;
+        }
+        int tc = 0;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) tc += nearer_raw(elem_w(el[j])) ? 1 : 0;
-            if (tie_lo) tc = 16 - tc;
+        for (int j = 0; j < 16; ++j) tc += elem_w(el[j]) < u ? 1 : 0;
+        if (__builtin_expect(anyhard, 0)) {
+            int te = 0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) te += (j < nvalid && nearer_lo(elem_w(el[j]))) ? 1 : 0;
+            if (hard) tc = te;
         }
         if (cl < 0) tc = 0;
         Bcur = (searching && cl >= 0) ? rbase + tc : 0;  // p == 0 or no chunk below the boundary: 0
@@ -1864,24 +1901,12 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             lowD = xd;
             lowN = xn;
         }
-        if (WAVES > 2) load_pieces();
         double nD = lane_above(lowD), nN = lane_above(lowN);
         if (p == K - 1 || cl_next <= cl) { nD = 0.0; nN = 0.0; }
         D += nD;
         N += nN;
-        // level-0 pieces, then the whole groups of 4 chunks in between from the running sums in LDS
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            D += pc[k].x;
-            N += pc[k].y;
-        }
-        {
-            int ga = la0 >> 2, gb = rb0 >> 2;
-            if (la0 >= rb0) { ga = 0; gb = 0; }
-            const double2 da = ppd[ga], db = ppd[gb], na = ppn[ga], nb = ppn[gb];
-            D += dd_diff(db, da);
-            N += dd_diff(nb, na);
-        }
+        D += midD;
+        N += midN;
         if (summing) {
             Dk = D;
             Nk = N;
