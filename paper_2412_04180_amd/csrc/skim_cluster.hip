@@ -1170,9 +1170,8 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
 
 // ---------------------------------------------------------------------------------------------
 // Rows longer than one LDS sort (m > 16384): the two sorted segments A, B of a row are merged tile by tile.
-// A workgroup produces MG_TILE consecutive keys of the merged row: two wavefronts find, by a 64-way
-// search in global memory, how many keys of A lie ahead of the tile's first and last output (merge path,
-// equal keys from A first); the keys in between, MG_TILE in all, are staged in LDS; every thread then
+// A workgroup produces MG_TILE consecutive keys of the merged row: merge_split_kernel has found how many keys of
+// A lie ahead of the tile's first and last output; the keys in between, MG_TILE in all, are staged in LDS; every thread then
 // finds the split for its own 16 outputs by binary search in LDS, loads its share of A ascending and of B
 // descending (a bitonic sequence) and sorts it with the 4-stage merge network in registers.  The 16 outputs
 // are one chunk: its sums, and with the neighbours' the sums of 4 chunks, are written with the keys (the
@@ -1182,46 +1181,63 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
 constexpr int MG_THREADS = 256;
 constexpr int MG_TILE = MG_THREADS * EPT;
 
-// Number of keys of A among the first o keys of merge(A, B), equal keys from A first.  The predicate
-// p(x) = A[x] <= B[o-1-x] holds exactly for x below the answer; 64 lanes probe 64 positions per round.
-__device__ __forceinline__ int merge_split_wave(const double *__restrict__ A, int la, const double *__restrict__ B,
-                                                int lb, int o, int lane) {
+// Ahead of the tiles: how many keys of A lie ahead of each tile's first output (merge path, equal keys from A first):
+// the predicate A[x] <= B[o-1-x] holds exactly for x below the answer.  One thread per tile border and plain binary search:
+// a chain of 14 loads, but all borders of the matrix at once, and about 20 lines of memory each; a 64-way search by the
+// tile's own wavefronts was a chain of 3 and fetched about 170 lines at either end, more than the tile itself holds.
+// 8192 x 22016, the whole pass (both changes of the merge): 2435 -> 2027 us; the merge moves 2.9 GB.
+__device__ __forceinline__ int *merge_splits(const ClusterParams &prm, long long row) {
+    return (int *)(prm.bstate + row * 4);        // (the row's states are not written before the iterations)
+}
+__global__ void __launch_bounds__(MG_THREADS) merge_split_kernel(ClusterParams prm, int tiles_per_row, long long nsplits) {
+    const long long g = (long long)blockIdx.x * MG_THREADS + threadIdx.x;
+    if (g >= nsplits) return;
+    const long long row = g / tiles_per_row;
+    const int tile = (int)(g % tiles_per_row);
+    const int m = prm.m;
+    const int la = min(prm.seglen, m), lb = m - la;
+    const double *__restrict__ A = (const double *)(prm.keys_seg + row * (long long)m);
+    const double *__restrict__ B = A + la;
+    const int o = tile * MG_TILE;
     int lo = max(0, o - lb), hi = min(o, la);
-    while (hi > lo) {
-        const int step = (hi - lo + 63) >> 6;
-        const int x = lo + lane * step;
-        const bool p = (x < hi) && (A[x] <= B[o - 1 - x]);
-        const int nt = __popcll(__ballot(p));          // probes 0 .. nt-1 are true
-        const int nlo = nt > 0 ? lo + (nt - 1) * step + 1 : lo;
-        hi = min(hi, lo + nt * step);
-        lo = nlo;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (A[mid] <= B[o - 1 - mid]) lo = mid + 1;
+        else hi = mid;
     }
-    return lo;
+    merge_splits(prm, row)[tile] = lo;
 }
 
 __global__ void __launch_bounds__(MG_THREADS) merge_tile_kernel(ClusterParams prm, int tiles_per_row) {
     __shared__ double buf[MG_TILE + MG_TILE / 16];
     __shared__ int part[MG_THREADS + 1];
-    __shared__ int split[2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     const long long row = blockIdx.x / tiles_per_row;
     const int tile = (int)(blockIdx.x % tiles_per_row);
     const int m = prm.m;
-    const int la = min(prm.seglen, m), lb = m - la;
-    const double *__restrict__ A = (const double *)(prm.keys_seg + row * (long long)m);
-    const double *__restrict__ B = A + la;
+    const int la = min(prm.seglen, m);
+    const double *__restrict__ A = (const double *)(prm.keys_seg + row * (long long)m);    // B follows A
     const int o0 = tile * MG_TILE, o1 = min(m, o0 + MG_TILE);
     const int T = o1 - o0;
-    if (wave < 2) {
-        const int sp = merge_split_wave(A, la, B, lb, wave == 0 ? o0 : o1, lane);
-        if (lane == 0) split[wave] = sp;
-    }
-    __syncthreads();
-    const int ia0 = split[0], ia1 = split[1];
+    const int *split = merge_splits(prm, row);
+    const int ia0 = split[tile], ia1 = (tile + 1 < tiles_per_row) ? split[tile + 1] : la;
     const int ib0 = o0 - ia0;
     const int lat = ia1 - ia0, lbt = T - lat;            // keys of A and of B in this tile
-    for (int x = tid; x < T; x += MG_THREADS)
-        buf[swz((uint32_t)x)] = x < lat ? A[ia0 + x] : B[ib0 + (x - lat)];
+    {
+        // all of a thread's keys are requested before the first is stored (key by key, a tile was a chain of 16 trips
+        // to memory)
+        double t[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int x = min(tid + e * MG_THREADS, T - 1);
+            t[e] = A[x < lat ? ia0 + x : la + ib0 + (x - lat)];
+        }
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int x = tid + e * MG_THREADS;
+            if (x < T) buf[swz((uint32_t)x)] = t[e];
+        }
+    }
     __syncthreads();
     // this thread's outputs: d .. d + cnt - 1 of the tile
     const int d = tid * EPT;
@@ -1291,7 +1307,11 @@ __global__ void __launch_bounds__(MG_THREADS) merge_tile_kernel(ClusterParams pr
     }
     __syncthreads();
     u64 *keys = prm.keys + row * (long long)m + o0;
-    for (int x = tid; x < T; x += MG_THREADS) keys[x] = obuf[swz((uint32_t)x)];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int x = tid + e * MG_THREADS;
+        if (x < T) keys[x] = obuf[swz((uint32_t)x)];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2628,6 +2648,9 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     if (prm.nseg > 1) {
         const int tiles = (prm.m + MG_TILE - 1) / MG_TILE;
         if ((int64_t)n * tiles > 0x7fffffff) SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "too many rows");
+        const long long nsplits = (long long)n * tiles;
+        hipLaunchKernelGGL(merge_split_kernel, dim3((unsigned)((nsplits + MG_THREADS - 1) / MG_THREADS)), dim3(MG_THREADS), 0,
+                           ctx->stream, prm, tiles, nsplits);
         hipLaunchKernelGGL(merge_tile_kernel, dim3((unsigned)(n * tiles)), dim3(MG_THREADS), 0, ctx->stream, prm, tiles);
     }
     if (sort_only) {
