@@ -10,6 +10,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace {
 
 constexpr int GA_THREADS = 1024;
@@ -219,6 +221,228 @@ __global__ void __launch_bounds__(GA_THREADS) greedy_select_kernel(const double 
     }
 }
 
+// Tables of at most three upgrades per row and GR_THREADS * 12 rows, which is every table of 1 .. 4 bits on a layer of up
+// to 12288 rows: a thread keeps the keys of its rows in registers from the error table to the bit widths, so that no key
+// is written or read again.  One workgroup, bound by the length of its chain of barriers: the threshold is found by cutting
+// the interval between the least and the largest key into 1024 bins and going on inside the bin that holds the T-th
+// largest, until at most 64 keys are left, which every wavefront ranks against each other (two or three cuts; a cut by
+// the keys' own digits took up to eight, the first two with all keys in a handful of bins).  Every wavefront works the
+// outcome of a cut out for itself.  Tables of 8192 rows 112 -> 22.6 us, 11008 rows 74 -> 32.5, 4096 24 -> 14.8, 512 10 -> 7.3
+// (kernel times; larger tables and wider bit ranges take greedy_select_kernel).
+constexpr int GR_NU = 3, GR_BINS = 1024, GR_LIST = 64;
+constexpr int GR_MAX_RPT = 12;
+
+// inclusive sum over the 64 lanes / over each row of 16 lanes
+template <bool ROWS16>
+__device__ __forceinline__ int scan_incl(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);   // row_shr:8
+    if (!ROWS16) {
+        x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1, 3
+        x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2, 3
+    }
+    return x;
+}
+__device__ __forceinline__ u64 readlane_u64(u64 x, int l) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), l);
+    return ((u64)hi << 32) | lo;
+}
+
+// RPT: rows per thread (row tid + r * GA_THREADS in slot r).
+template <int RPT>
+__global__ void __launch_bounds__(GA_THREADS) greedy_rows_kernel(const double *__restrict__ E, int n, int bmin, int nb, int T,
+                                                                uint8_t *__restrict__ bits, long long *__restrict__ info,
+                                                                long long budget) {
+    // three sets of bins in turn: the set of the next cut is cleared while this one is filled, and the set of the cut
+    // before may still be read then
+    __shared__ __align__(16) int hist[3][GR_BINS];
+    __shared__ u64 list[GR_LIST];
+    __shared__ u64 wmin[GA_THREADS / 64], wmax[GA_THREADS / 64];
+    __shared__ int wsum[RPT][GA_THREADS / 64];
+    __shared__ int listn, cnt[8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nu = nb - 1, nk = n * nu;
+
+    u64 key[RPT][GR_NU];
+    {
+        double e[RPT][GR_NU + 1];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            const int i = min(tid + r * GA_THREADS, n - 1);
+#pragma unroll
+            for (int j = 0; j <= GR_NU; ++j) e[r][j] = E[(long long)i * nb + min(j, nu)];
+        }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            double k = 0.0;
+#pragma unroll
+            for (int j = 0; j < GR_NU; ++j) {
+                const double g = e[r][j] - e[r][j + 1];
+                k = (j == 0 || g < k) ? g : k;
+                key[r][j] = ordered_key(k);
+            }
+        }
+    }
+    auto valid = [&](int r, int j) -> bool { return j < nu && tid + r * GA_THREADS < n; };
+
+    u64 thr = 0;
+    int R = 0;                     // keys equal to the threshold that are still taken, in index order
+    bool ties = false;             // fewer than there are
+    if (T > 0 && T < nk) {
+        u64 lo = ~0ull, hi = 0ull;
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+#pragma unroll
+            for (int j = 0; j < GR_NU; ++j)
+                if (valid(r, j)) {
+                    lo = min(lo, key[r][j]);
+                    hi = max(hi, key[r][j]);
+                }
+        for (int d = 32; d >= 1; d >>= 1) {
+            lo = min(lo, (u64)__shfl_xor((long long)lo, d, 64));
+            hi = max(hi, (u64)__shfl_xor((long long)hi, d, 64));
+        }
+        if (lane == 0) {
+            wmin[wave] = lo;
+            wmax[wave] = hi;
+        }
+        hist[0][tid] = 0;
+        if (tid == 0) listn = 0;
+        __syncthreads();
+        for (int w = 0; w < GA_THREADS / 64; ++w) {
+            lo = min(lo, wmin[w]);
+            hi = max(hi, wmax[w]);
+        }
+        lo = readlane_u64(lo, 0);
+        hi = readlane_u64(hi, 0);
+        // the least shift that leaves fewer than GR_BINS bins
+        int shift = max(0, 64 - 10 - (int)__builtin_clzll((hi - lo) | 1ull));
+        int rank = T;              // among the keys of [lo, hi]
+        static_assert(GR_BINS == 1024 && GA_THREADS == GR_BINS, "10 bits a cut, one bin cleared per thread");
+        for (int pass = 0;; ++pass) {
+            int *h = hist[pass % 3];
+            hist[(pass + 1) % 3][tid] = 0;
+            const u64 span = hi - lo;
+#pragma unroll
+            for (int r = 0; r < RPT; ++r)
+#pragma unroll
+                for (int j = 0; j < GR_NU; ++j) {
+                    const u64 x = key[r][j] - lo;      // (keys below lo wrap around to large values)
+                    if (valid(r, j) && x <= span) atomicAdd(&h[(int)(x >> shift)], 1);
+                }
+            __syncthreads();
+            // the bin of the rank-th largest: 16 bins per lane, then the 16 bins of that lane
+            const int4 *h4 = (const int4 *)(h + 16 * lane);
+            int mine = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int4 c = h4[q];
+                mine += (c.x + c.y) + (c.z + c.w);
+            }
+            const int inc = scan_incl<false>(mine);
+            const int above = __builtin_amdgcn_readlane(inc, 63) - inc;       // keys in the bins of higher lanes
+            const int L = __ffsll((long long)__ballot(above < rank && rank <= above + mine)) - 1;      // exactly one lane
+            const int aboveL = __builtin_amdgcn_readlane(above, L), mineL = __builtin_amdgcn_readlane(mine, L);
+            const int c1 = lane < 16 ? h[16 * L + lane] : 0;
+            const int above1 = aboveL + mineL - scan_incl<true>(c1);
+            const int L1 = __ffsll((long long)__ballot(lane < 16 && above1 < rank && rank <= above1 + c1)) - 1;
+            rank -= __builtin_amdgcn_readlane(above1, L1);
+            const int left = __builtin_amdgcn_readlane(c1, L1);
+            lo += (u64)(16 * L + L1) << shift;
+            hi = lo + ((1ull << shift) - 1ull);
+            if (shift == 0) {      // one value left
+                thr = lo;
+                R = rank;
+                ties = left > rank;
+                break;
+            }
+            if (left <= GR_LIST) {
+                const u64 sp = hi - lo;
+#pragma unroll
+                for (int r = 0; r < RPT; ++r)
+#pragma unroll
+                    for (int j = 0; j < GR_NU; ++j)
+                        if (valid(r, j) && key[r][j] - lo <= sp) list[min(atomicAdd(&listn, 1), GR_LIST - 1)] = key[r][j];
+                __syncthreads();
+                const u64 x = lane < left ? list[lane] : 0ull;
+                int gt = 0, eq = 0;
+                for (int q = 0; q < left; ++q) {
+                    const u64 y = list[q];
+                    gt += y > x ? 1 : 0;
+                    eq += y == x ? 1 : 0;
+                }
+                const int l = __ffsll((long long)__ballot(lane < left && gt < rank && rank <= gt + eq)) - 1;
+                thr = readlane_u64(x, l);
+                R = rank - __builtin_amdgcn_readlane(gt, l);
+                ties = __builtin_amdgcn_readlane(eq, l) > R;
+                break;
+            }
+            shift = max(0, shift - 10);
+        }
+    }
+    // equal keys ahead of this thread's, in index order (rows ascending: slot by slot, thread by thread)
+    int before[RPT];
+    if (tid < 8) cnt[tid] = 0;
+    if (ties) {                    // (the same in every thread)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            int c = 0;
+#pragma unroll
+            for (int j = 0; j < GR_NU; ++j) c += (valid(r, j) && key[r][j] == thr) ? 1 : 0;
+            const int inc = scan_incl<false>(c);
+            before[r] = inc - c;
+            if (lane == 63) wsum[r][wave] = inc;
+        }
+    }
+    __syncthreads();
+    if (ties) {
+        int total = 0;
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            for (int w = 0; w < GA_THREADS / 64; ++w) {
+                if (w == wave) before[r] += total;
+                total += wsum[r][w];
+            }
+        }
+    }
+    // the widths, counted per wavefront with ballots
+    int wcnt[GR_NU + 1] = {0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        int up = 0, eqs = ties ? before[r] : 0;
+#pragma unroll
+        for (int j = 0; j < GR_NU; ++j) {
+            if (j >= nu) continue;
+            bool take;
+            if (T <= 0) take = false;
+            else if (T >= nk) take = true;
+            else if (!ties) take = key[r][j] >= thr;
+            else take = key[r][j] > thr || (key[r][j] == thr && eqs++ < R);
+            up += take ? 1 : 0;
+        }
+        const int i = tid + r * GA_THREADS;
+        if (i < n) bits[i] = (uint8_t)(bmin + up);
+#pragma unroll
+        for (int v = 0; v <= GR_NU; ++v) wcnt[v] += __popcll(__ballot(i < n && up == v));
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int v = 0; v <= GR_NU; ++v)
+            if (wcnt[v]) atomicAdd(&cnt[bmin + v], wcnt[v]);
+    }
+    __syncthreads();
+    if (tid < 8) info[tid] = cnt[tid];
+    if (tid == 0) {
+        long long spent = 0;
+        for (int b = 0; b < 8; ++b) spent += (long long)cnt[b] * b;
+        info[8] = spent;
+        info[9] = budget;
+    }
+}
+
 }  // namespace
 
 extern "C" skim_status skim_greedy_allocate_device(skim_ctx *ctx, const double *E, int64_t n, int bmin, int bmax,
@@ -232,9 +456,22 @@ extern "C" skim_status skim_greedy_allocate_device(skim_ctx *ctx, const double *
     if (B < (int64_t)bmin * n || B > (int64_t)bmax * n)
         SKIM_FAIL(ctx, SKIM_ERR_BUDGET, "budget %lld outside [%lld, %lld]", (long long)B, (long long)(bmin * n), (long long)(bmax * n));
     const int nb = bmax - bmin + 1;
+    const int64_t T = B - (int64_t)bmin * n;      // upgrades to take
     const size_t need = (size_t)n * (nb > 1 ? nb - 1 : 1) * sizeof(u64);
     if (!ctx->ws || ctx->ws_bytes < need)
         SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
+    if (nb - 1 <= GR_NU && n <= (int64_t)GR_MAX_RPT * GA_THREADS) {
+        auto launch = [&](auto rpt) {
+            hipLaunchKernelGGL(greedy_rows_kernel<decltype(rpt)::value>, dim3(1), dim3(GA_THREADS), 0, ctx->stream, E, (int)n, bmin,
+                               nb, (int)T, bits, (long long *)info, (long long)B);
+        };
+        if (n <= GA_THREADS) launch(std::integral_constant<int, 1>{});
+        else if (n <= 4 * GA_THREADS) launch(std::integral_constant<int, 4>{});
+        else if (n <= 8 * GA_THREADS) launch(std::integral_constant<int, 8>{});
+        else launch(std::integral_constant<int, GR_MAX_RPT>{});
+        SKIM_HIP(ctx, hipGetLastError());
+        return SKIM_OK;
+    }
     const size_t key_bytes = (size_t)n * (nb > 1 ? nb - 1 : 1) * sizeof(u64);
     const int keys_in_lds = key_bytes <= GA_LDS_KEYS;
     if (keys_in_lds && !ctx->greedy_lds_enabled) {
@@ -243,7 +480,7 @@ extern "C" skim_status skim_greedy_allocate_device(skim_ctx *ctx, const double *
         ctx->greedy_lds_enabled = 1;
     }
     hipLaunchKernelGGL(greedy_select_kernel, dim3(1), dim3(GA_THREADS), keys_in_lds ? key_bytes : 0, ctx->stream, E,
-                       (long long)n, bmin, nb, (long long)(B - (int64_t)bmin * n), (u64 *)ctx->ws, bits, (long long *)info,
+                       (long long)n, bmin, nb, (long long)T, (u64 *)ctx->ws, bits, (long long *)info,
                        (long long)B, keys_in_lds);
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;

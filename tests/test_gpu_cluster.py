@@ -405,6 +405,31 @@ def test_device_greedy_equals_host_and_oracle(ctx, gpu_lib, kind, n, avg):
         assert np.array_equal(got, oracle.greedy(E, avg)["bits"])
 
 
+@pytest.mark.parametrize("kind", ["smooth", "ties", "nonmonotone", "dead rows"])
+@pytest.mark.parametrize("n", [63, 1024, 1025, 4097, 8193, 12288, 12289])
+@pytest.mark.parametrize("bmin,bmax", [(1, 4), (2, 3), (3, 7)])
+def test_device_greedy_where_the_rows_per_thread_change(ctx, gpu_lib, kind, n, bmin, bmax):
+    """Tables at the ends of the ranges that the variants with the keys in registers serve, and beyond them (more rows,
+    more than three upgrades per row): the host function's bits, for budgets from one upgrade to all but one.  Dead rows:
+    reductions of zero next to values over forty orders of magnitude (the keys crowd at either end of their range)."""
+    rng = np.random.default_rng(n + bmax + len(kind))
+    nb = bmax - bmin + 1
+    if kind == "dead rows":
+        E = np.cumsum(10.0 ** rng.uniform(-40, 0, (n, nb)), axis=1)[:, ::-1].copy()
+        E[rng.random(n) < 0.3] = 0.0
+    else:
+        E = np.concatenate([_tables(rng, n, kind) for _ in range(2)], axis=1)[:, :nb].copy()
+    for up in (1, n // 3, (nb - 1) * n // 2, (nb - 1) * n - 1):
+        avg = bmin + up / n
+        out = ctx.greedy_allocate_device(dev(E), avg, bmin=bmin, bmax=bmax)
+        torch.cuda.synchronize()
+        bits_h, spent, budget = gpu_lib.greedy_allocate(E, avg, bmin=bmin, bmax=bmax)
+        assert np.array_equal(out["bits"].cpu().numpy(), bits_h)
+        info = out["info"].cpu().numpy()
+        assert info[8] == spent == budget == info[9]
+        assert np.array_equal(info[:8], np.bincount(bits_h, minlength=8))
+
+
 @pytest.mark.parametrize("kind", ["smooth", "ties", "nonmonotone", "flat"])
 @pytest.mark.parametrize("n,avg,bmin,bmax", [(1, 2.0, 1, 4), (7, 1.0, 1, 4), (7, 4.0, 1, 4), (100, 2.5, 1, 4),
                                              (129, 3.2, 1, 4), (1000, 3.2, 1, 4), (4096, 3.2, 1, 4),
