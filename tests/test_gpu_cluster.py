@@ -370,6 +370,37 @@ def test_unpack_and_dequant_matvec_match_oracle(ctx, gpu_lib, n, m, with_alpha):
     assert np.all(np.abs(yf2.cpu().numpy().astype(np.float64) - yref) <= 1e-5 * scale)
 
 
+@pytest.mark.parametrize("m", [1, 3, 31, 257, 1022, 4099, 4160])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_unpack_at_any_alignment(ctx, gpu_lib, m, offset):
+    """Rows shorter than four columns up to more than one round of a workgroup, the matrix at any multiple of four bytes:
+    bit-exact, and nothing written outside the matrix."""
+    n = 23
+    rng = np.random.default_rng(m)
+    bits = np.repeat(np.arange(1, 5), 6)[:n].astype(np.uint8)[rng.permutation(n)]
+    W = rng.standard_normal((n, m)).astype(np.float32)
+    cent = np.sort(rng.standard_normal((n, 16)), axis=1)
+    upper = np.full((n, 16), -np.inf, np.float32)
+    for i in range(n):
+        K = 1 << bits[i]
+        upper[i, :K] = cent[i, :K]
+        upper[i, K - 1] = 10.0
+    pk = ctx.pack(dev(W), dev(bits), dev(cent), dev(upper), bits_host=bits)
+    al = skim_synth.make_alpha(5, m)
+    args = (pk["codes"].cpu().numpy().view(np.uint32), pk["group_word_offset"].cpu().numpy(),
+            pk["row_perm"].cpu().numpy(), pk["codebooks"].cpu().numpy().view(np.uint16), m)
+    for alpha in (None, al):
+        ald = None if alpha is None else dev(alpha)
+        buf = torch.full((n * m + 8,), 7.0, device="cuda")
+        ctx._check(ctx.lib.skim_unpack(ctx.h, pk["codes"].data_ptr(), pk["group_word_offset"].data_ptr(), pk["row_perm"].data_ptr(),
+                                       pk["codebooks"].data_ptr(), ald.data_ptr() if ald is not None else None, n, m,
+                                       buf.data_ptr() + 4 * offset))
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[offset:offset + n * m].reshape(n, m), oracle.unpack(*args, alpha=alpha))
+        assert np.all(got[:offset] == 7.0) and np.all(got[offset + n * m:] == 7.0)
+
+
 def _tables(rng, n, kind):
     if kind == "smooth":
         g = np.sort(rng.random((n, 3)), axis=1)[:, ::-1] * rng.random((n, 1))
