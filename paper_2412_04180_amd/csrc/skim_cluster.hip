@@ -1328,10 +1328,11 @@ struct LevelMap {
     int nlev;        // levels 0 .. nlev-1 of the second-moment tree
     int n[8];        // entries per level
     int roff[8];     // byte offset of the second-moment sums of level >= 2 inside the row's LDS block
-    int w16_off, ppd_off, ppn_off, bytes;   // first weights; running sums of s and of s*w (n[1] + 1 double2 each)
+    int w16_off, ppd_off, ppn_off, bytes;   // first weights; running sums of s and of s*w (np + 1 double2 each)
+    int np;          // groups the running sums are kept for: n[1] groups of 4 chunks, or (wide) n[2] groups of 16
     int n2, t1_off, t2_off;                 // search tree over the first weights: every 8th, every 64th (n2 of them)
 };
-__host__ __device__ inline LevelMap level_map(int n1u) {
+__host__ __device__ inline LevelMap level_map(int n1u, bool wide) {
     LevelMap L;
     L.w16_off = 0;
     int o = ((n1u + 7) & ~7) * 4;
@@ -1349,10 +1350,11 @@ __host__ __device__ inline LevelMap level_map(int n1u) {
     } while (n > 1);
     for (int k = lv + 1; k < 8; ++k) L.n[k] = 0;
     L.nlev = lv + 1;
+    L.np = wide ? L.n[2] : L.n[1];
     L.ppd_off = o;
-    o += (L.n[1] + 1) * 16;
+    o += (L.np + 1) * 16;
     L.ppn_off = o;
-    o += (L.n[1] + 1) * 16;
+    o += (L.np + 1) * 16;
     L.roff[0] = 0;
     L.roff[1] = 0;
     for (int k = 2; k < 8; ++k) {
@@ -1430,14 +1432,16 @@ __device__ __forceinline__ double quick_div(double n, double d) {
 }
 
 // RAGGED: the row length is not a multiple of 16, so the last chunk holds fewer than 16 keys.
-// WAVES: wavefronts per SIMD the kernel is compiled for.  2 needs no spills (187 registers); when a matrix has more
-// rows than 2 per SIMD can hold at once, 3 (168 registers, about 70 of them spilled) finishes sooner all the same.
-template <bool RAGGED, int WAVES>
-__global__ void __launch_bounds__(ITER_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
+// WIDE: the running sums are kept ahead of every 16 chunks instead of every 4, and a range takes up to 3 + 3 sums of
+// 4 chunks more from global memory, requested with the chunk sums.  The LDS of a long row is mostly running sums: at 22016
+// keys per row 4 workgroups fitted a compute unit and the kernel waited on latency with one wavefront per SIMD; now 8
+// fit (8192 x 22016: 456 -> 379 us).  Rows of which 8 workgroups fit anyway do without the extra loads.
+template <bool RAGGED, bool WIDE>
+__global__ void __launch_bounds__(ITER_THREADS) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 3, WIDE ? 2 : 3)))
 lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int m = prm.m;
-    const int n1u = (m + 15) >> 4;   // LM = level_map(n1u), worked out by the host
+    const int n1u = (m + 15) >> 4;   // LM = level_map(n1u, WIDE), worked out by the host
     const int lane = threadIdx.x;
     const int h = lane >> 5, l5 = lane & 31;
 
@@ -1446,7 +1450,8 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     // array and row): the groups' sums, the first 512 first weights, the first 64 level-2 second moments.
     const int nhalf = (2ll * blockIdx.x + 1 < nrows) ? 2 : 1;
     const int ng = LM.n[1];
-    const int per = (ng + ITER_THREADS - 1) / ITER_THREADS;     // groups per lane: at most 8 (rows of up to 32768 keys)
+    // groups of 4 chunks per lane: at most 8 (rows of up to 32768 keys); whole groups of 16 chunks where those count
+    const int per = WIDE ? 4 * ((LM.np + ITER_THREADS - 1) / ITER_THREADS) : (ng + ITER_THREADS - 1) / ITER_THREADS;
     double2 qv[2][8];
     float t8[2][8];
     double rq4[2][4];
@@ -1495,7 +1500,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 #pragma unroll
             for (int u = 0; u < 8; ++u) put_w16(j0 + u * ITER_THREADS + lane, t[u]);
         }
-        // running sums ahead of every group of 4 chunks, pp[ng] = row total.  A lane takes `per` consecutive
+        // running sums ahead of every group of 4 (WIDE: 16) chunks, pp[np] = row total.  A lane takes `per` consecutive
         // groups; one double-double scan over the lanes per quantity.
         {
             double2 *ppd = (double2 *)(blkw + LM.ppd_off), *ppn = (double2 *)(blkw + LM.ppn_off);
@@ -1519,19 +1524,22 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 for (int k = 0; k < N; ++k) {
                     const int q = lane * per + k;
                     if (k < per && q < ng) {
-                        ppd[q] = rd;
-                        ppn[q] = rn;
+                        if (!WIDE || (k & 3) == 0) {
+                            ppd[WIDE ? q >> 2 : q] = rd;
+                            ppn[WIDE ? q >> 2 : q] = rn;
+                        }
                         rd = dd_add(rd, make_double2(qv[hh][k].x, 0.0));
                         rn = dd_add(rn, make_double2(qv[hh][k].y, 0.0));
                         if (q == ng - 1) {
-                            ppd[ng] = rd;
-                            ppn[ng] = rn;
+                            ppd[LM.np] = rd;
+                            ppn[LM.np] = rn;
                         }
                     }
                 }
             };
-            if (per == 1) scan(std::integral_constant<int, 1>{});
-            else if (per <= 3) scan(std::integral_constant<int, 3>{});
+            if (WIDE && per == 4) scan(std::integral_constant<int, 4>{});
+            else if (!WIDE && per == 1) scan(std::integral_constant<int, 1>{});
+            else if (!WIDE && per <= 3) scan(std::integral_constant<int, 3>{});
             else scan(std::integral_constant<int, 8>{});
         }
         // second moments: level 2 from the groups' sums in global memory
@@ -1590,26 +1598,45 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     const double2 *ppd = (const double2 *)(blk + LM.ppd_off), *ppn = (const double2 *)(blk + LM.ppn_off);
     const u64 *__restrict__ keys = prm.keys + rowc * (long long)m;
     const double2 *__restrict__ L1 = prm.L1 + rowc * prm.n1;
+    const double2 *__restrict__ Q = prm.Q + rowc * prm.nq;
 
     // ---- weighted-quantile start with strictly increasing ranks ---------------------------------
     int r = 0;
     float wstart = 0.0f;     // weight of the key at rank r, when r ends up inside the chunk read below
     bool wstart_ok = false;
     {
-        const double total = ppd[ng].x;
+        const double total = ppd[LM.np].x;
         const double tau = total * (double)(2 * p + 1) / (double)(2 * K);
         // largest group g with pre[g] < tau (pre[0] = 0 < tau)
-        int lo = 0, hi = on ? ng - 1 : 0;
+        int lo = 0, hi = on ? LM.np - 1 : 0;
         while (__ballot(lo < hi)) {
             const int mid = (lo + hi + 1) >> 1;
-            const double x = ppd[min(mid, ng)].x;
+            const double x = ppd[min(mid, LM.np)].x;
             if (lo < hi) {
                 if (x < tau) lo = mid; else hi = mid - 1;
             }
         }
         // chunk inside the group: largest chunk whose running sum ahead of it is < tau
-        int chunk = 4 * lo;
         double acc = ppd[lo].x;
+        if (WIDE) {     // group of 4 chunks inside the group of 16, in the same way
+            lo *= 4;
+            double dq[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) dq[k] = (on && lo + k + 1 < ng) ? Q[lo + k].x : 0.0;
+            bool go = on;
+            const int g0 = lo;
+            double2 pre = ppd[g0 >> 2];      // (both words: what the running sums of groups of 4 would hold)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                pre = dd_add(pre, make_double2(dq[k], 0.0));
+                go = go && (g0 + k + 1 < ng) && (pre.x < tau);
+                if (go) {
+                    acc = pre.x;
+                    lo = g0 + k + 1;
+                }
+            }
+        }
+        int chunk = 4 * lo;
         u64 el[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) el[j] = NEUTRAL_KEY;
@@ -1833,12 +1860,28 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             }
             int ga = la0 >> 2, gb = rb0 >> 2;
             if (la0 >= rb0) { ga = 0; gb = 0; }
+            double2 pq[6];
+            if (WIDE) {     // up to 3 + 3 groups of 4 at the ends of the groups of 16
+                const int ha = min(gb, (ga + 3) & ~3), hb = max(ha, gb & ~3);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    pq[k] = (resum && ga + k < ha) ? Q[ga + k] : make_double2(0.0, 0.0);
+                    pq[3 + k] = (resum && hb + k < gb) ? Q[hb + k] : make_double2(0.0, 0.0);
+                }
+                ga = ha >> 2;
+                gb = hb >> 2;
+                if (ha >= hb) { ga = 0; gb = 0; }
+            }
             const double2 da = ppd[ga], db = ppd[gb], na = ppn[ga], nb = ppn[gb];
             double sD = dd_diff(db, da), sN = dd_diff(nb, na);
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
                 sD += pc[k].x;
                 sN += pc[k].y;
+                if (WIDE) {
+                    sD += pq[k].x;
+                    sN += pq[k].y;
+                }
             }
             if (resum) {
                 midD = sD;
@@ -2013,7 +2056,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         if (on && !emptyk && Dk > 0.0) Ep = fma(v, fma(v, Dk, -2.0 * Nk), Rp);
     }
     // per bit width: the clusters' errors added in position order by the lane of position 0
-    double *escr = (double *)(smem + 2 * (size_t)LM.bytes);
+    double *escr = (double *)smem;      // (over the rows' tables, which nothing reads any more)
     __syncthreads();
     escr[lane] = Ep;
     escr[64 + lane] = Rp;
@@ -2525,7 +2568,10 @@ skim_status validate_inputs(skim_ctx *ctx, const ClusterParams &prm, int64_t n) 
 
 size_t sort_lds_bytes(int P) { return (size_t)(P + P / 16) * 8; }
 
-size_t lloyd_lds_bytes(int m) { return 2 * (size_t)level_map((m + 15) >> 4).bytes + 128 * sizeof(double); }
+size_t lloyd_lds_bytes(const LevelMap &lm) {
+    const size_t tables = 2 * (size_t)lm.bytes, errors = 128 * sizeof(double);     // the errors at the end lie over the tables
+    return tables > errors ? tables : errors;
+}
 
 // Scratch layout of one call (inside the caller's workspace).
 skim_status carve_cluster_ws(skim_ctx *ctx, ClusterParams &prm, int64_t n, double **cent_scratch) {
@@ -2658,26 +2704,25 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
         return SKIM_OK;
     }
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[1], ctx->stream));
-    const LevelMap lm = level_map((prm.m + 15) >> 4);
+    LevelMap lm = level_map((prm.m + 15) >> 4, false);
     {
-        // Two wavefronts per SIMD = up to 8 workgroups per compute unit, three = up to 12, both as far as the LDS
-        // has room.  A workgroup's time hardly depends on how many are resident, so the kernel takes as many rounds of
-        // workgroups as it needs to seat them all; the three-wavefront variant (about an eighth slower per round)
-        // is taken when it saves more rounds than that.
-        const size_t llds = lloyd_lds_bytes(prm.m);
+        // Running sums at every 4 chunks as long as they leave the LDS room for 8 workgroups a compute unit (two wavefronts
+        // per SIMD; registers allow three).
+        const bool wide = 8 * (lloyd_lds_bytes(lm) + 256) > (size_t)ctx->lds_limit;
+        if (wide) lm = level_map((prm.m + 15) >> 4, true);
+        const size_t llds = lloyd_lds_bytes(lm);
         const long long wgs = (n + 1) / 2;
-        const long long fit = (long long)((size_t)ctx->lds_limit / (llds + 256));
-        const long long seats2 = ctx->num_cu * max(1ll, min(8ll, fit)), seats3 = ctx->num_cu * max(1ll, min(12ll, fit));
-        const long long rounds2 = (wgs + seats2 - 1) / seats2, rounds3 = (wgs + seats3 - 1) / seats3;
-        const bool three = 9 * rounds3 < 8 * rounds2;
         const dim3 grid((unsigned)wgs), block(ITER_THREADS);
-        if (prm.m & 15) {
-            if (three) hipLaunchKernelGGL((lloyd_iter_kernel<true, 3>), grid, block, llds, ctx->stream, prm, (long long)n, lm);
-            else hipLaunchKernelGGL((lloyd_iter_kernel<true, 2>), grid, block, llds, ctx->stream, prm, (long long)n, lm);
-        } else {
-            if (three) hipLaunchKernelGGL((lloyd_iter_kernel<false, 3>), grid, block, llds, ctx->stream, prm, (long long)n, lm);
-            else hipLaunchKernelGGL((lloyd_iter_kernel<false, 2>), grid, block, llds, ctx->stream, prm, (long long)n, lm);
-        }
+        auto launch = [&](auto ragged, auto w) {
+            hipLaunchKernelGGL((lloyd_iter_kernel<decltype(ragged)::value, decltype(w)::value>), grid, block,
+                               llds, ctx->stream, prm, (long long)n, lm);
+        };
+        auto pick = [&](auto ragged) {
+            if (wide) launch(ragged, std::true_type{});
+            else launch(ragged, std::false_type{});
+        };
+        if (prm.m & 15) pick(std::true_type{});
+        else pick(std::false_type{});
     }
     hipLaunchKernelGGL(finish_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, ctx->stream, prm);
     if (ctx->profiling) {

@@ -112,6 +112,18 @@ def test_ragged_row_lengths(ctx, m):
     assert excused <= 1
 
 
+@pytest.mark.parametrize("m", [11264, 11808, 12289, 14000, 16384])
+def test_rows_whose_running_sums_are_kept_for_groups_of_16_chunks(ctx, m):
+    """Rows of one sort on either side of the length from which the iterations keep their running sums for wider groups,
+    with an element that outweighs the rest, a row of one value and part-filled last groups."""
+    W, S = skim_synth.make_ws_small(m, 6, m, dup_frac=0.05)
+    S[1, m // 3] = 1e12
+    W[4] = 0.25
+    ref, out, excused = check_table(ctx, W, S)
+    bits = np.array([1, 2, 3, 4, 3, 2], np.uint8)
+    check_rows(ctx, W, S, bits)
+
+
 @pytest.mark.parametrize("m", [16385, 16400, 20000, 32768])
 def test_rows_longer_than_one_lds_sort(ctx, m):
     W, S = skim_synth.make_ws_small(m, 6, m, dup_frac=0.05)
@@ -399,6 +411,26 @@ def test_unpack_at_any_alignment(ctx, gpu_lib, m, offset):
         got = buf.cpu().numpy()
         assert np.array_equal(got[offset:offset + n * m].reshape(n, m), oracle.unpack(*args, alpha=alpha))
         assert np.all(got[:offset] == 7.0) and np.all(got[offset + n * m:] == 7.0)
+
+
+@pytest.mark.parametrize("n,m", [(1, 33), (5, 8225), (2051, 2080), (4100, 4128), (16400, 2080), (600, 16416), (300, 32768)])
+def test_matvec_shapes(ctx, n, m):
+    """Sizes at which a workgroup takes 2, 4 or 8 rows (part-filled last ones; bit widths changing inside one) and one or
+    several rounds of columns, against the float64 product with the unpacked matrix."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    W = torch.randn((n, m), device="cuda", generator=g)
+    bits = (torch.arange(n, device="cuda") % 4 + 1).to(torch.uint8)
+    cent = torch.sort(torch.randn((n, 16), device="cuda", generator=g), dim=1)[0].double()
+    upper = cent.float()
+    pk = ctx.pack(W, bits, cent, upper, bits_host=bits.cpu().numpy())
+    al = dev(skim_synth.make_alpha(5, m))
+    x = torch.randn(m, device="cuda", generator=g)
+    Wq = ctx.unpack(pk, m, alpha=al).double()
+    ref, scale = Wq @ x.double(), Wq.abs() @ x.double().abs()
+    y, yf = ctx.dequant_matvec(pk, m, x, alpha=al), ctx.dequant_matvec_f32(pk, m, x, alpha=al)
+    torch.cuda.synchronize()
+    assert bool(((y - ref).abs() <= 1e-12 * scale).all())
+    assert bool(((yf.double() - ref).abs() <= 1e-5 * scale).all())
 
 
 def _tables(rng, n, kind):
