@@ -413,7 +413,7 @@ def test_unpack_at_any_alignment(ctx, gpu_lib, m, offset):
         assert np.all(got[:offset] == 7.0) and np.all(got[offset + n * m:] == 7.0)
 
 
-@pytest.mark.parametrize("n,m", [(1, 33), (5, 8225), (2051, 2080), (4100, 4128), (16400, 2080), (600, 16416), (300, 32768)])
+@pytest.mark.parametrize("n,m", [(1, 5), (3, 33), (5, 8225), (2051, 2088), (4100, 4128), (8200, 2049), (600, 16411), (300, 32768)])
 def test_matvec_shapes(ctx, n, m):
     """Sizes at which a workgroup takes 2, 4 or 8 rows (part-filled last ones; bit widths changing inside one) and one or
     several rounds of columns, against the float64 product with the unpacked matrix."""
@@ -431,6 +431,35 @@ def test_matvec_shapes(ctx, n, m):
     torch.cuda.synchronize()
     assert bool(((y - ref).abs() <= 1e-12 * scale).all())
     assert bool(((yf.double() - ref).abs() <= 1e-5 * scale).all())
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 16384, 16385, 33000])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_pack_row_order(ctx, n, offset):
+    """Positions of the packed rows where the number of rows a thread of the plan takes changes, rows left out among them
+    (bits 0 and 7), the bits at any address."""
+    m = 16
+    g = torch.Generator(device="cuda").manual_seed(n)
+    W = torch.randn((n, m), device="cuda", generator=g)
+    cent = torch.sort(torch.randn((n, 16), device="cuda", generator=g), dim=1)[0].double()
+    buf = torch.zeros(n + 8, dtype=torch.uint8, device="cuda")
+    bits = buf[offset:offset + n]
+    bits.copy_(torch.randint(0, 6, (n,), device="cuda", generator=g))
+    bits[bits == 5] = 7
+    b = bits.cpu().numpy()
+    codes = torch.zeros(n, 4, dtype=torch.int32, device="cuda")
+    gwo, perm = torch.zeros(6, dtype=torch.int64, device="cuda"), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cbs = torch.zeros(n * 16, dtype=torch.int16, device="cuda")
+    ctx.ensure_workspace(n, m)
+    up = cent.float()
+    ctx._check(ctx.lib.skim_pack(ctx.h, W.data_ptr(), None, n, m, m, bits.data_ptr(), cent.data_ptr(), up.data_ptr(),
+                                 codes.data_ptr(), gwo.data_ptr(), perm.data_ptr(), cbs.data_ptr(), None))
+    torch.cuda.synchronize()
+    want = np.concatenate([np.flatnonzero(b == q) for q in (1, 2, 3, 4)])
+    got = perm.cpu().numpy()
+    assert np.array_equal(got[:len(want)], want) and np.all(got[len(want):] == -1)
+    sizes = [int((b == q).sum()) * ((m * q + 31) // 32) for q in (1, 2, 3, 4)]
+    assert gwo.cpu().numpy().tolist() == [0] + np.cumsum([0] + sizes).tolist()
 
 
 def _tables(rng, n, kind):
