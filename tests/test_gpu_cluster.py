@@ -283,6 +283,49 @@ def test_weights_converted_from_a_16_bit_format(ctx, fmt):
     check_rows(ctx, W[rows], S[rows], bits)
 
 
+@pytest.mark.parametrize("m", [64, 200, 1040])
+@pytest.mark.parametrize("values", [3, 5, 17, 40])
+def test_centroids_that_start_on_equal_weights(ctx, m, values):
+    """Rows of few distinct weights whose sensitivity lies on a few neighbouring ranks: runs of 2 to 16 positions with the same
+    value, at the bottom, in the middle and at the top of every bit width, over the first iterations and until they stay."""
+    rng = np.random.default_rng(100 * m + values)
+    n = 24
+    W = rng.choice((np.arange(values, dtype=np.float32) - values // 2) / 8.0, (n, m)).astype(np.float32)
+    S = rng.random((n, m)).astype(np.float32)
+    for i in range(n):          # most of the row's mass on one value
+        S[i, W[i] == np.unique(W[i])[(i * values // n) % len(np.unique(W[i]))]] *= 1000.0 ** (i % 3)
+    for iters in (1, 2, 30):
+        check_table(ctx, W, S, iters=iters)
+    check_rows(ctx, W, S, rng.integers(1, 5, n).astype(np.uint8))
+
+
+@pytest.mark.parametrize("m", [18, 2047, 2052, 4100])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_labels_at_any_alignment(ctx, m, offset):
+    """The label pass with 16- and 4-byte accesses and the one column by column give the same labels, scaled or not."""
+    n = 9
+    W, S = skim_synth.make_ws_small(m, n, m)
+    bits = dev(np.arange(n).astype(np.uint8) % 4 + 1)
+    buf = torch.zeros((n, m + 7), device="cuda")
+    buf[:, offset:offset + m] = dev(W)
+    Sb = torch.zeros((n, m + 7), device="cuda")
+    Sb[:, offset:offset + m] = dev(S)
+    for al in (None, dev(skim_synth.make_alpha(3, m))):
+        a = ctx.cluster_rows(dev(W), dev(S), bits, alpha=al)
+        b = ctx.cluster_rows(buf[:, offset:offset + m], Sb[:, offset:offset + m], bits, alpha=al)
+        lab = torch.zeros(n * m + 4, dtype=torch.uint8, device="cuda")[offset:offset + n * m].view(n, m)
+        c = ctx.cluster_rows(dev(W), dev(S), bits, alpha=al, out=dict(a, labels=lab))
+        torch.cuda.synchronize()
+        wt = dev(W) if al is None else dev(W) / al
+        for i in range(n):
+            K = 1 << (i % 4 + 1)
+            up = a["upper"][i, :K]
+            order = torch.argsort(up, stable=True)
+            want = order[torch.searchsorted(up[order], wt[i])].to(torch.uint8)
+            assert torch.equal(a["labels"][i], want)
+        assert torch.equal(a["labels"], b["labels"]) and torch.equal(a["labels"], c["labels"])
+
+
 def test_pack_mixed_bits_matches_oracle_layout(ctx):
     n, m = 97, 1111
     W, S = skim_synth.make_ws_small(80, n, m)
