@@ -2231,31 +2231,64 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
         // disjoint and ordered by position; empty ones have upper = -inf)
         // thr[0..K) holds the bounds by position; positions are ordered by centroid, and so are the
         // bounds of the non-empty ones.  Empty positions (-inf) are skipped by carrying the running
-        // maximum forward, which keeps the array sorted for the binary search.
-        if (tid == 0) {
-            float run = -INFINITY;
-            int lastl = thl[0];
-            for (int k = 0; k < 16; ++k) {
-                if (thr[k] == -INFINITY) {
-                    thr[k] = run;          // an empty range: nothing is <= run that was not caught before
-                    thl[k] = lastl;
-                } else {
-                    run = thr[k];
-                    lastl = thl[k];
+        // maximum forward, which keeps the array sorted for the binary search; their label is that of the position
+        // carried (the first position's where none is).
+        if (tid < 64) {
+            const int k = lane & 15;
+            float x = thr[k];
+            int from = x == -INFINITY ? 0 : k;
+#pragma unroll
+            for (int d = 1; d < 16; d <<= 1) {
+                const float y = __shfl_up(x, d, 16);
+                const int g = __shfl_up(from, d, 16);
+                if (k >= d) {
+                    x = fmaxf(x, y);
+                    from = max(from, g);
                 }
             }
+            const int l = thl[from];
+            thr[k] = x;          // (four times the same)
+            thl[k] = l;
         }
         __syncthreads();
         const float *Wr = prm.W + row * prm.ld;
         uint8_t *Lr = prm.labels + row * (long long)m;
-        for (int j = tid; j < m; j += FIN_THREADS) {
-            const float w = Wr[j];
-            const float wt = prm.alpha ? __fdiv_rn(w, prm.alpha[j]) : w;
+        auto label = [&](float wt) -> uint32_t {
             int pos = (thr[7] < wt) ? 8 : 0;
             pos += (thr[pos + 3] < wt) ? 4 : 0;
             pos += (thr[pos + 1] < wt) ? 2 : 0;
             pos += (thr[pos] < wt) ? 1 : 0;
-            Lr[j] = (uint8_t)thl[pos];
+            return (uint32_t)thl[pos];
+        };
+        // four neighbouring columns a thread where the rows of W, alpha and the labels allow 16- and 4-byte accesses, the
+        // loads of two steps in flight (column by column before; 4096 x 4096, the whole kernel with
+        // alpha: 34.5 -> 24.6 us)
+        const int head = (((uintptr_t)Wr | (uintptr_t)prm.alpha) & 15) == 0 && ((uintptr_t)Lr & 3) == 0 ? (m & ~3) : 0;
+        constexpr int LU = 2;
+        for (int j0 = 4 * tid; j0 < head; j0 += 4 * LU * FIN_THREADS) {
+            float4 w[LU], al[LU];
+#pragma unroll
+            for (int u = 0; u < LU; ++u) {
+                const int j = j0 + 4 * u * FIN_THREADS;
+                w[u] = al[u] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                if (j < head) {
+                    w[u] = *(const float4 *)(Wr + j);
+                    if (prm.alpha) al[u] = *(const float4 *)(prm.alpha + j);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < LU; ++u) {
+                const int j = j0 + 4 * u * FIN_THREADS;
+                if (prm.alpha)
+                    w[u] = make_float4(__fdiv_rn(w[u].x, al[u].x), __fdiv_rn(w[u].y, al[u].y), __fdiv_rn(w[u].z, al[u].z),
+                                       __fdiv_rn(w[u].w, al[u].w));
+                const uint32_t l = label(w[u].x) | (label(w[u].y) << 8) | (label(w[u].z) << 16) | (label(w[u].w) << 24);
+                if (j < head) *(uint32_t *)(Lr + j) = l;
+            }
+        }
+        for (int j = head + tid; j < m; j += FIN_THREADS) {
+            const float w = Wr[j];
+            Lr[j] = (uint8_t)label(prm.alpha ? __fdiv_rn(w, prm.alpha[j]) : w);
         }
     }
 }
