@@ -4,8 +4,9 @@
 // Same order as the host function: upgrade j of a row is taken when the running minimum
 // k_j = min(g_1 .. g_j) of the row's reductions comes up, and the greedy loop takes the
 // upgrades in the order (k descending, row ascending, j ascending).  The first T = budget -
-// n * bmin of them are found by a most-significant-digit radix selection on the keys
-// (8 digits of 8 bits, one workgroup), ties at the threshold value in index order.
+// n * bmin of them are found in one workgroup: by cuts of the keys' interval with the keys in registers
+// (greedy_rows_kernel: the usual tables), or by a most-significant-digit radix selection (greedy_select_kernel:
+// 8 digits of 8 bits), ties at the threshold value in index order.
 #include "skim_common.h"
 
 #include <math.h>
@@ -68,8 +69,8 @@ __global__ void __launch_bounds__(GA_THREADS) greedy_select_kernel(const double 
     if (tid < 8) cnt[tid] = 0;
     __syncthreads();
 
-    // up to 16 keys per thread stay in registers over the eight passes (tables of up to 5461 rows
-    // at three upgrades per row); larger tables re-read the keys from global memory
+    // up to 16 keys per thread stay in registers over the eight passes (tables of up to 4096 rows
+    // at four upgrades per row); larger tables re-read the keys from global memory
     constexpr int KPT = 16;
     const bool in_regs = nk <= (long long)GA_THREADS * KPT;
     u64 rk[KPT];
