@@ -482,6 +482,8 @@ def bench_scale_loop(ctx, torch, np, skim_synth, iters=3):
     torch.cuda.synchronize()
     t_train = e[2].elapsed_time(e[3])
     trace = tr["loss_trace"].cpu().numpy()
+    loss_blocks = (m + 255) // 256
+    loss_share = (loss_blocks + 1) / (2 * loss_blocks)
     return {"workload": "4096x4096, H 4096^2, 3 bits", "scale_step_ms": round(t_step / iters, 4),
             "hessian_131072x4096_ms": round(t_h, 3),
             # 2 N m^2 flops of the full product per second; the kernel computes the tiles on and above the diagonal
@@ -497,11 +499,12 @@ def bench_scale_loop(ctx, torch, np, skim_synth, iters=3):
             "recluster_ms": round(t_cluster / iters, 4), "layer_loss_ms": round(t_loss / iters, 4),
             # 2 n m^2 flops of the contraction per second of the whole layer-loss call.  The contraction runs on the
             # bf16 matrix cores with every float32 operand cut into three bfloat16 pieces (the six leading piece
-            # products per k: float32-grade result): the matrix cores execute 6 x 2 n m^2 flops
+            # products per k: float32-grade result); H being symmetric, the loss takes the 256-column blocks on and below
+            # its diagonal: the matrix cores execute 6 x 2 n m^2 flops times (blocks + 1) / (2 blocks)
             "layer_loss_tflops": round(flops / (t_loss / iters * 1e-3) / 1e12, 2),
-            "layer_loss_executed_bf16_tflops": round(6 * flops / (t_loss / iters * 1e-3) / 1e12, 1),
+            "layer_loss_executed_bf16_tflops": round(loss_share * 6 * flops / (t_loss / iters * 1e-3) / 1e12, 1),
             "mfma_bf16_peak_tflops": 2500.0,
-            "layer_loss_frac_of_mfma_peak": round(6 * flops / (t_loss / iters * 1e-3) / 1e12 / 2500.0, 4),
+            "layer_loss_frac_of_mfma_peak": round(loss_share * 6 * flops / (t_loss / iters * 1e-3) / 1e12 / 2500.0, 4),
             "mfma_f32_peak_tflops": MFMA_F32_PEAK_TFLOPS,
             "layer_loss_over_f32_mfma_peak": round(flops / (t_loss / iters * 1e-3) / 1e12 / MFMA_F32_PEAK_TFLOPS, 4),
             "loss_after_each_iteration": losses}
