@@ -285,10 +285,14 @@ skim_status skim_dequant_matvec_f32(skim_ctx *ctx, const uint32_t *codes, const 
  * The call works with any workspace or none, but only with one of at least
  * skim_hessian_workspace_bytes(ctx, N, m) bytes can it split the activations of a tile
  * over several compute units (partial tiles live there; up to about 4 x (compute units)
- * x 256 KB beyond one tile each). */
+ * x 256 KB beyond one tile each).
+ * skim_hessian_from_activations_scratch is the same call with the caller's scratch (dev, 256-byte
+ * aligned; NULL = none) in the place of the registered workspace, which it leaves alone. */
 size_t skim_hessian_workspace_bytes(const skim_ctx *ctx, int64_t N, int64_t m);
 skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m,
                                           float *H);
+skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m, float *H,
+                                                  void *scratch, size_t scratch_bytes);
 
 /* Layer-wise (L-full) loss of Alg. 2 with fixed labels:
  *   c   = calc_centroids(W * alpha^-1, L)      (weighted means, weights S alpha^2)

@@ -25,7 +25,7 @@ EXPORTS = ["skim_create", "skim_destroy", "skim_last_error", "skim_workspace_byt
            "skim_profile_enable", "skim_profile_last", "skim_validate_enable",
            "skim_error_table", "skim_error_table_lfull", "skim_cluster_rows", "skim_select_allocated", "skim_greedy_allocate", "skim_greedy_allocate_device",
            "skim_dp_allocate_scratch_bytes", "skim_dp_allocate", "skim_kmeans_optimal_scratch_bytes", "skim_kmeans_optimal",
-           "skim_packed_words", "skim_codebook_entries", "skim_pack", "skim_pack_static", "skim_layer_loss", "skim_scale_step", "skim_train_scale", "skim_unpack", "skim_dequant_matvec", "skim_dequant_matvec_f32", "skim_hessian_workspace_bytes", "skim_hessian_from_activations"]
+           "skim_packed_words", "skim_codebook_entries", "skim_pack", "skim_pack_static", "skim_layer_loss", "skim_scale_step", "skim_train_scale", "skim_unpack", "skim_dequant_matvec", "skim_dequant_matvec_f32", "skim_hessian_workspace_bytes", "skim_hessian_from_activations", "skim_hessian_from_activations_scratch"]
 
 
 class SkimError(RuntimeError):
@@ -88,6 +88,7 @@ def load_library():
         lib.skim_hessian_workspace_bytes.argtypes = [vp, i64, i64]
         lib.skim_hessian_workspace_bytes.restype = C.c_size_t
         lib.skim_hessian_from_activations.argtypes = [vp, vp, i64, i64, vp]
+        lib.skim_hessian_from_activations_scratch.argtypes = [vp, vp, i64, i64, vp, vp, C.c_size_t]
         lib.skim_unpack.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp]
         lib.skim_dequant_matvec.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp, vp]
         lib.skim_dequant_matvec_f32.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp, vp]
@@ -149,6 +150,7 @@ class Context:
             raise SkimError(st, self.lib.skim_last_error(None).decode())
         self.h = h
         self._ws = None
+        self._hessian_blocks = []
 
     def close(self):
         if getattr(self, "h", None):
@@ -169,9 +171,7 @@ class Context:
         return int(self.lib.skim_workspace_bytes(n, m))
 
     def ensure_workspace(self, n, m):
-        self._ensure_bytes(self.workspace_bytes(n, m))
-
-    def _ensure_bytes(self, need):
+        need = self.workspace_bytes(n, m)
         if self._ws is None or self._ws.numel() < need:
             # allocated on the context's stream: torch's allocator then ties the lifetime of the old block to
             # the work already queued on that stream
@@ -360,13 +360,31 @@ class Context:
                                              _dp(labels), _dp(loss), _dp(row_loss)))
         return dict(loss=loss, row_loss=row_loss)
 
+    def _hessian_scratch(self, need):
+        """Scratch of the Hessian: not the workspace, which captured calls may hold (as they may hold a block of this one:
+        a block that has become too small is kept until the context goes; sizes double, so all blocks together stay below
+        twice the last).  None while the stream is captured, or where the card has no room: the call then runs without."""
+        t = self.torch
+        blocks = self._hessian_blocks
+        if blocks and blocks[-1].numel() >= need:
+            return blocks[-1]
+        with t.cuda.stream(self.stream):
+            if need == 0 or t.cuda.is_current_stream_capturing():
+                return None
+            try:
+                blocks.append(t.empty(max(need, 2 * blocks[-1].numel() if blocks else 0), dtype=t.uint8, device=self.device))
+            except t.cuda.OutOfMemoryError:
+                return None
+        return blocks[-1]
+
     def hessian_from_activations(self, X_bf16, out=None):
         """H = X^T X / N for X: device tensor N x m of dtype bfloat16 (or its int16/uint16 bit patterns)."""
         N, m = X_bf16.shape
         assert X_bf16.is_contiguous() and X_bf16.element_size() == 2
         H = out if out is not None else self.empty((m, m), self.torch.float32)
-        self._ensure_bytes(int(self.lib.skim_hessian_workspace_bytes(self.h, N, m)))
-        self._check(self.lib.skim_hessian_from_activations(self.h, _dp(X_bf16), N, m, _dp(H)))
+        scratch = self._hessian_scratch(int(self.lib.skim_hessian_workspace_bytes(self.h, N, m)))
+        self._check(self.lib.skim_hessian_from_activations_scratch(self.h, _dp(X_bf16), N, m, _dp(H), _dp(scratch),
+                                                                   0 if scratch is None else scratch.numel()))
         return H
 
     def unpack(self, pk, m, alpha=None):

@@ -333,12 +333,18 @@ extern "C" size_t skim_hessian_workspace_bytes(const skim_ctx *ctx, int64_t N, i
 
 extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m,
                                                      float *H) {
+    return skim_hessian_from_activations_scratch(ctx, X_bf16, N, m, H, ctx ? ctx->ws : nullptr, ctx ? ctx->ws_bytes : 0);
+}
+
+extern "C" skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m, float *H,
+                                                             void *scratch, size_t scratch_bytes) {
     skim_status st = skim_enter(ctx);
     if (st != SKIM_OK) return st;
     if (!X_bf16 || !H) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_hessian_from_activations: NULL argument");
     if (N < 1 || m < 2 || (m & 1) || m > 0x7fffffff || ((uintptr_t)X_bf16 & 3))
         SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "skim_hessian_from_activations: need N >= 1, m even, X 4-byte aligned (N=%lld m=%lld)",
                   (long long)N, (long long)m);
+    if (scratch && ((uintptr_t)scratch & 255)) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_hessian_from_activations: scratch must be 256-byte aligned");
     if (!ctx->xtx_lds_enabled) {
         SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
         SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
@@ -346,14 +352,14 @@ extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16
     }
     const int nt = (int)((m + XT - 1) / XT);
     const int G = ctx->num_cu;
-    // Without a workspace that holds the partial tiles the splits are given up, then the slots altogether
+    // Without scratch that holds the partial tiles the splits are given up, then the slots altogether
     TilePlan plan;
     const long long tiles = (long long)nt * (nt + 1) / 2;
     const int nstage = (int)((N + XK - 1) / XK);
     bool direct = true;
     for (int whole = 0; whole < 2 && direct; ++whole)
-        direct = !ctx->ws || (size_t)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, whole != 0) * TILE_SLOT_BYTES >
-                                 ctx->ws_bytes;
+        direct = !scratch || (size_t)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, whole != 0) * TILE_SLOT_BYTES >
+                                 scratch_bytes;
     if (direct) (void)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, true);
     long long grid = 0;
     for (int p = 0; p < plan.nph; ++p) {
@@ -361,7 +367,7 @@ extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16
         if (items > grid) grid = items;
     }
     if (grid > G) grid = G;
-    float4 *slots = direct ? nullptr : (float4 *)ctx->ws;
+    float4 *slots = direct ? nullptr : (float4 *)scratch;
     if (direct)
         hipLaunchKernelGGL(xtx_big_kernel<true>, dim3((unsigned)grid), dim3(X_THREADS), X_LDS_BYTES, ctx->stream, X_bf16, (long long)N,
                            (long long)m, H, nt, plan, slots);
