@@ -79,7 +79,9 @@ skim_status skim_destroy(skim_ctx *ctx);
  * call); ctx == NULL returns the text of the last skim_create failure. */
 const char *skim_last_error(const skim_ctx *ctx);
 
-/* Scratch needed by any call on an n x m matrix (bytes), and its registration.
+/* Scratch for any call on a matrix of at most n rows and m columns (bytes; it grows with both, so
+ * the size for the largest layer serves all), and its registration.  A smaller one is refused where a call cannot
+ * do with it; up to 256 MB of it are partial tiles without which the scale steps run, slower.
  * dev pointer, 256-byte aligned, must stay valid while calls use it. */
 size_t skim_workspace_bytes(int64_t n, int64_t m);
 skim_status skim_set_workspace(skim_ctx *ctx, void *dev_ptr, size_t bytes);

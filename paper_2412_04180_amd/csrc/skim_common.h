@@ -87,5 +87,8 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
                                     double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
                                     int kept_n, bool h_ready);
 
-// Bytes of the partial tiles a scale step on an n x m layer uses on a device with num_cu compute units.
-size_t skim_dwh_slot_bytes(int64_t n, int64_t m, int num_cu);
+// Room for the partial tiles of a scale step on any layer of at most n rows and m columns.
+size_t skim_dwh_slot_bytes(int64_t n, int64_t m);
+
+// What no call on an n x m matrix can do without: skim_workspace_bytes less those partial tiles.
+size_t skim_workspace_least(int64_t n, int64_t m);

@@ -124,7 +124,7 @@ extern "C" skim_status skim_profile_last(skim_ctx *ctx, float *sort_ms, float *l
 
 extern "C" const char *skim_last_error(const skim_ctx *ctx) { return ctx ? ctx->err : g_create_err; }
 
-extern "C" size_t skim_workspace_bytes(int64_t n, int64_t m) {
+size_t skim_workspace_least(int64_t n, int64_t m) {
     if (n < 0 || m < 0) return 0;
     const size_t N = (size_t)n, M = (size_t)m;
     const size_t ti = (N + 255) / 256, tj = (M + 255) / 256, nstrip = (N + 7) / 8;
@@ -134,7 +134,6 @@ extern "C" size_t skim_workspace_bytes(int64_t n, int64_t m) {
     b += 2 * N * 16 * sizeof(double);    // centroids and masses from fixed labels
     b += (ti * tj + 256) * 256 * sizeof(double) + N * sizeof(double);   // row sums of the loss, piece by piece (256 pieces beyond one per tile) and in all
     b += nstrip * (M + 1) * sizeof(double);    // per-strip column sums of the gradient and shares of the loss
-    b += skim_dwh_slot_bytes(n, m, 256);   // partial tiles of P where the tiles are split to fill the chip
     b += N * 30 * sizeof(double);        // centroid scratch of skim_error_table when the caller wants none
     b += N * (14 * M + 8192);            // clustering: sorted keys (8 B per weight), per-chunk sums and Lloyd state between the kernels
     if (M > 16384) b += N * 8 * M + N * 8 + 256;   // rows sorted in two halves: the unmerged keys, a mass flag per half
@@ -142,6 +141,11 @@ extern "C" size_t skim_workspace_bytes(int64_t n, int64_t m) {
     b += N * 4 * sizeof(double) + 1024;  // L-full error table: S-diag errors and the loss scalar at the tail
     b += N * (16 * sizeof(float) + sizeof(double)) + 1024;   // scale training: thresholds and errors of the re-clustering
     return b + 20 * 256;                 // alignment slack (every piece is 256-byte aligned)
+}
+
+extern "C" size_t skim_workspace_bytes(int64_t n, int64_t m) {
+    if (n < 0 || m < 0) return 0;
+    return skim_workspace_least(n, m) + skim_dwh_slot_bytes(n, m);   // partial tiles of P where the tiles are split to fill the chip
 }
 
 extern "C" skim_status skim_set_workspace(skim_ctx *ctx, void *dev_ptr, size_t bytes) {

@@ -15,7 +15,7 @@ extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, con
         SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_error_table_lfull: W, S, H, E_full, centroids_all, upper_all, labels_work must not be NULL");
     if (bmin < 1 || bmax > SKIM_MAX_BITS || bmin > bmax) SKIM_FAIL(ctx, SKIM_ERR_ARG, "bit range [%d,%d] outside 1..4", bmin, bmax);
     if (n < 1) SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "n = %lld out of range", (long long)n);
-    if (ctx->ws_bytes < skim_workspace_bytes(n, m))
+    if (ctx->ws_bytes < skim_workspace_least(n, m))
         SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
     const int nb = bmax - bmin + 1;
     // the tail of the workspace holds what must survive the calls below (they carve from its start)

@@ -917,10 +917,16 @@ skim_status check_shape(skim_ctx *ctx, int64_t n, int64_t m, int64_t ld) {
 
 }  // namespace
 
-size_t skim_dwh_slot_bytes(int64_t n, int64_t m, int num_cu) {
-    if (n < 1 || m < GK || (n + TILE - 1) / TILE * ((m + TILE - 1) / TILE) > 0x7fffffffll) return 0;
-    TilePlan plan;
-    return (size_t)dwh_plan(plan, n, m, num_cu) * TILE_SLOT_BYTES;
+// A bound that grows with n and m, so that a workspace made for the largest layer serves every smaller one: the plan cuts a
+// tile into stages of at least G_MIN_STAGES, and no more than PLAN_SPLIT_PHASES of its phases hold split tiles, each at
+// most one piece per compute unit (256 of them).
+size_t skim_dwh_slot_bytes(int64_t n, int64_t m) {
+    const int64_t maxsplit = m / GK / G_MIN_STAGES, most = PLAN_SPLIT_PHASES * 256;
+    if (n < 1 || maxsplit < 2) return 0;
+    const int64_t ti = (n + TILE - 1) / TILE, tj = (m + TILE - 1) / TILE;
+    if (ti >= most || tj >= most || maxsplit >= most) return (size_t)most * TILE_SLOT_BYTES;
+    const int64_t slots = ti * tj * maxsplit;
+    return (size_t)(slots < most ? slots : most) * TILE_SLOT_BYTES;
 }
 
 extern "C" skim_status skim_layer_loss(skim_ctx *ctx, const float *W, const float *S, const float *alpha,
@@ -1027,7 +1033,7 @@ extern "C" skim_status skim_train_scale(skim_ctx *ctx, const float *W, const flo
         SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_train_scale: NULL argument");
     if (outer < 1 || steps < 0 || t0 < 1 || kmeans_iters < 1)
         SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_train_scale: need outer >= 1, steps >= 0, t0 >= 1, kmeans_iters >= 1");
-    if (ctx->ws_bytes < skim_workspace_bytes(n, m))
+    if (ctx->ws_bytes < skim_workspace_least(n, m))
         SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
     // per-row clustering outputs that the caller does not ask for live at the tail of the workspace
     // (the calls below carve from its start)

@@ -50,7 +50,7 @@ long long plan_rest(int rem, int G, int nstage, int maxsplit, int phase_cost, in
 long long skim_make_plan(TilePlan &plan, int G, long long tiles, int nstage, int min_stages, int phase_cost, bool whole) {
     const int maxsplit = !whole && nstage / min_stages > 1 ? nstage / min_stages : 1;
     plan = TilePlan{};
-    plan_rest((int)tiles, G, nstage, maxsplit, phase_cost, whole ? 1 : 4, plan.ntile, plan.split, plan.nph);
+    plan_rest((int)tiles, G, nstage, maxsplit, phase_cost, whole ? 1 : PLAN_SPLIT_PHASES, plan.ntile, plan.split, plan.nph);
     long long t = 0, slots = 0;
     for (int p = 0; p < plan.nph; ++p) {
         plan.tile0[p] = (int)t;

@@ -37,6 +37,7 @@ __device__ __forceinline__ void copy_to_lds(uint32_t dst, uint32_t voff, int4v r
 constexpr int TILE = 256;
 constexpr size_t TILE_SLOT_BYTES = (size_t)TILE * TILE * sizeof(float);
 constexpr int PLAN_MAX_PHASES = 6;
+constexpr int PLAN_SPLIT_PHASES = 4;       // at most so many of them hold split tiles
 
 // How the tiles of a product are shared out: phase p takes tiles tile0 .. tile0 + ntile - 1 and cuts the summation of
 // each into `split` equal parts; part q of tile t is one piece of work.  Its sums go to a partial tile ("slot") of its own,

@@ -40,6 +40,13 @@ def test_workspace_bytes_grows_with_shape(lib):
     assert 2 * 4096 * 4096 * 4 <= a < b
 
 
+def test_workspace_of_the_largest_layer_holds_every_smaller_one(lib):
+    ns = [1, 255, 256, 257, 512, 1021, 1024, 2048, 3328, 3840, 4096, 8192, 11008, 22016]
+    ms = [16, 256, 272, 512, 1024, 2048, 3584, 4096, 4112, 8192, 11008, 16384, 16400, 22016, 32768]
+    size = np.array([[lib.skim_workspace_bytes(n, m) for m in ms] for n in ns], dtype=np.int64)
+    assert np.all(np.diff(size, axis=0) > 0) and np.all(np.diff(size, axis=1) > 0)
+
+
 def test_packed_sizes(lib):
     bits = np.array([1, 2, 3, 4, 3], np.uint8)
     assert skim.packed_words(bits, 100) == sum((100 * int(b) + 31) // 32 for b in bits)

@@ -253,3 +253,26 @@ def test_loss_and_scale_step_on_other_tile_plans(ctx, n, m, K):
     assert np.all(np.abs(out["row_loss"].cpu().numpy() - rl) <= RTOL * np.abs(rl) + 1e-9 * ref["loss"] / n)
     g = step["grad"].cpu().numpy().astype(np.float64)
     assert np.all(np.abs(g - ref["grad"]) <= RTOL * np.abs(ref["grad"]) + 1e-6 * np.abs(ref["grad"]).max())
+
+
+def test_training_and_lfull_table_run_without_the_partial_tiles(gpu_lib):
+    """The partial tiles of the contraction are optional: a workspace that lacks just them is accepted, and the results are
+    those of the full one up to the order of float32 sums (1e-6 over the terms of a row, times the steps)."""
+    n, m = 70, 2064                                  # 9 tiles of 129 stages, each cut into at most 8 parts of 16 or more
+    W, S, labels, H, al = make_case(7, n, m, 8, N=64)
+    Wd, Sd, Hd, bits = dev(W), dev(S), dev(H), dev(np.full(n, 3, np.uint8))
+    results = []
+    for short in (0, 9 * 8 * 256 * 256 * 4):
+        c = gpu_lib.Context(0)
+        size = c.workspace_bytes(n, m) - short
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        c._check(c.lib.skim_set_workspace(c.h, ws.data_ptr(), size))
+        c.ensure_workspace = lambda n, m: None
+        alpha, am, av = dev(al), dev(np.zeros(m, np.float32)), dev(np.zeros(m, np.float32))
+        tr = c.train_scale(Wd, Sd, Hd, bits, alpha, am, av, steps=3)
+        tab = c.error_table_lfull(Wd, Sd, Hd)
+        torch.cuda.synchronize()
+        results.append((tr["loss_trace"].cpu().numpy(), alpha.cpu().numpy(), tab["E_full"].cpu().numpy()))
+        c.close()
+    for full, least in zip(*results):
+        np.testing.assert_allclose(least, full, rtol=RTOL)
