@@ -300,13 +300,13 @@ skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t 
  *   c   = calc_centroids(W * alpha^-1, L)      (weighted means, weights S alpha^2)
  *   dW  = W - replace(c, L) * alpha
  *   loss = tr(dW H dW^T) = sum_i dW_i H dW_i^T  (Sec. 3.4, L-full; H ~ X X^T)
- * H: dev m x m float32 (symmetric).  labels: dev uint8 n x m.  loss: dev
+ * H: dev m x m float32.  labels: dev uint8 n x m.  loss: dev
  * float64 scalar.  row_loss: dev float64[n] (the L-full error of each channel),
  * may be NULL.  The contraction dW*H accumulates in float32 on the bf16 matrix cores, with every
  * float32 operand cut exactly into three bfloat16 pieces and the six leading piece products taken
  * per k (what is dropped is below 2^-24 of each product, the size of float32's own rounding).
- * H must be symmetric, as the H of Sec. 3.4 is: its row j is read for its column j, and the loss
- * takes the blocks below the diagonal twice instead of those above it.  The final reductions are
+ * Half of the products are taken, with the mean of H and its transpose (for a symmetric H, as the H
+ * of Sec. 3.4 is, that is H; for another one the loss is the same).  The final reductions are
  * float64.  m must be a multiple of 16. */
 skim_status skim_layer_loss(skim_ctx *ctx, const float *W, const float *S, const float *alpha,
                             const float *H, int64_t n, int64_t m, int64_t ld,
@@ -337,7 +337,8 @@ skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, const float *S
  * and an Adam update of alpha / adam_m / adam_v (dev float32[m], in place).
  * t is the 1-based step number (selects the decayed learning rate and the bias
  * correction).  loss_before: dev float64 scalar (loss at the incoming alpha).
- * grad_out: dev float32[m], may be NULL. */
+ * grad_out: dev float32[m], may be NULL.  H must be symmetric: the gradient is formed for such an H, and for m a
+ * multiple of 32 from 128 up row j of H is read for its column j. */
 skim_status skim_scale_step(skim_ctx *ctx, const float *W, const float *S, const float *H,
                             int64_t n, int64_t m, int64_t ld, const uint8_t *labels, float *alpha,
                             float *adam_m, float *adam_v, int64_t t, const skim_adam_opts *opts,

@@ -278,16 +278,50 @@ __global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *
 // products with piece indices i + j <= 4 carry everything down to 2^-24 of |x y| -- the size of float32's own
 // rounding -- and v_mfma_f32_32x32x16_bf16 does one of them for 16 k in half the time v_mfma_f32_32x32x2_f32
 // needs for 2 k: 6 x 32 clocks against 512 per 16 k.  Accumulation is float32 in the matrix core either way.
-// H (m x m float32, symmetric, m % 16 == 0) -> its planes, row j of the planes = row j of H = column j of H.
-// lower: only the columns up to the end of the 256-column block that holds j (all that the loss needs).
-__global__ void __launch_bounds__(256) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, bool lower) {
-    const long long g = (long long)blockIdx.x * 256 + threadIdx.x;     // 8 consecutive k of one row
-    const long long per_row = m >> 3;
-    if (g >= m * per_row) return;
-    const long long j = g / per_row, k = (g - j * per_row) << 3;
-    if (lower && k >= ((j | (TILE - 1)) + 1)) return;
-    const float4 a = *(const float4 *)(H + j * m + k), b = *(const float4 *)(H + j * m + k + 4);
-    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+// H (m x m float32, m % 16 == 0) -> its planes.
+//   SPLIT_ROWS     row j of the planes = row j of H (its column j where H is symmetric)
+//   SPLIT_COLUMNS  row j of the planes = column j of H
+//   SPLIT_LOWER    what the loss needs: the columns up to the end of the 256-column block that holds j; those ahead of the
+//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself)
+// A workgroup takes 64 rows x 32 k; the transposed tile goes through LDS, so both are read in whole lines.
+enum SplitMode { SPLIT_ROWS, SPLIT_COLUMNS, SPLIT_LOWER };
+constexpr int SPLIT_J = 64, SPLIT_K = 32, SPLIT_THREADS = 256;
+struct SplitTile {
+    float t[SPLIT_K][SPLIT_J + 1];
+};
+__device__ __forceinline__ void split_tile(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode, long long tile,
+                                           SplitTile &tr) {
+    const int tid = threadIdx.x;
+    const long long tk = (m + SPLIT_K - 1) / SPLIT_K;
+    const long long j0 = tile / tk * SPLIT_J, k0 = tile % tk * SPLIT_K;
+    if (mode == SPLIT_LOWER && k0 > (j0 | (TILE - 1))) return;
+    const bool turned = mode == SPLIT_COLUMNS || (mode == SPLIT_LOWER && k0 < (j0 & ~(long long)(TILE - 1)));
+    if (turned) {          // (the same in the whole workgroup)
+        const long long k = k0 + (tid >> 3), j = j0 + 8 * (tid & 7);
+        if (k < m && j < m) {
+            const float4 a = *(const float4 *)(H + k * m + j), b = *(const float4 *)(H + k * m + j + 4);
+            float *o = &tr.t[tid >> 3][8 * (tid & 7)];
+            o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+            o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+        }
+        __syncthreads();
+    }
+    const int oct = tid & 3;
+    const long long j = j0 + (tid >> 2), k = k0 + 8 * oct;       // 8 consecutive k of one row
+    if (j >= m || k >= m) return;
+    float x[8];
+    if (mode != SPLIT_COLUMNS) {
+        const float4 a = *(const float4 *)(H + j * m + k), b = *(const float4 *)(H + j * m + k + 4);
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    }
+    if (turned) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float y = tr.t[8 * oct + e][tid >> 2];
+            x[e] = (mode == SPLIT_COLUMNS || x[e] == y) ? y : 0.5f * x[e] + 0.5f * y;
+        }
+    }
     uint32_t p[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
@@ -296,6 +330,11 @@ __global__ void __launch_bounds__(256) split_rows_kernel(const float *__restrict
     for (int q = 0; q < 3; ++q)
         *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
                                               p[q][6] | (p[q][7] << 16));
+}
+inline long long split_tiles(int64_t m) { return (m + SPLIT_J - 1) / SPLIT_J * ((m + SPLIT_K - 1) / SPLIT_K); }
+__global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode) {
+    __shared__ SplitTile tr;
+    split_tile(H, m, Hp, mode, blockIdx.x, tr);
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -516,8 +555,8 @@ __global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, l
 }
 
 // 4096^3: 0.33 ms, of which the 136 stages of every workgroup take 0.28; the full product with its row sums: 0.67.
-// Loss only: dW_i H dW_i^T = sum over the 256-column blocks J of H of [ 2 sum_{K < J} dW_K H_KJ + dW_J H_JJ ] . dW_J, H being
-// symmetric: half the products.  The stages of all tiles -- tile (I, J) has those of the blocks K <= J -- form one line that is
+// Loss only: dW_i H dW_i^T = sum over the 256-column blocks J of H of [ 2 sum_{K < J} dW_K H_KJ + dW_J H_JJ ] . dW_J, the H_KJ
+// those of the mean of H and its transpose: half the products.  The stages of all tiles -- tile (I, J) has those of the blocks K <= J -- form one line that is
 // cut into equal pieces, one per workgroup; the loss is linear in the sums, so the pieces of a tile need not meet: each
 // multiplies its own sums by dW_J and leaves 256 row sums (float64) behind, at partial[(tile + workgroup) * 256 ..] (tiles
 // and workgroups both count up along the line, so no two pieces share a number).
@@ -873,9 +912,11 @@ skim_status enable_lds(skim_ctx *ctx) {
     return SKIM_OK;
 }
 
-void launch_split(skim_ctx *ctx, const LossWs &w, const float *H, int64_t m, bool lower) {
-    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((m * (m / 8) + 255) / 256)), dim3(256), 0, ctx->stream, H, (long long)m, w.Hp, lower);
+void launch_split(skim_ctx *ctx, const LossWs &w, const float *H, int64_t m, SplitMode mode) {
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)split_tiles(m)), dim3(SPLIT_THREADS), 0, ctx->stream, H, (long long)m, w.Hp, (int)mode);
 }
+// P = dW H, and with rows of H for its columns only where H has to be symmetric (m a multiple of 32 from 128 up)
+SplitMode step_split(int64_t m) { return (m % 32) != 0 || m < 128 ? SPLIT_COLUMNS : SPLIT_ROWS; }
 
 // rows of W and S start 16-byte aligned, alpha is, and the labels of a row start 4-byte aligned (m is a multiple of 16)
 bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t *labels, int64_t ld) {
@@ -949,7 +990,7 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
     launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    if (!h_ready) launch_split(ctx, w, H, m, true);
+    if (!h_ready) launch_split(ctx, w, H, m, SPLIT_LOWER);
     hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
                        (long long)m, w.line, w.partial);
     hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
@@ -987,7 +1028,7 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     if ((st = carve(ctx, n, m, true, w)) != SKIM_OK) return st;
     launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, nullptr, 0, 0);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    if (!h_ready) launch_split(ctx, w, H, m, false);
+    if (!h_ready) launch_split(ctx, w, H, m, step_split(m));
     {
         long long grid = 0;
         for (int p = 0; p < w.plan.nph; ++p) grid = max(grid, (long long)w.plan.ntile[p] * w.plan.split[p]);
@@ -1059,7 +1100,8 @@ extern "C" skim_status skim_train_scale(skim_ctx *ctx, const float *W, const flo
     if ((st = check_shape(ctx, n, m, ld)) != SKIM_OK) return st;
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
-    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss_trace + slot, nullptr, 1, nullptr, 0, 0, steps > 0)) !=
+    // (the loss takes other pieces of H than the steps)
+    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss_trace + slot, nullptr, 1, nullptr, 0, 0, false)) !=
         SKIM_OK)
         return st;
     SKIM_HIP(ctx, hipMemcpyAsync(centroids, w.cent, (size_t)n * 16 * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));

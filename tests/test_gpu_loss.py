@@ -276,3 +276,42 @@ def test_training_and_lfull_table_run_without_the_partial_tiles(gpu_lib):
         c.close()
     for full, least in zip(*results):
         np.testing.assert_allclose(least, full, rtol=RTOL)
+
+
+@pytest.mark.parametrize("n,m", [(5, 16), (33, 112), (40, 272), (70, 544), (300, 1040)])
+def test_loss_of_a_hessian_that_is_not_symmetric(ctx, n, m):
+    """The loss takes half of the products, and must not take one triangle of H for the other: dW_i H dW_i^T for any H,
+    against float64 (5e-7 of the sum of the products' magnitudes: float32 sums of up to 1040 terms, as seen 2e-8), and
+    the steps of a training and its last loss alike."""
+    W, S, labels, _, al = make_case(n * m, n, m, 8)
+    H = np.random.default_rng(m).standard_normal((m, m)).astype(np.float32)
+    H[:, : m // 3] *= 30.0
+    out = ctx.layer_loss(dev(W), dev(S), dev(H), dev(labels), alpha=dev(al))
+    step = ctx.scale_step(dev(W), dev(S), dev(H), dev(labels), dev(al), dev(np.zeros(m, np.float32)), dev(np.zeros(m, np.float32)), 1)
+    alpha = dev(al)
+    tr = ctx.train_scale(dev(W), dev(S), dev(H), dev(np.full(n, 3, np.uint8)), alpha, dev(np.zeros(m, np.float32)),
+                         dev(np.zeros(m, np.float32)), steps=1)
+    torch.cuda.synchronize()
+    c, _ = oracle.centroids_from_labels(W, S, labels, al)
+
+    def rows(lab, c, al):
+        dW = W.astype(np.float64) - al.astype(np.float64)[None, :] * np.take_along_axis(c, lab.astype(np.int64), 1)
+        return ((dW @ H.astype(np.float64)) * dW).sum(1), ((np.abs(dW) @ np.abs(H).astype(np.float64)) * np.abs(dW)).sum(1)
+
+    ref, mag = rows(labels, c, al)
+    assert np.all(np.abs(out["row_loss"].cpu().numpy() - ref) <= 5e-7 * mag)
+    for loss in (out["loss"], step["loss_before"]):
+        assert abs(loss.item() - ref.sum()) <= 5e-7 * mag.sum()
+    ref, mag = rows(tr["labels"].cpu().numpy(), tr["centroids"].cpu().numpy(), alpha.cpu().numpy())
+    assert abs(tr["loss_trace"][-1].item() - ref.sum()) <= 5e-7 * mag.sum()
+
+
+@pytest.mark.parametrize("n,m", [(33, 112), (40, 272)])
+def test_lfull_table_of_a_hessian_that_is_not_symmetric(ctx, n, m):
+    W, S = skim_synth.make_ws_small(5, n, m)
+    H = np.random.default_rng(m).standard_normal((m, m)).astype(np.float32)
+    Hs = ((H.astype(np.float64) + H.T) / 2)
+    got = ctx.error_table_lfull(dev(W), dev(S), dev(H), bmin=2, bmax=3)["E_full"].cpu().numpy()
+    sym = ctx.error_table_lfull(dev(W), dev(S), dev(Hs.astype(np.float32)), bmin=2, bmax=3)["E_full"].cpu().numpy()
+    scale = np.abs(H).sum() / m * (W.astype(np.float64) ** 2).sum(1)[:, None]        # far above |dW| |H| |dW|
+    assert np.all(np.abs(got - sym) <= 1e-6 * scale)
