@@ -27,6 +27,7 @@ __device__ __forceinline__ uint32_t bf16_rn(float f) {      // finite f
 __device__ __forceinline__ float bf16_f32(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ void split3(float x, uint32_t &p1, uint32_t &p2, uint32_t &p3) {
     p1 = bf16_rn(x);
+    if ((p1 & 0x7FFFu) == 0x7F80u && fabsf(x) <= __FLT_MAX__) --p1;      // above bfloat16's largest: that one, and the rest to the others
     float r = x - bf16_f32(p1);       // exact
     p2 = bf16_rn(r);
     r -= bf16_f32(p2);                // exact; at most 8 significant bits are left

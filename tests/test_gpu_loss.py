@@ -315,3 +315,22 @@ def test_lfull_table_of_a_hessian_that_is_not_symmetric(ctx, n, m):
     sym = ctx.error_table_lfull(dev(W), dev(S), dev(Hs.astype(np.float32)), bmin=2, bmax=3)["E_full"].cpu().numpy()
     scale = np.abs(H).sum() / m * (W.astype(np.float64) ** 2).sum(1)[:, None]        # far above |dW| |H| |dW|
     assert np.all(np.abs(got - sym) <= 1e-6 * scale)
+
+
+@pytest.mark.parametrize("m", [48, 112, 160])
+def test_loss_with_entries_above_the_largest_bfloat16(ctx, m):
+    """The first piece of a float32 value is its bfloat16 rounding, which must not be infinity: float32 reaches
+    3.4028e38, bfloat16 3.3895e38."""
+    n = 20
+    rng = np.random.default_rng(m)
+    W = (rng.standard_normal((n, m)) * 1e-19).astype(np.float32)
+    S = np.ones((n, m), np.float32)
+    labels = rng.integers(0, 4, (n, m)).astype(np.uint8)
+    H = np.diag(rng.choice([3.4028234e38, -3.4e38, 3.398e38, 3.3895e38, 1e38], m).astype(np.float32))
+    out = ctx.layer_loss(dev(W), dev(S), dev(H), dev(labels))
+    torch.cuda.synchronize()
+    c, _ = oracle.centroids_from_labels(W, S, labels, None)
+    dW = W.astype(np.float64) - np.take_along_axis(c, labels.astype(np.int64), 1)
+    h = np.diag(H).astype(np.float64)[None, :]
+    got = out["row_loss"].cpu().numpy()
+    assert np.all(np.abs(got - (h * dW ** 2).sum(1)) <= 5e-7 * (np.abs(h) * dW ** 2).sum(1))
