@@ -190,17 +190,22 @@ __device__ __forceinline__ uint32_t mv_codes(const uint32_t *__restrict__ rw, ui
     return (uint32_t)((((unsigned long long)w1 << 32) | w0) >> sh);
 }
 
+// (Four octets go into one sum, and that into the lane's; float: an octet's products in two chains of four ahead of that.  One
+// chain through all of a lane's columns rounds at the size of the whole sum each time: in float32 1.4 times the error
+// at 11008 columns, 1.8 at 22016.)
 template <int B, typename T>
 __device__ __forceinline__ T mv_dot(uint32_t v, const float *cb, const MvColumns<T> &c, T acc) {
     constexpr uint32_t mask4 = ((1u << B) - 1u) << 2;       // the code times 4: byte offset of a float
+    T half[2];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int sh = e * B;
         const uint32_t off = (sh >= 2 ? v >> (sh - 2) : v << (2 - sh)) & mask4;
         const float w = *(const float *)((const char *)cb + off);
-        if constexpr (sizeof(T) == 4) acc = fmaf(w, c.x[e], acc);
+        if constexpr (sizeof(T) == 4) half[e & 1] = e < 2 ? w * c.x[e] : fmaf(w, c.x[e], half[e & 1]);
         else acc = fma((T)__fmul_rn(c.a[e], w), c.x[e], acc);
     }
+    if constexpr (sizeof(T) == 4) acc += half[0] + half[1];
     return acc;
 }
 
@@ -219,7 +224,10 @@ __device__ __forceinline__ void mv_same(const uint32_t *__restrict__ codes, cons
     mv_columns<T, ALIGNED>(c, x, alpha, o * 8, m);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) v[r] = mv_codes<B>(rw + (size_t)r * wpr, o, wpr);
-    for (;;) {
+    T part[ROWS];                // the sums of up to four octets
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) part[r] = (T)0;
+    for (uint32_t step = 1;; ++step) {
         const uint32_t on = o + nth;
         const bool more = on < noct;
         MvColumns<T> cn;
@@ -230,13 +238,22 @@ __device__ __forceinline__ void mv_same(const uint32_t *__restrict__ codes, cons
             for (int r = 0; r < ROWS; ++r) vn[r] = mv_codes<B>(rw + (size_t)r * wpr, on, wpr);
         }
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) acc[r] = mv_dot<B, T>(v[r], cbf[r], c, acc[r]);
+        for (int r = 0; r < ROWS; ++r) part[r] = mv_dot<B, T>(v[r], cbf[r], c, part[r]);
+        if ((step & 3) == 0) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                acc[r] += part[r];
+                part[r] = (T)0;
+            }
+        }
         if (!more) break;
         c = cn;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) v[r] = vn[r];
         o = on;
     }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r] += part[r];
 }
 
 template <typename T, bool ALIGNED, int ROWS>

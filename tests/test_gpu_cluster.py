@@ -476,6 +476,24 @@ def test_matvec_shapes(ctx, n, m):
     assert bool(((yf.double() - ref).abs() <= 1e-5 * scale).all())
 
 
+@pytest.mark.parametrize("n,m,bound", [(2048, 11008, 1.65e-9), (2048, 22016, 1.35e-9), (1024, 100000, 0.85e-9)])
+def test_float32_matvec_adds_in_short_chains(ctx, n, m, bound):
+    """The float32 product may not run one chain of additions through a lane's columns: its error, against the sum of the
+    products' magnitudes, would not fall with the length of the row as that of a sum of short chains does.  rms over the
+    rows: 1.40e-9, 1.05e-9, 0.59e-9 (1.59e-9, 1.16e-9, 0.62e-9 with 32 columns a chain pair), with one chain 1.98e-9, 1.87e-9,
+    1.73e-9; four seeds agree to 7 %, and the bound lies between."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    bits = (torch.arange(n, device="cuda") % 4 + 1).to(torch.uint8)
+    cent = torch.sort(torch.randn((n, 16), device="cuda", generator=g), dim=1)[0].double()
+    pk = ctx.pack(torch.randn((n, m), device="cuda", generator=g), bits, cent, cent.float(), bits_host=bits.cpu().numpy())
+    x = torch.randn(m, device="cuda", generator=g)
+    Wq = ctx.unpack(pk, m).double()
+    ref, scale = Wq @ x.double(), Wq.abs() @ x.double().abs()
+    err = (ctx.dequant_matvec_f32(pk, m, x).double() - ref) / scale
+    rms = float((err * err).mean().sqrt())
+    assert rms <= bound, f"{rms:.3e}"
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 16384, 16385, 33000])
 @pytest.mark.parametrize("offset", [0, 3])
 def test_pack_row_order(ctx, n, offset):
