@@ -280,14 +280,13 @@ skim_status skim_dequant_matvec_f32(skim_ctx *ctx, const uint32_t *codes, const 
 /* Layer-wise Hessian proxy from calibration activations (Sec. 3.4):
  *   H = X^T X / N,  X: dev N x m bfloat16 (bit patterns, row-major, one activation
  *   vector per row; 4-byte aligned, m even),  H: dev m x m float32.
- * bf16 MFMA with float32 accumulation over chunks of at most 8192 activations, the chunks
- * added up in float32 and float64; only the tiles on and above the diagonal are computed.
- * Every entry within 1e-5 of sqrt(H_jj H_ll) for N up to about 10^6; H comes out symmetric
- * bit for bit.  H is written only (its previous contents do not matter).
- * The call works with any workspace or none, but only with one of at least
- * skim_hessian_workspace_bytes(ctx, N, m) bytes can it split the activations of a tile
- * over several compute units (partial tiles live there; up to about 4 x (compute units)
- * x 256 KB beyond one tile each).
+ * bf16 MFMA with float32 accumulation over chunks of at most 2048 activations, the chunks
+ * added up in float64; for m > 2560 a multiple of 8 and X 16-byte aligned, chunks of at most 8192, some of
+ * them added up in float32.  Every entry within 1e-5 of sqrt(H_jj H_ll) for N up to about 10^6; H comes out
+ * symmetric bit for bit.  H is written only (its previous contents do not matter).
+ * The call works with any workspace or none, but only with scratch can it split the activations of a tile over several
+ * compute units and sum narrow layers in the faster kernel: skim_hessian_workspace_bytes(ctx, N, m) bytes (for X 16-byte
+ * aligned) let it do both as it likes best, fewer cost time.
  * skim_hessian_from_activations_scratch is the same call with the caller's scratch (dev, 256-byte
  * aligned; NULL = none) in the place of the registered workspace, which it leaves alone. */
 size_t skim_hessian_workspace_bytes(const skim_ctx *ctx, int64_t N, int64_t m);

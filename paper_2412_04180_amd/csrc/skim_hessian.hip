@@ -1,10 +1,15 @@
 // Layer-wise Hessian proxy from calibration activations (Sec. 3.4: H ~ X X^T in the paper's
 // column convention; here X is N x m row-major, one activation vector per row, so
 // H = X^T X / N, m x m).  bf16 inputs, bf16 MFMA (v_mfma_f32_32x32x16_bf16) with float32
-// accumulation over chunks of at most 8192 activations.  Only the 256 x 256 tiles on and above the
-// diagonal are computed; where there are fewer of them than compute units the activations of a tile are
+// accumulation over chunks of activations.  Only the 256 x 256 tiles on and above the diagonal are
+// computed; where there are fewer of them than compute units the activations of a tile are
 // split over several workgroups, whose partial tiles a second kernel adds up (float64) and mirrors.
+// Layers of up to 2560 columns (and wider ones that the 16-byte loads of rows do not divide) have chunks of at most 2048
+// activations, all added up in float64; the others chunks of 8192, those of one workgroup added up in float32.
+// Without scratch for partial tiles the former take a kernel of 128 x 128 tiles with float64 sums in registers.
 #include "skim_tiles.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -23,6 +28,10 @@ constexpr int X_PANEL_BYTES = XK * XT * 2; // one operand panel of a stage, acti
 constexpr int X_STAGE_BYTES = 2 * X_PANEL_BYTES;
 constexpr size_t X_LDS_BYTES = (size_t)X_BUFS * X_STAGE_BYTES;
 constexpr int X_CHUNK = 8192 / XK;         // stages summed in float32 registers before they are added to memory
+constexpr int X_PIECE = 2048 / XK;         // ... before their leading halves go to memory (float64 sums)
+constexpr int X_WIDE_TILES = 11;           // rows of so many tiles or more may be summed in chunks of X_CHUNK
+constexpr size_t X_PIECE_BYTES = TILE_SLOT_BYTES / 2;
+constexpr size_t X_SCRATCH_MOST = 256ull << 20;
 constexpr int X_MIN_STAGES = 8;            // no workgroup gets a shorter share of the activations than this
 constexpr int X_PHASE_COST = 24;           // a phase and its partial tiles, in stages of 0.8 us (256 KB per workgroup)
 
@@ -64,14 +73,25 @@ __device__ __forceinline__ bf16x8 operand(uint32_t addr, int off) {
 // third less, but their 256 accumulators and two operand sets spill: 4.3 ms).  Four stages of 32 activations in LDS (128
 // KB): the loads of stage s + 4 go out as soon as everybody has read stage s, i.e. three and a half stages ahead; the
 // operands of the next half stage are read between the MFMAs of this one, so the barrier in the middle costs little.
-// Bound: the power the matrix cores draw.  131072 x 4096 (1.18 PFLOP/s executed): MFMAs busy 76 % of the cycles, at 1.4 GHz
+// Bound: the power the matrix cores draw.  131072 x 4096 (1.23 PFLOP/s executed): MFMAs busy 76 % of the cycles, at 1.4 GHz
 // instead of 2.4; no bank conflicts; 4.3 GB read past L2 of 1.07 GB.  1.90 ms; with one workgroup per tile on 136 of the
-// 256 CUs, X staged through registers and transposed there: 3.60.  16384 x 2048: 85 us, of which the partial tiles (66 MB
-// written, read again by xtx_finish_kernel) take about 30; the 128 x 128 full-product kernel this replaces: 485.
-// DIRECT: the partial sums are added up in H itself (every tile is one workgroup's), not in slots.
-template <bool DIRECT>
+// 256 CUs, X staged through registers and transposed there: 3.60.  16384 x 2048: 94 us, of which the partial tiles and pieces
+// (99 MB written, read again by xtx_finish_kernel) take about 35; the 128 x 128 full-product kernel: 484.
+// SUM_IN_H: the chunks are added up in H itself (every tile is one workgroup's); SUM_IN_SLOTS: in the partial tiles.
+// SUM_PIECES: nothing is added up here.  At the end of a chunk that is not a workgroup's last, the leading 8 bits of the
+// sums, a bfloat16 each, go to memory (128 KB) and only what is left of them stays in the accumulators, exactly: the
+// roundings of the next chunk are those of sums that start from next to nothing, and xtx_finish_kernel adds all of it up in
+// float64.  (Whole partial tiles per chunk would be twice the memory and as much more to write and read.)  rms error of all
+// entries, in units of sqrt(H_jj H_ll), of float64 registers in the 128 x 128 kernel / chunks of 8192 in float32 / pieces:
+// 16384 x 2048 3.1 / 3.5 / 2.5 e-9 (484 / 88 / 94 us), 131072 x 2048 1.8 / 2.9 / 1.8 e-9 (4149 / 524 / 598 us), 65536 x 2560
+// 1.9 / 3.3 / 1.9 e-9; the diagonal's 1.04 / 1.19 / 0.86, 0.75 / 1.11 / 0.76, 0.81 / 1.30 / 0.79 e-7.
+enum SumMode { SUM_IN_H, SUM_IN_SLOTS, SUM_PIECES };
+// pieces of a workgroup's share of `stages` stages beyond its last chunk
+__host__ __device__ __forceinline__ int pieces_of(int stages) { return (stages - 1) / X_PIECE; }
+template <int MODE>
 __global__ void __launch_bounds__(X_THREADS) __attribute__((amdgpu_waves_per_eu(X_WAVES / 4, X_WAVES / 4)))
-xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *H, int nt, TilePlan plan, float4 *slots) {
+xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *H, int nt, TilePlan plan, float4 *slots, uint4 *pieces,
+               int nslot) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave / X_WC, wc = wave % X_WC;
@@ -169,8 +189,10 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
             };
             read_ops(s0, 0, a0, b0);
             bool first = true;
-            for (int c0 = s0; c0 < s1; c0 += X_CHUNK) {
-                const int c1 = min(c0 + X_CHUNK, s1);
+            // (pieces: as many for every share of the phase, in chunks of equal length)
+            const int npiece = MODE == SUM_PIECES ? pieces_of((nstage + split - 1) / split) : 0;
+            for (int c0 = s0, c1, piece = 0; c0 < s1; c0 = c1, ++piece) {
+                c1 = MODE == SUM_PIECES ? s0 + (int)((long long)(s1 - s0) * (piece + 1) / (npiece + 1)) : min(c0 + X_CHUNK, s1);
                 for (int st = c0; st < c1; ++st) {
                     read_ops(st, 1, a1, b1);
                     multiply(a0, b0);
@@ -193,9 +215,30 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
                     }
                     __builtin_amdgcn_sched_group_barrier(0x008, 4 * X_BY - 4 - X_BY, 0);
                 }
+                if constexpr (MODE == SUM_PIECES) {
+                    if (c1 < s1) {
+                        uint4 *pp = pieces + (((size_t)piece * nslot + plan.slot0[p] + v) * X_WAVES + swave) * (4 * X_BY * 2 * 64) + lane;
+#pragma unroll
+                        for (int xy = 0; xy < 4 * X_BY; ++xy) {
+                            floatx16 &c = acc[xy / X_BY][xy % X_BY];
+                            uint32_t o[8];
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) {
+                                const uint32_t u = __float_as_uint(c[e]);
+                                if (e & 1) o[e >> 1] |= u & 0xFFFF0000u;
+                                else o[e >> 1] = u >> 16;
+                                // (an infinite sum stays in both)
+                                c[e] = fabsf(c[e]) <= __FLT_MAX__ ? c[e] - __uint_as_float(u & 0xFFFF0000u) : c[e];
+                            }
+                            pp[(2 * xy) * 64] = make_uint4(o[0], o[1], o[2], o[3]);
+                            pp[(2 * xy + 1) * 64] = make_uint4(o[4], o[5], o[6], o[7]);
+                        }
+                        continue;
+                    }
+                }
                 // the chunk's sums go to memory.  Accumulator element e of a 32 x 32 tile: row = 8*(e/4) + 4*(lane/32)
                 // + e%4, column = lane%32.
-                if constexpr (!DIRECT) {
+                if constexpr (MODE != SUM_IN_H) {
                     // partial tile: wavefront by wavefront, its accumulators' quarters as 16 bytes per lane
                     constexpr int XY = 4 * X_BY;
                     // (not through buffer stores with a scalar offset: their first data register may not be overwritten by the
@@ -203,7 +246,7 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
                     floatx4 *sp = (floatx4 *)slots + ((size_t)(plan.slot0[p] + v) * X_WAVES + swave) * (XY * 4 * 64) + lane;
                     floatx4 o[2][4];      // what is there already, one accumulator block ahead
                     auto old = [&](int xy) {
-                        if (first) return;
+                        if (MODE == SUM_PIECES || first) return;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) o[xy & 1][q] = sp[(xy * 4 + q) * 64];
                     };
@@ -216,7 +259,7 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
                         for (int q = 0; q < 4; ++q) {
                             floatx4 t;
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) t[e] = c[4 * q + e] + (first ? 0.f : o[xy & 1][q][e]);
+                            for (int e = 0; e < 4; ++e) t[e] = c[4 * q + e] + (MODE == SUM_PIECES || first ? 0.f : o[xy & 1][q][e]);
                             sp[(xy * 4 + q) * 64] = t;
                         }
                     }
@@ -259,13 +302,16 @@ xtx_big_kernel(const uint16_t *__restrict__ X, long long N, long long m, float *
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The partial tiles of a split tile added up, and every tile off the diagonal mirrored.  One wavefront per 32 x 32 block.
-__global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, long long m, int nt, TilePlan plan,
-                                                         const float4 *__restrict__ slots) {
+// The partial tiles (and pieces) of a tile added up, and every tile off the diagonal mirrored.  One wavefront per 32 x 32 block.
+// run (NULL: none): running sums of the tiles from tile0 on, where the activations are taken in several passes; first: it
+// holds nothing yet; last: the sums go to H.
+__global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, double inv, int nstage, long long m, int nt, TilePlan plan,
+                                                         const float4 *__restrict__ slots, const uint4 *__restrict__ pieces, int nslot,
+                                                         int tile0, double2 *__restrict__ run, bool first, bool last) {
     __shared__ float tr[4][32][33];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int tile = blockIdx.x >> 4, blk = (blockIdx.x & 15) * 4 + wave;       // 64 blocks of a tile
+    const int tile = tile0 + (blockIdx.x >> 4), blk = (blockIdx.x & 15) * 4 + wave;       // 64 blocks of a tile
     int p = 0;
     while (p + 1 < plan.nph && tile >= plan.tile0[p + 1]) ++p;
     int bi, bj;
@@ -278,21 +324,44 @@ __global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, 
         const int rlim = (int)min(m - ib, 32ll), clim = (int)min(m - jb, 32ll);
         float v[16];
         if (split > 0) {
-            const double inv = 1.0 / (double)N;
-            const float4 *sp = slots + ((size_t)(plan.slot0[p] + tile - plan.tile0[p]) * X_WAVES + ow) * (XY * 4 * 64) + xy * 256 + lane;
-            const size_t step = (size_t)plan.ntile[p] * (8 * 8 * 4 * 64);       // from one part's slot to the next
+            const size_t slot = (size_t)(plan.slot0[p] + tile - plan.tile0[p]), step = (size_t)plan.ntile[p];       // from one part's to the next
+            const int npiece = pieces ? pieces_of((nstage + split - 1) / split) : 0;
             double s[16];
+            double2 *rp = run + ((size_t)(tile - tile0) * 64 + blk) * (8 * 64) + lane;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[e] = 0.0;
-            for (int q = 0; q < split; ++q, sp += step) {
+            for (int k = 0; k < 8; ++k) {
+                const double2 r = run && !first ? rp[k * 64] : make_double2(0.0, 0.0);
+                s[2 * k] = r.x;
+                s[2 * k + 1] = r.y;
+            }
+            const uint4 *pp = pieces + (slot * X_WAVES + ow) * (XY * 2 * 64) + xy * 128 + lane;
+            for (int c = 0; c < npiece; ++c, pp += (size_t)nslot * (X_PIECE_BYTES / 16)) {
+#pragma unroll 4
+                for (int q = 0; q < split; ++q) {
+                    const uint4 *o = pp + q * step * (X_PIECE_BYTES / 16);
+                    const uint4 lo = o[0], hi = o[64];
+                    const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) s[e] += (double)__uint_as_float(e & 1 ? w[e >> 1] & 0xFFFF0000u : w[e >> 1] << 16);
+                }
+            }
+            const float4 *sp = slots + (slot * X_WAVES + ow) * (XY * 4 * 64) + xy * 256 + lane;
+#pragma unroll 2
+            for (int q = 0; q < split; ++q) {
+                const float4 *f = sp + q * step * (TILE_SLOT_BYTES / 16);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const float4 o = sp[k * 64];
+                    const float4 o = f[k * 64];
                     s[4 * k] += o.x;
                     s[4 * k + 1] += o.y;
                     s[4 * k + 2] += o.z;
                     s[4 * k + 3] += o.w;
                 }
+            }
+            if (!last) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) rp[k * 64] = make_double2(s[2 * k], s[2 * k + 1]);
+                return;
             }
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
@@ -321,14 +390,194 @@ __global__ void __launch_bounds__(256) xtx_finish_kernel(float *H, long long N, 
     }
 }
 
+// How `tiles` tiles (at most one per compute unit) are summed in float64 with at most `cap` bytes of scratch: all activations
+// in one pass, or in several with running sums, whatever needs no more.  False: not with so little.
+struct PiecePlan {
+    TilePlan plan;
+    int passes, nslot, npiece;
+    size_t bytes;
+    size_t run_offset() const { return (size_t)nslot * (TILE_SLOT_BYTES + npiece * X_PIECE_BYTES); }
+};
+bool piece_plan(PiecePlan &pp, int G, int tiles, int nstage, size_t cap) {
+    for (pp.passes = 1; pp.passes <= nstage; ++pp.passes) {
+        const int stages = (nstage + pp.passes - 1) / pp.passes;
+        pp.nslot = (int)skim_make_plan(pp.plan, G, tiles, stages, X_MIN_STAGES, X_PHASE_COST, false);
+        pp.npiece = 0;
+        for (int p = 0; p < pp.plan.nph; ++p) {
+            const int n = pieces_of((stages + pp.plan.split[p] - 1) / pp.plan.split[p]);
+            if (n > pp.npiece) pp.npiece = n;
+        }
+        pp.bytes = pp.run_offset() + (pp.passes > 1 ? (size_t)tiles * 2 * TILE_SLOT_BYTES : 0);
+        if (pp.bytes <= cap) return true;
+        if (pp.npiece == 0 && stages <= X_PIECE) break;
+    }
+    return false;
+}
+// tiles of one group: all, or an equal share of them that leaves no compute unit two
+int group_tiles(long long tiles, int G) {
+    const long long groups = (tiles + G - 1) / G;
+    return (int)((tiles + groups - 1) / groups);
+}
+size_t piece_bytes(long long tiles, int nstage, int G) {
+    PiecePlan pp;
+    const int T = group_tiles(tiles, G), rest = (int)(tiles % T);
+    size_t b = piece_plan(pp, G, T, nstage, X_SCRATCH_MOST) ? pp.bytes : 0;
+    if (rest && piece_plan(pp, G, rest, nstage, X_SCRATCH_MOST) && pp.bytes > b) b = pp.bytes;
+    return b;
+}
+
+// float64 sums (what every N of up to 2048 has in any case): rows that are narrow, or not whole 16-byte pieces
+bool needs_float64(const void *X, long long N, long long m, int nt) {
+    return (nt < X_WIDE_TILES || (m % 8) != 0 || ((uintptr_t)X & 15) != 0) && N > (long long)X_PIECE * XK;
+}
+
+// ---- without scratch: 128 x 128 tiles, all of them, the chunks (2048 activations) added up in float64 registers --------------
+// (131072 x 512: 3.9 ms, 16384 x 2048: 0.48 ms; with a workgroup per 256 x 256 tile a narrow layer has fewer of them than
+// compute units, and 1024 x 512 took 47 us instead of 32)
+constexpr int HT = 128;            // output tile (rows and columns of H = columns of X)
+constexpr int HK = 64;             // activations per LDS tile
+constexpr int HK_PAD = HK + 8;     // bf16 per LDS row: 144 bytes (16-byte aligned; operand reads and staging
+                                   // stores of a 16-lane group fall into distinct banks)
+constexpr int H_THREADS = 256;
+constexpr int FLUSH_TILES = 32;    // float32 accumulators are added into float64 every 32 tiles = 2048 activations
+
+// LDS tile T[c][k]: column c of the X tile, HK consecutive activations (k contiguous: one
+// ds_read_b128 gives a lane its 8 bf16 of an MFMA operand).
+struct XTile {
+    uint16_t t[HT][HK_PAD];
+};
+constexpr size_t H_LDS_BYTES = 4 * sizeof(XTile);     // two operands, double-buffered
+
+// Half of the workgroup stages each operand tile.  One thread moves 8 activations x 8 neighbouring columns:
+// eight 16-byte loads (a wavefront covers 8 activation rows x 128 contiguous bytes per instruction), an
+// 8 x 8 transpose of 16-bit values in registers, eight 16-byte LDS stores (one per column).
+struct Staged {
+    uint32_t r[8][4];
+};
+__device__ __forceinline__ void load_task(const uint16_t *__restrict__ X, long long N, long long m, long long k0,
+                                          long long c0, int st, bool vec, Staged &s) {
+    const int ab = st & 7, cg = st >> 3;             // 8-activation block, 8-column group
+    const long long c = c0 + 8 * cg;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const long long k = k0 + 8 * ab + t;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (k < N) {
+            const uint16_t *src = X + k * m + c;
+            if (vec && c + 8 <= m) {
+                v = *(const uint4 *)src;             // m % 8 == 0 and X 16-byte aligned
+            } else {
+                uint32_t e[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) e[q] = (c + q < m) ? src[q] : 0u;
+                v = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            }
+        }
+        s.r[t][0] = v.x; s.r[t][1] = v.y; s.r[t][2] = v.z; s.r[t][3] = v.w;
+    }
+}
+// columns [cb, ce) of the task's 8 (compile-time bounds once the caller's loop is unrolled): the 8 activations of
+// column 8 cg + c go to 16-byte slot `slot` of that column's LDS row
+__device__ __forceinline__ void store_cols(uint16_t (*T)[HK_PAD], int cg, int slot, const Staged &s, int cb, int ce) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        if (c < cb || c >= ce) continue;
+        uint32_t o[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t a = s.r[2 * d][c >> 1], b = s.r[2 * d + 1][c >> 1];
+            o[d] = (c & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
+        }
+        *(uint4 *)&T[8 * cg + c][8 * slot] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+__device__ __forceinline__ void store_task(XTile &T, int st, const Staged &s) { store_cols(T.t, st >> 3, st & 7, s, 0, 8); }
+
+__global__ void __launch_bounds__(H_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) xtx_kernel(const uint16_t *__restrict__ X, long long N, long long m,
+                                                        float *__restrict__ H, int vec) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    XTile *TI = (XTile *)smem, *TJ = TI + 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wr = wave >> 1, wc = wave & 1;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const long long i0 = (long long)blockIdx.y * HT, j0 = (long long)blockIdx.x * HT;
+    // threads 0..127 stage the tile of columns i0.., threads 128..255 the tile of columns j0..
+    const int st = tid & 127;
+    const bool stage_j = tid >= 128;
+    const long long sc0 = stage_j ? j0 : i0;
+    XTile *const ST = stage_j ? TJ : TI;
+
+    floatx16 acc[2][2];
+    double acc64[2][2][16];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                acc[a][b][e] = 0.f;
+                acc64[a][b][e] = 0.0;
+            }
+
+    const long long ntile = (N + HK - 1) / HK;
+    Staged sg;
+    load_task(X, N, m, 0, sc0, st, vec != 0, sg);
+    store_task(ST[0], st, sg);
+    __syncthreads();
+    for (long long kt = 0; kt < ntile; ++kt) {
+        const int buf = (int)(kt & 1);
+        if (kt + 1 < ntile) load_task(X, N, m, (kt + 1) * HK, sc0, st, vec != 0, sg);
+#pragma unroll
+        for (int ks = 0; ks < HK / 16; ++ks) {
+            // operand of a lane: 8 consecutive activations 16 ks + 8 (lane / 32) .. + 7 of one column
+            const int kk = 16 * ks + 8 * lhi;
+            const bf16x8 a0 = *(const bf16x8 *)&TI[buf].t[wr * 64 + l32][kk];
+            const bf16x8 a1 = *(const bf16x8 *)&TI[buf].t[wr * 64 + 32 + l32][kk];
+            const bf16x8 b0 = *(const bf16x8 *)&TJ[buf].t[wc * 64 + l32][kk];
+            const bf16x8 b1 = *(const bf16x8 *)&TJ[buf].t[wc * 64 + 32 + l32][kk];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
+        }
+        if ((kt % FLUSH_TILES) == FLUSH_TILES - 1 || kt + 1 == ntile) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        acc64[a][b][e] += (double)acc[a][b][e];
+                        acc[a][b][e] = 0.f;
+                    }
+        }
+        if (kt + 1 < ntile) store_task(ST[buf ^ 1], st, sg);
+        __syncthreads();
+    }
+
+    // accumulator element e of a 32 x 32 tile: row = 8*(e/4) + 4*(lane/32) + e%4, column = lane%32
+    const double inv = 1.0 / (double)N;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const long long i = i0 + wr * 64 + a * 32 + 8 * (e >> 2) + 4 * lhi + (e & 3);
+                const long long j = j0 + wc * 64 + b * 32 + l32;
+                if (i < m && j < m) H[i * m + j] = (float)(acc64[a][b][e] * inv);
+            }
+}
+
 }  // namespace
 
 extern "C" size_t skim_hessian_workspace_bytes(const skim_ctx *ctx, int64_t N, int64_t m) {
     if (!ctx || N < 1 || m < 1 || m > 0x7fffffff) return 0;
     TilePlan plan;
-    const int64_t nt = (m + XT - 1) / XT;
-    return (size_t)skim_make_plan(plan, ctx->num_cu, nt * (nt + 1) / 2, (int)((N + XK - 1) / XK), X_MIN_STAGES, X_PHASE_COST, false) *
-           TILE_SLOT_BYTES;
+    const int64_t nt = (m + XT - 1) / XT, tiles = nt * (nt + 1) / 2;
+    const int nstage = (int)((N + XK - 1) / XK);
+    if (needs_float64(nullptr, N, m, (int)nt)) return piece_bytes(tiles, nstage, ctx->num_cu);
+    return (size_t)skim_make_plan(plan, ctx->num_cu, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, false) * TILE_SLOT_BYTES;
 }
 
 extern "C" skim_status skim_hessian_from_activations(skim_ctx *ctx, const uint16_t *X_bf16, int64_t N, int64_t m,
@@ -346,36 +595,82 @@ extern "C" skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, cons
                   (long long)N, (long long)m);
     if (scratch && ((uintptr_t)scratch & 255)) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_hessian_from_activations: scratch must be 256-byte aligned");
     if (!ctx->xtx_lds_enabled) {
-        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
-        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
+        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<SUM_IN_H>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
+        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<SUM_IN_SLOTS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
+        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_big_kernel<SUM_PIECES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)X_LDS_BYTES));
+        SKIM_HIP(ctx, hipFuncSetAttribute((const void *)xtx_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)H_LDS_BYTES));
         ctx->xtx_lds_enabled = 1;
     }
     const int nt = (int)((m + XT - 1) / XT);
     const int G = ctx->num_cu;
-    // Without scratch that holds the partial tiles the splits are given up, then the slots altogether
     TilePlan plan;
     const long long tiles = (long long)nt * (nt + 1) / 2;
     const int nstage = (int)((N + XK - 1) / XK);
+    const double inv = 1.0 / (double)N;
+    auto launch = [&](auto mode, const TilePlan &plan, const uint16_t *X, long long Np, float4 *slots, uint4 *pieces, int nslot) {
+        long long grid = 0;
+        for (int p = 0; p < plan.nph; ++p) {
+            const long long items = (long long)plan.ntile[p] * plan.split[p];
+            if (items > grid) grid = items;
+        }
+        if (grid > G) grid = G;
+        hipLaunchKernelGGL(xtx_big_kernel<decltype(mode)::value>, dim3((unsigned)grid), dim3(X_THREADS), X_LDS_BYTES, ctx->stream, X, Np,
+                           (long long)m, H, nt, plan, slots, pieces, nslot);
+    };
+    auto finish = [&](const TilePlan &plan, int stages, const float4 *slots, const uint4 *pieces, int nslot, int tile0, long long ntile,
+                      double2 *run, bool first, bool last) {
+        hipLaunchKernelGGL(xtx_finish_kernel, dim3((unsigned)(ntile * 16)), dim3(256), 0, ctx->stream, H, inv, stages, (long long)m, nt, plan,
+                           slots, pieces, nslot, tile0, run, first, last);
+    };
+    const bool float64 = needs_float64(X_bf16, N, m, nt);
+    PiecePlan pp;
+    bool fits = false;
+    int T = group_tiles(tiles, G);
+    if (float64 && scratch)
+        for (;; T = (T + 1) / 2) {
+            const int rest = (int)(tiles % T);
+            fits = (!rest || piece_plan(pp, G, rest, nstage, scratch_bytes)) && piece_plan(pp, G, T, nstage, scratch_bytes);
+            if (fits || T == 1) break;
+        }
+    if (fits) {
+        for (long long t0 = 0; t0 < tiles; t0 += T) {
+            const int ntile = (int)(tiles - t0 < T ? tiles - t0 : T);
+            if (ntile < T) (void)piece_plan(pp, G, ntile, nstage, scratch_bytes);
+            plan = pp.plan;
+            for (int p = 0; p < plan.nph; ++p) plan.tile0[p] += (int)t0;
+            float4 *slots = (float4 *)scratch;
+            uint4 *pieces = (uint4 *)((char *)scratch + (size_t)pp.nslot * TILE_SLOT_BYTES);
+            double2 *run = pp.passes > 1 ? (double2 *)((char *)scratch + pp.run_offset()) : nullptr;
+            for (int q = 0; q < pp.passes; ++q) {
+                const long long s0 = (long long)nstage * q / pp.passes, s1 = (long long)nstage * (q + 1) / pp.passes;
+                const long long Np = (N < s1 * XK ? N : s1 * XK) - s0 * XK;
+                launch(std::integral_constant<int, SUM_PIECES>{}, plan, X_bf16 + s0 * XK * m, Np, slots, pieces, pp.nslot);
+                finish(plan, (int)(s1 - s0), slots, pieces, pp.nslot, (int)t0, ntile, run, q == 0, q == pp.passes - 1);
+            }
+        }
+        SKIM_HIP(ctx, hipGetLastError());
+        return SKIM_OK;
+    }
+    // Without scratch that holds the partial tiles the splits are given up, then the slots altogether
     bool direct = true;
     for (int whole = 0; whole < 2 && direct; ++whole)
         direct = !scratch || (size_t)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, whole != 0) * TILE_SLOT_BYTES >
                                  scratch_bytes;
-    if (direct) (void)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, true);
-    long long grid = 0;
-    for (int p = 0; p < plan.nph; ++p) {
-        const long long items = (long long)plan.ntile[p] * plan.split[p];
-        if (items > grid) grid = items;
+    if (float64 || (direct && nt < X_WIDE_TILES)) {
+        const int vec = (m % 8 == 0) && (((uintptr_t)X_bf16 & 15) == 0);     // rows of X start 16-byte aligned
+        const unsigned ntiles = (unsigned)((m + HT - 1) / HT);
+        hipLaunchKernelGGL(xtx_kernel, dim3(ntiles, ntiles), dim3(H_THREADS), H_LDS_BYTES, ctx->stream, X_bf16, (long long)N, (long long)m, H, vec);
+        SKIM_HIP(ctx, hipGetLastError());
+        return SKIM_OK;
     }
-    if (grid > G) grid = G;
-    float4 *slots = direct ? nullptr : (float4 *)scratch;
-    if (direct)
-        hipLaunchKernelGGL(xtx_big_kernel<true>, dim3((unsigned)grid), dim3(X_THREADS), X_LDS_BYTES, ctx->stream, X_bf16, (long long)N,
-                           (long long)m, H, nt, plan, slots);
-    else
-        hipLaunchKernelGGL(xtx_big_kernel<false>, dim3((unsigned)grid), dim3(X_THREADS), X_LDS_BYTES, ctx->stream, X_bf16, (long long)N,
-                           (long long)m, H, nt, plan, slots);
-    hipLaunchKernelGGL(xtx_finish_kernel, dim3((unsigned)(tiles * 16)), dim3(256), 0, ctx->stream, H, (long long)N, (long long)m, nt,
-                       plan, (const float4 *)slots);
+    if (direct) {
+        (void)skim_make_plan(plan, G, tiles, nstage, X_MIN_STAGES, X_PHASE_COST, true);
+        launch(std::integral_constant<int, SUM_IN_H>{}, plan, X_bf16, (long long)N, nullptr, nullptr, 0);
+        finish(plan, nstage, nullptr, nullptr, 0, 0, tiles, nullptr, true, true);
+    } else {
+        launch(std::integral_constant<int, SUM_IN_SLOTS>{}, plan, X_bf16, (long long)N, (float4 *)scratch, nullptr, 0);
+        finish(plan, nstage, (const float4 *)scratch, nullptr, 0, 0, tiles, nullptr, true, true);
+    }
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;
 }

@@ -334,3 +334,61 @@ def test_loss_with_entries_above_the_largest_bfloat16(ctx, m):
     h = np.diag(H).astype(np.float64)[None, :]
     got = out["row_loss"].cpu().numpy()
     assert np.all(np.abs(got - (h * dW ** 2).sum(1)) <= 5e-7 * (np.abs(h) * dW ** 2).sum(1))
+
+
+def hessian_reference(Xb):
+    """X^T X / N in float64 on the device (operands contiguous), and the entries' scale sqrt(H_jj H_ll)."""
+    N, m = Xb.shape
+    H = torch.zeros((m, m), device="cuda", dtype=torch.float64)
+    for r in range(0, N, 16384):
+        x = Xb[r:r + 16384].double()
+        H += x.T.contiguous() @ x
+    H /= N
+    d = H.diagonal().clone()
+    return H, torch.sqrt(d[:, None] * d[None, :])
+
+
+@pytest.mark.parametrize("N,m,scratch,bound", [
+    (16384, 2048, True, 1.10e-7), (65536, 2560, True, 0.95e-7), (16384, 4098, True, 1.15e-7),      # pieces: one, several, whole tiles
+    (4096, 512, False, 2.0e-7), (262144, 256, False, 0.85e-7)])                                    # float64 registers
+def test_hessian_of_narrow_layers_adds_chunks_of_2048_in_float64(gpu_lib, N, m, scratch, bound):
+    """Rows of up to 2560 columns (and wider ones whose rows are not whole 16-byte pieces): float32 sums run over 2048
+    activations, the rest is float64.  rms error of the diagonal, whose sums only grow: at most 1.04e-7, 0.81e-7, 1.04e-7, 1.70e-7,
+    0.73e-7 so; with chunks of 8192 or parts added up in float32 1.19e-7, 1.30e-7, 2.78e-7, 3.03e-7, 1.12e-7.  The sums of m
+    columns agree to a few per cent between seeds; the bound lies between."""
+    gen = torch.Generator(device="cuda").manual_seed(N + m)
+    Xb = torch.randn((N, m), device="cuda", generator=gen).to(torch.bfloat16)
+    ref, _ = hessian_reference(Xb)
+    c = gpu_lib.Context(0)
+    H = torch.empty((m, m), device="cuda")
+    if scratch:
+        c.hessian_from_activations(Xb, out=H)
+    else:
+        c._check(c.lib.skim_hessian_from_activations(c.h, Xb.data_ptr(), N, m, H.data_ptr()))
+    err = H.double().diagonal() / ref.diagonal() - 1.0
+    rms = float((err * err).mean().sqrt())
+    assert rms <= bound, f"{rms:.3e}"
+    c.close()
+
+
+@pytest.mark.parametrize("N,m,offset,sizes", [
+    (16500, 300, 0, (67 << 20, 13 << 20, 1 << 20, 0)),          # one pass, several, too little, none
+    (70001, 514, 0, (256 << 20, 40 << 20, 16 << 20)),           # pieces; several passes with pieces
+    (2100, 5890, 0, (200 << 20, 60 << 20, 30 << 20)),           # two groups of tiles; one pass, several; smaller groups
+    (4200, 2816, 2, (160 << 20, 0))])                           # a wide layer whose rows start between 16-byte borders
+def test_hessian_with_any_scratch(gpu_lib, N, m, offset, sizes):
+    """Passes with running sums, groups of tiles and the kernel that needs no scratch, against float64: within 1e-6 of
+    sqrt(H_jj H_ll) (chunks of 2048 of up to 128 roundings each: at most 3.8e-6, seen 4e-7)."""
+    gen = torch.Generator(device="cuda").manual_seed(N + m)
+    flat = torch.randn(N * m + offset, device="cuda", generator=gen).to(torch.bfloat16)
+    Xb = flat[offset:].view(N, m)
+    ref, scale = hessian_reference(Xb)
+    c = gpu_lib.Context(0)
+    for size in sizes:
+        H = torch.full((m, m), float("nan"), device="cuda")
+        block = torch.empty(max(size, 256), dtype=torch.uint8, device="cuda")
+        c._check(c.lib.skim_hessian_from_activations_scratch(c.h, Xb.data_ptr(), N, m, H.data_ptr(), block.data_ptr() if size else None, size))
+        worst = float(((H.double() - ref).abs() / scale).max())
+        assert worst <= 1e-6, f"scratch {size}: {worst:.3e}"
+        assert torch.equal(H, H.T.contiguous())
+    c.close()
