@@ -375,7 +375,8 @@ def test_hessian_of_narrow_layers_adds_chunks_of_2048_in_float64(gpu_lib, N, m, 
     (16500, 300, 0, (67 << 20, 13 << 20, 1 << 20, 0)),          # one pass, several, too little, none
     (70001, 514, 0, (256 << 20, 40 << 20, 16 << 20)),           # pieces; several passes with pieces
     (2100, 5890, 0, (200 << 20, 60 << 20, 30 << 20)),           # two groups of tiles; one pass, several; smaller groups
-    (4200, 2816, 2, (160 << 20, 0))])                           # a wide layer whose rows start between 16-byte borders
+    (4200, 2816, 2, (160 << 20, 0)),                            # a wide layer whose rows start between 16-byte borders
+    (1500, 5888, 0, (128 << 20, 80 << 20, 67 << 20, 64 << 20, 8 << 20))])    # a round of whole tiles and the rest together; apart; in H itself
 def test_hessian_with_any_scratch(gpu_lib, N, m, offset, sizes):
     """Passes with running sums, groups of tiles and the kernel that needs no scratch, against float64: within 1e-6 of
     sqrt(H_jj H_ll) (chunks of 2048 of up to 128 roundings each: at most 3.8e-6, seen 4e-7)."""
