@@ -73,6 +73,65 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *p, bool vec) {
     return vec ? *(const uint32_t *)p : (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
 }
 
+// H (m x m float32, m % 16 == 0) -> its planes.
+//   SPLIT_ROWS     row j of the planes = row j of H (its column j where H is symmetric)
+//   SPLIT_COLUMNS  row j of the planes = column j of H
+//   SPLIT_LOWER    what the loss needs: the columns up to the end of the 256-column block that holds j; those ahead of the
+//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself)
+// A workgroup takes 64 rows x 32 k; the transposed tile goes through LDS, so both are read in whole lines.
+enum SplitMode { SPLIT_ROWS, SPLIT_COLUMNS, SPLIT_LOWER };
+constexpr int SPLIT_J = 64, SPLIT_K = 32, SPLIT_THREADS = 256;
+struct SplitTile {
+    float t[SPLIT_K][SPLIT_J + 1];
+};
+__device__ __forceinline__ void split_tile(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode, long long tile,
+                                           SplitTile &tr) {
+    const int tid = threadIdx.x;
+    const long long tk = (m + SPLIT_K - 1) / SPLIT_K;
+    const long long j0 = tile / tk * SPLIT_J, k0 = tile % tk * SPLIT_K;
+    if (mode == SPLIT_LOWER && k0 > (j0 | (TILE - 1))) return;
+    const bool turned = mode == SPLIT_COLUMNS || (mode == SPLIT_LOWER && k0 < (j0 & ~(long long)(TILE - 1)));
+    if (turned) {          // (the same in the whole workgroup)
+        const long long k = k0 + (tid >> 3), j = j0 + 8 * (tid & 7);
+        if (k < m && j < m) {
+            const float4 a = *(const float4 *)(H + k * m + j), b = *(const float4 *)(H + k * m + j + 4);
+            float *o = &tr.t[tid >> 3][8 * (tid & 7)];
+            o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+            o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+        }
+        __syncthreads();
+    }
+    const int oct = tid & 3;
+    const long long j = j0 + (tid >> 2), k = k0 + 8 * oct;       // 8 consecutive k of one row
+    if (j >= m || k >= m) return;
+    float x[8];
+    if (mode != SPLIT_COLUMNS) {
+        const float4 a = *(const float4 *)(H + j * m + k), b = *(const float4 *)(H + j * m + k + 4);
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    }
+    if (turned) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float y = tr.t[8 * oct + e][tid >> 2];
+            x[e] = (mode == SPLIT_COLUMNS || x[e] == y) ? y : 0.5f * x[e] + 0.5f * y;
+        }
+    }
+    uint32_t p[3][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
+    uint16_t *dst = Hp + plane_index(j, k, m);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
+                                              p[q][6] | (p[q][7] << 16));
+}
+inline long long split_tiles(int64_t m) { return (m + SPLIT_J - 1) / SPLIT_J * ((m + SPLIT_K - 1) / SPLIT_K); }
+__global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode) {
+    __shared__ SplitTile tr;
+    split_tile(H, m, Hp, mode, blockIdx.x, tr);
+}
+
 // Per row: weighted cluster sums with fixed labels -> centroids c (n x 16 float64),
 // masses Den (n x 16 float64), and the row of dW as three bfloat16 pieces per value.
 // BITS == 0: labels are read.  BITS == 1 .. 4: they are worked out from the clusters' upper bounds (the largest member of each
@@ -85,22 +144,34 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *p, bool vec) {
 // two passes; 0: longer rows are read twice.  Bound: HBM (9 to 14 bytes read and 6 written per weight):
 // 66 us at 4096 x 4096, 252 MB (54 us at the rate of a copy); one workgroup per row, its pieces in 32-byte scraps: 81.
 // Labels from bounds: 60 to 72 us, instead of 66 and 27 for a kernel that writes them first.
-constexpr int ROWP_WAVES = 16, ROWP_COPIES = 8;      // copies of the bins per wavefront, picked by the lane
-template <int BITS, int KEEP>
-__global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
+// WPR: wavefronts per row: four, or one for rows of up to 256 columns, which one step of a wavefront holds (11008 x 32: 25.6 ->
+// 10.1 us).  That variant cuts H into its pieces as well, in workgroups behind those of the rows: such a layer's call is
+// mostly launches.
+constexpr int ROWP_ROWS = 4, ROWP_COPIES = 8;      // copies of the bins per wavefront, picked by the lane
+constexpr int ROWP_NARROW = 256;
+template <int BITS, int KEEP, int WPR>
+__global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
                                                                    long long m, long long ld, const uint8_t *labels, const float *upper,
                                                                    long long upper_stride, uint8_t *labels_out, double *cent, double *Den,
                                                                    uint16_t *dWp, const double *kept, long long kept_stride, int kept_n,
-                                                                   bool vec4) {
-    constexpr int WAVES = ROWP_WAVES, K = 1 << BITS, NSC = BITS == 4 ? 3 : K - 1;
+                                                                   bool vec4, const float *H, uint16_t *Hp, int split_mode) {
+    if constexpr (WPR == 1) {
+        __shared__ SplitTile tr;
+        const long long groups = (n + ROWP_ROWS - 1) / ROWP_ROWS;
+        if (blockIdx.x >= groups) {
+            split_tile(H, m, Hp, split_mode, blockIdx.x - groups, tr);
+            return;
+        }
+    }
+    constexpr int WAVES = ROWP_ROWS * WPR, STEP = 256 * WPR, K = 1 << BITS, NSC = BITS == 4 ? 3 : K - 1;
     __shared__ double binD[WAVES][ROWP_COPIES][16], binN[WAVES][ROWP_COPIES][16];
     __shared__ double csh[WAVES][16];
     __shared__ __align__(16) float thr[WAVES][16];
     __shared__ int thl[WAVES][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int sub = wave & 3;                                       // quarter of the row's steps
-    const bool live = (long long)blockIdx.x * 4 + (wave >> 2) < n;
-    const long long row = live ? (long long)blockIdx.x * 4 + (wave >> 2) : n - 1;
+    const int sub = wave % WPR;                                     // its share of the row's steps
+    const bool live = (long long)blockIdx.x * ROWP_ROWS + wave / WPR < n;
+    const long long row = live ? (long long)blockIdx.x * ROWP_ROWS + wave / WPR : n - 1;
     const long long mm = live ? m : 0;                              // (a row past the end has no columns)
     const float *Wr = W + row * ld, *Sr = S + row * ld;
     const uint8_t *Lr = BITS == 0 ? labels + row * m : nullptr;
@@ -197,10 +268,10 @@ __global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *
     if constexpr (KEEP > 0) {
 #pragma unroll
         for (int it = 0; it < KEEP; ++it)
-            if (j0 + 1024 * it < mm) first_pass(it, j0 + 1024 * it);
+            if (j0 + STEP * it < mm) first_pass(it, j0 + STEP * it);
     } else {
 #pragma unroll 2
-        for (long long j = j0; j < mm; j += 1024) first_pass(0, j);
+        for (long long j = j0; j < mm; j += STEP) first_pass(0, j);
     }
 #pragma unroll
     for (int k = 0; k < REGS; ++k) {
@@ -215,18 +286,20 @@ __global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *
     }
     __syncthreads();
     {
-        // 16 clusters; the bins of one of the row's four wavefronts in every 16 lanes
+        // 16 clusters; four wavefronts a row: the bins of one of them in every 16 lanes
         double d = 0.0, nn = 0.0;
-        const int bw = (wave & ~3) + (lane >> 4);
+        const int bw = WPR == 4 ? (wave & ~3) + (lane >> 4) : wave;
 #pragma unroll
         for (int q = 0; q < ROWP_COPIES; ++q) {
             d += binD[bw][q][lane & 15];
             nn += binN[bw][q][lane & 15];
         }
-        d += __shfl_xor(d, 16, 64);
-        nn += __shfl_xor(nn, 16, 64);
-        d += __shfl_xor(d, 32, 64);
-        nn += __shfl_xor(nn, 32, 64);
+        if constexpr (WPR == 4) {
+            d += __shfl_xor(d, 16, 64);
+            nn += __shfl_xor(nn, 16, 64);
+            d += __shfl_xor(d, 32, 64);
+            nn += __shfl_xor(nn, 32, 64);
+        }
         if (lane < 16) {
             const double c = d > 0.0 ? nn / d : ((kept && lane < kept_n) ? kept[row * kept_stride + lane] : 0.0);
             csh[wave][lane] = c;
@@ -253,10 +326,10 @@ __global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *
     if constexpr (KEEP > 0) {
 #pragma unroll
         for (int it = 0; it < KEEP; ++it)
-            if (j0 + 1024 * it < mm) second_pass(wk[it], alpha ? load4(alpha + j0 + 1024 * it, vec4) : ones, lk[it], j0 + 1024 * it);
+            if (j0 + STEP * it < mm) second_pass(wk[it], alpha ? load4(alpha + j0 + STEP * it, vec4) : ones, lk[it], j0 + STEP * it);
     } else {
 #pragma unroll 2
-        for (long long j = j0; j < mm; j += 1024) {
+        for (long long j = j0; j < mm; j += STEP) {
             const float4 w4 = load4(Wr + j, vec4);
             const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
             uint32_t l4;
@@ -279,65 +352,6 @@ __global__ void __launch_bounds__(64 * ROWP_WAVES) row_prep_kernel(const float *
 // products with piece indices i + j <= 4 carry everything down to 2^-24 of |x y| -- the size of float32's own
 // rounding -- and v_mfma_f32_32x32x16_bf16 does one of them for 16 k in half the time v_mfma_f32_32x32x2_f32
 // needs for 2 k: 6 x 32 clocks against 512 per 16 k.  Accumulation is float32 in the matrix core either way.
-// H (m x m float32, m % 16 == 0) -> its planes.
-//   SPLIT_ROWS     row j of the planes = row j of H (its column j where H is symmetric)
-//   SPLIT_COLUMNS  row j of the planes = column j of H
-//   SPLIT_LOWER    what the loss needs: the columns up to the end of the 256-column block that holds j; those ahead of the
-//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself)
-// A workgroup takes 64 rows x 32 k; the transposed tile goes through LDS, so both are read in whole lines.
-enum SplitMode { SPLIT_ROWS, SPLIT_COLUMNS, SPLIT_LOWER };
-constexpr int SPLIT_J = 64, SPLIT_K = 32, SPLIT_THREADS = 256;
-struct SplitTile {
-    float t[SPLIT_K][SPLIT_J + 1];
-};
-__device__ __forceinline__ void split_tile(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode, long long tile,
-                                           SplitTile &tr) {
-    const int tid = threadIdx.x;
-    const long long tk = (m + SPLIT_K - 1) / SPLIT_K;
-    const long long j0 = tile / tk * SPLIT_J, k0 = tile % tk * SPLIT_K;
-    if (mode == SPLIT_LOWER && k0 > (j0 | (TILE - 1))) return;
-    const bool turned = mode == SPLIT_COLUMNS || (mode == SPLIT_LOWER && k0 < (j0 & ~(long long)(TILE - 1)));
-    if (turned) {          // (the same in the whole workgroup)
-        const long long k = k0 + (tid >> 3), j = j0 + 8 * (tid & 7);
-        if (k < m && j < m) {
-            const float4 a = *(const float4 *)(H + k * m + j), b = *(const float4 *)(H + k * m + j + 4);
-            float *o = &tr.t[tid >> 3][8 * (tid & 7)];
-            o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-            o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-        }
-        __syncthreads();
-    }
-    const int oct = tid & 3;
-    const long long j = j0 + (tid >> 2), k = k0 + 8 * oct;       // 8 consecutive k of one row
-    if (j >= m || k >= m) return;
-    float x[8];
-    if (mode != SPLIT_COLUMNS) {
-        const float4 a = *(const float4 *)(H + j * m + k), b = *(const float4 *)(H + j * m + k + 4);
-        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-    }
-    if (turned) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float y = tr.t[8 * oct + e][tid >> 2];
-            x[e] = (mode == SPLIT_COLUMNS || x[e] == y) ? y : 0.5f * x[e] + 0.5f * y;
-        }
-    }
-    uint32_t p[3][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
-    uint16_t *dst = Hp + plane_index(j, k, m);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
-                                              p[q][6] | (p[q][7] << 16));
-}
-inline long long split_tiles(int64_t m) { return (m + SPLIT_J - 1) / SPLIT_J * ((m + SPLIT_K - 1) / SPLIT_K); }
-__global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode) {
-    __shared__ SplitTile tr;
-    split_tile(H, m, Hp, mode, blockIdx.x, tr);
-}
-
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8;
 constexpr int G_THREADS = 512;                     // 8 wavefronts, two per SIMD: 2 x 4, each 128 x 64 of the 256 x 256 tile
@@ -570,13 +584,15 @@ struct LossLine {
     __host__ __device__ __forceinline__ int owner(long long stage) const { return (int)(((stage + 1) * G - 1) / total); }
 };
 constexpr int LOSS_MAX_WG = 256;
+constexpr int LOSS_MIN_STAGES = 4;      // a piece is this long, or a whole tile where that is shorter (256 x 256: 20 us, 31 with 16 stages)
 inline LossLine loss_line(int64_t n, int64_t m, int num_cu) {
     LossLine l;
     l.tj = (int)((m + TILE - 1) / TILE);
     l.nk = (int)(m / GK);
     l.per_row = l.before(l.tj - 1) + l.stages(l.tj - 1);
     l.total = l.per_row * ((n + TILE - 1) / TILE);
-    const long long most = l.total / G_MIN_STAGES > 1 ? l.total / G_MIN_STAGES : 1;
+    const int least = l.nk < LOSS_MIN_STAGES ? l.nk : LOSS_MIN_STAGES;
+    const long long most = l.total / least > 1 ? l.total / least : 1;
     l.G = num_cu < LOSS_MAX_WG ? num_cu : LOSS_MAX_WG;
     if (l.G > most) l.G = (int)most;
     return l;
@@ -924,30 +940,38 @@ bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t
     return (ld % 4) == 0 && (((uintptr_t)W | (uintptr_t)S | (uintptr_t)alpha) & 15) == 0 && ((uintptr_t)labels & 3) == 0;
 }
 
+// split: what to cut H into as well (the caller launches it where it is still to be done on return)
 template <int BITS>
 void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
                           const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride,
-                          int kept_n) {
-    const dim3 grid((unsigned)((n + 3) / 4)), block(64 * ROWP_WAVES);
+                          int kept_n, const float *H, bool &split, SplitMode mode) {
     const bool vec4 = rows_vec4(W, S, alpha, BITS == 0 ? labels : bd.labels_out, ld);
-    auto launch = [&](auto keep) {
-        hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value>), grid, block, 0, ctx->stream, W, S, alpha, (long long)n, (long long)m,
-                           (long long)ld, labels, bd.upper, (long long)bd.upper_stride, bd.labels_out, w.cent, w.Den, w.dWp, kept,
-                           (long long)kept_stride, kept_n, vec4);
+    const long long groups = (n + ROWP_ROWS - 1) / ROWP_ROWS;
+    auto launch = [&](auto keep, auto wpr, long long blocks) {
+        constexpr int WPR = decltype(wpr)::value;
+        hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value, WPR>), dim3((unsigned)blocks), dim3(64 * ROWP_ROWS * WPR), 0, ctx->stream,
+                           W, S, alpha, (long long)n, (long long)m, (long long)ld, labels, bd.upper, (long long)bd.upper_stride, bd.labels_out,
+                           w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n, vec4, H, w.Hp, (int)mode);
     };
-    if (m <= 4 * 1024) launch(std::integral_constant<int, 4>{});
-    else if (m <= 11 * 1024) launch(std::integral_constant<int, 11>{});
-    else launch(std::integral_constant<int, 0>{});
+    using four = std::integral_constant<int, 4>;
+    if (m <= ROWP_NARROW) {
+        launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, groups + (split ? split_tiles(m) : 0));
+        split = false;
+    } else if (m <= 4 * 1024) launch(std::integral_constant<int, 4>{}, four{}, groups);
+    else if (m <= 11 * 1024) launch(std::integral_constant<int, 11>{}, four{}, groups);
+    else launch(std::integral_constant<int, 0>{}, four{}, groups);
 }
 void launch_row_prep(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
-                     const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride, int kept_n) {
+                     const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride, int kept_n,
+                     const float *H, bool split, SplitMode mode) {
     switch (bd.bits) {
-        case 0: launch_row_prep_bits<0>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
-        case 1: launch_row_prep_bits<1>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
-        case 2: launch_row_prep_bits<2>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
-        case 3: launch_row_prep_bits<3>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
-        default: launch_row_prep_bits<4>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n); break;
+        case 0: launch_row_prep_bits<0>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 1: launch_row_prep_bits<1>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 2: launch_row_prep_bits<2>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 3: launch_row_prep_bits<3>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        default: launch_row_prep_bits<4>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
     }
+    if (split) launch_split(ctx, w, H, m, mode);
 }
 
 skim_status check_shape(skim_ctx *ctx, int64_t n, int64_t m, int64_t ld) {
@@ -989,9 +1013,8 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
     if ((uintptr_t)H & 15) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: H must be 16-byte aligned");
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
-    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    if (!h_ready) launch_split(ctx, w, H, m, SPLIT_LOWER);
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n, H, !h_ready, SPLIT_LOWER);
     hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
                        (long long)m, w.line, w.partial);
     hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
@@ -1027,9 +1050,8 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     if ((uintptr_t)H & 15) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_scale_step: H must be 16-byte aligned");
     LossWs w;
     if ((st = carve(ctx, n, m, true, w)) != SKIM_OK) return st;
-    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, nullptr, 0, 0);
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    if (!h_ready) launch_split(ctx, w, H, m, step_split(m));
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, nullptr, 0, 0, H, !h_ready, step_split(m));
     {
         long long grid = 0;
         for (int p = 0; p < w.plan.nph; ++p) grid = max(grid, (long long)w.plan.ntile[p] * w.plan.split[p]);

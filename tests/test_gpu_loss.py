@@ -114,7 +114,7 @@ def test_loss_argument_errors(ctx, gpu_lib):
         ctx.layer_loss(dev(W), dev(S), dev(H), dev(labels))
 
 
-@pytest.mark.parametrize("n,m,with_alpha,zero_s", [(40, 144, False, 0.0), (130, 512, True, 0.0), (64, 1024, True, 0.0),
+@pytest.mark.parametrize("n,m,with_alpha,zero_s", [(40, 144, False, 0.0), (41, 256, True, 0.0), (130, 512, True, 0.0), (64, 1024, True, 0.0),
                                                    (48, 144, False, 0.9), (48, 272, True, 0.97)])
 def test_lfull_error_table_matches_oracle(ctx, n, m, with_alpha, zero_s):
     """Error pre-recording with the layer-wise error: every (row, bit width) entry against the oracle
@@ -237,6 +237,7 @@ def test_hessian_plans_match_oracle(gpu_lib, N, m, workspace):
 
 @pytest.mark.parametrize("n,m,K", [
     (3, 4112, 16), (9, 11280, 8),       # rows of 5 .. 11 steps kept in registers, longer ones read twice; row groups part empty
+    (7, 256, 16), (1030, 32, 8),        # one wavefront a row, H cut in the same launch; a workgroup of the loss for every tile
     (70, 2064, 4),                      # few tiles: every one split; a last stage of 16 columns past a multiple of 32
     (8200, 2080, 16)])                  # more tiles than workgroups: one round of whole tiles, then split ones
 def test_loss_and_scale_step_on_other_tile_plans(ctx, n, m, K):
