@@ -1,7 +1,7 @@
 """GPU parity: clustering, error table, allocation and packing against the CPU oracle.
 
 Bar: labels, thresholds, allocations, packed codes and codebooks bit-exact;
-centroids and errors within 1e-5 relative (the benchmark spec).  A decision whose oracle
+centroids and errors within 1e-5 relative.  A decision whose oracle
 margin is below 1e-9 may legitimately fall the other way (the two sides sum in
 different orders); the oracle counts such decisions per (row, bit width), only
 those entries are excused from the exact comparison, and they are still checked
@@ -497,8 +497,8 @@ def test_float32_matvec_adds_in_short_chains(ctx, n, m, bound):
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 16384, 16385, 33000])
 @pytest.mark.parametrize("offset", [0, 3])
 def test_pack_row_order(ctx, n, offset):
-    """Positions of the packed rows where the number of rows a thread of the plan takes changes, rows left out among them
-    (bits 0 and 7), the bits at any address."""
+    """Positions of the packed rows against a stable sort by bit width: fewer rows than the plan's workgroup has threads, and
+    more (a thread then counts several), rows left out among them (bits 0 and 7), the bits at any address."""
     m = 16
     g = torch.Generator(device="cuda").manual_seed(n)
     W = torch.randn((n, m), device="cuda", generator=g)

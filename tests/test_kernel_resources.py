@@ -39,14 +39,47 @@ def test_sort_kernel_variants_for_rows_up_to_12288_keep_their_keys_in_registers(
     assert found == 2
 
 
+def scratch_inside_mfma_loops(source, kernel):
+    """Scratch instructions between the first and the last MFMA of every instantiation of a kernel, by its mangled name."""
+    from paper_2412_04180_amd import _build
+
+    flags = [f for f in _build.HIPCC_FLAGS if f != "-shared"]
+    r = subprocess.run([HIPCC] + flags + ["-Wno-inline-asm", "--cuda-device-only", "-S", "-I", os.path.join(ROOT, "include"), "-I", _build.CSRC,
+                                          "-x", "hip", os.path.join(_build.CSRC, source), "-o", "-"],
+                       stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    found = {}
+    for m in re.finditer(r"^(\S*\d" + kernel + r"(?:I\S*)?E?Ev?P\S*):.*?s_endpgm", r.stdout, re.S | re.M):
+        lines = m.group(0).splitlines()
+        mfma = [i for i, line in enumerate(lines) if "v_mfma" in line]
+        assert mfma, m.group(1)
+        found[m.group(1)] = sum("scratch_" in line for line in lines[mfma[0]:mfma[-1]])
+    return found
+
+
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_hessian_kernel_for_wide_layers_does_not_spill():
     """Two wavefronts per SIMD, 128 accumulator registers each: a reload from scratch memory inside the MFMA loop
-    waits behind every tile load in flight (the memory counter is in-order)."""
+    waits behind every tile load in flight (the memory counter is in-order).  All three ways of summing the chunks."""
     r = resource_remarks("skim_hessian.hip")
-    m = re.search(r"Function Name: \S*xtx_big_kernel.*?LDS Size", r.stdout, re.S)
-    assert m, "no resource remarks for xtx_big_kernel"
-    scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1))
-    occupancy = int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", m.group(0)).group(1))
-    assert scratch == 0, f"xtx_big_kernel spills {scratch} bytes per lane into scratch memory"
-    assert occupancy == 2
+    found = list(re.finditer(r"Function Name: \S*xtx_big_kernel.*?LDS Size", r.stdout, re.S))
+    assert len(found) == 3, "resource remarks for xtx_big_kernel"
+    for m in found:
+        scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1))
+        occupancy = int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", m.group(0)).group(1))
+        assert scratch == 0, f"xtx_big_kernel spills {scratch} bytes per lane into scratch memory"
+        assert occupancy == 2
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_contraction_kernels_do_not_spill_in_their_stage_loops():
+    """The same holds for the contraction with H.  dwh_loss_kernel parks 11 registers of its epilogue's addresses in scratch
+    memory ahead of the loop and reads them behind it, which is no harm."""
+    r = resource_remarks("skim_loss.hip")
+    for kernel, limit in (("dwh_kernel", 0), ("dwh_loss_kernel", 64)):
+        m = re.search(r"Function Name: \S*\d" + kernel + r".*?LDS Size", r.stdout, re.S)
+        assert m, f"no resource remarks for {kernel}"
+        assert int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1)) <= limit
+        assert int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", m.group(0)).group(1)) == 2
+        inside = scratch_inside_mfma_loops("skim_loss.hip", kernel)
+        assert len(inside) == 1 and not any(inside.values()), inside
