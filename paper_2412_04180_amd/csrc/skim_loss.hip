@@ -144,6 +144,9 @@ __global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *
 // two passes; 0: longer rows are read twice.  Bound: HBM (9 to 14 bytes read and 6 written per weight):
 // 66 us at 4096 x 4096, 252 MB (54 us at the rate of a copy); one workgroup per row, its pieces in 32-byte scraps: 81.
 // Labels from bounds: 60 to 72 us, instead of 66 and 27 for a kernel that writes them first.
+// KEEP = 11 against reading twice, 11008 columns: labels read 164 / 204 us, 1 to 4 bits 168 / 188, 189 / 200, 173 / 216, 169 / 209; 4608
+// columns 73 / 76, 82 / 78, 100 / 92, 83 / 94, 82 / 91 (one and two bits, whose sums take registers, keep a part of the row in scratch memory
+// and gain from 8192 columns on; one bound for all of them).
 // WPR: wavefronts per row: four, or one for rows of up to 256 columns, which one step of a wavefront holds (11008 x 32: 25.6 ->
 // 10.1 us).  That variant cuts H into its pieces as well, in workgroups behind those of the rows: such a layer's call is
 // mostly launches.
