@@ -303,7 +303,8 @@ skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t 
  * float64 scalar.  row_loss: dev float64[n] (the L-full error of each channel),
  * may be NULL.  The contraction dW*H accumulates in float32 on the bf16 matrix cores, with every
  * float32 operand cut exactly into three bfloat16 pieces and the six leading piece products taken
- * per k (what is dropped is below 2^-24 of each product, the size of float32's own rounding).
+ * per k (what is dropped is below 2^-24 of each product, the size of float32's own rounding; values below about
+ * 2^-110 in magnitude lose digits to the range of the pieces).
  * Half of the products are taken, with the mean of H and its transpose (for a symmetric H, as the H
  * of Sec. 3.4 is, that is H; for another one the loss is the same).  The final reductions are
  * float64.  m must be a multiple of 16. */
