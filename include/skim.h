@@ -301,10 +301,11 @@ skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t 
  *   loss = tr(dW H dW^T) = sum_i dW_i H dW_i^T  (Sec. 3.4, L-full; H ~ X X^T)
  * H: dev m x m float32.  labels: dev uint8 n x m.  loss: dev
  * float64 scalar.  row_loss: dev float64[n] (the L-full error of each channel),
- * may be NULL.  The contraction dW*H accumulates in float32 on the bf16 matrix cores, with every
- * float32 operand cut exactly into three bfloat16 pieces and the six leading piece products taken
- * per k (what is dropped is below 2^-24 of each product, the size of float32's own rounding; values below about
- * 2^-110 in magnitude lose digits to the range of the pieces).
+ * may be NULL.  The contraction dW*H accumulates in float32 on the matrix cores: both operands are scaled by
+ * powers of two (per channel of H, per row of dW) and cut into two binary16 pieces of 23 bits together, and the three
+ * leading piece products taken per k (what is dropped is at most 2^-22 of each product, 2^-25 in the mean square; an entry of dW
+ * that, weighed by its channel's scale, is below 2^-16 of the largest of its row loses digits, its error staying below 2^-39 of that
+ * one, and so does an H_jl below 2^-15 of the largest its channels allow).  The loss takes the diagonal of H in float64.
  * Half of the products are taken, with the mean of H and its transpose (for a symmetric H, as the H
  * of Sec. 3.4 is, that is H; for another one the loss is the same).  The final reductions are
  * float64.  m must be a multiple of 16. */

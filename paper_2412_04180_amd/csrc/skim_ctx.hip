@@ -129,8 +129,10 @@ size_t skim_workspace_least(int64_t n, int64_t m) {
     const size_t N = (size_t)n, M = (size_t)m;
     const size_t ti = (N + 255) / 256, tj = (M + 255) / 256, nstrip = (N + 7) / 8;
     size_t b = 0;
-    b += 3 * N * M * sizeof(uint16_t) + N * M * sizeof(float);   // scale step: dW (as three bfloat16 pieces per value) and P
-    b += 3 * M * M * sizeof(uint16_t);   // the pieces of H
+    b += 2 * N * M * sizeof(uint16_t) + N * M * sizeof(float);   // scale step: dW (as two binary16 pieces per value) and P
+    b += 2 * M * M * sizeof(uint16_t);   // the pieces of H
+    b += M * sizeof(uint32_t) + (N + 256) * sizeof(int) + M * sizeof(float) + N * sizeof(double);   // the scales of both; the diagonal of H, the rows' losses on it
+    b += 4 * 4 * M;                      // (rows of dW are stored in groups of four)
     b += 2 * N * 16 * sizeof(double);    // centroids and masses from fixed labels
     b += (ti * tj + 256) * 256 * sizeof(double) + N * sizeof(double);   // row sums of the loss, piece by piece (256 pieces beyond one per tile) and in all
     b += nstrip * (M + 1) * sizeof(double);    // per-strip column sums of the gradient and shares of the loss

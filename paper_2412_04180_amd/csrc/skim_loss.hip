@@ -4,8 +4,8 @@
 //
 //   c_ik  = sum_{j in k} s~_ij w~_ij / sum_{j in k} s~_ij      (calc_centroids(W*alpha^-1, L))
 //   dW_ij = w_ij - alpha_j c_{i,L_ij}                           (W - replace(c, L) * alpha)
-//   P     = dW H            matrix cores, float32 accumulation (the path's one dense contraction): bf16 MFMA on
-//                           three-piece splits of the float32 operands; where only the loss is wanted, half of it
+//   P     = dW H            matrix cores, float32 accumulation (the path's one dense contraction): fp16 MFMA on
+//                           two-piece splits of the scaled float32 operands; where only the loss is wanted, half of it
 //   loss  = sum_ij P_ij dW_ij                                   float64 reduction
 //   dloss/dalpha_l = -2 sum_i [ P_il c_{i,L_il}
 //                    + Q_{i,L_il} s_il (w_il - 2 alpha_l c_{i,L_il}) / D_{i,L_il} ],
@@ -18,28 +18,37 @@
 
 namespace {
 
-// Pieces of a float32 value for the contraction on the bf16 matrix cores (see dwh_kernel)
-__device__ __forceinline__ uint32_t bf16_rn(float f) {      // finite f
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
+// Pieces of a float32 value for the contraction on the matrix cores (see dwh_kernel): two binary16 values, the rounding of
+// x and the rounding of the rest.  |x| < 2^15.  From 2^-1 up they carry 23 of its 24 bits or all (the rest has 12 bits of
+// which the second piece keeps 11: every fourth x loses its last), below that everything down to 2^-25.
+__device__ __forceinline__ void split2(float x, uint32_t &p1, uint32_t &p2) {
+    const _Float16 h = (_Float16)x;
+    const _Float16 l = (_Float16)(x - (float)h);       // (the difference is exact)
+    p1 = (uint32_t)__builtin_bit_cast(uint16_t, h);
+    p2 = (uint32_t)__builtin_bit_cast(uint16_t, l);
 }
-__device__ __forceinline__ float bf16_f32(uint32_t h) { return __uint_as_float(h << 16); }
-__device__ __forceinline__ void split3(float x, uint32_t &p1, uint32_t &p2, uint32_t &p3) {
-    p1 = bf16_rn(x);
-    if ((p1 & 0x7FFFu) == 0x7F80u && fabsf(x) <= __FLT_MAX__) --p1;      // above bfloat16's largest: that one, and the rest to the others
-    float r = x - bf16_f32(p1);       // exact
-    p2 = bf16_rn(r);
-    r -= bf16_f32(p2);                // exact; at most 8 significant bits are left
-    p3 = bf16_rn(r);
-}
+__device__ __forceinline__ float piece_f32(uint32_t h) { return (float)__builtin_bit_cast(_Float16, (uint16_t)h); }
+
+// The scales, powers of two, which cost no digits.  binary16 has little range, so both operands are balanced first:
+//   e_j   half the exponent of the largest magnitude in row j and column j of H.  |H_jl| <= min(max_j, max_l), so
+//         H''_jl = H_jl 2^(H_SHIFT - e_j - e_l) lies below 2^15, whatever H is; for an H of activations it is their correlation
+//         matrix times 2^H_SHIFT, within a factor of two.
+//   r_i   the exponent of the largest dW_ij 2^e_j of row i; dW''_ij = dW_ij 2^(e_j - r_i + D_SHIFT) lies below 2^15.
+//   P_il  = 2^(r_i + e_l - H_SHIFT - D_SHIFT) sum_j dW''_ij H''_jl
+//   dW_i H dW_i^T = 2^(2 (r_i - D_SHIFT) - H_SHIFT) sum_jl dW''_ij H''_jl dW''_il
+// Digits are lost where an entry is 2^16 times smaller than the largest of its row of dW'' (or a correlation below 2^-15), and
+// what such an entry loses is below 2^-39 of that largest one.
+constexpr int H_SHIFT = 14, D_SHIFT = 15;
+__device__ __forceinline__ int h_exponent(uint32_t max_bits) { return ((int)(max_bits >> 23) - 126) >> 1; }      // -63 .. 64; max < 2^(2 e + 2)
+__device__ __forceinline__ int value_exponent(float x) { return x == 0.0f ? -1024 : __builtin_amdgcn_frexp_expf(x); }      // |x| < 2^this
+
 // Layout of a split matrix ("planes"): groups of 4 rows; a group holds, for every block of 16 k, its 4 rows' [piece 1 (16) |
-// piece 2 (16) | piece 3 (16)], 384 contiguous bytes.  A tile reads whole 128-byte lines for a 16-k step, and the four
+// piece 2 (16)], 256 contiguous bytes.  A tile reads whole 128-byte lines for a 16-k step, and the four
 // rows one workgroup writes are one contiguous region of memory.
 constexpr int GK = 16;
 __host__ __device__ __forceinline__ size_t plane_rows(long long rows) { return (size_t)(rows + 3) & ~(size_t)3; }      // rows stored
 __device__ __forceinline__ size_t plane_index(long long row, long long k, long long m) {
-    return ((size_t)(row >> 2) * (size_t)(m >> 4) + (size_t)(k >> 4)) * 192 + (size_t)(row & 3) * 48 + (size_t)(k & 15);     // piece p at + 16 p
+    return ((size_t)(row >> 2) * (size_t)(m >> 4) + (size_t)(k >> 4)) * 128 + (size_t)(row & 3) * 32 + (size_t)(k & 15);     // piece p at + 16 p
 }
 
 constexpr int PREP_THREADS = 256;
@@ -77,15 +86,16 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *p, bool vec) {
 //   SPLIT_ROWS     row j of the planes = row j of H (its column j where H is symmetric)
 //   SPLIT_COLUMNS  row j of the planes = column j of H
 //   SPLIT_LOWER    what the loss needs: the columns up to the end of the 256-column block that holds j; those ahead of the
-//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself)
+//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself).  The
+//                  diagonal is left out: row_prep_kernel adds its share of the loss up in float64
 // A workgroup takes 64 rows x 32 k; the transposed tile goes through LDS, so both are read in whole lines.
 enum SplitMode { SPLIT_ROWS, SPLIT_COLUMNS, SPLIT_LOWER };
 constexpr int SPLIT_J = 64, SPLIT_K = 32, SPLIT_THREADS = 256;
 struct SplitTile {
     float t[SPLIT_K][SPLIT_J + 1];
 };
-__device__ __forceinline__ void split_tile(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode, long long tile,
-                                           SplitTile &tr) {
+__device__ __forceinline__ void split_tile(const float *__restrict__ H, long long m, const uint32_t *__restrict__ hmax,
+                                           uint16_t *__restrict__ Hp, int mode, long long tile, SplitTile &tr) {
     const int tid = threadIdx.x;
     const long long tk = (m + SPLIT_K - 1) / SPLIT_K;
     const long long j0 = tile / tk * SPLIT_J, k0 = tile % tk * SPLIT_K;
@@ -117,52 +127,120 @@ __device__ __forceinline__ void split_tile(const float *__restrict__ H, long lon
             x[e] = (mode == SPLIT_COLUMNS || x[e] == y) ? y : 0.5f * x[e] + 0.5f * y;
         }
     }
-    uint32_t p[3][8];
+    if (mode == SPLIT_LOWER) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) split3(x[e], p[0][e], p[1][e], p[2][e]);
+        for (int e = 0; e < 8; ++e)
+            if (k + e == j) x[e] = 0.0f;
+    }
+    const uint4 ma = *(const uint4 *)(hmax + k), mb = *(const uint4 *)(hmax + k + 4);
+    const uint32_t mk[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+    const int ej = H_SHIFT - h_exponent(hmax[j]);
+    uint32_t p[2][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split2(ldexpf(x[e], ej - h_exponent(mk[e])), p[0][e], p[1][e]);
     uint16_t *dst = Hp + plane_index(j, k, m);
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 2; ++q)
         *(uint4 *)(dst + 16 * q) = make_uint4(p[q][0] | (p[q][1] << 16), p[q][2] | (p[q][3] << 16), p[q][4] | (p[q][5] << 16),
                                               p[q][6] | (p[q][7] << 16));
 }
 inline long long split_tiles(int64_t m) { return (m + SPLIT_J - 1) / SPLIT_J * ((m + SPLIT_K - 1) / SPLIT_K); }
-__global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *__restrict__ H, long long m, uint16_t *__restrict__ Hp, int mode) {
+__global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *__restrict__ H, long long m, const uint32_t *__restrict__ hmax,
+                                                                   uint16_t *__restrict__ Hp, int mode) {
     __shared__ SplitTile tr;
-    split_tile(H, m, Hp, mode, blockIdx.x, tr);
+    split_tile(H, m, hmax, Hp, mode, blockIdx.x, tr);
+}
+
+// hdiag = the diagonal of H; hmax[j] = bits of the largest magnitude in row j and column j of H (bits of magnitudes order like the magnitudes).
+// Short matrices: a workgroup works out 16 of them, no atomics between workgroups and nothing to clear.
+constexpr int HMAX_DIRECT = 1024;
+__global__ void __launch_bounds__(256) hmax_direct_kernel(const float *__restrict__ H, int m, uint32_t *__restrict__ hmax, float *__restrict__ hdiag) {
+    __shared__ uint32_t top[16];
+    const int a = threadIdx.x & 15, b = threadIdx.x >> 4, j0 = 16 * blockIdx.x;       // m is a multiple of 16
+    if (threadIdx.x < 16) top[threadIdx.x] = 0u;
+    __syncthreads();
+    uint32_t r = 0u, c = 0u;
+#pragma unroll 4
+    for (int k = 0; k < m; k += 16) {
+        r = max(r, __float_as_uint(fabsf(H[(long long)(j0 + b) * m + k + a])));
+        c = max(c, __float_as_uint(fabsf(H[(long long)(k + b) * m + j0 + a])));
+    }
+    atomicMax(&top[b], r);
+    atomicMax(&top[a], c);
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        hmax[j0 + threadIdx.x] = top[threadIdx.x];
+        hdiag[j0 + threadIdx.x] = H[(long long)(j0 + threadIdx.x) * (m + 1)];
+    }
+}
+// Longer ones: H is read once, 64 rows x 256 columns a workgroup, into a cleared hmax.
+constexpr int HMAX_ROWS = 64, HMAX_COLS = 256;
+__global__ void __launch_bounds__(256) hmax_clear_kernel(const float *__restrict__ H, long long m, uint32_t *__restrict__ hmax, float *__restrict__ hdiag) {
+    const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (j >= m) return;
+    hmax[j] = 0u;
+    hdiag[j] = H[j * (m + 1)];
+}
+__global__ void __launch_bounds__(256) hmax_kernel(const float *__restrict__ H, long long m, int tiles_x, uint32_t *__restrict__ hmax) {
+    __shared__ uint32_t cols[4][HMAX_COLS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long j0 = (long long)(blockIdx.x / tiles_x) * HMAX_ROWS + 16 * wave, k = (long long)(blockIdx.x % tiles_x) * HMAX_COLS + 4 * lane;
+    float4 x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = (j0 + i < m && k < m) ? *(const float4 *)(H + (j0 + i) * m + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t c[4] = {0u, 0u, 0u, 0u};
+    uint32_t mine = 0u;          // lane i < 16: the largest of row j0 + i
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t b[4] = {__float_as_uint(fabsf(x[i].x)), __float_as_uint(fabsf(x[i].y)), __float_as_uint(fabsf(x[i].z)), __float_as_uint(fabsf(x[i].w))};
+        uint32_t r = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c[q] = max(c[q], b[q]);
+            r = max(r, b[q]);
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) r = max(r, (uint32_t)__shfl_xor((int)r, o, 64));
+        if (lane == i) mine = r;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cols[wave][4 * lane + q] = c[q];
+    if (lane < 16 && j0 + lane < m) atomicMax(&hmax[j0 + lane], mine);
+    __syncthreads();
+    const long long l = (long long)(blockIdx.x % tiles_x) * HMAX_COLS + tid;
+    if (l < m) atomicMax(&hmax[l], max(max(cols[0][tid], cols[1][tid]), max(cols[2][tid], cols[3][tid])));
 }
 
 // Per row: weighted cluster sums with fixed labels -> centroids c (n x 16 float64),
-// masses Den (n x 16 float64), and the row of dW as three bfloat16 pieces per value.
+// masses Den (n x 16 float64), and the row of dW as two scaled pieces per value with the exponent of its scale (rexp).
 // BITS == 0: labels are read.  BITS == 1 .. 4: they are worked out from the clusters' upper bounds (the largest member of each
 // cluster, -inf for an empty one) at upper + row * upper_stride: the cluster with the smallest bound >= w~; labels_out
 // (optional) receives them.
 // kept (optional): per row, at kept + row * kept_stride, the centroid a cluster keeps when its members carry no
 // sensitivity mass (what the clustering that produced the labels left there); without it such a centroid is 0.
 // A workgroup takes 4 rows (one group of the planes: it writes one contiguous region), four wavefronts each, four columns
-// per lane and step.  KEEP > 0: the row takes at most KEEP steps, and its weights and labels stay in registers between the
-// two passes; 0: longer rows are read twice.  Bound: HBM (9 to 14 bytes read and 6 written per weight):
-// 66 us at 4096 x 4096, 252 MB (54 us at the rate of a copy); one workgroup per row, its pieces in 32-byte scraps: 81.
-// Labels from bounds: 60 to 72 us, instead of 66 and 27 for a kernel that writes them first.
-// KEEP = 11 against reading twice, 11008 columns: labels read 164 / 204 us, 1 to 4 bits 168 / 188, 189 / 200, 173 / 216, 169 / 209; 4608
-// columns 73 / 76, 82 / 78, 100 / 92, 83 / 94, 82 / 91 (one and two bits, whose sums take registers, keep a part of the row in scratch memory
-// and gain from 8192 columns on; one bound for all of them).
+// per lane and step.  KEEP > 0: the row takes at most KEEP steps, and its weights and labels (then its dW and their columns' exponents)
+// stay in registers; 0: longer rows are read three times, the largest entry of dW being needed ahead of the first piece.  Bound: HBM
+// (9 to 14 bytes read and 4 written per weight): 61 us at 4096 x 4096 (67 with three pieces), 218 MB; held to 64 registers two workgroups
+// share a compute unit (69 registers: 75 us).
 // WPR: wavefronts per row: four, or one for rows of up to 256 columns, which one step of a wavefront holds (11008 x 32: 25.6 ->
 // 10.1 us).  That variant cuts H into its pieces as well, in workgroups behind those of the rows: such a layer's call is
 // mostly launches.
 constexpr int ROWP_ROWS = 4, ROWP_COPIES = 8;      // copies of the bins per wavefront, picked by the lane
 constexpr int ROWP_NARROW = 256;
-template <int BITS, int KEEP, int WPR>
-__global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
+// DIAG: for the loss, the row's share of the diagonal of H as well.
+template <int BITS, int KEEP, int WPR, bool DIAG>
+__global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_waves_per_eu(KEEP > 4 || KEEP == 0 ? 4 : 8))) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
                                                                    long long m, long long ld, const uint8_t *labels, const float *upper,
                                                                    long long upper_stride, uint8_t *labels_out, double *cent, double *Den,
                                                                    uint16_t *dWp, const double *kept, long long kept_stride, int kept_n,
-                                                                   bool vec4, const float *H, uint16_t *Hp, int split_mode) {
+                                                                   bool vec4, const float *H, const uint32_t *hmax, uint16_t *Hp,
+                                                                   int split_mode, int *rexp, const float *hdiag, double *rdiag) {
     if constexpr (WPR == 1) {
         __shared__ SplitTile tr;
         const long long groups = (n + ROWP_ROWS - 1) / ROWP_ROWS;
         if (blockIdx.x >= groups) {
-            split_tile(H, m, Hp, split_mode, blockIdx.x - groups, tr);
+            split_tile(H, m, hmax, Hp, split_mode, blockIdx.x - groups, tr);
             return;
         }
     }
@@ -171,6 +249,8 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) row_prep_kernel(const fl
     __shared__ double csh[WAVES][16];
     __shared__ __align__(16) float thr[WAVES][16];
     __shared__ int thl[WAVES][16];
+    __shared__ int wexp[WAVES];
+    __shared__ double wdiag[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = wave % WPR;                                     // its share of the row's steps
     const bool live = (long long)blockIdx.x * ROWP_ROWS + wave / WPR < n;
@@ -313,66 +393,131 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) row_prep_kernel(const fl
         }
         __builtin_amdgcn_wave_barrier();      // (one wavefront's LDS accesses execute in order)
     }
-    auto second_pass = [&](const float4 &w4, const float4 &a4, uint32_t l4, long long j) {
+    // four entries of dW and the exponents e_j of their columns (a byte each); the largest exponent of the row so far
+    // and, for the loss, its diagonal share: the sum of dW_ij^2 H_jj in float64
+    int top = -1024;
+    double dsum = 0.0;
+    auto form_four = [&](float4 &w4, const float4 &a4, uint32_t &l4, long long j) {
         const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
-        uint32_t pc[3][4];
+        const uint4 h4 = *(const uint4 *)(hmax + j);
+        const uint32_t hv[4] = {h4.x, h4.y, h4.z, h4.w};
+        const float4 g4 = DIAG ? *(const float4 *)(hdiag + j) : ones;
+        const float gv[4] = {g4.x, g4.y, g4.z, g4.w};
+        float d[4];
+        uint32_t ex = 0u;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float d = (float)((double)wv[e] - (double)av[e] * csh[wave][(l4 >> (8 * e)) & 15u]);
-            split3(d, pc[0][e], pc[1][e], pc[2][e]);
+            const double dd = (double)wv[e] - (double)av[e] * csh[wave][(l4 >> (8 * e)) & 15u];
+            if (DIAG) dsum = fma(dd * dd, (double)gv[e], dsum);
+            d[e] = (float)dd;
+            const int ej = h_exponent(hv[e]);
+            top = max(top, value_exponent(d[e]) + ej);
+            ex |= ((uint32_t)ej & 0xFFu) << (8 * e);
         }
+        w4 = make_float4(d[0], d[1], d[2], d[3]);
+        l4 = ex;
+    };
+    auto write_four = [&](const float4 &d4, uint32_t e4, int shift, long long j) {
+        const float d[4] = {d4.x, d4.y, d4.z, d4.w};
+        uint32_t pc[2][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split2(ldexpf(d[e], shift + (int)(int8_t)(e4 >> (8 * e))), pc[0][e], pc[1][e]);
         uint16_t *o = dWp + plane_index(row, j, m);   // four neighbouring k stay inside one block of 16
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
+        for (int q = 0; q < 2; ++q)
             *(uint2 *)(o + 16 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
+    };
+    // (rows that do not stay in registers are formed twice more: for their largest entry, and to be written)
+    auto form_step = [&](float4 &w4, uint32_t &l4, long long j) {
+        w4 = load4(Wr + j, vec4);
+        const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
+        if (BITS == 0) {
+            l4 = load4(Lr + j, vec4);
+        } else {
+            const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
+            l4 = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) l4 |= (uint32_t)label_of(alpha ? __fdiv_rn(wv[e], av[e]) : wv[e]) << (8 * e);
+        }
+        form_four(w4, a4, l4, j);
     };
     if constexpr (KEEP > 0) {
 #pragma unroll
         for (int it = 0; it < KEEP; ++it)
-            if (j0 + STEP * it < mm) second_pass(wk[it], alpha ? load4(alpha + j0 + STEP * it, vec4) : ones, lk[it], j0 + STEP * it);
+            if (j0 + STEP * it < mm) form_four(wk[it], alpha ? load4(alpha + j0 + STEP * it, vec4) : ones, lk[it], j0 + STEP * it);
     } else {
 #pragma unroll 2
         for (long long j = j0; j < mm; j += STEP) {
-            const float4 w4 = load4(Wr + j, vec4);
-            const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
+            float4 w4;
             uint32_t l4;
-            if (BITS == 0) {
-                l4 = load4(Lr + j, vec4);
-            } else {
-                const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
-                l4 = 0u;
+            form_step(w4, l4, j);
+        }
+    }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) l4 |= (uint32_t)label_of(alpha ? __fdiv_rn(wv[e], av[e]) : wv[e]) << (8 * e);
-            }
-            second_pass(w4, a4, l4, j);
+    for (int o = 32; o >= 1; o >>= 1) {
+        top = max(top, __shfl_xor(top, o, 64));
+        if (DIAG) dsum += __shfl_xor(dsum, o, 64);
+    }
+    if constexpr (WPR == 4) {
+        if (lane == 0) {
+            wexp[wave] = top;
+            wdiag[wave] = dsum;
+        }
+        __syncthreads();
+        dsum = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            top = max(top, wexp[(wave & ~3) + q]);
+            dsum += wdiag[(wave & ~3) + q];
+        }
+    }
+    if (top < -1000) top = 0;          // a row of zeros
+    if (sub == 0 && lane == 0 && live) {
+        rexp[row] = top;
+        if (DIAG) rdiag[row] = dsum;
+    }
+    if constexpr (KEEP > 0) {
+#pragma unroll
+        for (int it = 0; it < KEEP; ++it)
+            if (j0 + STEP * it < mm) write_four(wk[it], lk[it], D_SHIFT - top, j0 + STEP * it);
+    } else {
+#pragma unroll 2
+        for (long long j = j0; j < mm; j += STEP) {
+            float4 w4;
+            uint32_t l4;
+            form_step(w4, l4, j);
+            write_four(w4, l4, D_SHIFT - top, j);
         }
     }
 }
 
-// ---- the contraction on the bf16 matrix cores ------------------------------------------------------------------
-// A float32 value is the exact sum of three bfloat16 values (8 + 8 + 8 significant bits, each piece the rounding of
-// what the pieces before it leave), so x y = sum over the nine products of pieces, each exact in float32.  The six
-// products with piece indices i + j <= 4 carry everything down to 2^-24 of |x y| -- the size of float32's own
-// rounding -- and v_mfma_f32_32x32x16_bf16 does one of them for 16 k in half the time v_mfma_f32_32x32x2_f32
-// needs for 2 k: 6 x 32 clocks against 512 per 16 k.  Accumulation is float32 in the matrix core either way.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8;
+// ---- the contraction on the matrix cores -------------------------------------------------------------------------
+// A float32 value x scaled as above is p1 + p2, two binary16 values, up to its last bit (see split2), so x y is the sum of four
+// products of pieces, each exact in float32.  The three with p1 q1, p1 q2, p2 q1 carry everything but p2 q2, at most 2^-22
+// of |x y| and 2^-25 in the mean square, of either sign.  v_mfma_f32_32x32x16_f16 does one of them for 16 k in 32 clocks: 96, where
+// the six leading products of three bfloat16 pieces took 192 and v_mfma_f32_32x32x2_f32 takes 512.  Accumulation is float32 in the
+// matrix core either way; half as many roundings of the sums make up for the last bit of the operands.  Against float64,
+// relative 2-norms of P here / with three bfloat16 pieces: 512 columns 1.8 / 2.2e-7, 1552 1.5 / 2.2e-7, 4096 2.2 / 2.4e-7, 8192 2.8 / 3.3e-7
+// (channels correlated through 8 common factors: 2.2 / 1.9e-7, 2.0 / 2.1e-7, 2.7 / 3.0e-7, 3.7 / 4.2e-7); rms of the row losses, whose
+// diagonal part is left to float64: 512 columns 0.2 / 6.0e-8, 4096 0.4 / 6.1e-8 (correlated: 7.0e-8 / 1.0e-7, 1.3e-7 / 1.8e-7).
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) half8_t lds_half8;
 constexpr int G_THREADS = 512;                     // 8 wavefronts, two per SIMD: 2 x 4, each 128 x 64 of the 256 x 256 tile
-constexpr int G_BUFS = 3;
-constexpr uint32_t G_PANEL_BYTES = TILE * 96;      // one operand of one 16-k stage: 24 KB
+constexpr int G_BUFS = 4;                          // a power of two
+constexpr uint32_t G_PANEL_BYTES = TILE * 64;      // one operand of one 16-k stage: 16 KB
 constexpr uint32_t G_STAGE_BYTES = 2 * G_PANEL_BYTES;
-constexpr size_t G_LDS_BYTES = (size_t)G_BUFS * G_STAGE_BYTES;      // 147456
-constexpr int G_LOADS = G_STAGE_BYTES / (1024 * (G_THREADS / 64));  // 1 KB copies of a wavefront per stage: 6
+constexpr size_t G_LDS_BYTES = (size_t)G_BUFS * G_STAGE_BYTES;      // 131072
+constexpr int G_LOADS = G_STAGE_BYTES / (1024 * (G_THREADS / 64));  // 1 KB copies of a wavefront per stage: 4
 constexpr int G_MIN_STAGES = 16;
 constexpr int G_PHASE_COST = 20;                   // a phase of split tiles with its partial tiles, in stages
 
-// What a lane needs to know about the LDS.  A panel holds its rows one after the other (96 bytes each: six 16-byte units,
-// unit 2 p + h = piece p, k 8 h .. 8 h + 7), except that the units of the rows with bit 3 set are rotated by one: any 16
-// rows then read one unit from 64 different banks.
+// What a lane needs to know about the LDS.  A panel holds its rows one after the other (64 bytes each: four 16-byte units,
+// unit 2 p + h = piece p, k 8 h .. 8 h + 7), the units of row r rotated by r / 4: any 16 rows then read one unit from 64
+// different banks.
 struct DwhLane {
     uint32_t voff[G_LOADS];      // source of its copies inside the tile's rows
     uint32_t dst;                // their first kilobyte (the same in the whole wavefront)
-    uint32_t ra[3], rb[3];       // operand addresses of the three pieces, A block x at + x * 3072, B block y likewise
+    uint32_t ra[2], rb[2];       // operand addresses of the two pieces, A block x at + x * 2048, B block y likewise
     int swave, wr, wc, l32, lhi;
     __device__ __forceinline__ DwhLane(uint32_t lds0, int tid, long long m) {
         const int lane = tid & 63, wave = tid >> 6;
@@ -384,25 +529,24 @@ struct DwhLane {
 #pragma unroll
         for (int i = 0; i < G_LOADS; ++i) {
             const int c = ((wave & 3) * G_LOADS + i) * 64 + lane;
-            const int row = c / 6, pos = c - 6 * row;
-            const int unit = (pos + 6 - ((row >> 3) & 1)) % 6;
-            voff[i] = (uint32_t)((row >> 2) * m * 24) + (uint32_t)((row & 3) * 96 + unit * 16);
+            const int row = c >> 2, unit = (c - (row >> 2)) & 3;
+            voff[i] = (uint32_t)((row >> 2) * m * 16) + (uint32_t)((row & 3) * 64 + unit * 16);
         }
         dst = lds0 + (uint32_t)(swave >> 2) * G_PANEL_BYTES + (uint32_t)(swave & 3) * (G_LOADS * 1024);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const uint32_t u = (uint32_t)((2 * p + lhi + ((l32 >> 3) & 1)) % 6) * 16;
-            ra[p] = lds0 + (uint32_t)(wr * 128 + l32) * 96 + u;
-            rb[p] = lds0 + G_PANEL_BYTES + (uint32_t)(wc * 64 + l32) * 96 + u;
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t u = (uint32_t)((2 * p + lhi + (l32 >> 2)) & 3) * 16;
+            ra[p] = lds0 + (uint32_t)(wr * 128 + l32) * 64 + u;
+            rb[p] = lds0 + G_PANEL_BYTES + (uint32_t)(wc * 64 + l32) * 64 + u;
         }
     }
 };
 
 // acc = (rows arow0 .. of A) (rows brow0 .. of B)^T over the 16-k stages [s0, s1), from the planes of two matrices of m columns;
 // with HALVED the sums are doubled ahead of stage sdouble.  Rows past the end of either matrix carry no meaning.
-// 16 k are 48 MFMAs and 18 operand reads per wavefront.  The operands of the next quarter of a stage are read between the
+// 16 k are 24 MFMAs and 12 operand reads per wavefront.  The operands of the next quarter of a stage are read between the
 // MFMAs of this one; the barrier stands ahead of the last quarter: past it the next stage is complete in LDS and this
-// one's place is free for the stage after the next two.
+// one's place is free for the stage after the next three.
 template <bool HALVED>
 __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhLane &L, const uint16_t *Ap, long long arows,
                                                long long arow0, const uint16_t *Bp, long long brows, long long brow0, long long m,
@@ -414,39 +558,38 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
     const bool isb = L.swave >= 4;
-    const long long rows = isb ? brows : arows, skip = ((isb ? brow0 : arow0) >> 2) * m * 24 + (long long)s0 * 384;
-    LdsSource src{(uint64_t)(uintptr_t)(isb ? Bp : Ap) + (uint64_t)skip, (long long)plane_rows(rows) * m * 6 - skip};
+    const long long rows = isb ? brows : arows, skip = ((isb ? brow0 : arow0) >> 2) * m * 16 + (long long)s0 * 256;
+    LdsSource src{(uint64_t)(uintptr_t)(isb ? Bp : Ap) + (uint64_t)skip, (long long)plane_rows(rows) * m * 4 - skip};
     int ahead = s1 - s0;         // stages still to be requested (past the end nothing is read: zeros arrive)
     auto issue = [&](uint32_t buf) {
         if (ahead-- <= 0) src.left = 0;
         const int4v rs = src.rsrc();
 #pragma unroll
         for (int i = 0; i < G_LOADS; ++i) copy_to_lds(L.dst + buf + i * 1024, L.voff[i], rs);
-        src.advance(384);
+        src.advance(256);
     };
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the LDS is free
-    issue(0);
-    issue(G_STAGE_BYTES);
-    issue(2 * G_STAGE_BYTES);
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * G_LOADS) : "memory");
-    bf16x8_t a[2][3], b[2][2][3];
+#pragma unroll
+    for (int q = 0; q < G_BUFS; ++q) issue(q * G_STAGE_BYTES);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((G_BUFS - 1) * G_LOADS) : "memory");
+    half8_t a[2][2], b[2][2][2];
     auto read_a = [&](int set, uint32_t buf, int x) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) a[set][p] = *(lds_bf16x8 *)(L.ra[p] + buf + x * 3072);
+        for (int p = 0; p < 2; ++p) a[set][p] = *(lds_half8 *)(L.ra[p] + buf + x * 2048);
     };
     auto read_b = [&](int set, uint32_t buf) {
 #pragma unroll
         for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[set][y][p] = *(lds_bf16x8 *)(L.rb[p] + buf + y * 3072);
+            for (int p = 0; p < 2; ++p) b[set][y][p] = *(lds_half8 *)(L.rb[p] + buf + y * 2048);
     };
     auto multiply = [&](int x, int as, int bs) {     // smallest products first
-        constexpr int PA[6] = {2, 1, 0, 0, 1, 0}, PB[6] = {0, 1, 2, 1, 0, 0};
+        constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
 #pragma unroll
-        for (int q = 0; q < 6; ++q)
+        for (int q = 0; q < 3; ++q)
 #pragma unroll
             for (int y = 0; y < 2; ++y)
-                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[as][PA[q]], b[bs][y][PB[q]], acc[x][y], 0, 0, 0);
+                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[as][PA[q]], b[bs][y][PB[q]], acc[x][y], 0, 0, 0);
     };
     uint32_t cur = 0;
     read_b(0, cur);
@@ -461,26 +604,28 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[x][y][e] += acc[x][y][e];
         }
-        const uint32_t nxt = cur == 2 * G_STAGE_BYTES ? 0 : cur + G_STAGE_BYTES;
+        const uint32_t nxt = (cur + G_STAGE_BYTES) & (G_BUFS * G_STAGE_BYTES - 1);
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             read_a((x + 1) & 1, cur, x + 1);
             multiply(x, x & 1, BS);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // an MFMA, the three reads, the other MFMAs
-            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 11, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // an MFMA, the two reads, the other MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 5, 0);
         }
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G_LOADS) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G_BUFS - 2) * G_LOADS) : "memory");
         issue(cur);
         read_b(BS ^ 1, nxt);
         read_a(0, nxt, 0);
         multiply(3, 1, BS);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-        for (int q = 0; q < 9; ++q) {
+        for (int q = 0; q < 4; ++q) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         cur = nxt;
     };
     for (int st = s0;;) {
@@ -491,13 +636,13 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
     }
 }
 
-// What bounds it: the power the matrix cores draw.  4096^3: 0.53 ms = 1.56 PFLOP/s of executed piece products (a bf16
-// product of the same size by the library: 1.25), MFMAs busy 88 % of the cycles at 1.7 GHz instead of 2.4, no bank
-// conflicts.  256 x 128 tiles staged through registers, 32 k per barrier: 0.67 ms, 62 % busy.
+// What bounds it: the power the matrix cores draw.  4096^3: 0.31 ms = 1.32 PFLOP/s of executed piece products (a bf16
+// product of the same size by the library: 1.10), MFMAs busy 84 % of the cycles at 1.66 GHz instead of 2.4, no bank
+// conflicts.  Six products of bfloat16 pieces: 0.54 ms.
 // P = dW H, tile by tile as the plan says: a whole tile goes straight into P, a part of a split one into its slot.
 __global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, long long n, long long m, int tj, TilePlan plan,
-           float *__restrict__ P, floatx4 *__restrict__ slots) {
+dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, const int *__restrict__ rexp, const uint32_t *__restrict__ hmax,
+           long long n, long long m, int tj, TilePlan plan, float *__restrict__ P, floatx4 *__restrict__ slots) {
     extern __shared__ __align__(16) unsigned char g_smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid, m);
@@ -525,18 +670,24 @@ dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, lon
             } else {
                 const long long rb = row0 + L.wr * 128 + 4 * L.lhi, cb = col0 + L.wc * 64 + L.l32;
                 float *pp = P + rb * m + cb;
+                const int *re = rexp + rb;
                 long long mm = m;
                 int rlim = (int)min(n - rb, 4096ll), clim = (int)min(m - cb, 4096ll);
-                asm volatile("" : "+v"(pp), "+s"(mm), "+v"(rlim), "+v"(clim));     // the addresses are worked out here, not ahead of the loop
+                asm volatile("" : "+v"(pp), "+v"(re), "+s"(mm), "+v"(rlim), "+v"(clim));     // the addresses are worked out here, not ahead of the loop
+                const int e0 = clim > 0 ? h_exponent(hmax[cb]) - H_SHIFT - D_SHIFT : 0, e1 = clim > 32 ? h_exponent(hmax[cb + 32]) - H_SHIFT - D_SHIFT : 0;
 #pragma unroll
                 for (int x = 0; x < 4; ++x)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int r = x * 32 + 8 * (e >> 2) + (e & 3);
-                        float *q = pp + r * mm;
-                        if (r < rlim) {
-                            if (clim > 0) q[0] = acc[x][0][e];
-                            if (clim > 32) q[32] = acc[x][1][e];
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const int4v ri = *(const int4v *)(re + x * 32 + 8 * q4);       // (rexp has room for whole tiles)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = x * 32 + 8 * q4 + e;
+                            float *q = pp + r * mm;
+                            if (r < rlim) {
+                                if (clim > 0) q[0] = ldexpf(acc[x][0][4 * q4 + e], ri[e] + e0);
+                                if (clim > 32) q[32] = ldexpf(acc[x][1][4 * q4 + e], ri[e] + e1);
+                            }
                         }
                     }
             }
@@ -546,7 +697,8 @@ dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, lon
 }
 
 // P of the split tiles: their parts added up.  One wavefront per 32 x 32 block (16 workgroups per tile).
-__global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, long long n, long long m, int tj, TilePlan plan, int ph,
+__global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, const int *__restrict__ rexp, const uint32_t *__restrict__ hmax,
+                                                        long long n, long long m, int tj, TilePlan plan, int ph,
                                                         const floatx4 *__restrict__ slots) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -565,14 +717,16 @@ __global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, l
 #pragma unroll
         for (int q = 0; q < 4; ++q) s[q] += sp[q * 64];
     }
+    if (cb >= m) return;
+    const int ec = h_exponent(hmax[cb]) - H_SHIFT - D_SHIFT;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (rb + 8 * q + e < n && cb < m) P[(rb + 8 * q + e) * m + cb] = s[q][e];
+            if (rb + 8 * q + e < n) P[(rb + 8 * q + e) * m + cb] = ldexpf(s[q][e], rexp[rb + 8 * q + e] + ec);
 }
 
-// 4096^3: 0.33 ms, of which the 136 stages of every workgroup take 0.28; the full product with its row sums: 0.67.
+// 4096^3: 0.20 ms (0.33 with six products of bfloat16 pieces), MFMAs busy 68 % of the cycles.
 // Loss only: dW_i H dW_i^T = sum over the 256-column blocks J of H of [ 2 sum_{K < J} dW_K H_KJ + dW_J H_JJ ] . dW_J, the H_KJ
 // those of the mean of H and its transpose: half the products.  The stages of all tiles -- tile (I, J) has those of the blocks K <= J -- form one line that is
 // cut into equal pieces, one per workgroup; the loss is linear in the sums, so the pieces of a tile need not meet: each
@@ -602,8 +756,8 @@ inline LossLine loss_line(int64_t n, int64_t m, int num_cu) {
 }
 
 __global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, long long n, long long m, LossLine line,
-                double *__restrict__ partial) {
+dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, const int *__restrict__ rexp, long long n, long long m,
+                LossLine line, double *__restrict__ partial) {
     extern __shared__ __align__(16) unsigned char g_smem[];
     const int tid = threadIdx.x;
     const DwhLane L((uint32_t)(uintptr_t)(lds_byte *)g_smem, tid, m);
@@ -636,19 +790,19 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
                 for (int x = 0; x < 4; ++x) {
                     __builtin_amdgcn_sched_barrier(0);      // (one block's loads at a time: the registers hold the sums)
                     const long long c = col0 + L.wr * 128 + x * 32 + 4 * L.lhi;
-                    uint2 d[4][3];
+                    uint2 d[4][2];
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
-                        for (int p = 0; p < 3; ++p)
+                        for (int p = 0; p < 2; ++p)
                             d[q][p] = c + 8 * q < m ? *(const uint2 *)(Ap + plane_index(r, c + 8 * q, m) + 16 * p) : make_uint2(0u, 0u);
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const int sh = (e & 1) * 16;
-                            auto piece = [&](int p) { return bf16_f32(((e < 2 ? d[q][p].x : d[q][p].y) >> sh) & 0xFFFFu); };
-                            const float dw = (piece(0) + piece(1)) + piece(2);     // exact
+                            auto piece = [&](int p) { return piece_f32(((e < 2 ? d[q][p].x : d[q][p].y) >> sh) & 0xFFFFu); };
+                            const float dw = piece(0) + piece(1);     // exact
                             t += (double)acc[x][y][4 * q + e] * (double)dw;         // (columns past the matrix: dw = 0)
                         }
                 }
@@ -659,7 +813,7 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
         __syncthreads();
         if (tid < TILE) {
             double *o = partial + ((long long)I * line.tj + J + g) * TILE + tid;
-            o[0] = (rsum[tid] + rsum[TILE + tid]) * twice;
+            o[0] = ldexp((rsum[tid] + rsum[TILE + tid]) * twice, 2 * (rexp[row0 + tid] - D_SHIFT) - H_SHIFT);
             // (a workgroup that starts with a tile leaves a number unused behind the piece before it)
             if (s0 == 0 && at == line.start(g) && g > 0) o[-TILE] = 0.0;
         }
@@ -668,15 +822,15 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// row_loss[i] = the pieces of the tiles of its row, in the order of the line; left in rows[i] for the total.
-__global__ void __launch_bounds__(256) loss_rows_kernel(const double *__restrict__ partial, LossLine line, long long n, double *rows,
+// row_loss[i] = the share of the diagonal and the pieces of the tiles of its row, in the order of the line; left in rows[i] for the total.
+__global__ void __launch_bounds__(256) loss_rows_kernel(const double *__restrict__ partial, const double *__restrict__ rdiag, LossLine line, long long n, double *rows,
                                                         double *row_loss, long long row_stride) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const int I = blockIdx.x;
     const long long first = (long long)I * line.per_row;
     const long long p0 = (long long)I * line.tj + line.owner(first), p1 = (long long)I * line.tj + line.tj - 1 + line.owner(first + line.per_row - 1);
-    double tot = 0.0;
+    double tot = rdiag[i];
 #pragma unroll 8
     for (long long p = p0; p <= p1; ++p) tot += partial[p * TILE + threadIdx.x];
     if (row_loss) row_loss[i * row_stride] = tot;
@@ -874,6 +1028,10 @@ __global__ void __launch_bounds__(ADAM_COLS * ADAM_GROUPS) adam_kernel(const dou
 struct LossWs {
     float *P;
     uint16_t *dWp, *Hp;      // pieces of dW and of H
+    uint32_t *hmax;          // largest magnitudes of H (their scales)
+    float *hdiag;            // the diagonal of H
+    int *rexp;               // exponents of the rows of dW
+    double *rdiag;           // the rows' losses on the diagonal
     double *cent, *Den, *partial, *rows, *gpart, *lossp;
     floatx4 *slots;
     TilePlan plan;
@@ -901,11 +1059,14 @@ skim_status carve(skim_ctx *ctx, int64_t n, int64_t m, bool grad, LossWs &w) {
     w.tj = (int)((m + TILE - 1) / TILE);
     w.tiles = (n + TILE - 1) / TILE * w.tj;
     // (H first: skim_train_scale and skim_error_table_lfull keep its pieces across their steps)
-    w.Hp = (uint16_t *)cur.take((size_t)m * m * 3 * sizeof(uint16_t));
-    w.dWp = (uint16_t *)cur.take(plane_rows(n) * m * 3 * sizeof(uint16_t));
+    w.Hp = (uint16_t *)cur.take((size_t)m * m * 2 * sizeof(uint16_t));
+    w.hmax = (uint32_t *)cur.take((size_t)m * sizeof(uint32_t));
+    w.hdiag = (float *)cur.take((size_t)m * sizeof(float));
+    w.dWp = (uint16_t *)cur.take(plane_rows(n) * m * 2 * sizeof(uint16_t));
+    w.rexp = (int *)cur.take((((size_t)n + TILE - 1) & ~(size_t)(TILE - 1)) * sizeof(int));
     w.cent = (double *)cur.take((size_t)n * 16 * sizeof(double));
     w.Den = (double *)cur.take((size_t)n * 16 * sizeof(double));
-    bool ok = w.dWp && w.Hp && w.cent && w.Den;
+    bool ok = w.dWp && w.Hp && w.hmax && w.hdiag && w.rexp && w.cent && w.Den;
     if (grad) {
         w.P = (float *)cur.take((size_t)n * m * sizeof(float));
         w.gpart = (double *)cur.take((size_t)w.nstrip * m * sizeof(double));
@@ -918,7 +1079,8 @@ skim_status carve(skim_ctx *ctx, int64_t n, int64_t m, bool grad, LossWs &w) {
         w.line = loss_line(n, m, ctx->num_cu);
         w.partial = (double *)cur.take((size_t)(w.tiles + w.line.G) * TILE * sizeof(double));
         w.rows = (double *)cur.take((size_t)n * sizeof(double));
-        ok = ok && w.partial && w.rows;
+        w.rdiag = (double *)cur.take((size_t)n * sizeof(double));
+        ok = ok && w.partial && w.rows && w.rdiag;
     }
     if (!ok) SKIM_FAIL(ctx, SKIM_ERR_WORKSPACE, "workspace missing or smaller than skim_workspace_bytes(n, m)");
     return SKIM_OK;
@@ -933,7 +1095,17 @@ skim_status enable_lds(skim_ctx *ctx) {
 }
 
 void launch_split(skim_ctx *ctx, const LossWs &w, const float *H, int64_t m, SplitMode mode) {
-    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)split_tiles(m)), dim3(SPLIT_THREADS), 0, ctx->stream, H, (long long)m, w.Hp, (int)mode);
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)split_tiles(m)), dim3(SPLIT_THREADS), 0, ctx->stream, H, (long long)m, (const uint32_t *)w.hmax, w.Hp,
+                       (int)mode);
+}
+void launch_hmax(skim_ctx *ctx, const LossWs &w, const float *H, int64_t m) {
+    if (m <= HMAX_DIRECT) {
+        hipLaunchKernelGGL(hmax_direct_kernel, dim3((unsigned)(m / 16)), dim3(256), 0, ctx->stream, H, (int)m, w.hmax, w.hdiag);
+        return;
+    }
+    const int64_t tx = (m + HMAX_COLS - 1) / HMAX_COLS, ty = (m + HMAX_ROWS - 1) / HMAX_ROWS;
+    hipLaunchKernelGGL(hmax_clear_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, ctx->stream, H, (long long)m, w.hmax, w.hdiag);
+    hipLaunchKernelGGL(hmax_kernel, dim3((unsigned)(tx * ty)), dim3(256), 0, ctx->stream, H, (long long)m, (int)tx, w.hmax);
 }
 // P = dW H, and with rows of H for its columns only where H has to be symmetric (m a multiple of 32 from 128 up)
 SplitMode step_split(int64_t m) { return (m % 32) != 0 || m < 128 ? SPLIT_COLUMNS : SPLIT_ROWS; }
@@ -944,7 +1116,7 @@ bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t
 }
 
 // split: what to cut H into as well (the caller launches it where it is still to be done on return)
-template <int BITS>
+template <int BITS, bool DIAG>
 void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
                           const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride,
                           int kept_n, const float *H, bool &split, SplitMode mode) {
@@ -952,9 +1124,10 @@ void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const f
     const long long groups = (n + ROWP_ROWS - 1) / ROWP_ROWS;
     auto launch = [&](auto keep, auto wpr, long long blocks) {
         constexpr int WPR = decltype(wpr)::value;
-        hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value, WPR>), dim3((unsigned)blocks), dim3(64 * ROWP_ROWS * WPR), 0, ctx->stream,
+        hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value, WPR, DIAG>), dim3((unsigned)blocks), dim3(64 * ROWP_ROWS * WPR), 0, ctx->stream,
                            W, S, alpha, (long long)n, (long long)m, (long long)ld, labels, bd.upper, (long long)bd.upper_stride, bd.labels_out,
-                           w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n, vec4, H, w.Hp, (int)mode);
+                           w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n, vec4, H, (const uint32_t *)w.hmax, w.Hp, (int)mode, w.rexp,
+                           (const float *)w.hdiag, w.rdiag);
     };
     using four = std::integral_constant<int, 4>;
     if (m <= ROWP_NARROW) {
@@ -967,12 +1140,16 @@ void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const f
 void launch_row_prep(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
                      const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride, int kept_n,
                      const float *H, bool split, SplitMode mode) {
+    if (split) launch_hmax(ctx, w, H, m);
     switch (bd.bits) {
-        case 0: launch_row_prep_bits<0>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        case 1: launch_row_prep_bits<1>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        case 2: launch_row_prep_bits<2>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        case 3: launch_row_prep_bits<3>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        default: launch_row_prep_bits<4>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 0:
+            if (mode == SPLIT_LOWER) launch_row_prep_bits<0, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode);
+            else launch_row_prep_bits<0, false>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode);
+            break;
+        case 1: launch_row_prep_bits<1, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 2: launch_row_prep_bits<2, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 3: launch_row_prep_bits<3, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        default: launch_row_prep_bits<4, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
     }
     if (split) launch_split(ctx, w, H, m, mode);
 }
@@ -1018,10 +1195,10 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
     launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n, H, !h_ready, SPLIT_LOWER);
-    hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
-                       (long long)m, w.line, w.partial);
+    hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (const int *)w.rexp,
+                       (long long)n, (long long)m, w.line, w.partial);
     hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
-                       w.line, (long long)n, w.rows, row_loss, (long long)row_stride);
+                       (const double *)w.rdiag, w.line, (long long)n, w.rows, row_loss, (long long)row_stride);
     if (loss) hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double *)w.rows, (long long)n, loss);
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;
@@ -1059,12 +1236,12 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
         long long grid = 0;
         for (int p = 0; p < w.plan.nph; ++p) grid = max(grid, (long long)w.plan.ntile[p] * w.plan.split[p]);
         if (grid > ctx->num_cu) grid = ctx->num_cu;
-        hipLaunchKernelGGL(dwh_kernel, dim3((unsigned)grid), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (long long)n,
-                           (long long)m, w.tj, w.plan, w.P, w.slots);
+        hipLaunchKernelGGL(dwh_kernel, dim3((unsigned)grid), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (const int *)w.rexp,
+                           (const uint32_t *)w.hmax, (long long)n, (long long)m, w.tj, w.plan, w.P, w.slots);
         for (int p = 0; p < w.plan.nph; ++p)
             if (w.plan.split[p] > 1)
-                hipLaunchKernelGGL(dwh_parts_kernel, dim3((unsigned)(w.plan.ntile[p] * 16)), dim3(256), 0, ctx->stream, w.P, (long long)n,
-                                   (long long)m, w.tj, w.plan, p, (const floatx4 *)w.slots);
+                hipLaunchKernelGGL(dwh_parts_kernel, dim3((unsigned)(w.plan.ntile[p] * 16)), dim3(256), 0, ctx->stream, w.P,
+                                   (const int *)w.rexp, (const uint32_t *)w.hmax, (long long)n, (long long)m, w.tj, w.plan, p, (const floatx4 *)w.slots);
     }
     // rows of W, S, P start 16-byte aligned and the labels of a row 4-byte aligned (m is a multiple of 16)
     const bool vec4 = rows_vec4(W, S, alpha, labels, ld) && ((uintptr_t)w.P & 15) == 0;

@@ -1,8 +1,8 @@
 """GPU parity: layer loss tr(dW H dW^T), scale gradient and Adam step against the CPU oracle.
 
 Bar: loss, per-row loss, gradient and updated alpha within 1e-5
-relative.  The contraction runs on the bf16 matrix cores with every float32
-operand cut into three bfloat16 pieces and float32 accumulation; the
+relative.  The contraction runs on the matrix cores with every float32
+operand scaled and cut into two binary16 pieces and float32 accumulation; the
 oracle is float64 throughout.  Parity is per call on identical inputs: the
 oracle is fed the same W, S, H, labels and alpha as the GPU.
 """
@@ -324,8 +324,7 @@ def test_lfull_table_of_a_hessian_that_is_not_symmetric(ctx, n, m):
 
 @pytest.mark.parametrize("m", [48, 112, 160])
 def test_loss_with_entries_above_the_largest_bfloat16(ctx, m):
-    """The first piece of a float32 value is its bfloat16 rounding, which must not be infinity: float32 reaches
-    3.4028e38, bfloat16 3.3895e38."""
+    """No piece of a finite float32 value may be infinity: float32 reaches 3.4028e38, bfloat16 3.3895e38, binary16 65504."""
     n = 20
     rng = np.random.default_rng(m)
     W = (rng.standard_normal((n, m)) * 1e-19).astype(np.float32)
@@ -398,3 +397,58 @@ def test_hessian_with_any_scratch(gpu_lib, N, m, offset, sizes):
         assert worst <= 1e-6, f"scratch {size}: {worst:.3e}"
         assert torch.equal(H, H.T.contiguous())
     c.close()
+
+
+# (16 magnitudes a workgroup; one tile and several of the other kernel, the last ones partly empty; rows kept in registers and read again)
+@pytest.mark.parametrize("n,m", [(5, 16), (70, 272), (33, 1040), (20, 4112), (5, 11280)])
+def test_loss_of_channels_and_rows_of_very_different_magnitude(ctx, n, m):
+    """The scales of the pieces: channels of H from 2^-30 to 2^30 with some that are dead, rows of W from 1e-30 to 1e15, one of zeros
+    and one next to the subnormal numbers (dW is a float32 value: steps of 1.4e-45, 1.4e-9 of that row's), W within a row from 2^-12 to 1 times the largest.  Against float64, in units of the sum of the products'
+    magnitudes: both operands of a product are off by 2^-23 of themselves at most and 2^-22 of it is dropped, 4.8e-7 if all
+    of them conspired, and the float32 sums add 5e-8 at these widths."""
+    gen = torch.Generator(device="cuda").manual_seed(m)
+
+    def normal(*shape):
+        return torch.randn(shape, device="cuda", generator=gen)
+
+    X = normal(64, m)
+    scale = torch.exp2(torch.randint(-15, 16, (m,), device="cuda", generator=gen).float())
+    scale[:: 7] = 0.0
+    X = X * scale
+    H = X.T.contiguous() @ X
+    H = ((H + H.T) / 2).contiguous()
+    rows = torch.logspace(-30, 15, n, device="cuda")
+    W = normal(n, m) * rows[:, None] * torch.exp2(-torch.randint(0, 13, (n, m), device="cuda", generator=gen).float())
+    W[1] = 0.0
+    W[2] = normal(m) * 1e-36
+    S = torch.ones(n, m, device="cuda")
+    labels = torch.randint(0, 4, (n, m), device="cuda", generator=gen, dtype=torch.uint8)
+    out = ctx.layer_loss(W, S, H, labels)
+    c, _ = oracle.centroids_from_labels(W.cpu().numpy(), S.cpu().numpy(), labels.cpu().numpy(), None)
+    dW = W.double() - torch.from_numpy(c).cuda().gather(1, labels.long())
+    Hd = H.double()
+    ref, mag = ((dW @ Hd) * dW).sum(1), ((dW.abs() @ Hd.abs()) * dW.abs()).sum(1)
+    err = (out["row_loss"] - ref).abs()
+    assert bool((err <= 5.3e-7 * mag).all()), f"{float((err / mag.clamp_min(1e-300)).max()):.3e}"
+    assert out["row_loss"][1].item() == 0.0
+    # P and the gradient, with the rows in float32's range for products with H
+    W = normal(n, m) * torch.exp2(-torch.randint(0, 13, (n, m), device="cuda", generator=gen).float())
+    alpha = torch.exp(normal(m) * 0.1)
+    step = ctx.scale_step(W, S, H, labels, alpha.clone(), torch.zeros(m, device="cuda"), torch.zeros(m, device="cuda"), 1)
+    a = alpha.double()
+    wt, st = (W / alpha).double(), (alpha * alpha).double().expand(n, m)
+    L = labels.long()
+    D = torch.zeros(n, 16, device="cuda", dtype=torch.float64).scatter_add_(1, L, st.contiguous())
+    c = torch.zeros_like(D).scatter_add_(1, L, st * wt) / D.clamp_min(1e-300)
+    ck = c.gather(1, L)
+    dW = W.double() - a * ck
+
+    def gradient(P, s):         # s = 1: the sums themselves; the magnitudes of all terms otherwise
+        f = (lambda x: x) if s else torch.abs
+        R = torch.zeros_like(D).scatter_add_(1, L, f(P * a)) / D.clamp_min(1e-300)
+        t = W.double() - 2 * a * ck
+        return 2 * (f(P * ck) + R.gather(1, L) * f(t)).sum(0)
+
+    g, mag = -gradient(dW @ Hd, True), gradient(dW.abs() @ Hd.abs(), False)
+    assert bool(((step["grad"].double() - g).abs() <= 6e-7 * mag).all())
+    assert abs(step["loss_before"].item() - float(((dW @ Hd) * dW).sum())) <= 6e-7 * float(((dW.abs() @ Hd.abs()) * dW.abs()).sum())
