@@ -636,6 +636,14 @@ __device__ __forceinline__ void dwh_accumulate(floatx16 (&acc)[4][2], const DwhL
     }
 }
 
+// Row and column of tile t: column by column in bands of 4 rows of tiles, so that the 32 tiles an XCD works on share 4 panels of dW
+// and 8 of H.
+__device__ __forceinline__ void tile_place(int t, int rows, int tj, int &i, int &j) {
+    const int band = t / (4 * tj), h = min(4, rows - 4 * band), rem = t - band * 4 * tj;
+    j = rem / h;
+    i = 4 * band + rem - j * h;
+}
+
 // What bounds it: the power the matrix cores draw.  4096^3: 0.31 ms = 1.32 PFLOP/s of executed piece products (a bf16
 // product of the same size by the library: 1.10), MFMAs busy 84 % of the cycles at 1.66 GHz instead of 2.4, no bank
 // conflicts.  Six products of bfloat16 pieces: 0.54 ms.
@@ -652,8 +660,9 @@ dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, con
         const int ntile = plan.ntile[p], split = plan.split[p];
         for (int v = me; v < ntile * split; v += G) {
             const int part = v / ntile, t = plan.tile0[p] + v - part * ntile;
-            const int ti = t / tj;
-            const long long row0 = (long long)ti * TILE, col0 = (long long)(t - ti * tj) * TILE;
+            int ti, tc;
+            tile_place(t, (int)((n + TILE - 1) / TILE), tj, ti, tc);
+            const long long row0 = (long long)ti * TILE, col0 = (long long)tc * TILE;
             const int s0 = (int)((long long)nk * part / split), s1 = (int)((long long)nk * (part + 1) / split);
             floatx16 acc[4][2];
             dwh_accumulate<false>(acc, L, Ap, n, row0, Hp, m, col0, m, s0, s1, -1);
@@ -703,10 +712,12 @@ __global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, c
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
     const int tv = blockIdx.x >> 4, blk = (blockIdx.x & 15) * 4 + wave;
-    const int t = plan.tile0[ph] + tv, ti = t / tj;
+    const int t = plan.tile0[ph] + tv;
+    int ti, tc;
+    tile_place(t, (int)((n + TILE - 1) / TILE), tj, ti, tc);
     const int ow = blk >> 3, xy = blk & 7;
     const long long rb = (long long)ti * TILE + (ow >> 2) * 128 + (xy >> 1) * 32 + 4 * lhi;
-    const long long cb = (long long)(t - ti * tj) * TILE + (ow & 3) * 64 + (xy & 1) * 32 + l32;
+    const long long cb = (long long)tc * TILE + (ow & 3) * 64 + (xy & 1) * 32 + l32;
     const floatx4 *sp = slots + ((size_t)(plan.slot0[ph] + tv) * 8 + ow) * (8 * 4 * 64) + xy * 256 + lane;
     const size_t step = (size_t)plan.ntile[ph] * (8 * 8 * 4 * 64);
     floatx4 s[4];
@@ -735,7 +746,12 @@ __global__ void __launch_bounds__(256) dwh_parts_kernel(float *__restrict__ P, c
 struct LossLine {
     int tj, G, nk;              // column blocks, workgroups, stages of the longest tile
     long long per_row, total;   // stages of a row of tiles, of all
-    __host__ __device__ __forceinline__ long long before(int j) const { return 8ll * j * (j + 1); }          // of the tiles ahead of J in its row
+    // A row's tiles follow each other as J = tj - 1, 0, tj - 2, 1, ...: two neighbours have 16 (tj + 1) stages together, so where the
+    // pieces are about half of that, the workgroups of an XCD walk through the same K of dW and of H at the same time
+    __host__ __device__ __forceinline__ int tile(int q) const { return (q & 1) ? q >> 1 : tj - 1 - (q >> 1); }
+    __host__ __device__ __forceinline__ long long before(int q) const {      // stages ahead of the q-th tile of a row
+        return 16ll * (tj + 1) * (q >> 1) + ((q & 1) ? 16ll * (tj - (q >> 1)) : 0) - (q > 0 ? 16 * tj - nk : 0);
+    }
     __host__ __device__ __forceinline__ int stages(int j) const { return 16 * (j + 1) < nk ? 16 * (j + 1) : nk; }
     __host__ __device__ __forceinline__ long long start(int g) const { return total * g / G; }               // first stage of workgroup g
     __host__ __device__ __forceinline__ int owner(long long stage) const { return (int)(((stage + 1) * G - 1) / total); }
@@ -746,7 +762,7 @@ inline LossLine loss_line(int64_t n, int64_t m, int num_cu) {
     LossLine l;
     l.tj = (int)((m + TILE - 1) / TILE);
     l.nk = (int)(m / GK);
-    l.per_row = l.before(l.tj - 1) + l.stages(l.tj - 1);
+    l.per_row = l.before(l.tj - 1) + l.stages(l.tile(l.tj - 1));
     l.total = l.per_row * ((n + TILE - 1) / TILE);
     const int least = l.nk < LOSS_MIN_STAGES ? l.nk : LOSS_MIN_STAGES;
     const long long most = l.total / least > 1 ? l.total / least : 1;
@@ -767,9 +783,9 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
     while (at < end) {
         const int I = (int)(at / line.per_row);
         const int in_row = (int)(at - (long long)I * line.per_row);
-        int J = 0;
-        while (J + 1 < line.tj && line.before(J + 1) <= in_row) ++J;
-        const int s0 = in_row - (int)line.before(J);
+        int q = 0;
+        while (q + 1 < line.tj && line.before(q + 1) <= in_row) ++q;
+        const int J = line.tile(q), s0 = in_row - (int)line.before(q);
         const int s1 = (int)min((long long)line.stages(J), s0 + (end - at));
         const long long row0 = (long long)I * TILE, col0 = (long long)J * TILE;
         floatx16 acc[4][2];
@@ -812,7 +828,7 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
         }
         __syncthreads();
         if (tid < TILE) {
-            double *o = partial + ((long long)I * line.tj + J + g) * TILE + tid;
+            double *o = partial + ((long long)I * line.tj + q + g) * TILE + tid;
             o[0] = ldexp((rsum[tid] + rsum[TILE + tid]) * twice, 2 * (rexp[row0 + tid] - D_SHIFT) - H_SHIFT);
             // (a workgroup that starts with a tile leaves a number unused behind the piece before it)
             if (s0 == 0 && at == line.start(g) && g > 0) o[-TILE] = 0.0;
