@@ -70,22 +70,23 @@ static inline int skim_block_offset(int bmin, int b) {  // start of block b insi
 skim_status skim_pack_static_setup(skim_ctx *ctx);
 
 // Labels that are worked out from the clusters' upper bounds instead of read: 2^bits bounds per row at upper + i *
-// upper_stride (bits = 0: labels are read); labels_out (may be NULL) receives them.
+// upper_stride (bits = 0: labels are read), with the clusters' centroids at centroids + i * centroid_stride; labels_out (may be
+// NULL) receives them.
 struct skim_label_bounds {
     int bits = 0;
     const float *upper = nullptr;
     int64_t upper_stride = 0;
+    const double *centroids = nullptr;
+    int64_t centroid_stride = 0;
     uint8_t *labels_out = nullptr;
 };
 
-// skim_layer_loss with the per-row losses written at a stride (row i at row_loss[i * row_stride]).  kept (may be
-// NULL): kept_n centroids per row at kept + i * kept_stride, used for clusters whose members carry no mass.  loss may be
+// skim_layer_loss with the per-row losses written at a stride (row i at row_loss[i * row_stride]).  loss may be
 // NULL.  h_ready: the pieces of H are where the last such call with the same n, m left them in the workspace.
 skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *S, const float *alpha, const float *H,
                                     int64_t n, int64_t m, int64_t ld, const uint8_t *labels,
                                     const skim_label_bounds &bounds, double *loss,
-                                    double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
-                                    int kept_n, bool h_ready);
+                                    double *row_loss, int64_t row_stride, bool h_ready);
 
 // Room for the partial tiles of a scale step on any layer of at most n rows and m columns.
 size_t skim_dwh_slot_bytes(int64_t n, int64_t m);

@@ -33,10 +33,12 @@ extern "C" skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, con
         bounds.upper = upper_all + off;
         bounds.upper_stride = stride;
         bounds.labels_out = b == bmax ? labels_work : nullptr;
-        // a cluster whose members carry no sensitivity mass keeps the centroid the clustering left it with
-        // (the value the packed codebook holds), not the 0 a weighted mean over no mass would give
+        // the centroids are the clustering's, the weighted means of these labels; a cluster whose members carry no
+        // sensitivity mass keeps the one it was left with (the value the packed codebook holds)
+        bounds.centroids = centroids_all + off;
+        bounds.centroid_stride = stride;
         if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, nullptr, bounds, nullptr, E_full + (b - bmin), nb,
-                                          centroids_all + off, stride, 1 << b, b > bmin)) != SKIM_OK)
+                                          b > bmin)) != SKIM_OK)
             return st;
     }
     return SKIM_OK;

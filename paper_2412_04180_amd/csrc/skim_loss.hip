@@ -213,16 +213,15 @@ __global__ void __launch_bounds__(256) hmax_kernel(const float *__restrict__ H, 
 
 // Per row: weighted cluster sums with fixed labels -> centroids c (n x 16 float64),
 // masses Den (n x 16 float64), and the row of dW as two scaled pieces per value with the exponent of its scale (rexp).
-// BITS == 0: labels are read.  BITS == 1 .. 4: they are worked out from the clusters' upper bounds (the largest member of each
+// BITS == 0: labels are read.  BITS == 1 .. 4: the labels are worked out from the clusters' upper bounds (the largest member of each
 // cluster, -inf for an empty one) at upper + row * upper_stride: the cluster with the smallest bound >= w~; labels_out
-// (optional) receives them.
-// kept (optional): per row, at kept + row * kept_stride, the centroid a cluster keeps when its members carry no
-// sensitivity mass (what the clustering that produced the labels left there); without it such a centroid is 0.
+// (optional) receives them.  The centroids are those of the clustering then, at given + row * given_stride -- the weighted means of
+// these labels, and for a cluster whose members carry no sensitivity mass what the clustering kept -- and S is not read.
 // A workgroup takes 4 rows (one group of the planes: it writes one contiguous region), four wavefronts each, four columns
 // per lane and step.  KEEP > 0: the row takes at most KEEP steps, and its weights and labels (then its dW and their columns' exponents)
 // stay in registers; 0: longer rows are read three times, the largest entry of dW being needed ahead of the first piece.  Bound: HBM
-// (9 to 14 bytes read and 4 written per weight): 61 us at 4096 x 4096 (67 with three pieces), 218 MB; held to 64 registers two workgroups
-// share a compute unit (69 registers: 75 us).
+// (9 to 13 bytes read and 4 written per weight): 61 us at 4096 x 4096 (67 with three pieces), 218 MB; held to 64 registers two workgroups
+// share a compute unit (69 registers: 75 us).  With labels from bounds 4 bytes read: 42 us (60 to 75 with the sums of S).
 // WPR: wavefronts per row: four, or one for rows of up to 256 columns, which one step of a wavefront holds (11008 x 32: 25.6 ->
 // 10.1 us).  That variant cuts H into its pieces as well, in workgroups behind those of the rows: such a layer's call is
 // mostly launches.
@@ -233,7 +232,7 @@ template <int BITS, int KEEP, int WPR, bool DIAG>
 __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_waves_per_eu(KEEP > 4 || KEEP == 0 ? 4 : 8))) row_prep_kernel(const float *W, const float *S, const float *alpha, long long n,
                                                                    long long m, long long ld, const uint8_t *labels, const float *upper,
                                                                    long long upper_stride, uint8_t *labels_out, double *cent, double *Den,
-                                                                   uint16_t *dWp, const double *kept, long long kept_stride, int kept_n,
+                                                                   uint16_t *dWp, const double *given, long long given_stride,
                                                                    bool vec4, const float *H, const uint32_t *hmax, uint16_t *Hp,
                                                                    int split_mode, int *rexp, const float *hdiag, double *rdiag) {
     if constexpr (WPR == 1) {
@@ -245,8 +244,8 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
         }
     }
     constexpr int WAVES = ROWP_ROWS * WPR, STEP = 256 * WPR, K = 1 << BITS, NSC = BITS == 4 ? 3 : K - 1;
-    __shared__ double binD[WAVES][ROWP_COPIES][16], binN[WAVES][ROWP_COPIES][16];
-    __shared__ double csh[WAVES][16];
+    __shared__ double binD[BITS == 0 ? WAVES : 1][ROWP_COPIES][16], binN[BITS == 0 ? WAVES : 1][ROWP_COPIES][16];
+    __shared__ double csh[WAVES][16];             // centroids by label; BITS > 0: by position among the ascending bounds
     __shared__ __align__(16) float thr[WAVES][16];
     __shared__ int thl[WAVES][16];
     __shared__ int wexp[WAVES];
@@ -259,11 +258,6 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
     const float *Wr = W + row * ld, *Sr = S + row * ld;
     const uint8_t *Lr = BITS == 0 ? labels + row * m : nullptr;
     uint8_t *Lo = BITS > 0 && labels_out ? labels_out + row * m : nullptr;
-#pragma unroll
-    for (int q = 0; q < ROWP_COPIES / 4; ++q) {
-        (&binD[wave][0][0])[64 * q + lane] = 0.0;
-        (&binN[wave][0][0])[64 * q + lane] = 0.0;
-    }
     float ts[NSC > 0 ? NSC : 1];
     if constexpr (BITS > 0) {
         // bounds ascending (empty clusters, -inf, first; equal ones by cluster), +inf beyond the last
@@ -280,13 +274,14 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
             }
             thr[wave][rank] = up;
             thl[wave][rank] = lane;
+            if (lane < K) csh[wave][rank] = given[row * given_stride + lane];
         }
-        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_wave_barrier();      // (one wavefront's LDS accesses execute in order)
 #pragma unroll
         for (int k = 0; k < NSC; ++k)
             ts[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(thr[wave][BITS == 4 ? 4 * k + 3 : k])));
     }
-    auto label_of = [&](float wt) -> int {      // position = number of bounds below the weight
+    auto position_of = [&](float wt) -> int {      // number of bounds below the weight
         int pos = 0;
         if (BITS == 4) {
             int q = 0;
@@ -298,77 +293,46 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
 #pragma unroll
             for (int k = 0; k < NSC; ++k) pos += (ts[k] < wt) ? 1 : 0;
         }
-        return thl[wave][pos];
+        return pos;
     };
-    double *myD = binD[wave][lane & (ROWP_COPIES - 1)], *myN = binN[wave][lane & (ROWP_COPIES - 1)];
-    // two or four clusters: their sums in registers (in the bins most lanes of a wavefront would meet on the same few addresses)
-    constexpr int REGS = BITS == 1 || BITS == 2 ? K : 0;
-    double rd[REGS > 0 ? REGS : 1], rn[REGS > 0 ? REGS : 1];
+    const float4 ones = make_float4(1.f, 1.f, 1.f, 1.f);
+    const long long j0 = 4ll * (lane + 64 * sub);
+    float4 wk[KEEP > 0 ? KEEP : 1];
+    uint32_t lk[KEEP > 0 ? KEEP : 1];
+    if constexpr (BITS == 0) {
 #pragma unroll
-    for (int k = 0; k < REGS; ++k) rd[k] = rn[k] = 0.0;
-    // the four weights and labels of one step: sums; returns the labels
-    auto add_four = [&](const float4 &w4, const float4 &s4, const float4 &a4, uint32_t l4) -> uint32_t {
-        const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
-        uint32_t out = 0u;
+        for (int q = 0; q < ROWP_COPIES / 4; ++q) {
+            (&binD[wave][0][0])[64 * q + lane] = 0.0;
+            (&binN[wave][0][0])[64 * q + lane] = 0.0;
+        }
+        double *myD = binD[wave][lane & (ROWP_COPIES - 1)], *myN = binN[wave][lane & (ROWP_COPIES - 1)];
+        auto add_step = [&](int it, long long j) {
+            const float4 w4 = load4(Wr + j, vec4), s4 = load4(Sr + j, vec4);
+            const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
+            const uint32_t l4 = load4(Lr + j, vec4);
+            const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float wt = alpha ? __fdiv_rn(wv[e], av[e]) : wv[e];
-            const float st = alpha ? __fmul_rn(__fmul_rn(sv[e], av[e]), av[e]) : sv[e];
-            const int l = BITS == 0 ? (int)((l4 >> (8 * e)) & 15u) : label_of(wt);
-            out |= (uint32_t)l << (8 * e);
-            if constexpr (REGS > 0) {
-#pragma unroll
-                for (int k = 0; k < REGS; ++k) {
-                    const double sk = l == k ? (double)st : 0.0;
-                    rd[k] += sk;
-                    rn[k] = fma(sk, (double)wt, rn[k]);
-                }
-            } else {
+            for (int e = 0; e < 4; ++e) {
+                const float wt = alpha ? __fdiv_rn(wv[e], av[e]) : wv[e];
+                const float st = alpha ? __fmul_rn(__fmul_rn(sv[e], av[e]), av[e]) : sv[e];
+                const int l = (int)((l4 >> (8 * e)) & 15u);
                 atomicAdd(&myD[l], (double)st);
                 atomicAdd(&myN[l], (double)st * (double)wt);
             }
-        }
-        return out;
-    };
-    const float4 ones = make_float4(1.f, 1.f, 1.f, 1.f);
-    float4 wk[KEEP > 0 ? KEEP : 1];
-    uint32_t lk[KEEP > 0 ? KEEP : 1];
-    auto first_pass = [&](int it, long long j) {
-        const float4 w4 = load4(Wr + j, vec4), s4 = load4(Sr + j, vec4);
-        const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
-        const uint32_t l4 = add_four(w4, s4, a4, BITS == 0 ? load4(Lr + j, vec4) : 0u);
-        if (BITS > 0 && Lo) {
-            if (vec4) *(uint32_t *)(Lo + j) = l4;
-            else
-                for (int e = 0; e < 4; ++e) Lo[j + e] = (uint8_t)(l4 >> (8 * e));
-        }
-        if (KEEP > 0) {
-            wk[KEEP > 0 ? it : 0] = w4;
-            lk[KEEP > 0 ? it : 0] = l4;
-        }
-    };
-    const long long j0 = 4ll * (lane + 64 * sub);
-    if constexpr (KEEP > 0) {
+            if (KEEP > 0) {
+                wk[KEEP > 0 ? it : 0] = w4;
+                lk[KEEP > 0 ? it : 0] = l4;
+            }
+        };
+        if constexpr (KEEP > 0) {
 #pragma unroll
-        for (int it = 0; it < KEEP; ++it)
-            if (j0 + STEP * it < mm) first_pass(it, j0 + STEP * it);
-    } else {
+            for (int it = 0; it < KEEP; ++it)
+                if (j0 + STEP * it < mm) add_step(it, j0 + STEP * it);
+        } else {
 #pragma unroll 2
-        for (long long j = j0; j < mm; j += STEP) first_pass(0, j);
-    }
-#pragma unroll
-    for (int k = 0; k < REGS; ++k) {
-        for (int o = 32; o >= 1; o >>= 1) {
-            rd[k] += __shfl_xor(rd[k], o, 64);
-            rn[k] += __shfl_xor(rn[k], o, 64);
+            for (long long j = j0; j < mm; j += STEP) add_step(0, j);
         }
-        if (lane == 0) {
-            binD[wave][0][k] = rd[k];
-            binN[wave][0][k] = rn[k];
-        }
-    }
-    __syncthreads();
-    {
+        __syncthreads();
         // 16 clusters; four wavefronts a row: the bins of one of them in every 16 lanes
         double d = 0.0, nn = 0.0;
         const int bw = WPR == 4 ? (wave & ~3) + (lane >> 4) : wave;
@@ -384,14 +348,14 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
             nn += __shfl_xor(nn, 32, 64);
         }
         if (lane < 16) {
-            const double c = d > 0.0 ? nn / d : ((kept && lane < kept_n) ? kept[row * kept_stride + lane] : 0.0);
+            const double c = d > 0.0 ? nn / d : 0.0;
             csh[wave][lane] = c;
             if (sub == 0 && live) {
                 cent[row * 16 + lane] = c;
                 Den[row * 16 + lane] = d;
             }
         }
-        __builtin_amdgcn_wave_barrier();      // (one wavefront's LDS accesses execute in order)
+        __builtin_amdgcn_wave_barrier();
     }
     // four entries of dW and the exponents e_j of their columns (a byte each); the largest exponent of the row so far
     // and, for the loss, its diagonal share: the sum of dW_ij^2 H_jj in float64
@@ -427,30 +391,47 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
         for (int q = 0; q < 2; ++q)
             *(uint2 *)(o + 16 * q) = make_uint2(pc[q][0] | (pc[q][1] << 16), pc[q][2] | (pc[q][3] << 16));
     };
-    // (rows that do not stay in registers are formed twice more: for their largest entry, and to be written)
-    auto form_step = [&](float4 &w4, uint32_t &l4, long long j) {
+    // one step of the row from memory: labels (or positions, then the labels go out where they are wanted), dW, exponents
+    auto form_step = [&](float4 &w4, uint32_t &l4, long long j, bool out) {
         w4 = load4(Wr + j, vec4);
         const float4 a4 = alpha ? load4(alpha + j, vec4) : ones;
         if (BITS == 0) {
             l4 = load4(Lr + j, vec4);
         } else {
             const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, av[4] = {a4.x, a4.y, a4.z, a4.w};
+            int pos[4];
             l4 = 0u;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) l4 |= (uint32_t)label_of(alpha ? __fdiv_rn(wv[e], av[e]) : wv[e]) << (8 * e);
+            for (int e = 0; e < 4; ++e) {
+                pos[e] = position_of(alpha ? __fdiv_rn(wv[e], av[e]) : wv[e]);
+                l4 |= (uint32_t)pos[e] << (8 * e);
+            }
+            if (out && Lo) {
+                uint32_t lab = 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lab |= (uint32_t)thl[wave][pos[e]] << (8 * e);
+                if (vec4) *(uint32_t *)(Lo + j) = lab;
+                else
+                    for (int e = 0; e < 4; ++e) Lo[j + e] = (uint8_t)(lab >> (8 * e));
+            }
         }
         form_four(w4, a4, l4, j);
     };
+    // (rows that do not stay in registers are formed for their largest entry, and again to be written)
     if constexpr (KEEP > 0) {
 #pragma unroll
         for (int it = 0; it < KEEP; ++it)
-            if (j0 + STEP * it < mm) form_four(wk[it], alpha ? load4(alpha + j0 + STEP * it, vec4) : ones, lk[it], j0 + STEP * it);
+            if (j0 + STEP * it < mm) {
+                const long long j = j0 + STEP * it;
+                if (BITS == 0) form_four(wk[it], alpha ? load4(alpha + j, vec4) : ones, lk[it], j);
+                else form_step(wk[it], lk[it], j, true);
+            }
     } else {
 #pragma unroll 2
         for (long long j = j0; j < mm; j += STEP) {
             float4 w4;
             uint32_t l4;
-            form_step(w4, l4, j);
+            form_step(w4, l4, j, true);
         }
     }
 #pragma unroll
@@ -485,7 +466,7 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
         for (long long j = j0; j < mm; j += STEP) {
             float4 w4;
             uint32_t l4;
-            form_step(w4, l4, j);
+            form_step(w4, l4, j, false);
             write_four(w4, l4, D_SHIFT - top, j);
         }
     }
@@ -1134,15 +1115,14 @@ bool rows_vec4(const float *W, const float *S, const float *alpha, const uint8_t
 // split: what to cut H into as well (the caller launches it where it is still to be done on return)
 template <int BITS, bool DIAG>
 void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
-                          const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride,
-                          int kept_n, const float *H, bool &split, SplitMode mode) {
+                          const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const float *H, bool &split, SplitMode mode) {
     const bool vec4 = rows_vec4(W, S, alpha, BITS == 0 ? labels : bd.labels_out, ld);
     const long long groups = (n + ROWP_ROWS - 1) / ROWP_ROWS;
     auto launch = [&](auto keep, auto wpr, long long blocks) {
         constexpr int WPR = decltype(wpr)::value;
         hipLaunchKernelGGL((row_prep_kernel<BITS, decltype(keep)::value, WPR, DIAG>), dim3((unsigned)blocks), dim3(64 * ROWP_ROWS * WPR), 0, ctx->stream,
                            W, S, alpha, (long long)n, (long long)m, (long long)ld, labels, bd.upper, (long long)bd.upper_stride, bd.labels_out,
-                           w.cent, w.Den, w.dWp, kept, (long long)kept_stride, kept_n, vec4, H, (const uint32_t *)w.hmax, w.Hp, (int)mode, w.rexp,
+                           w.cent, w.Den, w.dWp, bd.centroids, (long long)bd.centroid_stride, vec4, H, (const uint32_t *)w.hmax, w.Hp, (int)mode, w.rexp,
                            (const float *)w.hdiag, w.rdiag);
     };
     using four = std::integral_constant<int, 4>;
@@ -1154,18 +1134,18 @@ void launch_row_prep_bits(skim_ctx *ctx, const float *W, const float *S, const f
     else launch(std::integral_constant<int, 0>{}, four{}, groups);
 }
 void launch_row_prep(skim_ctx *ctx, const float *W, const float *S, const float *alpha, int64_t n, int64_t m, int64_t ld,
-                     const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const double *kept, int64_t kept_stride, int kept_n,
-                     const float *H, bool split, SplitMode mode) {
+                     const uint8_t *labels, const skim_label_bounds &bd, const LossWs &w, const float *H, bool split,
+                     SplitMode mode) {
     if (split) launch_hmax(ctx, w, H, m);
     switch (bd.bits) {
         case 0:
-            if (mode == SPLIT_LOWER) launch_row_prep_bits<0, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode);
-            else launch_row_prep_bits<0, false>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode);
+            if (mode == SPLIT_LOWER) launch_row_prep_bits<0, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode);
+            else launch_row_prep_bits<0, false>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode);
             break;
-        case 1: launch_row_prep_bits<1, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        case 2: launch_row_prep_bits<2, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        case 3: launch_row_prep_bits<3, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
-        default: launch_row_prep_bits<4, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, kept, kept_stride, kept_n, H, split, mode); break;
+        case 1: launch_row_prep_bits<1, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode); break;
+        case 2: launch_row_prep_bits<2, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode); break;
+        case 3: launch_row_prep_bits<3, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode); break;
+        default: launch_row_prep_bits<4, true>(ctx, W, S, alpha, n, m, ld, labels, bd, w, H, split, mode); break;
     }
     if (split) launch_split(ctx, w, H, m, mode);
 }
@@ -1195,13 +1175,12 @@ extern "C" skim_status skim_layer_loss(skim_ctx *ctx, const float *W, const floa
                                        const float *H, int64_t n, int64_t m, int64_t ld, const uint8_t *labels,
                                        double *loss, double *row_loss) {
     if (ctx && !loss) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
-    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss, row_loss, 1, nullptr, 0, 0, false);
+    return skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss, row_loss, 1, false);
 }
 
 skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *S, const float *alpha, const float *H,
                                     int64_t n, int64_t m, int64_t ld, const uint8_t *labels, const skim_label_bounds &bounds, double *loss,
-                                    double *row_loss, int64_t row_stride, const double *kept, int64_t kept_stride,
-                                    int kept_n, bool h_ready) {
+                                    double *row_loss, int64_t row_stride, bool h_ready) {
     skim_status st = skim_enter(ctx);
     if (st != SKIM_OK) return st;
     if (!W || !S || !H || (!labels && !bounds.upper)) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_layer_loss: NULL argument");
@@ -1210,7 +1189,7 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, kept, kept_stride, kept_n, H, !h_ready, SPLIT_LOWER);
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, H, !h_ready, SPLIT_LOWER);
     hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (const int *)w.rexp,
                        (long long)n, (long long)m, w.line, w.partial);
     hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
@@ -1247,7 +1226,7 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     LossWs w;
     if ((st = carve(ctx, n, m, true, w)) != SKIM_OK) return st;
     if ((st = enable_lds(ctx)) != SKIM_OK) return st;
-    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, nullptr, 0, 0, H, !h_ready, step_split(m));
+    launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, skim_label_bounds{}, w, H, !h_ready, step_split(m));
     {
         long long grid = 0;
         for (int p = 0; p < w.plan.nph; ++p) grid = max(grid, (long long)w.plan.ntile[p] * w.plan.split[p]);
@@ -1320,7 +1299,7 @@ extern "C" skim_status skim_train_scale(skim_ctx *ctx, const float *W, const flo
     LossWs w;
     if ((st = carve(ctx, n, m, false, w)) != SKIM_OK) return st;
     // (the loss takes other pieces of H than the steps)
-    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss_trace + slot, nullptr, 1, nullptr, 0, 0, false)) !=
+    if ((st = skim_layer_loss_strided(ctx, W, S, alpha, H, n, m, ld, labels, skim_label_bounds{}, loss_trace + slot, nullptr, 1, false)) !=
         SKIM_OK)
         return st;
     SKIM_HIP(ctx, hipMemcpyAsync(centroids, w.cent, (size_t)n * 16 * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
