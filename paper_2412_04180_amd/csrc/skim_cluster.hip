@@ -22,7 +22,7 @@
 // Arithmetic on every decision path is float64 and uses the same predicates as the
 // definition: |w - c_lo| versus |w - c_hi| with the lower cluster index winning equal
 // distances; centroids with no weight mass keep their value.
-#include "skim_common.h"
+#include "skim_tiles.h"
 
 #include <math.h>
 
@@ -1331,6 +1331,7 @@ struct LevelMap {
     int w16_off, ppd_off, ppn_off, bytes;   // first weights; running sums of s and of s*w (np + 1 double2 each)
     int np;          // groups the running sums are kept for: n[1] groups of 4 chunks, or (wide) n[2] groups of 16
     int n2, t1_off, t2_off;                 // search tree over the first weights: every 8th, every 64th (n2 of them)
+    int t3_off, keys_off;                   // rows kept in LDS: every 512th first weight (0: none), the sorted keys
 };
 __host__ __device__ inline LevelMap level_map(int n1u, bool wide) {
     LevelMap L;
@@ -1355,6 +1356,7 @@ __host__ __device__ inline LevelMap level_map(int n1u, bool wide) {
     o += (L.np + 1) * 16;
     L.ppn_off = o;
     o += (L.np + 1) * 16;
+    L.t3_off = L.keys_off = 0;
     L.roff[0] = 0;
     L.roff[1] = 0;
     for (int k = 2; k < 8; ++k) {
@@ -1364,6 +1366,34 @@ __host__ __device__ inline LevelMap level_map(int n1u, bool wide) {
     L.bytes = o;
     return L;
 }
+// A row of m keys kept in LDS as a whole, in pieces of G keys: their first weights (under w16_off) with the tree over them, the keys
+// themselves and the running sums ahead of every piece (np pieces).
+__host__ __device__ inline LevelMap level_map_resident(int m, int G) {
+    LevelMap L = level_map((m + 15) >> 4, false);
+    L.np = (m + G - 1) / G;
+    L.n2 = (L.np + 63) >> 6;
+    const int n3 = (L.n2 + 7) >> 3;
+    int o = ((L.np + 7) & ~7) * 4;
+    L.t1_off = o;
+    o += L.n2 * 32;
+    L.t2_off = o;
+    o += n3 * 32;
+    L.t3_off = n3 > 1 ? o : 0;
+    if (n3 > 1) o += 32;
+    L.ppd_off = o = (o + 15) & ~15;
+    o += (L.np + 1) * 16;
+    L.ppn_off = o;
+    o += (L.np + 1) * 16;
+    for (int k = 2; k < 8; ++k) {
+        L.roff[k] = o;
+        o += ((L.n[k] * 8) + 15) & ~15;
+    }
+    L.keys_off = o;
+    o += (m * 8 + 1023) & ~1023;            // (copied in kilobytes)
+    L.bytes = o;
+    return L;
+}
+constexpr int RESIDENT_MAX_PIECES = 4096;      // the tree's top node has 8 entries
 
 // Double-double arithmetic on (hi, lo) pairs held in a double2 (x = hi, y = lo).
 __device__ __forceinline__ double2 dd_add(double2 a, double2 b) {
@@ -1407,6 +1437,7 @@ __device__ __forceinline__ double2 dd_wave_scan_incl(double2 x) {
 }
 
 constexpr int ITER_THREADS = 64;   // one wavefront serves two rows
+constexpr int RESIDENT_THREADS = 128;      // ... of which each has a wavefront while rows kept in LDS are laid out
 constexpr int MAX_LEVELS = 8;
 
 // One lane per cluster.  A row takes 30 lanes of a half wavefront: bit width 1 on lanes 0-1, 2 on
@@ -1431,18 +1462,41 @@ __device__ __forceinline__ double quick_div(double n, double d) {
     return fma(fma(-d, q, n), r, q);
 }
 
+// How many keys of a sorted run lie below a threshold, without a compare: the sign bits of the differences are shifted into a word
+// (a key's bit and one instruction each; a compare with a carry-in addition behind it waits for the mask in between).  u is finite; the
+// weights are finite or +inf, which counts as above.
+__device__ __forceinline__ uint32_t shift_sign_in(uint32_t word, float x) {
+    return __builtin_amdgcn_alignbit(word, __float_as_uint(x), 31);
+}
+__device__ __forceinline__ int count_below(const float4 &x, const float4 &y, float u) {
+    uint32_t a = 0u, b = 0u;
+    a = shift_sign_in(a, __fsub_rn(x.x, u));
+    b = shift_sign_in(b, __fsub_rn(y.x, u));
+    a = shift_sign_in(a, __fsub_rn(x.y, u));
+    b = shift_sign_in(b, __fsub_rn(y.y, u));
+    a = shift_sign_in(a, __fsub_rn(x.z, u));
+    b = shift_sign_in(b, __fsub_rn(y.z, u));
+    a = shift_sign_in(a, __fsub_rn(x.w, u));
+    b = shift_sign_in(b, __fsub_rn(y.w, u));
+    return __builtin_popcount(a) + __builtin_popcount(b);
+}
+
 // RAGGED: the row length is not a multiple of 16, so the last chunk holds fewer than 16 keys.
 // WIDE: the running sums are kept ahead of every 16 chunks instead of every 4, and a range takes up to 3 + 3 sums of
 // 4 chunks more from global memory, requested with the chunk sums.  The LDS of a long row is mostly running sums: at 22016
 // keys per row 4 workgroups fitted a compute unit and the kernel waited on latency with one wavefront per SIMD; now 8
 // fit (8192 x 22016: 456 -> 379 us).  Rows of which 8 workgroups fit anyway do without the extra loads.
-template <bool RAGGED, bool WIDE>
-__global__ void __launch_bounds__(ITER_THREADS) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 3, WIDE ? 2 : 3)))
+// G > 0: the rows are kept in LDS as a whole, keys and running sums ahead of every G of them: no trip to memory inside the iterations, no
+// chunk sums, and only G keys to add up at a boundary (none with G = 1: a cluster is the difference of two running sums).  For matrices
+// of which the LDS holds enough rows at a time: see launch_cluster.
+template <bool RAGGED, bool WIDE, int G>
+__global__ void __launch_bounds__(G > 0 ? RESIDENT_THREADS : ITER_THREADS) __attribute__((amdgpu_waves_per_eu(G > 0 ? 4 : WIDE ? 2 : 3, G > 0 ? 4 : WIDE ? 2 : 3)))
 lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int m = prm.m;
-    const int n1u = (m + 15) >> 4;   // LM = level_map(n1u, WIDE), worked out by the host
-    const int lane = threadIdx.x;
+    constexpr int CH = G > 0 ? G : 16;      // keys of a piece
+    const int n1u = (m + CH - 1) / CH;      // LM = level_map(n1u, WIDE) or level_map_resident(m, G), worked out by the host
+    const int lane = threadIdx.x & 63, mine = G > 0 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int h = lane >> 5, l5 = lane & 31;
 
     // ---- prologue: both rows' first weights, running sums and second-moment levels into LDS -------
@@ -1457,19 +1511,28 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     double rq4[2][4];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
+        if (G > 0 && hh != mine) continue;
         const long long rr = 2ll * blockIdx.x + (hh < nhalf ? hh : 0);
-        const double2 *gq = prm.Q + rr * prm.nq;
-        const float *gw = prm.w16 + rr * prm.n1;
         const double *grq = prm.RQ + rr * prm.nq;
+        if constexpr (G == 0) {
+            const double2 *gq = prm.Q + rr * prm.nq;
+            const float *gw = prm.w16 + rr * prm.n1;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = lane * per + k;
-            qv[hh][k] = (k < per && q < ng) ? gq[q] : make_double2(0.0, 0.0);
-        }
+            for (int k = 0; k < 8; ++k) {
+                const int q = lane * per + k;
+                qv[hh][k] = (k < per && q < ng) ? gq[q] : make_double2(0.0, 0.0);
+            }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int j = u * ITER_THREADS + lane;
-            t8[hh][u] = (j < n1u) ? gw[j] : 0.0f;
+            for (int u = 0; u < 8; ++u) {
+                const int j = u * ITER_THREADS + lane;
+                t8[hh][u] = (j < n1u) ? gw[j] : 0.0f;
+            }
+        } else if (hh < nhalf) {
+            // the row's keys straight into LDS (8 bytes past an odd row's end are read with it, and replaced below)
+            const LdsSource src{(uint64_t)(uintptr_t)(prm.keys + rr * (long long)m), (8ll * m + 15) & ~15ll};
+            const int4v rs = src.rsrc();
+            const uint32_t dst = (uint32_t)(uintptr_t)(lds_byte *)smem + (uint32_t)(hh * LM.bytes + LM.keys_off);
+            for (int k = 0; k < 8 * m; k += 1024) copy_to_lds((uint32_t)__builtin_amdgcn_readfirstlane((int)(dst + k)), (uint32_t)(k + 16 * lane), rs);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) rq4[hh][k] = (LM.nlev > 2 && 4 * lane + k < ng) ? grq[4 * lane + k] : 0.0;
@@ -1477,70 +1540,73 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
         if (hh >= nhalf) break;
+        if (G > 0 && hh != mine) continue;
         const long long rr = 2ll * blockIdx.x + hh;
         unsigned char *blkw = smem + (size_t)hh * LM.bytes;
-        float *w16w = (float *)(blkw + LM.w16_off), *t1w = (float *)(blkw + LM.t1_off), *t2w = (float *)(blkw + LM.t2_off);
-        const float *gw = prm.w16 + rr * prm.n1;
-        // (the weights and both levels of the tree over them are filled up with +inf, which counts as above everything)
-        auto put_w16 = [&](int j, float w) {
-            const float x = j < n1u ? w : INFINITY;
-            if (j < ((n1u + 7) & ~7)) w16w[j] = x;
-            if ((j & 7) == 0 && j < 64 * LM.n2) t1w[j >> 3] = x;
-            if ((j & 63) == 0 && j < 64 * ((LM.n2 + 3) & ~3)) t2w[j >> 6] = x;
-        };
+        if constexpr (G == 0) {
+            float *w16w = (float *)(blkw + LM.w16_off), *t1w = (float *)(blkw + LM.t1_off), *t2w = (float *)(blkw + LM.t2_off);
+            const float *gw = prm.w16 + rr * prm.n1;
+            // (the weights and both levels of the tree over them are filled up with +inf, which counts as above everything)
+            auto put_w16 = [&](int j, float w) {
+                const float x = j < n1u ? w : INFINITY;
+                if (j < ((n1u + 7) & ~7)) w16w[j] = x;
+                if ((j & 7) == 0 && j < 64 * LM.n2) t1w[j >> 3] = x;
+                if ((j & 63) == 0 && j < 64 * ((LM.n2 + 3) & ~3)) t2w[j >> 6] = x;
+            };
 #pragma unroll
-        for (int u = 0; u < 8; ++u) put_w16(u * ITER_THREADS + lane, t8[hh][u]);
-        for (int j0 = 8 * ITER_THREADS; j0 < n1u; j0 += 8 * ITER_THREADS) {
-            float t[8];
+            for (int u = 0; u < 8; ++u) put_w16(u * ITER_THREADS + lane, t8[hh][u]);
+            for (int j0 = 8 * ITER_THREADS; j0 < n1u; j0 += 8 * ITER_THREADS) {
+                float t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = j0 + u * ITER_THREADS + lane;
-                t[u] = (j < n1u) ? gw[j] : 0.0f;
+                for (int u = 0; u < 8; ++u) {
+                    const int j = j0 + u * ITER_THREADS + lane;
+                    t[u] = (j < n1u) ? gw[j] : 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) put_w16(j0 + u * ITER_THREADS + lane, t[u]);
             }
+            // running sums ahead of every group of 4 (WIDE: 16) chunks, pp[np] = row total.  A lane takes `per` consecutive
+            // groups; one double-double scan over the lanes per quantity.
+            {
+                double2 *ppd = (double2 *)(blkw + LM.ppd_off), *ppn = (double2 *)(blkw + LM.ppn_off);
+                auto scan = [&](auto cnt) {
+                    constexpr int N = decltype(cnt)::value;
+                    double2 md = make_double2(0.0, 0.0), mn = make_double2(0.0, 0.0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) put_w16(j0 + u * ITER_THREADS + lane, t[u]);
-        }
-        // running sums ahead of every group of 4 (WIDE: 16) chunks, pp[np] = row total.  A lane takes `per` consecutive
-        // groups; one double-double scan over the lanes per quantity.
-        {
-            double2 *ppd = (double2 *)(blkw + LM.ppd_off), *ppn = (double2 *)(blkw + LM.ppn_off);
-            auto scan = [&](auto cnt) {
-                constexpr int N = decltype(cnt)::value;
-                double2 md = make_double2(0.0, 0.0), mn = make_double2(0.0, 0.0);
+                    for (int k = 0; k < N; ++k) {
+                        md = dd_add(md, make_double2(qv[hh][k].x, 0.0));
+                        mn = dd_add(mn, make_double2(qv[hh][k].y, 0.0));
+                    }
+                    const double2 id = dd_wave_scan_incl(md), in = dd_wave_scan_incl(mn);
+                    // sums of the lanes below: the inclusive sums shifted up by one lane
+                    double2 rd = make_double2(lane_below(id.x), lane_below(id.y));
+                    double2 rn = make_double2(lane_below(in.x), lane_below(in.y));
+                    if (lane == 0) {
+                        rd = make_double2(0.0, 0.0);
+                        rn = make_double2(0.0, 0.0);
+                    }
 #pragma unroll
-                for (int k = 0; k < N; ++k) {
-                    md = dd_add(md, make_double2(qv[hh][k].x, 0.0));
-                    mn = dd_add(mn, make_double2(qv[hh][k].y, 0.0));
-                }
-                const double2 id = dd_wave_scan_incl(md), in = dd_wave_scan_incl(mn);
-                // sums of the lanes below: the inclusive sums shifted up by one lane
-                double2 rd = make_double2(lane_below(id.x), lane_below(id.y));
-                double2 rn = make_double2(lane_below(in.x), lane_below(in.y));
-                if (lane == 0) {
-                    rd = make_double2(0.0, 0.0);
-                    rn = make_double2(0.0, 0.0);
-                }
-#pragma unroll
-                for (int k = 0; k < N; ++k) {
-                    const int q = lane * per + k;
-                    if (k < per && q < ng) {
-                        if (!WIDE || (k & 3) == 0) {
-                            ppd[WIDE ? q >> 2 : q] = rd;
-                            ppn[WIDE ? q >> 2 : q] = rn;
-                        }
-                        rd = dd_add(rd, make_double2(qv[hh][k].x, 0.0));
-                        rn = dd_add(rn, make_double2(qv[hh][k].y, 0.0));
-                        if (q == ng - 1) {
-                            ppd[LM.np] = rd;
-                            ppn[LM.np] = rn;
+                    for (int k = 0; k < N; ++k) {
+                        const int q = lane * per + k;
+                        if (k < per && q < ng) {
+                            if (!WIDE || (k & 3) == 0) {
+                                ppd[WIDE ? q >> 2 : q] = rd;
+                                ppn[WIDE ? q >> 2 : q] = rn;
+                            }
+                            rd = dd_add(rd, make_double2(qv[hh][k].x, 0.0));
+                            rn = dd_add(rn, make_double2(qv[hh][k].y, 0.0));
+                            if (q == ng - 1) {
+                                ppd[LM.np] = rd;
+                                ppn[LM.np] = rn;
+                            }
                         }
                     }
-                }
-            };
-            if (WIDE && per == 4) scan(std::integral_constant<int, 4>{});
-            else if (!WIDE && per == 1) scan(std::integral_constant<int, 1>{});
-            else if (!WIDE && per <= 3) scan(std::integral_constant<int, 3>{});
-            else scan(std::integral_constant<int, 8>{});
+                };
+                if (WIDE && per == 4) scan(std::integral_constant<int, 4>{});
+                else if (!WIDE && per == 1) scan(std::integral_constant<int, 1>{});
+                else if (!WIDE && per <= 3) scan(std::integral_constant<int, 3>{});
+                else scan(std::integral_constant<int, 8>{});
+            }
         }
         // second moments: level 2 from the groups' sums in global memory
         if (LM.nlev > 2) {
@@ -1556,11 +1622,78 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             }
         }
     }
+    if constexpr (G > 0) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // the copies above
+        if (mine < nhalf) {
+            const int np = LM.np;
+            unsigned char *blkw = smem + (size_t)mine * LM.bytes;
+            u64 *kw = (u64 *)(blkw + LM.keys_off);
+            double2 *ppdw = (double2 *)(blkw + LM.ppd_off), *ppnw = (double2 *)(blkw + LM.ppn_off);
+            // the last piece is filled up with keys above every threshold, without mass
+            if (lane < np * G - m) kw[m + lane] = (u64)0x7F7FFFFFu << 32;
+            __builtin_amdgcn_wave_barrier();     // (a wavefront's LDS accesses execute in order)
+            // Running sums ahead of every piece, pp[np] = row total: a lane takes `each` consecutive pieces (an odd number: the
+            // lanes' LDS addresses then spread over the banks), one double-double scan over the lanes per quantity.  A piece's
+            // own sums wait in its place of ppd.
+            const int each = ((np + 63) / 64) | 1, c0 = lane * each;
+            double2 rd = make_double2(0.0, 0.0), rn = rd;
+            for (int k = 0; k < each; ++k) {
+                const int c = c0 + k;
+                const u64x2 *kp = (const u64x2 *)(kw + (size_t)min(c, np - 1) * G);
+                double d = 0.0, nn = 0.0;
+#pragma unroll
+                for (int j = 0; j < G / 2; ++j) {          // (lanes whose pieces start in the same banks begin at different keys)
+                    const u64x2 e2 = kp[(j + lane / (32 / G)) & (G / 2 - 1)];
+                    const double s0 = (double)plain_s(e2.x), s1 = (double)plain_s(e2.y);
+                    d += s0;
+                    nn = fma(s0, (double)elem_w(e2.x), nn);
+                    d += s1;
+                    nn = fma(s1, (double)elem_w(e2.y), nn);
+                }
+                if (c < np) {
+                    ppdw[c] = make_double2(d, nn);
+                    rd = dd_add(rd, make_double2(d, 0.0));
+                    rn = dd_add(rn, make_double2(nn, 0.0));
+                }
+            }
+            const double2 id = dd_wave_scan_incl(rd), in = dd_wave_scan_incl(rn);
+            // sums of the lanes below: the inclusive sums shifted up by one lane
+            rd = make_double2(lane_below(id.x), lane_below(id.y));
+            rn = make_double2(lane_below(in.x), lane_below(in.y));
+            if (lane == 0) rd = rn = make_double2(0.0, 0.0);
+            for (int k = 0; k < each; ++k) {
+                const int c = c0 + k;
+                if (c < np) {
+                    const double2 x = ppdw[c];
+                    ppdw[c] = rd;
+                    ppnw[c] = rn;
+                    rd = dd_add(rd, make_double2(x.x, 0.0));
+                    rn = dd_add(rn, make_double2(x.y, 0.0));
+                    if (c == np - 1) {
+                        ppdw[np] = rd;
+                        ppnw[np] = rn;
+                    }
+                }
+            }
+            // the first weights and the tree over them, filled up with +inf
+            const float *wts = (const float *)kw + 1;        // (the weight is a key's upper word)
+            auto fill = [&](int off, int count, int step) {
+                float *t = (float *)(blkw + off);
+#pragma unroll 4
+                for (int i = lane; i < count; i += 64) t[i] = i * step < np ? wts[2 * min(i * step, np - 1) * G] : INFINITY;
+            };
+            fill(LM.w16_off, (np + 7) & ~7, 1);
+            fill(LM.t1_off, 8 * LM.n2, 8);
+            fill(LM.t2_off, 8 * ((LM.n2 + 7) >> 3), 64);
+            if (LM.t3_off) fill(LM.t3_off, 8, 512);
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int lv = 3; lv < MAX_LEVELS; ++lv) {
         if (lv < LM.nlev) {
             for (int hh = 0; hh < nhalf; ++hh) {
+                if (G > 0 && hh != mine) continue;
                 unsigned char *blkw = smem + (size_t)hh * LM.bytes;
                 const double *rsrc = (const double *)(blkw + LM.roff[lv - 1]);
                 double *rdst = (double *)(blkw + LM.roff[lv]);
@@ -1575,6 +1708,8 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             __syncthreads();
         }
     }
+
+    if (G > 0 && mine > 0) return;       // one wavefront for the rest: no barrier follows
 
     // ---- lane -> (row, bit width, position) ------------------------------------------------------
     const long long row = 2ll * blockIdx.x + h;
@@ -1597,6 +1732,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     const float *w16 = (const float *)(blk + LM.w16_off);
     const double2 *ppd = (const double2 *)(blk + LM.ppd_off), *ppn = (const double2 *)(blk + LM.ppn_off);
     const u64 *__restrict__ keys = prm.keys + rowc * (long long)m;
+    const u64 *lkeys = (const u64 *)(blk + LM.keys_off);       // G > 0
     const double2 *__restrict__ L1 = prm.L1 + rowc * prm.n1;
     const double2 *__restrict__ Q = prm.Q + rowc * prm.nq;
 
@@ -1636,11 +1772,26 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 }
             }
         }
-        int chunk = 4 * lo;
-        u64 el[16];
+        int chunk = G > 0 ? lo : 4 * lo;
+        u64 el[CH];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) el[j] = NEUTRAL_KEY;
-        if (on) {
+        for (int j = 0; j < CH; ++j) el[j] = NEUTRAL_KEY;
+        if (G > 0 && on) {
+            const int r0 = chunk * CH;
+            int found = min(r0 + CH - 1, m - 1);
+            bool hit = false;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                el[j] = lkeys[r0 + j];
+                acc += (double)plain_s(el[j]);
+                if (!hit && r0 + j < m && acc >= tau) {
+                    found = r0 + j;
+                    hit = true;
+                }
+            }
+            r = found;
+        }
+        if constexpr (G == 0) if (on) {
             double dch[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) dch[k] = (chunk + k + 1 < n1u) ? L1[chunk + k].x : 0.0;
@@ -1677,21 +1828,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             }
             r = found;
         }
-        int prev = -1;
-        for (int k = 0; k < 16; ++k) {
-            int rk = __shfl(r, from_pos(k), 64);
-            if (k < K) {
-                rk = max(rk, prev + 1);
-                rk = min(rk, m - K + k);
-                if (p == k) r = rk;
-                prev = rk;
-            }
+        // r_k = min(max(raw_k, r_(k-1) + 1), m - K + k): r_k - k is the running maximum of raw_k - k, held below m - K
+        r -= p;
+#pragma unroll
+        for (int d = 1; d < 16; d <<= 1) {
+            const int below = __shfl_up(r, d, 64);
+            if (p >= d) r = max(r, below);
         }
+        r = min(r, m - K) + p;
         if (on) {
             // the repair seldom moves a rank out of the 16 keys already in registers
-            const int off = r - chunk * 16;
+            const int off = r - chunk * CH;
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
+            for (int j = 0; j < CH; ++j)
                 if (off == j) { wstart = elem_w(el[j]); wstart_ok = true; }
         }
     }
@@ -1709,13 +1858,20 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 
     // the boundary chunk of the previous iteration stays in registers: late iterations move a boundary by a few
     // ranks, inside the same 16 keys, and then the lane asks the memory system for nothing
-    u64 el[16];
+    u64 el[CH];
     int cl_held = -2;
     // so do the sums over the whole chunks between the boundary chunks [a0_held, b0_held)
     int a0_held = 0, b0_held = 0;
     double midD = 0.0, midN = 0.0;
     const float4 *w16q = (const float4 *)w16, *t1q = (const float4 *)(blk + LM.t1_off), *t2q = (const float4 *)(blk + LM.t2_off);
     const int n2q = (LM.n2 + 3) >> 2;
+    // G > 0: the top node of the tree stays in registers
+    float4 top0 = make_float4(0.f, 0.f, 0.f, 0.f), top1 = top0;
+    if constexpr (G > 0) {
+        const float4 *tq = (const float4 *)(blk + (LM.t3_off ? LM.t3_off : LM.t2_off));
+        top0 = tq[0];
+        top1 = tq[1];
+    }
     for (int it = 0; it < prm.iters; ++it) {
         if (__ballot(!done) == 0) break;
         const bool live = !done;     // this lane's bit width still iterates
@@ -1785,25 +1941,29 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         const double mid = 0.5 * (vlo + v);
         const float t = __fadd_rn((float)mid, 0.0f);
         const int tb = __float_as_int(t);
-        const float u = nearer_lo(t) ? __int_as_float(tb >= 0 ? tb + 1 : tb - 1) : t;
-        const bool hard = searching && !(fabs(mid) > 0x1p-24 * fmax(fabs(v), fabs(vlo)) && v - vlo > 0x1p-30 * wabs);
+        float u = nearer_lo(t) ? __int_as_float(tb >= 0 ? tb + 1 : tb - 1) : t;
+        const bool finite = fabsf(u) < INFINITY;
+        const bool hard = searching && !(fabs(mid) > 0x1p-24 * fmax(fabs(v), fabs(vlo)) && v - vlo > 0x1p-30 * wabs && finite);
         const bool anyhard = __ballot(hard) != 0;
+        if (!finite) u = 0.0f;       // (the searches below rely on it)
 
         // ---- chunk of the boundary: lo = number of chunks whose first key is nearer to the lower centroid (a prefix of
         // the chunks): three levels of a search tree, 8 first weights per node (one trip to the LDS each)
         int lo = 0;
         {
-            int c2 = 0;
-            for (int q = 0; q < n2q; ++q) {
-                const float4 x = t2q[q];
-                c2 += (x.x < u ? 1 : 0) + (x.y < u ? 1 : 0) + (x.z < u ? 1 : 0) + (x.w < u ? 1 : 0);
+            auto node = [&](const float4 *p) -> int { return count_below(p[0], p[1], u); };
+            int b1;
+            if constexpr (G > 0) {
+                b1 = max(count_below(top0, top1, u) - 1, 0);
+                if (LM.t3_off) b1 = 8 * b1 + max(node(t2q + 2 * b1) - 1, 0);
+            } else {
+                int c2 = 0;
+                for (int q = 0; q < n2q; ++q) {
+                    const float4 x = t2q[q];
+                    c2 += (x.x < u ? 1 : 0) + (x.y < u ? 1 : 0) + (x.z < u ? 1 : 0) + (x.w < u ? 1 : 0);
+                }
+                b1 = max(c2 - 1, 0);
             }
-            const int b1 = max(c2 - 1, 0);
-            auto node = [&](const float4 *p) -> int {
-                const float4 x = p[0], y = p[1];
-                return (x.x < u ? 1 : 0) + (x.y < u ? 1 : 0) + (x.z < u ? 1 : 0) + (x.w < u ? 1 : 0) + (y.x < u ? 1 : 0) +
-                       (y.y < u ? 1 : 0) + (y.z < u ? 1 : 0) + (y.w < u ? 1 : 0);
-            };
             const int b0 = 8 * b1 + max(node(t1q + 2 * b1) - 1, 0);
             lo = 8 * b0 + node(w16q + 2 * b0);
         }
@@ -1837,13 +1997,22 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 
         // ---- one round of global loads: the boundary chunk's keys and the level-0 pieces ----------
         // (lanes without a boundary chunk read the row's first chunk and ignore it)
-        const int rbase = cl * 16;
+        const int rbase = cl * CH;
         const int cl_want = cl >= 0 ? cl : 0;
-        const bool reload = cl_want != cl_held;
-        if (reload) {
-            const u64x2_a8 *kv = (const u64x2_a8 *)(keys + cl_want * 16);
+        bool reload = false;
+        if constexpr (G > 0) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < CH; ++j) el[j] = lkeys[cl_want * CH + j];
+            const double2 da = ppd[a0], db = ppd[b0], na = ppn[a0], nb = ppn[b0];
+            midD = dd_diff(db, da);
+            midN = dd_diff(nb, na);
+        } else {
+            reload = cl_want != cl_held;
+        }
+        if (reload) {
+            const u64x2_a8 *kv = (const u64x2_a8 *)(keys + cl_want * CH);
+#pragma unroll
+            for (int j = 0; j < CH / 2; ++j) {
                 const u64x2 t2 = kv[j];
                 el[2 * j] = t2.x;
                 el[2 * j + 1] = t2.y;
@@ -1852,8 +2021,8 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         }
         // the whole chunks in between: up to 3 + 3 chunk sums (requested with the keys), the whole groups of 4 chunks as the
         // difference of the running sums in LDS
-        const bool resum = summing && (a0 != a0_held || b0 != b0_held);
-        if (__ballot(resum) != 0) {
+        const bool resum = G == 0 && summing && (a0 != a0_held || b0 != b0_held);
+        if (G == 0 && __ballot(resum) != 0) {
             const int la0 = min(b0, (a0 + 3) & ~3), rb0 = max(la0, b0 & ~3);
             double2 pc[6];
 #pragma unroll
@@ -1895,20 +2064,34 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         }
 
         // rank inside the chunk
-        const int nvalid = RAGGED ? m - rbase : 16;
+        const int nvalid = RAGGED || G > 0 ? m - rbase : CH;
         if (RAGGED && reload) {     // keys past the end of the row are not this row's: above every threshold, without mass
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j >= m - cl_want * 16) el[j] = (u64)0x7F7FFFFFu << 32;
+            for (int j = 0; j < CH; ++j)
+                if (j >= m - cl_want * CH) el[j] = (u64)0x7F7FFFFFu << 32;
         }
-        int tc = 0;
+        uint32_t lowbits = 0u;           // bit j: key j is below the boundary
+        if constexpr (CH >= 8) {         // (two chains)
+            uint32_t upper8 = 0u;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) tc += elem_w(el[j]) < u ? 1 : 0;
+            for (int j = CH / 2 - 1; j >= 0; --j) {
+                upper8 = shift_sign_in(upper8, __fsub_rn(elem_w(el[CH / 2 + j]), u));
+                lowbits = shift_sign_in(lowbits, __fsub_rn(elem_w(el[j]), u));
+            }
+            lowbits |= upper8 << (CH / 2);
+        } else {
+#pragma unroll
+            for (int j = CH - 1; j >= 0; --j) lowbits = shift_sign_in(lowbits, __fsub_rn(elem_w(el[j]), u));
+        }
+        int tc = __builtin_popcount(lowbits);
         if (__builtin_expect(anyhard, 0)) {
             int te = 0;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) te += (j < nvalid && nearer_lo(elem_w(el[j]))) ? 1 : 0;
-            if (hard) tc = te;
+            for (int j = 0; j < CH; ++j) te += (j < nvalid && nearer_lo(elem_w(el[j]))) ? 1 : 0;
+            if (hard) {
+                tc = te;
+                lowbits = (1u << te) - 1u;
+            }
         }
         if (cl < 0) tc = 0;
         Bcur = (searching && cl >= 0) ? rbase + tc : 0;  // p == 0 or no chunk below the boundary: 0
@@ -1931,21 +2114,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             idxold = idx;
         }
 
-        // own chunk: its first tl keys (below the boundary) go to the cluster below, the keys from
+        // own chunk: its first keys (lowbits, below the boundary) go to the cluster below, the keys from
         // there up to th (the next boundary, if it falls into this chunk) are this cluster's
         const bool own = searching && cl >= 0;
-        const int tl = own ? tc : 0;
-        const int th = own ? min(16, Bnext - rbase) : 0;
+        if (!own) lowbits = 0u;
+        const int th = own ? min(CH, Bnext - rbase) : 0;
+        const uint32_t ownbits = ((1u << th) - 1u) & ~lowbits;
         double lowD = 0.0, lowN = 0.0, D = 0.0, N = 0.0;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float sf = plain_s(el[j]);
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t sbits = (uint32_t)el[j];
             const double wd = (double)elem_w(el[j]);
-            // tl <= th: the keys below th minus those below tl are the cluster's own (the difference is s or 0, exactly)
-            const float sl = (j < tl) ? sf : 0.0f;
-            const float su = (j < th) ? sf : 0.0f;
-            const float sh = __fsub_rn(su, sl);
-            const double sld = (double)sl, shd = (double)sh;
+            const double sld = (double)__uint_as_float(sbits & (uint32_t)__builtin_amdgcn_sbfe((int)lowbits, j, 1));
+            const double shd = (double)__uint_as_float(sbits & (uint32_t)__builtin_amdgcn_sbfe((int)ownbits, j, 1));
             lowD += sld;
             lowN = fma(sld, wd, lowN);     // s * w of two floats is exact
             D += shd;
@@ -1977,6 +2158,9 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     // range [Bold_p, Bold_{p+1}); D, N are the sums the last iteration formed for the same range.  R comes
     // from the keys of the two partial chunks and the aligned pieces of the second-moment tree.
     double Ep = 0.0, Rp = 0.0;
+    int range_end = lane_above(Bold);      // the cluster's keys are [Bold, range_end)
+    if (p == K - 1) range_end = m;
+    u64 last_key = 0;
     {
         const int a = on ? max(Bold, 0) : 0;
         int bnd = lane_above(Bold);
@@ -1986,6 +2170,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         const u64x2_a8 *ka = (const u64x2_a8 *)(keys + (a & ~15));        // chunk of a (read whole, masked below)
         const u64x2_a8 *kb = (const u64x2_a8 *)(keys + (e1 < m ? e1 : 0));  // chunk that starts at e1
         u64 ea[16], eb[16];
+        if (on && !prm.bits && range_end > Bold) last_key = keys[range_end - 1];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const u64x2 t2 = ka[j], t3 = kb[j];
@@ -2051,17 +2236,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     }
     // per bit width: the clusters' errors added in position order by the lane of position 0
     double *escr = (double *)smem;      // (over the rows' tables, which nothing reads any more)
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (one wavefront)
     escr[lane] = Ep;
     escr[64 + lane] = Rp;
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     double err_b = 0.0;
     bool exact_b = false;
     if (on && p == 0) {
         double rtot = 0.0;
-        for (int k = 0; k < K; ++k) {
-            err_b += escr[lane + k];
-            rtot += escr[64 + lane + k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {           // (one after the other, requested together)
+            const double e = escr[min(lane + k, 63)], t = escr[64 + min(lane + k, 63)];
+            err_b += k < K ? e : 0.0;
+            rtot += k < K ? t : 0.0;
         }
         // cancellation leaves about 1e-16 * rtot of rounding in err_b: below 1e-9 * rtot (or negative, or
         // not a number) the error is evaluated key by key instead
@@ -2083,11 +2270,9 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     }
     // table mode: centroids, bounds and errors go out from here; finish_kernel only has the flagged errors left
     {
-        int b1 = lane_above(Bold);
-        if (p == K - 1) b1 = m;
         if (on && !prm.bits) {
             const long long obase = row * prm.stride + ((1 << b) - (1 << prm.bmin));
-            const float up = (b1 > Bold) ? elem_w(keys[b1 - 1]) : -INFINITY;
+            const float up = range_end > Bold ? elem_w(last_key) : -INFINITY;
             prm.cent[obase + idx] = v;
             if (prm.upper) prm.upper[obase + idx] = up;
             if (p == 0 && !exact_b) prm.E[row * (prm.bmax - prm.bmin + 1) + (b - prm.bmin)] = err_b;
@@ -2731,25 +2916,51 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
         return SKIM_OK;
     }
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[1], ctx->stream));
-    LevelMap lm = level_map((prm.m + 15) >> 4, false);
     {
-        // Running sums at every 4 chunks as long as they leave the LDS room for 8 workgroups a compute unit (two wavefronts
-        // per SIMD; registers allow three).
-        const bool wide = 8 * (lloyd_lds_bytes(lm) + 256) > (size_t)ctx->lds_limit;
-        if (wide) lm = level_map((prm.m + 15) >> 4, true);
-        const size_t llds = lloyd_lds_bytes(lm);
         const long long wgs = (n + 1) / 2;
         const dim3 grid((unsigned)wgs), block(ITER_THREADS);
-        auto launch = [&](auto ragged, auto w) {
-            hipLaunchKernelGGL((lloyd_iter_kernel<decltype(ragged)::value, decltype(w)::value>), grid, block,
-                               llds, ctx->stream, prm, (long long)n, lm);
-        };
-        auto pick = [&](auto ragged) {
-            if (wide) launch(ragged, std::true_type{});
-            else launch(ragged, std::false_type{});
-        };
-        if (prm.m & 15) pick(std::true_type{});
-        else pick(std::false_type{});
+        // Rows kept in LDS, in pieces of 4 keys or else of 8 (less LDS), where all workgroups are resident at once, or at most twice as many as
+        // are and these at least 4 a compute unit, or 8 a compute unit are.  Iterations and errors of a table in us, kept in LDS / over
+        // global memory: 512 x 512 38 / 61, 1021 x 2999 54 / 83, 4096 x 512 51 / 86, 11008 x 512 110 / 152, 4096 x 1024 84 / 101.  Beyond:
+        // 2048 x 2048 (2 of 4 resident) 84 / 78, 11008 x 1024 (6 of 22) 179 / 179, 4096 x 2048 (3 of 8) 144 / 112.
+        int G = 0;
+        LevelMap lm{};
+        for (int g = 4; g <= 8 && G == 0; g *= 2) {
+            const LevelMap t = level_map_resident(prm.m, g);
+            const long long fit = min((long long)ctx->lds_limit / (long long)(lloyd_lds_bytes(t) + 256), 8ll);
+            const long long each = (wgs + ctx->num_cu - 1) / ctx->num_cu;
+            if (t.np <= RESIDENT_MAX_PIECES && (each <= fit || (fit >= 4 && each <= 2 * fit) || fit >= 8)) {
+                G = g;
+                lm = t;
+            }
+        }
+        if (G > 0) {
+            const size_t llds = lloyd_lds_bytes(lm);
+            const void *kern = G == 4 ? (const void *)lloyd_iter_kernel<false, false, 4> : (const void *)lloyd_iter_kernel<false, false, 8>;
+            if (llds > 65536 && llds > ctx->lloyd_lds_enabled[G / 8]) {
+                SKIM_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)llds));
+                ctx->lloyd_lds_enabled[G / 8] = llds;
+            }
+            if (G == 4) hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 4>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, lm);
+            else hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 8>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, lm);
+        } else {
+            lm = level_map((prm.m + 15) >> 4, false);
+            // Running sums at every 4 chunks as long as they leave the LDS room for 8 workgroups a compute unit (two wavefronts
+            // per SIMD; registers allow three).
+            const bool wide = 8 * (lloyd_lds_bytes(lm) + 256) > (size_t)ctx->lds_limit;
+            if (wide) lm = level_map((prm.m + 15) >> 4, true);
+            const size_t llds = lloyd_lds_bytes(lm);
+            auto launch = [&](auto ragged, auto w) {
+                hipLaunchKernelGGL((lloyd_iter_kernel<decltype(ragged)::value, decltype(w)::value, 0>), grid, block,
+                                   llds, ctx->stream, prm, (long long)n, lm);
+            };
+            auto pick = [&](auto ragged) {
+                if (wide) launch(ragged, std::true_type{});
+                else launch(ragged, std::false_type{});
+            };
+            if (prm.m & 15) pick(std::true_type{});
+            else pick(std::false_type{});
+        }
     }
     hipLaunchKernelGGL(finish_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, ctx->stream, prm);
     if (ctx->profiling) {

@@ -693,3 +693,42 @@ def test_random_shapes_and_flavours(ctx, seed):
     assert excused <= 2
     bits = rng.integers(1, 5, n).astype(np.uint8)
     check_rows(ctx, W, S, bits, alpha=alpha, iters=iters)
+
+
+# (the last piece of 4 or 8 keys partly filled; 251, 256, 513 and 750 pieces: the search tree with and without a fourth level; two rows a
+# workgroup, the last one alone; rows in pieces of 4 and of 8 keys)
+@pytest.mark.parametrize("m,n,tiled", [(1003, 41, 6600), (1024, 40, 6600), (2050, 41, 1700), (3000, 900, 1100), (4100, 37, 600)])
+def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n, tiled):
+    """A small matrix has its rows in LDS while they iterate, a larger one does not: the same rows in either.  Bounds
+    (assignments) are equal; sums are taken in another order: centroids within 1e-13 of the row's largest weight times the number
+    of iterations, errors within 1e-13 of the row's second moment."""
+    rng = np.random.default_rng(m)
+    W = (rng.standard_normal((n, m)) * 0.02).astype(np.float32)
+    W = np.where(rng.random((n, m)) < 0.005, W * 10, W).astype(np.float32)
+    S = (rng.standard_t(3, (n, m)) ** 2).astype(np.float32)
+    W[1] = torch.from_numpy(W[1]).to(torch.bfloat16).float().numpy()        # every value many times
+    W[2], S[2] = np.concatenate([W[2, : m // 2], -W[2, : m - m // 2]]), 1.0  # midpoints that cancel
+    W[3] = 0.25                                                              # one value
+    W[4] = np.where(np.arange(m) % 3 == 0, 1.0, -1.0)
+    S[5] = 0.0
+    S[6] = np.where(np.arange(m) % 50 == 0, S[6], 0.0)                       # clusters without mass
+    big = np.float32(np.finfo(np.float32).max)
+    W[7] = rng.uniform(-1, 1, m).astype(np.float32) * big
+    W[7, ::100] = big
+    W[8] = rng.random(m).astype(np.float32) * np.float32(1e-38)
+    S[9] = np.float32(10.0) ** rng.integers(-18, 6, m)
+    Wd, Sd = dev(W), dev(S)
+    reps = -(-tiled // n)
+    Wt, St = Wd.repeat(reps, 1), Sd.repeat(reps, 1)
+    bits = torch.from_numpy(rng.integers(1, 5, n).astype(np.uint8)).cuda()
+    few, many = ctx.error_table(Wd, Sd), ctx.error_table(Wt, St)
+    rows_few, rows_many = ctx.cluster_rows(Wd, Sd, bits), ctx.cluster_rows(Wt, St, bits.repeat(reps))
+    torch.cuda.synchronize()
+    assert torch.equal(few["upper_all"], many["upper_all"][:n]) and torch.equal(few["upper_all"], many["upper_all"][-n:])
+    assert torch.equal(rows_few["labels"], rows_many["labels"][:n])
+    w, s = Wd.double(), Sd.double()
+    s = torch.where(s.sum(1, keepdim=True) > 0, s, torch.ones_like(s))
+    scale, moment = w.abs().amax(1, keepdim=True), (s * w * w).sum(1, keepdim=True)
+    assert bool(((few["centroids_all"] - many["centroids_all"][:n]).abs() <= 3e-12 * scale).all())
+    assert bool(((few["E"] - many["E"][:n]).abs() <= 1e-13 * moment).all())
+    assert bool(((rows_few["centroids"] - rows_many["centroids"][:n]).abs() <= 3e-12 * scale).all())
