@@ -40,95 +40,139 @@ __device__ __forceinline__ RowPlace place_row(const long long *gwo, long long m,
     return r;   // b == 0: p is past the last row
 }
 
-// The dense matrix: one workgroup per row, bound by the 4 bytes written per weight.  A thread takes four neighbouring
-// columns at a time: their 4 B code bits out of one or two words, one 16-byte store.  The columns ahead of the first
-// 16-byte border of the row (any m, any address of Wq) and behind the last whole four go one by one.  UNPACK_UNROLL
-// steps are in flight together, and the first of them is requested together with the row's codebook and index.
-// 4096 x 11008 with alpha: 76 -> 41 us, 4.8 TB/s (column by column with 4-byte stores before).
-constexpr int UNPACK_UNROLL = 4;
+// The dense matrix, bound by the 4 bytes written per weight.  A row is cut into segments of up to 4096 columns (multiples of 32: a
+// segment's codes are whole words); a workgroup takes one segment of every so many rows.  The codes, codebook and index of its
+// next row are on their way while the current one is written: with one workgroup per row and its codes asked for step by step,
+// codes that are not in a cache cost four trips to memory in a row, twice over.  The words go through LDS; a thread expands four
+// neighbouring columns at a time into one 16-byte store.  The columns ahead of the first 16-byte border of the segment (any m, any
+// address of Wq) and behind the last whole four go one by one.  ALIGNED: m is a multiple of 4, so the borders are the same in every row
+// and alpha stays in registers.
+// 4096 x 11008 with alpha, codes from memory: 37 us, 5.3 TB/s (67 with one workgroup per row; 49 with stores that stay in
+// the caches, which serve a reader that follows at once and everything else not: with a library product behind it 121, 126 and 110).
+constexpr uint32_t UNPACK_SEGMENT = 4096;
+constexpr int UNPACK_QUADS = UNPACK_SEGMENT / (4 * UNPACK_THREADS);       // of a thread, at most
+constexpr int UNPACK_WORDS = UNPACK_SEGMENT * 4 / 32 / UNPACK_THREADS;    // of a thread, at 4 bits
 
-template <int B, bool ALPHA>
-__device__ __forceinline__ void unpack_row(const uint32_t *__restrict__ rw, uint32_t m, uint32_t head, bool alpha_vec,
-                                           const float *__restrict__ alpha, const uint16_t *__restrict__ cb, const int *row_perm,
-                                           long long p, float *cbf, float *__restrict__ Wq) {
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+template <int B, bool ALPHA, bool ALIGNED>
+__device__ __forceinline__ void unpack_segment(const uint32_t *words, const float *cbf, uint32_t cols, uint32_t head, bool alpha_vec,
+                                               const float *__restrict__ alpha, const float4 (&al)[UNPACK_QUADS], float *__restrict__ out) {
     const uint32_t tid = threadIdx.x;
-    const uint32_t quads = (m - head) >> 2;
-    constexpr uint32_t STEP = UNPACK_THREADS * UNPACK_UNROLL;
-    uint32_t v[UNPACK_UNROLL];
-    float4 al[UNPACK_UNROLL];
-    // four codes from column j on, in the low 4 B bits (the second word is read only where the codes reach into it: it
-    // belongs to the row then)
-    auto load = [&](uint32_t q0) {
-#pragma unroll
-        for (int u = 0; u < UNPACK_UNROLL; ++u) {
-            const uint32_t q = q0 + u * UNPACK_THREADS;
-            v[u] = 0u;
-            if (q < quads) {
-                const uint32_t j = head + 4u * q, bit = j * B, wi = bit >> 5, sh = bit & 31u;
-                const uint32_t w0 = rw[wi], w1 = (sh + 4u * B > 32u) ? rw[wi + 1] : 0u;
-                v[u] = (uint32_t)((((unsigned long long)w1 << 32) | w0) >> sh);
-                if (ALPHA) {
-                    if (alpha_vec) al[u] = *(const float4 *)(alpha + j);
-                    else al[u] = make_float4(alpha[j], alpha[j + 1], alpha[j + 2], alpha[j + 3]);
-                }
-            }
-        }
-    };
-    load(tid);
-    if (tid < (1u << B)) cbf[tid] = __half2float(__ushort_as_half(cb[tid]));
-    const long long row = row_perm[p];
-    float *__restrict__ out = Wq + row * (long long)m;
-    __syncthreads();
+    const uint32_t quads = (cols - head) >> 2;
     constexpr uint32_t mask = (1u << B) - 1u;
-    for (uint32_t q0 = tid; q0 < quads; q0 += STEP) {
-        if (q0 != tid) load(q0);
 #pragma unroll
-        for (int u = 0; u < UNPACK_UNROLL; ++u) {
-            const uint32_t q = q0 + u * UNPACK_THREADS;
-            if (q < quads) {
-                float4 c = make_float4(cbf[v[u] & mask], cbf[(v[u] >> B) & mask], cbf[(v[u] >> (2 * B)) & mask],
-                                       cbf[(v[u] >> (3 * B)) & mask]);
-                if (ALPHA)
-                    c = make_float4(__fmul_rn(al[u].x, c.x), __fmul_rn(al[u].y, c.y), __fmul_rn(al[u].z, c.z),
-                                    __fmul_rn(al[u].w, c.w));
-                *(float4 *)(out + head + 4u * q) = c;
+    for (int u = 0; u < UNPACK_QUADS; ++u) {
+        const uint32_t q = tid + u * UNPACK_THREADS;
+        if (q < quads) {
+            const uint32_t j = head + 4u * q, bit = j * B, wi = bit >> 5, sh = bit & 31u;
+            const uint32_t v = (uint32_t)((((unsigned long long)words[wi + 1] << 32) | words[wi]) >> sh);      // (room for one word more)
+            float4 c = make_float4(cbf[v & mask], cbf[(v >> B) & mask], cbf[(v >> (2 * B)) & mask], cbf[(v >> (3 * B)) & mask]);
+            if (ALPHA) {
+                float4 a = al[u];
+                if (!ALIGNED) a = alpha_vec ? *(const float4 *)(alpha + j) : make_float4(alpha[j], alpha[j + 1], alpha[j + 2], alpha[j + 3]);
+                c = make_float4(__fmul_rn(a.x, c.x), __fmul_rn(a.y, c.y), __fmul_rn(a.z, c.z), __fmul_rn(a.w, c.w));
             }
+            __builtin_nontemporal_store(float4v{c.x, c.y, c.z, c.w}, (float4v *)(out + j));      // (the caches are left to the codes)
         }
     }
     // at most three columns at either end
     const uint32_t tail = head + 4u * quads;
-    if (tid < head + (m - tail)) {
+    if (tid < head + (cols - tail)) {
         const uint32_t j = tid < head ? tid : tail + (tid - head);
         const uint32_t bit = j * B, wi = bit >> 5, sh = bit & 31u;
-        uint32_t x = rw[wi] >> sh;
-        if ((32 % B) != 0 && sh + B > 32u) x |= rw[wi + 1] << (32u - sh);
+        const uint32_t x = (uint32_t)((((unsigned long long)words[wi + 1] << 32) | words[wi]) >> sh);
         const float c = cbf[x & mask];
         out[j] = ALPHA ? __fmul_rn(alpha[j], c) : c;
     }
 }
 
-template <bool ALPHA>
-__global__ void __launch_bounds__(UNPACK_THREADS) unpack_kernel(const uint32_t *codes, const long long *gwo, const int *row_perm,
-                                                               const uint16_t *codebooks, const float *alpha, long long m,
-                                                               float *Wq) {
-    __shared__ float cbf[16];
-    const long long p = blockIdx.x;
-    const RowPlace pl = place_row(gwo, m, p);
-    if (pl.b == 0) return;
-    // columns ahead of the first 16-byte border of this row: with m a multiple of 4 the same for every row; otherwise the
-    // row's index has to be known (one more trip to memory ahead of the codes)
-    const uint32_t base = (uint32_t)((uintptr_t)Wq >> 2) & 3u;
-    const uint32_t skew = (m & 3) ? (uint32_t)(((unsigned long long)row_perm[p] * (unsigned long long)m) & 3u) : 0u;
-    const uint32_t head = min((uint32_t)m, (0u - base - skew) & 3u);
-    const bool alpha_vec = ALPHA && (((uintptr_t)(alpha + head)) & 15) == 0;
-    const uint32_t *rw = codes + pl.word0;
-    const uint16_t *cb = codebooks + pl.cb0;
-    switch (pl.b) {
-        case 1: unpack_row<1, ALPHA>(rw, (uint32_t)m, head, alpha_vec, alpha, cb, row_perm, p, cbf, Wq); break;
-        case 2: unpack_row<2, ALPHA>(rw, (uint32_t)m, head, alpha_vec, alpha, cb, row_perm, p, cbf, Wq); break;
-        case 3: unpack_row<3, ALPHA>(rw, (uint32_t)m, head, alpha_vec, alpha, cb, row_perm, p, cbf, Wq); break;
-        default: unpack_row<4, ALPHA>(rw, (uint32_t)m, head, alpha_vec, alpha, cb, row_perm, p, cbf, Wq); break;
+template <bool ALPHA, bool ALIGNED>
+__global__ void __launch_bounds__(UNPACK_THREADS) unpack_kernel(const uint32_t *__restrict__ codes, const long long *__restrict__ gwo,
+                                                               const int *__restrict__ row_perm, const uint16_t *__restrict__ codebooks,
+                                                               const float *__restrict__ alpha, long long n, long long m, uint32_t seglen,
+                                                               float *__restrict__ Wq) {
+    __shared__ uint32_t words[2][UNPACK_WORDS * UNPACK_THREADS + 4];
+    __shared__ float cbf[2][16];
+    const uint32_t tid = threadIdx.x;
+    const long long c0 = (long long)blockIdx.x * seglen;
+    const uint32_t cols = (uint32_t)min((long long)seglen, m - c0);
+    const uint32_t base = (uint32_t)((uintptr_t)Wq >> 2) & 3u;            // (c0 is a multiple of 4)
+    auto head_of = [&](long long row) -> uint32_t {      // columns ahead of the first 16-byte border
+        const uint32_t skew = ALIGNED ? 0u : (uint32_t)(((unsigned long long)row * (unsigned long long)m) & 3u);
+        return min(cols, (0u - base - skew) & 3u);
+    };
+    // a row's words of this segment, its codebook and its index, on their way
+    uint32_t w[UNPACK_WORDS];
+    uint16_t cb = 0;
+    int row = 0, bits = 0;
+    auto fetch = [&](long long p) {
+        bits = 0;
+        if (p >= n) return;
+        const RowPlace pl = place_row(gwo, m, p);
+        bits = pl.b;
+        if (bits == 0) return;
+        const uint32_t count = (cols * (uint32_t)bits + 31u) >> 5;
+        const uint32_t *rw = codes + pl.word0 + (c0 >> 5) * bits;
+#pragma unroll
+        for (int k = 0; k < UNPACK_WORDS; ++k) w[k] = tid + k * UNPACK_THREADS < count ? rw[tid + k * UNPACK_THREADS] : 0u;
+        if (tid < (1u << bits)) cb = codebooks[pl.cb0 + tid];
+        row = row_perm[p];
+    };
+    long long p = blockIdx.y;
+    fetch(p);
+    float4 al[UNPACK_QUADS];
+    if (ALPHA && ALIGNED) {
+        alpha += c0;
+        const uint32_t head = head_of(0);
+        const bool vec = (((uintptr_t)(alpha + head)) & 15) == 0;
+#pragma unroll
+        for (int u = 0; u < UNPACK_QUADS; ++u) {
+            const uint32_t j = head + 4u * (tid + u * UNPACK_THREADS);
+            al[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j + 4 <= cols) al[u] = vec ? *(const float4 *)(alpha + j) : make_float4(alpha[j], alpha[j + 1], alpha[j + 2], alpha[j + 3]);
+        }
+    } else if (ALPHA) {
+        alpha += c0;
     }
+    for (int buf = 0; bits != 0; buf ^= 1) {
+#pragma unroll
+        for (int k = 0; k < UNPACK_WORDS; ++k) words[buf][tid + k * UNPACK_THREADS] = w[k];
+        if (tid < 16) cbf[buf][tid] = __half2float(__ushort_as_half(cb));
+        __syncthreads();
+        const int b = bits;
+        const uint32_t head = head_of(row);
+        float *out = Wq + (long long)row * m + c0;
+        p += gridDim.y;
+        fetch(p);
+        const bool vec = ALPHA && !ALIGNED && (((uintptr_t)(alpha + head)) & 15) == 0;
+        switch (b) {
+            case 1: unpack_segment<1, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            case 2: unpack_segment<2, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            case 3: unpack_segment<3, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            default: unpack_segment<4, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+        }
+    }
+}
+
+// Segments of equal length, and as many workgroups as are resident at once (6 a compute unit), in equal numbers of rows.
+void launch_unpack(skim_ctx *ctx, const uint32_t *codes, const int64_t *gwo, const int32_t *row_perm, const uint16_t *codebooks,
+                   const float *alpha, int64_t n, int64_t m, float *Wq) {
+    int64_t nseg = (m + UNPACK_SEGMENT - 1) / UNPACK_SEGMENT;
+    const int64_t seglen = ((m + nseg - 1) / nseg + 31) / 32 * 32;
+    nseg = (m + seglen - 1) / seglen;
+    const int64_t resident = 6ll * ctx->num_cu, rounds = (n * nseg + resident - 1) / resident;
+    const int64_t stride = (n + rounds - 1) / rounds;
+    auto launch = [&](auto al, auto aligned) {
+        hipLaunchKernelGGL((unpack_kernel<decltype(al)::value, decltype(aligned)::value>), dim3((unsigned)nseg, (unsigned)stride), dim3(UNPACK_THREADS), 0,
+                           ctx->stream, codes, (const long long *)gwo, row_perm, codebooks, alpha, (long long)n, (long long)m, (uint32_t)seglen, Wq);
+    };
+    auto pick = [&](auto al) {
+        if (m % 4 == 0) launch(al, std::true_type{});
+        else launch(al, std::false_type{});
+    };
+    if (alpha) pick(std::true_type{});
+    else pick(std::false_type{});
 }
 
 // The matrix-vector product.  A workgroup takes ROWS packed rows (8, or 4 or 2 where fewer leave compute units idle) and
@@ -360,12 +404,7 @@ extern "C" skim_status skim_unpack(skim_ctx *ctx, const uint32_t *codes, const i
     if (st != SKIM_OK) return st;
     if ((st = check_packed(ctx, codes, group_word_offset, row_perm, codebooks_fp16, n, m, "skim_unpack")) != SKIM_OK) return st;
     if (!Wq) SKIM_FAIL(ctx, SKIM_ERR_ARG, "skim_unpack: Wq must not be NULL");
-    if (alpha)
-        hipLaunchKernelGGL(unpack_kernel<true>, dim3((unsigned)n), dim3(UNPACK_THREADS), 0, ctx->stream, codes,
-                           (const long long *)group_word_offset, row_perm, codebooks_fp16, alpha, (long long)m, Wq);
-    else
-        hipLaunchKernelGGL(unpack_kernel<false>, dim3((unsigned)n), dim3(UNPACK_THREADS), 0, ctx->stream, codes,
-                           (const long long *)group_word_offset, row_perm, codebooks_fp16, alpha, (long long)m, Wq);
+    launch_unpack(ctx, codes, group_word_offset, row_perm, codebooks_fp16, alpha, n, m, Wq);
     SKIM_HIP(ctx, hipGetLastError());
     return SKIM_OK;
 }

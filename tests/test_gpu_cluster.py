@@ -456,6 +456,27 @@ def test_unpack_at_any_alignment(ctx, gpu_lib, m, offset):
         assert np.all(got[:offset] == 7.0) and np.all(got[offset + n * m:] == 7.0)
 
 
+@pytest.mark.parametrize("n,m", [(3200, 64), (1537, 1001), (900, 4097), (700, 8224), (2, 40000)])
+def test_unpack_of_several_rows_and_segments_a_workgroup(ctx, n, m):
+    """One to three rows a workgroup (the last round part-filled), one to ten segments of a row: bit-exact against the codes looked up one
+    by one on the device."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    bits = (torch.arange(n, device="cuda") % 4 + 1).to(torch.uint8)
+    cent = torch.sort(torch.randn((n, 16), device="cuda", generator=g), dim=1)[0].double()
+    K = (1 << bits.long())[:, None]
+    slot = torch.arange(16, device="cuda")[None, :]
+    upper = torch.where(slot < K - 1, cent.float(), torch.full_like(cent, 1e30).float())
+    W = torch.randn((n, m), device="cuda", generator=g)
+    al = dev(skim_synth.make_alpha(5, m))
+    pk = ctx.pack(W, bits, cent, upper, alpha=al, bits_host=bits.cpu().numpy())
+    label = torch.minimum((upper[:, None, :] < (W / al)[:, :, None]).logical_and(slot[None] < K[:, :, None]).sum(2), K - 1) if n * m < 4e6 else None
+    got = ctx.unpack(pk, m, alpha=al)
+    if label is None:        # (the masks of all weights at once would be large)
+        label = torch.cat([torch.minimum((upper[i:i + 100, None, :] < (W[i:i + 100] / al)[:, :, None]).logical_and(slot[None] < K[i:i + 100, :, None]).sum(2),
+                                         K[i:i + 100] - 1) for i in range(0, n, 100)])
+    assert torch.equal(got, al * cent.float().half().float().gather(1, label))
+
+
 @pytest.mark.parametrize("n,m", [(1, 5), (3, 33), (5, 8225), (2051, 2088), (4100, 4128), (8200, 2049), (600, 16411), (300, 32768)])
 def test_matvec_shapes(ctx, n, m):
     """Sizes at which a workgroup takes 2, 4 or 8 rows (part-filled last ones; bit widths changing inside one) and one or
