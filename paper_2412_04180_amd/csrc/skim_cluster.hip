@@ -1113,7 +1113,7 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
     if (prm.nseg > 1) {
         // one segment of a long row: sorted keys only; merge_tile_kernel does the rest
         u64 *kseg = prm.keys_seg + row * (long long)prm.m + col0;
-        for (int j = tid; j < m; j += nth) kseg[j] = sorted[swz((uint32_t)j)];
+        for (int j = tid; j < m; j += nth) __builtin_nontemporal_store(sorted[swz((uint32_t)j)], kseg + j);
         if (!buckets) __syncthreads();   // the LDS is refilled for the next unit (see the end of the loop)
         continue;
     }
@@ -1149,9 +1149,11 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
             prm.RQ[row * prm.nq + (tid >> 2)] = r4;
         }
     }
-    // sorted keys, compact and in rank order
+    // Sorted keys, compact and in rank order, with stores that do not stay in the caches: the next kernel reads a fraction of them, and
+    // everything else has the room (4096 x 11008, whole pass: 439 -> 432 us; with the stores of the halves and of the merge
+    // 8192 x 22016 1895 -> 1847; loads of W and S that do not stay either: 1.5 % slower, pack reads W again)
     u64 *keys = prm.keys + row * (long long)m;
-    for (int j = tid; j < m; j += nth) keys[j] = plain_key(sorted[swz((uint32_t)j)]);
+    for (int j = tid; j < m; j += nth) __builtin_nontemporal_store(plain_key(sorted[swz((uint32_t)j)]), keys + j);
     // The next unit refills the key region of the LDS.  On the bucket path it first works on its tables, which
     // lie beyond that region, and passes several barriers before its scatter; its bitonic branch has a barrier
     // of its own.  Without the bucket path the refill is immediate.
@@ -1310,7 +1312,7 @@ __global__ void __launch_bounds__(MG_THREADS) merge_tile_kernel(ClusterParams pr
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         const int x = tid + e * MG_THREADS;
-        if (x < T) keys[x] = obuf[swz((uint32_t)x)];
+        if (x < T) __builtin_nontemporal_store(obuf[swz((uint32_t)x)], keys + x);
     }
 }
 
