@@ -67,7 +67,7 @@ struct ClusterParams {
     u64 *keys_seg;
     int *segmass;         // per segment of a long row: nonzero when it holds sensitivity mass
     long long nwork;      // rows x segments: the units of work sort_kernel's workgroups share out
-    int *work_counters;   // [0] units handed out beyond every workgroup's first two, [1] workgroups done (both zero at launch)
+    int *work_counters;   // units handed out beyond every workgroup's first two (zero at launch); null: fixed shares
     int *vflag;           // validation result (one word of scratch)
     // bucket path of sort_kernel: value bins per thread (0: always the bitonic network) and the byte
     // offsets of its tables inside the dynamic LDS
@@ -904,7 +904,8 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
     int next = 0, par = 0;
     for (int work = (int)blockIdx.x; work < nwork; work = next, par ^= 1) {
     // the unit that is fetched while this one is sorted: the answer to the previous unit's claim
-    next = prm.bk_bpt > 0 ? __builtin_amdgcn_readfirstlane(next_slot[par]) : (int)min((long long)work + gridDim.x, prm.nwork);
+    const bool claims = prm.work_counters != nullptr;
+    next = claims ? __builtin_amdgcn_readfirstlane(next_slot[par]) : (int)min((long long)work + gridDim.x, prm.nwork);
     // the thread index is made opaque per unit: per-thread addresses are recomputed where they are
     // used instead of being hoisted out of this loop and held in registers through the sort
     int tid = tid0;
@@ -926,10 +927,14 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
     // of one of the unit's barriers; everybody reads it at the start of the next unit (this unit's word is
     // written again two units on, behind barriers every reader has passed by then)
     unsigned claim = 0u;
+    // A workgroup claims once for every unit but its last, so there are nwork - gridDim.x claims in all, and whoever gets the last
+    // number puts the counter back to zero for the next launch.  (A second counter, of workgroups that were done, cost 12 ns for each of
+    // them: atomics on one address from several XCDs go one after the other.  512 x 512 19.6 -> 15.6 us.)
     auto claim_next = [&]() {
-        if (more && tid == 0) claim = (unsigned)atomicAdd(prm.work_counters, 1);
+        if (claims && more && tid == 0) claim = (unsigned)atomicAdd(prm.work_counters, 1);
     };
     auto publish = [&]() {
+        if (claims && more && tid == 0 && claim == (unsigned)(prm.nwork - gridDim.x) - 1u) atomicExch(prm.work_counters, 0);
         if (tid == 0) next_slot[par ^ 1] = more ? (int)min(2ll * gridDim.x + (long long)claim, (long long)nwork) : nwork;
     };
     auto prefetch = [&](int part) {
@@ -1092,9 +1097,9 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
             if (sm.col(k) < prm.P) sorted[swz((uint32_t)sm.col(k))] = key[k];
         for (int j = tid + NS * nth; j < prm.P; j += nth) sorted[swz((uint32_t)j)] = PAD_KEY;   // padding no slot covers
         __syncthreads();
-        // (the variants with 16-byte loads serve fixed ranges of the padded length: 8 slots up to 8192 keys, 12 and
+        // (the variants serve fixed ranges of the padded length: 8 slots up to 8192 keys, 12 and
         // 16 slots 16384; only the networks a variant can be asked for are compiled into it)
-        if constexpr (VEC && NS > 8) {
+        if constexpr (NS > 8) {
             sort_row<14>((double *)sorted, (uint32_t)tid, m);
         } else {
             switch (prm.logP) {
@@ -1102,9 +1107,7 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
                 case 11: sort_row<11>((double *)sorted, (uint32_t)tid, m); break;
                 case 12: sort_row<12>((double *)sorted, (uint32_t)tid, m); break;
                 case 13: sort_row<13>((double *)sorted, (uint32_t)tid, m); break;
-                default:
-                    if constexpr (!VEC) sort_row<14>((double *)sorted, (uint32_t)tid, m);
-                    break;
+                default: break;
             }
         }
         fetch_unit<NS, VEC>(prm, more ? next : work, tid, nth, pw, ps, more);
@@ -1158,15 +1161,6 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
     // lie beyond that region, and passes several barriers before its scatter; its bitonic branch has a barrier
     // of its own.  Without the bucket path the refill is immediate.
     if (!buckets) __syncthreads();
-    }
-    // the last workgroup to get here leaves both counters at zero for the next launch (every claim of every
-    // workgroup has been answered by then: a workgroup uses the answers before it leaves its loop)
-    if (tid0 == 0) {
-        const int done = atomicAdd(prm.work_counters + 1, 1);
-        if (done == (int)gridDim.x - 1) {
-            atomicExch(prm.work_counters, 0);
-            atomicExch(prm.work_counters + 1, 0);
-        }
     }
 }
 
@@ -1232,7 +1226,7 @@ __global__ void __launch_bounds__(MG_THREADS) merge_tile_kernel(ClusterParams pr
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const int x = min(tid + e * MG_THREADS, T - 1);
-            t[e] = A[x < lat ? ia0 + x : la + ib0 + (x - lat)];
+            t[e] = __builtin_nontemporal_load(A + (x < lat ? ia0 + x : la + ib0 + (x - lat)));      // (read once: 8192 x 22016, whole pass, 1841 -> 1821 us)
         }
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
@@ -2838,14 +2832,14 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     int threads = prm.P / 8;
     if (threads > 1024) threads = 1024;
     if (threads < MIN_THREADS) threads = MIN_THREADS;
-    // 16-byte loads when every unit starts at a multiple of 16 bytes and has a multiple of 4 columns; then
-    // 8, 12 or 16 slots per thread, the least that covers the unit.  Otherwise 4-byte loads and 16 slots.
+    // 16-byte loads when every unit starts at a multiple of 16 bytes and has a multiple of 4 columns, otherwise 4-byte loads;
+    // 8, 12 or 16 slots per thread, the least that covers the unit (1021 x 2999, 4-byte loads, 16 / 8 slots: 49.5 / 42.3 us).
     const bool vec = ((uintptr_t)prm.W % 16 == 0) && ((uintptr_t)prm.S % 16 == 0) && (prm.ld % 4 == 0) && (prm.m % 4 == 0) &&
                      (prm.seglen % 4 == 0);
     const int per_thread = (prm.seglen + threads - 1) / threads;
-    const int variant = !vec ? 3 : (per_thread <= 8 ? 0 : (per_thread <= 12 ? 1 : 2));
+    const int slots = per_thread <= 8 ? 0 : (per_thread <= 12 ? 1 : 2), variant = slots + (vec ? 0 : 3);
     // (what the kernel variants rely on for the networks compiled into them)
-    if ((variant == 0 && prm.logP > 13) || ((variant == 1 || variant == 2) && prm.logP != 14))
+    if ((slots == 0 && prm.logP > 13) || (slots > 0 && prm.logP != 14))
         SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "internal: sort variant %d does not serve a padded length of 2^%d", variant, prm.logP);
     size_t lds = sort_lds_bytes(prm.P);
     if ((int64_t)lds > ctx->lds_limit)
@@ -2882,9 +2876,9 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
             lds = total;
         }
     }
-    const void *kern = variant == 0 ? (const void *)sort_kernel<8, true>
-                     : variant == 1 ? (const void *)sort_kernel<12, true>
-                     : variant == 2 ? (const void *)sort_kernel<16, true> : (const void *)sort_kernel<16, false>;
+    void (*const variants[6])(ClusterParams) = {sort_kernel<8, true>, sort_kernel<12, true>, sort_kernel<16, true>,
+                                                sort_kernel<8, false>, sort_kernel<12, false>, sort_kernel<16, false>};
+    const void *kern = (const void *)variants[variant];
     if (lds > 65536 && lds > ctx->sort_lds_enabled[variant]) {
         SKIM_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         ctx->sort_lds_enabled[variant] = lds;
@@ -2892,7 +2886,6 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     if (n == 0) return SKIM_OK;
     if ((int64_t)n * prm.nseg > 0x7fffffff) SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "too many rows");
     prm.nwork = (long long)n * prm.nseg;
-    prm.work_counters = ctx->sort_counters;
     // as many workgroups as the device holds at once (LDS and thread limits), each looping over its units
     int per_cu = (int)(ctx->lds_limit / (int64_t)(lds + 256));   // (+ the kernel's small static LDS)
     if (per_cu > 2048 / threads) per_cu = 2048 / threads;
@@ -2900,11 +2893,13 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     if (per_cu > 8) per_cu = 8;
     long long sort_grid = (long long)ctx->num_cu * per_cu;
     if (sort_grid > prm.nwork) sort_grid = prm.nwork;
+    // Short rows keep fixed shares: a claim takes 12 ns whoever makes it, and many workgroups on a compute unit even out by themselves
+    // (claimed / fixed, us: 11008 x 512 125 / 61, 22016 x 1024 255 / 129, 11008 x 2048 141 / 115; two units a workgroup of 512 threads,
+    // 2000 x 3001: 61 / 58; many, 11008 x 4096: 235 / 251; 1024 threads, 4096 x 11008: 221 / 224).
+    const bool claims = prm.bk_bpt > 0 && (threads > 512 || (threads > 256 && prm.nwork > 4 * sort_grid));
+    prm.work_counters = claims ? ctx->sort_counters : nullptr;
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
-    if (variant == 0) hipLaunchKernelGGL((sort_kernel<8, true>), dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
-    else if (variant == 1) hipLaunchKernelGGL((sort_kernel<12, true>), dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
-    else if (variant == 2) hipLaunchKernelGGL((sort_kernel<16, true>), dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
-    else hipLaunchKernelGGL((sort_kernel<16, false>), dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
+    hipLaunchKernelGGL(variants[variant], dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
     if (prm.nseg > 1) {
         const int tiles = (prm.m + MG_TILE - 1) / MG_TILE;
         if ((int64_t)n * tiles > 0x7fffffff) SKIM_FAIL(ctx, SKIM_ERR_SHAPE, "too many rows");

@@ -20,13 +20,13 @@ struct skim_ctx {
     int profiling;
     hipEvent_t ev[3];    // before sort, between sort and Lloyd, after Lloyd
     int ev_valid;
-    size_t sort_lds_enabled[4];   // dynamic LDS size each variant of the sort kernel has been allowed so far (through this context)
+    size_t sort_lds_enabled[6];   // dynamic LDS size each variant of the sort kernel has been allowed so far (through this context)
     size_t lloyd_lds_enabled[2];  // likewise of the iteration kernels that keep rows in LDS
     int greedy_lds_enabled, xtx_lds_enabled, gemm3_lds_enabled;   // the larger dynamic-LDS limit of these kernels has been set through this context
     int validate;        // check W, S, alpha of the clustering calls for values the method is not defined on
     void *pack_scratch;  // this device's address of the static scratch of skim_pack_static
-    int *sort_counters;  // device memory owned by the context: [0] units of work handed out by the running sort_kernel, [1] its workgroups
-                         // that are done; both are zero between launches (the last workgroup to finish clears them)
+    int *sort_counters;  // device memory owned by the context: units of work handed out by the running sort_kernel, zero between
+                         // launches (whoever takes the last one clears it)
 };
 
 #define SKIM_FAIL(ctx, code, ...)                                   \

@@ -753,3 +753,20 @@ def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n
     assert bool(((few["centroids_all"] - many["centroids_all"][:n]).abs() <= 3e-12 * scale).all())
     assert bool(((few["E"] - many["E"][:n]).abs() <= 1e-13 * moment).all())
     assert bool(((rows_few["centroids"] - rows_many["centroids"][:n]).abs() <= 3e-12 * scale).all())
+
+
+@pytest.mark.parametrize("n,m", [(2100, 4096), (2100, 4095), (700, 8200), (5000, 520), (600, 12287), (3, 4000)])
+def test_rows_shared_out_by_claims_or_in_fixed_shares(ctx, n, m):
+    """Many and few rows a workgroup, 16-byte and 4-byte loads with 8, 12 and 16 slots: every call after the first
+    finds the counter of the units as the first did, and a row's result does not depend on the others."""
+    W, S = skim_synth.make_ws_small(n, min(n, 300), m)
+    reps = -(-n // len(W))
+    Wd, Sd = dev(W).repeat(reps, 1)[:n].contiguous(), dev(S).repeat(reps, 1)[:n].contiguous()
+    first = ctx.error_table(Wd, Sd)
+    alone = ctx.error_table(Wd[:64].contiguous(), Sd[:64].contiguous())
+    for _ in range(2):
+        again = ctx.error_table(Wd, Sd)
+        assert all(torch.equal(first[k], again[k]) for k in ("E", "centroids_all", "upper_all"))
+    k = min(n, 64)
+    assert torch.equal(first["upper_all"][:k], alone["upper_all"][:k])
+    assert torch.equal(first["upper_all"], first["upper_all"][:300].repeat(reps, 1)[:n])
