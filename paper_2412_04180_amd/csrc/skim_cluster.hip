@@ -1,7 +1,7 @@
 // Per-row sensitivity-weighted 1-D K-means (Alg. 3, pre-recording loop and 12-15; the
 // re-clustering of W * alpha^-1 in Alg. 2) for gfx950.
 //
-// Three kernels per call.
+// Two kernels per error table, three per skim_cluster_rows.
 //  sort_kernel       one workgroup per row at a time: the row's (w~, s~) pairs become 64-bit keys
 //                    whose bit pattern, read as a float64, orders like (w~, s~); they are sorted
 //                    once in LDS (counting sort by value bin + two register passes; a bitonic
@@ -15,9 +15,9 @@
 //                    inside the chunk from its keys), then centroid = (sum of s~ w~) / (sum of
 //                    s~) over the range, assembled from the keys of the boundary chunks, a few
 //                    chunk sums and a difference of double-double running sums.  In table mode it
-//                    also writes centroids, bounds and errors.
-//  finish_kernel     one workgroup per row: errors the iteration kernel flagged (direct evaluation
-//                    over the sorted keys); for skim_cluster_rows centroids, thresholds, labels.
+//                    also writes centroids, bounds and errors, and is the last.
+//  finish_kernel     for skim_cluster_rows, one workgroup per row: centroids, thresholds, labels, and an error that
+//                    the second moments left too few digits of (direct evaluation over the sorted keys).
 //
 // Arithmetic on every decision path is float64 and uses the same predicates as the
 // definition: |w - c_lo| versus |w - c_hi| with the lower cluster index winning equal
@@ -2250,7 +2250,65 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         // not a number) the error is evaluated key by key instead
         exact_b = !(err_b >= 1e-9 * rtot) || !(err_b > 0.0);
     }
-    if (on) {
+    // table mode: an error that drowned in cancellation is summed up key by key here, s (w - c)^2 over the sorted row by the whole
+    // wavefront (rows of few distinct values; iterations with all four widths of every row: 4096 x 4096 115 us, 4096 x 20000 294; with a kernel
+    // of its own for this 120 and 260).  That kernel, launched
+    // over all rows of every table, took 4 us to find nothing to do.
+    u64 todo = prm.bits ? 0ull : __ballot(exact_b);
+    if (__builtin_expect(todo != 0, 0)) {
+        double *cpos = escr + 128;               // centroids and first ranks by lane
+        int *bpos = (int *)(cpos + 64);
+        cpos[lane] = v;
+        bpos[lane] = Bold;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        for (int hh = 0; hh < 2; ++hh) {         // a row's widths in one pass
+            // (the lanes of position 0: 0, 2, 6 and 14 of the row's half)
+            const uint32_t flags = (uint32_t)(todo >> (32 * hh));
+            if (flags == 0u) continue;
+            const u64 *__restrict__ kr = prm.keys + (2ll * blockIdx.x + hh) * (long long)m;
+            // per width, the same in every lane: the cluster of the first rank of the current 64, the rank where it ends, its centroid
+            double e[4] = {0.0, 0.0, 0.0, 0.0}, c[4] = {0.0, 0.0, 0.0, 0.0};
+            int at[4], nxt[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) at[w] = 32 * hh + (2 << w) - 2;
+            constexpr int EU = 8;       // loads in flight
+            for (int base0 = 0; base0 < m; base0 += EU * 64) {
+                u64 ke[EU];
+#pragma unroll
+                for (int q = 0; q < EU; ++q) ke[q] = base0 + 64 * q + lane < m ? kr[base0 + 64 * q + lane] : NEUTRAL_KEY;      // (past the row: no mass)
+#pragma unroll
+                for (int q = 0; q < EU; ++q) {
+                    const int base = base0 + 64 * q;
+                    const double wd = (double)elem_w(ke[q]), sd = (double)plain_s(ke[q]);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        if (!((flags >> ((2 << w) - 2)) & 1u)) continue;
+                        const int last = 32 * hh + (4 << w) - 3;
+                        if (base >= nxt[w]) {
+                            while (at[w] < last && __builtin_amdgcn_readfirstlane(bpos[at[w] + 1]) <= base) ++at[w];
+                            nxt[w] = at[w] < last ? __builtin_amdgcn_readfirstlane(bpos[at[w] + 1]) : 0x7fffffff;
+                            c[w] = cpos[at[w]];
+                        }
+                        double cc = c[w];
+                        if (base + 64 > nxt[w]) {       // a boundary inside this stretch: looked up lane by lane
+                            int pp = at[w];
+                            while (pp < last && bpos[pp + 1] <= base + lane) ++pp;
+                            cc = cpos[pp];
+                        }
+                        const double d = wd - cc;
+                        e[w] += sd * d * d;
+                    }
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) e[w] += __shfl_xor(e[w], o, 64);
+                if (exact_b && lane == 32 * hh + (2 << w) - 2) err_b = e[w];
+            }
+        }
+    }
+    if (on && prm.bits) {
         BitState *o = prm.bstate + row * 4 + (b - 1);
         o->cent[p] = v;
         o->idx[p] = idx;
@@ -2264,20 +2322,20 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             o->exact = exact_b ? 1 : 0;
         }
     }
-    // table mode: centroids, bounds and errors go out from here; finish_kernel only has the flagged errors left
+    // table mode: centroids, bounds and errors go out from here, and that was all
     {
         if (on && !prm.bits) {
             const long long obase = row * prm.stride + ((1 << b) - (1 << prm.bmin));
             const float up = range_end > Bold ? elem_w(last_key) : -INFINITY;
             prm.cent[obase + idx] = v;
             if (prm.upper) prm.upper[obase + idx] = up;
-            if (p == 0 && !exact_b) prm.E[row * (prm.bmax - prm.bmin + 1) + (b - prm.bmin)] = err_b;
+            if (p == 0) prm.E[row * (prm.bmax - prm.bmin + 1) + (b - prm.bmin)] = err_b;
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 3: errors, centroids, thresholds, labels from the final boundaries.
+// Kernel 3 (given bit widths): errors, centroids, thresholds, labels from the final boundaries.
 // ---------------------------------------------------------------------------------------------
 constexpr int FIN_THREADS = 256;
 constexpr int FIN_WAVES = FIN_THREADS / 64;
@@ -2291,14 +2349,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long row = blockIdx.x;
     const u64 *__restrict__ keys = prm.keys + row * (long long)m;
-    const int rowbits = prm.bits ? (int)prm.bits[row] : 0;
-    if (!prm.bits) {
-        // table mode: lloyd_iter_kernel has written everything except the errors it flagged for evaluation key by key
-        const BitState *st = prm.bstate + row * 4;
-        int todo = 0;
-        for (int bi = prm.bmin - 1; bi < prm.bmax; ++bi) todo |= st[bi].exact;
-        if (!todo) return;      // (the same for the whole workgroup)
-    }
+    const int rowbits = (int)prm.bits[row];
     {
         const int *src = (const int *)(prm.bstate + row * 4);
         int *dst = (int *)bs;
@@ -2306,8 +2357,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
     }
     __syncthreads();
     if (tid < 4) {
-        const int bb = tid + 1;
-        bs[tid].active = prm.bits ? (bb == rowbits) : (bb >= prm.bmin && bb <= prm.bmax);
+        bs[tid].active = tid + 1 == rowbits;
     }
     __syncthreads();
     // the row errors normally come from the clusters' second moments (lloyd_iter_kernel); a bit width whose
@@ -2370,7 +2420,6 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
     __syncthreads();
 
     // ---- outputs ------------------------------------------------------------------
-    const int nb = prm.bmax - prm.bmin + 1;
     if (wave == 0) {
         for (int bi = 0; bi < 4; ++bi) {
             if (!bs[bi].active) continue;
@@ -2380,25 +2429,17 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
                 err = 0.0;
                 for (int w2 = 0; w2 < FIN_WAVES; ++w2) err += red[bi * FIN_WAVES + w2];
             }
-            long long obase;
-            if (prm.bits) {
-                if (lane == 0) prm.E[row] = err;
-                obase = row * 16;
-            } else {
-                if (lane == 0 && bs[bi].exact) prm.E[row * nb + (bb - prm.bmin)] = err;
-                continue;       // centroids and bounds were written by lloyd_iter_kernel
-            }
+            const long long obase = row * 16;
+            if (lane == 0) prm.E[row] = err;
             if (lane < Kb) {
                 const int k = bs[bi].idx[lane];
                 const int b0 = bs[bi].B[lane], b1 = bs[bi].B[lane + 1];
                 const float up = (b1 > b0) ? elem_w(keys[b1 - 1]) : -INFINITY;
                 prm.cent[obase + k] = bs[bi].cent[lane];
                 if (prm.upper) prm.upper[obase + k] = up;
-                if (prm.bits) {
-                    thr[lane] = up;
-                    thl[lane] = k;
-                }
-            } else if (prm.bits && lane < 16) {
+                thr[lane] = up;
+                thl[lane] = k;
+            } else if (lane < 16) {
                 prm.cent[obase + lane] = 0.0;
                 if (prm.upper) prm.upper[obase + lane] = -INFINITY;
                 thr[lane] = INFINITY;
@@ -2406,7 +2447,7 @@ __global__ void __launch_bounds__(FIN_THREADS) finish_kernel(ClusterParams prm) 
             }
         }
     }
-    if (prm.bits && prm.labels) {
+    if (prm.labels) {
         __syncthreads();
         // label of a column: the cluster whose value range holds w~ (ranges are
         // disjoint and ordered by position; empty ones have upper = -inf)
@@ -2777,7 +2818,7 @@ skim_status validate_inputs(skim_ctx *ctx, const ClusterParams &prm, int64_t n) 
 size_t sort_lds_bytes(int P) { return (size_t)(P + P / 16) * 8; }
 
 size_t lloyd_lds_bytes(const LevelMap &lm) {
-    const size_t tables = 2 * (size_t)lm.bytes, errors = 128 * sizeof(double);     // the errors at the end lie over the tables
+    const size_t tables = 2 * (size_t)lm.bytes, errors = (128 + 64 + 32) * sizeof(double);     // what the end needs lies over the tables
     return tables > errors ? tables : errors;
 }
 
@@ -2959,7 +3000,7 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
             else pick(std::false_type{});
         }
     }
-    hipLaunchKernelGGL(finish_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, ctx->stream, prm);
+    if (prm.bits) hipLaunchKernelGGL(finish_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, ctx->stream, prm);
     if (ctx->profiling) {
         SKIM_HIP(ctx, hipEventRecord(ctx->ev[2], ctx->stream));
         ctx->ev_valid = 1;
