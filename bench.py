@@ -78,7 +78,7 @@ def counter_child():
 
 def collect_counters(timeout_s=150):
     """rocprofv3 --pmc over `bench.py --counter-child`, one run per counter group.  Returns
-    {kernel: {counter: median value per dispatch}} with kernels 'copy', 'sort', 'lloyd', 'finish', or raises."""
+    {kernel: {counter: median value per dispatch}} with kernels 'copy', 'sort', 'lloyd', or raises."""
     import csv
     import glob
     import shutil
@@ -104,14 +104,14 @@ def collect_counters(timeout_s=150):
             for row in csv.DictReader(open(files[0])):
                 name = row["Kernel_Name"]
                 kern = ("sort" if "sort_kernel" in name else "lloyd" if "lloyd_iter_kernel" in name else
-                        "finish" if "finish_kernel" in name else "copy" if "elementwise" in name else None)
+                        "copy" if "elementwise" in name else None)
                 if kern:
                     vals.setdefault((kern, row["Counter_Name"]), []).append(float(row["Counter_Value"]))
             for (kern, cname), v in vals.items():
                 res.setdefault(kern, {})[cname] = statistics.median(v)
         finally:
             shutil.rmtree(d, ignore_errors=True)
-    for k in ("copy", "sort", "lloyd", "finish"):
+    for k in ("copy", "sort", "lloyd"):
         if k not in res:
             raise RuntimeError(f"no dispatch of the {k} kernel in the counter output")
     return res
@@ -362,7 +362,7 @@ def main():
         copy_bytes = float(n) * m * 4
         ff = copy_bytes / counters["copy"]["FETCH_SIZE"]      # bytes per counter unit, from the copy of known size
         wf = copy_bytes / counters["copy"]["WRITE_SIZE"]
-        byt = {k: counters[k]["FETCH_SIZE"] * ff + counters[k]["WRITE_SIZE"] * wf for k in ("sort", "lloyd", "finish")}
+        byt = {k: counters[k]["FETCH_SIZE"] * ff + counters[k]["WRITE_SIZE"] * wf for k in ("sort", "lloyd")}
         c = counters["sort"]
         rf["traffic"] = round(byt["sort"])
         rf["traffic_source"] = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes of this run (median per dispatch), "
@@ -498,13 +498,13 @@ def bench_scale_loop(ctx, torch, np, skim_synth, iters=3):
             "lfull_error_table_tflops": round(4 * flops / (t_lfull * 1e-3) / 1e12, 2),
             "recluster_ms": round(t_cluster / iters, 4), "layer_loss_ms": round(t_loss / iters, 4),
             # 2 n m^2 flops of the contraction per second of the whole layer-loss call.  The contraction runs on the
-            # bf16 matrix cores with every float32 operand cut into three bfloat16 pieces (the six leading piece
+            # matrix cores with every float32 operand scaled and cut into two binary16 pieces (the three leading piece
             # products per k: float32-grade result); H being symmetric, the loss takes the 256-column blocks on and below
-            # its diagonal: the matrix cores execute 6 x 2 n m^2 flops times (blocks + 1) / (2 blocks)
+            # its diagonal: the matrix cores execute 3 x 2 n m^2 flops times (blocks + 1) / (2 blocks)
             "layer_loss_tflops": round(flops / (t_loss / iters * 1e-3) / 1e12, 2),
-            "layer_loss_executed_bf16_tflops": round(loss_share * 6 * flops / (t_loss / iters * 1e-3) / 1e12, 1),
-            "mfma_bf16_peak_tflops": 2500.0,
-            "layer_loss_frac_of_mfma_peak": round(loss_share * 6 * flops / (t_loss / iters * 1e-3) / 1e12 / 2500.0, 4),
+            "layer_loss_executed_f16_tflops": round(loss_share * 3 * flops / (t_loss / iters * 1e-3) / 1e12, 1),
+            "mfma_f16_peak_tflops": 2500.0,
+            "layer_loss_frac_of_mfma_peak": round(loss_share * 3 * flops / (t_loss / iters * 1e-3) / 1e12 / 2500.0, 4),
             "mfma_f32_peak_tflops": MFMA_F32_PEAK_TFLOPS,
             "layer_loss_over_f32_mfma_peak": round(flops / (t_loss / iters * 1e-3) / 1e12 / MFMA_F32_PEAK_TFLOPS, 4),
             "loss_after_each_iteration": losses}
