@@ -301,11 +301,12 @@ skim_status skim_hessian_from_activations_scratch(skim_ctx *ctx, const uint16_t 
  *   loss = tr(dW H dW^T) = sum_i dW_i H dW_i^T  (Sec. 3.4, L-full; H ~ X X^T)
  * H: dev m x m float32.  labels: dev uint8 n x m.  loss: dev
  * float64 scalar.  row_loss: dev float64[n] (the L-full error of each channel),
- * may be NULL.  The contraction dW*H accumulates in float32 on the matrix cores: both operands are scaled by
- * powers of two (per channel of H, per row of dW) and cut into two binary16 pieces of 23 bits together, and the three
- * leading piece products taken per k (what is dropped is at most 2^-22 of each product, 2^-25 in the mean square; an entry of dW
- * that, weighed by its channel's scale, is below 2^-16 of the largest of its row loses digits, its error staying below 2^-39 of that
- * one, and so does an H_jl below 2^-15 of the largest its channels allow).  The loss takes the diagonal of H in float64.
+ * may be NULL.  The diagonal of H is taken in float64.  The rest of the contraction dW*H accumulates in float32 on the
+ * matrix cores: both operands are scaled by powers of two (per channel of H, from its largest coupling to another channel; per row of
+ * dW) and cut into two binary16 pieces of 23 bits together, and the three leading piece products taken per k (what is dropped is at
+ * most 2^-22 of each product, for operands of many digits 2^-25 in the mean square).  An entry of dW that, weighed by its channel's
+ * scale, is below 2^-16 of the largest of its row loses digits, its error staying below 2^-39 of that one, and so does an H_jl below
+ * 2^-15 of the largest its channels allow; a channel without couplings neither loses digits nor costs others any.
  * Half of the products are taken, with the mean of H and its transpose (for a symmetric H, as the H
  * of Sec. 3.4 is, that is H; for another one the loss is the same).  The final reductions are
  * float64.  m must be a multiple of 16. */
@@ -338,7 +339,9 @@ skim_status skim_error_table_lfull(skim_ctx *ctx, const float *W, const float *S
  * and an Adam update of alpha / adam_m / adam_v (dev float32[m], in place).
  * t is the 1-based step number (selects the decayed learning rate and the bias
  * correction).  loss_before: dev float64 scalar (loss at the incoming alpha).
- * grad_out: dev float32[m], may be NULL.  H must be symmetric: the gradient is formed for such an H, and for m a
+ * grad_out: dev float32[m], may be NULL.  The products dW*H behind both are formed as in skim_layer_loss, the share of H's diagonal
+ * in float64: the digits that weakly driven channels lose in their couplings (see there) are missing from their entries of the gradient.
+ * H must be symmetric: the gradient is formed for such an H, and for m a
  * multiple of 32 from 128 up row j of H is read for its column j. */
 skim_status skim_scale_step(skim_ctx *ctx, const float *W, const float *S, const float *H,
                             int64_t n, int64_t m, int64_t ld, const uint8_t *labels, float *alpha,
@@ -354,7 +357,8 @@ skim_status skim_scale_step(skim_ctx *ctx, const float *W, const float *S, const
  * t0, t0+1, ... across the rounds; alpha, adam_m, adam_v: dev float32[m], in/out.
  * labels: dev uint8 n x m (out), centroids: dev float64 n x 16 (out).
  * loss_trace: dev float64[outer*steps + 1]: the loss before every step, then the loss
- * at the returned alpha.  Limits of skim_layer_loss apply (m multiple of 16, H aligned). */
+ * at the returned alpha.  Limits of skim_layer_loss apply (m multiple of 16, H aligned), and the arithmetic is that of
+ * skim_scale_step. */
 skim_status skim_train_scale(skim_ctx *ctx, const float *W, const float *S, const float *H,
                              int64_t n, int64_t m, int64_t ld, const uint8_t *bits,
                              int kmeans_iters, int outer, int steps, int64_t t0,

@@ -5,7 +5,8 @@
 //   c_ik  = sum_{j in k} s~_ij w~_ij / sum_{j in k} s~_ij      (calc_centroids(W*alpha^-1, L))
 //   dW_ij = w_ij - alpha_j c_{i,L_ij}                           (W - replace(c, L) * alpha)
 //   P     = dW H            matrix cores, float32 accumulation (the path's one dense contraction): fp16 MFMA on
-//                           two-piece splits of the scaled float32 operands; where only the loss is wanted, half of it
+//                           two-piece splits of the scaled float32 operands; where only the loss is wanted, half of it.
+//                           The diagonal of H in float64
 //   loss  = sum_ij P_ij dW_ij                                   float64 reduction
 //   dloss/dalpha_l = -2 sum_i [ P_il c_{i,L_il}
 //                    + Q_{i,L_il} s_il (w_il - 2 alpha_l c_{i,L_il}) / D_{i,L_il} ],
@@ -29,17 +30,26 @@ __device__ __forceinline__ void split2(float x, uint32_t &p1, uint32_t &p2) {
 }
 __device__ __forceinline__ float piece_f32(uint32_t h) { return (float)__builtin_bit_cast(_Float16, (uint16_t)h); }
 
+// The diagonal of H stays out of the pieces: its share of the loss and of P is added up in float64 (row_prep_kernel, grad_rows_kernel).
+// What a weak channel's column of P mostly is -- its own dW_il H_ll -- thus keeps its digits however strong the other channels are.
 // The scales, powers of two, which cost no digits.  binary16 has little range, so both operands are balanced first:
-//   e_j   half the exponent of the largest magnitude in row j and column j of H.  |H_jl| <= min(max_j, max_l), so
-//         H''_jl = H_jl 2^(H_SHIFT - e_j - e_l) lies below 2^15, whatever H is; for an H of activations it is their correlation
-//         matrix times 2^H_SHIFT, within a factor of two.
+//   e_j   half the exponent of the largest finite magnitude in row j and column j of H, the diagonal aside (-63 where there is none: a
+//         channel without couplings takes no part in the scales of the others).  |H_jl| <= min(max_j, max_l) for j != l, so
+//         H''_jl = H_jl 2^(H_SHIFT - e_j - e_l) lies below 2^15, whatever H is; for an H of activations that are alike coupled it is
+//         their correlations times 2^H_SHIFT over the largest one, within a factor of two.
 //   r_i   the exponent of the largest dW_ij 2^e_j of row i; dW''_ij = dW_ij 2^(e_j - r_i + D_SHIFT) lies below 2^15.
-//   P_il  = 2^(r_i + e_l - H_SHIFT - D_SHIFT) sum_j dW''_ij H''_jl
-//   dW_i H dW_i^T = 2^(2 (r_i - D_SHIFT) - H_SHIFT) sum_jl dW''_ij H''_jl dW''_il
-// Digits are lost where an entry is 2^16 times smaller than the largest of its row of dW'' (or a correlation below 2^-15), and
-// what such an entry loses is below 2^-39 of that largest one.
+//   P_il  = 2^(r_i + e_l - H_SHIFT - D_SHIFT) sum_j dW''_ij H''_jl  +  dW_il H_ll
+//   dW_i H dW_i^T = 2^(2 (r_i - D_SHIFT) - H_SHIFT) sum_jl dW''_ij H''_jl dW''_il  +  sum_l dW_il^2 H_ll
+// Digits are lost where an entry is 2^16 times smaller than the largest of its row of dW'' (or a coupling 2^15 times smaller than the
+// largest its channels allow), and what such an entry loses is below 2^-39 of that largest one.
 constexpr int H_SHIFT = 14, D_SHIFT = 15;
-__device__ __forceinline__ int h_exponent(uint32_t max_bits) { return ((int)(max_bits >> 23) - 126) >> 1; }      // -63 .. 64; max < 2^(2 e + 2)
+__device__ __forceinline__ int h_exponent(uint32_t max_bits) { return ((int)(max_bits >> 23) - 126) >> 1; }      // -63 .. 64; max < 2^(2 e + 1)
+// bits of |h| for the maximum over couplings: the diagonal and what is not finite don't count (an infinity or NaN then stays with the
+// columns and rows of P that meet it)
+__device__ __forceinline__ uint32_t coupling_bits(float h, bool diagonal) {
+    const uint32_t b = __float_as_uint(h) & 0x7FFFFFFFu;
+    return diagonal || b >= 0x7F800000u ? 0u : b;
+}
 __device__ __forceinline__ int value_exponent(float x) { return x == 0.0f ? -1024 : __builtin_amdgcn_frexp_expf(x); }      // |x| < 2^this
 
 // Layout of a split matrix ("planes"): groups of 4 rows; a group holds, for every block of 16 k, its 4 rows' [piece 1 (16) |
@@ -86,8 +96,8 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *p, bool vec) {
 //   SPLIT_ROWS     row j of the planes = row j of H (its column j where H is symmetric)
 //   SPLIT_COLUMNS  row j of the planes = column j of H
 //   SPLIT_LOWER    what the loss needs: the columns up to the end of the 256-column block that holds j; those ahead of the
-//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself).  The
-//                  diagonal is left out: row_prep_kernel adds its share of the loss up in float64
+//                  block are the mean of H and its transpose (dW_i H dW_i^T is that of the mean; with H symmetric, H itself)
+// The diagonal is left out of all of them.
 // A workgroup takes 64 rows x 32 k; the transposed tile goes through LDS, so both are read in whole lines.
 enum SplitMode { SPLIT_ROWS, SPLIT_COLUMNS, SPLIT_LOWER };
 constexpr int SPLIT_J = 64, SPLIT_K = 32, SPLIT_THREADS = 256;
@@ -127,11 +137,9 @@ __device__ __forceinline__ void split_tile(const float *__restrict__ H, long lon
             x[e] = (mode == SPLIT_COLUMNS || x[e] == y) ? y : 0.5f * x[e] + 0.5f * y;
         }
     }
-    if (mode == SPLIT_LOWER) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (k + e == j) x[e] = 0.0f;
-    }
+    for (int e = 0; e < 8; ++e)
+        if (k + e == j) x[e] = 0.0f;
     const uint4 ma = *(const uint4 *)(hmax + k), mb = *(const uint4 *)(hmax + k + 4);
     const uint32_t mk[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
     const int ej = H_SHIFT - h_exponent(hmax[j]);
@@ -151,7 +159,7 @@ __global__ void __launch_bounds__(SPLIT_THREADS) split_rows_kernel(const float *
     split_tile(H, m, hmax, Hp, mode, blockIdx.x, tr);
 }
 
-// hdiag = the diagonal of H; hmax[j] = bits of the largest magnitude in row j and column j of H (bits of magnitudes order like the magnitudes).
+// hdiag = the diagonal of H; hmax[j] = bits of the largest coupling in row j and column j of H (bits of magnitudes order like the magnitudes).
 // Short matrices: a workgroup works out 16 of them, no atomics between workgroups and nothing to clear.
 constexpr int HMAX_DIRECT = 1024;
 __global__ void __launch_bounds__(256) hmax_direct_kernel(const float *__restrict__ H, int m, uint32_t *__restrict__ hmax, float *__restrict__ hdiag) {
@@ -162,8 +170,8 @@ __global__ void __launch_bounds__(256) hmax_direct_kernel(const float *__restric
     uint32_t r = 0u, c = 0u;
 #pragma unroll 4
     for (int k = 0; k < m; k += 16) {
-        r = max(r, __float_as_uint(fabsf(H[(long long)(j0 + b) * m + k + a])));
-        c = max(c, __float_as_uint(fabsf(H[(long long)(k + b) * m + j0 + a])));
+        r = max(r, coupling_bits(H[(long long)(j0 + b) * m + k + a], j0 + b == k + a));
+        c = max(c, coupling_bits(H[(long long)(k + b) * m + j0 + a], j0 + a == k + b));
     }
     atomicMax(&top[b], r);
     atomicMax(&top[a], c);
@@ -192,7 +200,8 @@ __global__ void __launch_bounds__(256) hmax_kernel(const float *__restrict__ H, 
     uint32_t mine = 0u;          // lane i < 16: the largest of row j0 + i
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const uint32_t b[4] = {__float_as_uint(fabsf(x[i].x)), __float_as_uint(fabsf(x[i].y)), __float_as_uint(fabsf(x[i].z)), __float_as_uint(fabsf(x[i].w))};
+        const uint32_t b[4] = {coupling_bits(x[i].x, k == j0 + i), coupling_bits(x[i].y, k + 1 == j0 + i), coupling_bits(x[i].z, k + 2 == j0 + i),
+                               coupling_bits(x[i].w, k + 3 == j0 + i)};
         uint32_t r = 0u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -477,10 +486,12 @@ __global__ void __launch_bounds__(64 * ROWP_ROWS * WPR) __attribute__((amdgpu_wa
 // products of pieces, each exact in float32.  The three with p1 q1, p1 q2, p2 q1 carry everything but p2 q2, at most 2^-22
 // of |x y| and 2^-25 in the mean square, of either sign.  v_mfma_f32_32x32x16_f16 does one of them for 16 k in 32 clocks: 96, where
 // the six leading products of three bfloat16 pieces took 192 and v_mfma_f32_32x32x2_f32 takes 512.  Accumulation is float32 in the
-// matrix core either way; half as many roundings of the sums make up for the last bit of the operands.  Against float64,
-// relative 2-norms of P here / with three bfloat16 pieces: 512 columns 1.8 / 2.2e-7, 1552 1.5 / 2.2e-7, 4096 2.2 / 2.4e-7, 8192 2.8 / 3.3e-7
-// (channels correlated through 8 common factors: 2.2 / 1.9e-7, 2.0 / 2.1e-7, 2.7 / 3.0e-7, 3.7 / 4.2e-7); rms of the row losses, whose
-// diagonal part is left to float64: 512 columns 0.2 / 6.0e-8, 4096 0.4 / 6.1e-8 (correlated: 7.0e-8 / 1.0e-7, 1.3e-7 / 1.8e-7).
+// matrix core either way.  Half as many roundings of the sums and a diagonal that is left to float64 outweigh the last bit of the
+// operands.  Against float64, relative 2-norms here / with three bfloat16 pieces and the diagonal among them, channels of calibration
+// activations: P 0.08 / 2.2e-7 at 512 columns, 0.15 / 2.2e-7 at 1552, 0.26 / 1.9e-7 at 4096, 0.63 / 3.3e-7 at 8192; gradient 0.25 / 1.7e-7, 0.23 /
+// 2.5e-7, 0.23 / 1.6e-7, 0.27 / 3.1e-7; row losses 0.02 / 0.6e-7 to 0.06 / 0.7e-7.  Channels correlated through 8 common factors: P 1.3 / 1.9e-7,
+// 1.7 / 2.1e-7, 2.0 / 2.2e-7, 3.5 / 4.2e-7; gradient 0.7 / 1.5e-7, 0.7 / 1.2e-7, 1.1 / 1.8e-7, 2.3 / 3.6e-7; row losses 0.7 / 1.1e-7 to 2.0 / 2.6e-7.
+// (The diagonal among the pieces here too: correlated channels, 512 columns, P 2.2e-7, gradient 2.0e-7: further off than with three pieces.)
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) half8_t lds_half8;
 constexpr int G_THREADS = 512;                     // 8 wavefronts, two per SIMD: 2 x 4, each 128 x 64 of the 256 x 256 tile
@@ -628,7 +639,7 @@ __device__ __forceinline__ void tile_place(int t, int rows, int tj, int &i, int 
 // What bounds it: the power the matrix cores draw.  4096^3: 0.31 ms = 1.32 PFLOP/s of executed piece products (a bf16
 // product of the same size by the library: 1.10), MFMAs busy 84 % of the cycles at 1.66 GHz instead of 2.4, no bank
 // conflicts.  Six products of bfloat16 pieces: 0.54 ms.
-// P = dW H, tile by tile as the plan says: a whole tile goes straight into P, a part of a split one into its slot.
+// P = dW H (H without its diagonal), tile by tile as the plan says: a whole tile goes straight into P, a part of a split one into its slot.
 __global__ void __launch_bounds__(G_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 dwh_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp, const int *__restrict__ rexp, const uint32_t *__restrict__ hmax,
            long long n, long long m, int tj, TilePlan plan, float *__restrict__ P, floatx4 *__restrict__ slots) {
@@ -849,34 +860,36 @@ __global__ void __launch_bounds__(1024) loss_total_kernel(const double *rows, lo
     }
 }
 
-// Gradient terms.  One workgroup walks STRIP consecutive rows; per row it forms
+// Gradient terms.  P here is what dwh_kernel leaves (P without the diagonal's share) plus dW_ij H_jj, in float64.
+// One workgroup walks STRIP consecutive rows; per row it forms
 // Q_ik = sum_{j in k} P_ij alpha_j (LDS bins as in row_prep_kernel), then adds each column's term to the
 // thread's private column sums.  A thread owns the columns tid, tid + 256, ...: with REG (m <= 16 * 256)
 // their sums, alpha and the row's P and labels stay in registers, so a row is read from HBM once;
 // otherwise the sums live in gpart and the row is read twice.  gpart[strip][l] is reduced over the strips
-// afterwards.  The strip's share of the loss, sum P_ij dW_ij with dW as row_prep_kernel forms it, falls out on the way.
+// afterwards.  The strip's share of the loss, sum P_ij dW_ij, falls out on the way.
 constexpr int GRAD_NC = 16;
 
-template <bool REG>
+template <bool REG, bool VEC>
 __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) grad_rows_kernel(const float *W, const float *S, const float *alpha,
                                                                  long long n, long long m, long long ld,
-                                                                 const uint8_t *labels, const float *P,
+                                                                 const uint8_t *labels, const float *P, const float *hdiag,
                                                                  const double *cent, const double *Den,
-                                                                 double *gpart, double *lossp, bool vec4) {
+                                                                 double *gpart, double *lossp) {
     __shared__ double lsum[4];
     double lacc = 0.0;
     __shared__ double binQ[BIN_SETS][16];
-    __shared__ double rsh[16], csh[16];
+    __shared__ double rsh[16], cshs[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long r0 = (long long)blockIdx.x * STRIP;
     double *gp = gpart + (long long)blockIdx.x * m;
     double gacc[GRAD_NC];
     float al[GRAD_NC];
-    // The columns of a thread (REG): tid, tid + 256, ... -- or, when the rows can be read 16 bytes at a time (vec4),
+    __shared__ __align__(16) float hds[REG ? GRAD_NC : 1][PREP_THREADS];      // a thread's diagonal entries (it alone reads them)
+    // The columns of a thread (REG): tid, tid + 256, ... -- or, when the rows can be read 16 bytes at a time (VEC),
     // four groups of four neighbouring columns 4 (tid + 256 q) .. + 3: a quarter of the load instructions, and a
     // row then arrives in a third of the time.
     auto colof = [&](int c) -> long long {
-        return vec4 ? 4ll * (tid + (long long)(c >> 2) * PREP_THREADS) + (c & 3) : tid + (long long)c * PREP_THREADS;
+        return VEC ? 4ll * (tid + (long long)(c >> 2) * PREP_THREADS) + (c & 3) : tid + (long long)c * PREP_THREADS;
     };
     if (REG) {
 #pragma unroll
@@ -884,28 +897,34 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
             const long long l = colof(c);
             gacc[c] = 0.0;
             al[c] = l < m ? alpha[l] : 0.0f;
+            hds[c][tid] = l < m ? hdiag[l] : 0.0f;
         }
     } else {
         for (long long l = tid; l < m; l += PREP_THREADS) gp[l] = 0.0;
     }
     double *myQ = binQ[wave * BIN_COPIES + (lane & (BIN_COPIES - 1))];
+    // a row's centroids are requested while the row before it is worked on
+    double cen_k = tid < 16 ? cent[r0 * 16 + tid] : 0.0;
     for (long long row = r0; row < min(n, r0 + STRIP); ++row) {
+        double *csh = cshs[row & 1];
         const float *Pr = P + row * m;
         const uint8_t *Lr = labels + row * m;
         const float *Wr = W + row * ld, *Sr = S + row * ld;
         (&binQ[0][0])[tid] = 0.0;
-        // the row's cluster masses and centroids are requested now by the 16 threads that need them between the
+        // the row's cluster masses are requested now by the 16 threads that need them between the
         // barriers below, where every other thread waits for them
-        double den_k = 0.0, cen_k = 0.0;
+        double den_k = 0.0;
         if (tid < 16) {
             den_k = Den[row * 16 + tid];
-            cen_k = cent[row * 16 + tid];
+            csh[tid] = cen_k;
+            if (row + 1 < min(n, r0 + STRIP)) cen_k = cent[(row + 1) * 16 + tid];
         }
-        __syncthreads();      // bins cleared; the previous row's rsh/csh are no longer read
+        __syncthreads();      // bins cleared; the previous row's rsh is no longer read
         float pv[GRAD_NC], wv[GRAD_NC], sv[GRAD_NC];
+        double pd[GRAD_NC];
         int lv[GRAD_NC];
         if (REG) {
-            if (vec4) {
+            if constexpr (VEC) {
 #pragma unroll
                 for (int q = 0; q < GRAD_NC / 4; ++q) {
                     const long long l = colof(4 * q);
@@ -935,33 +954,41 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
                 }
             }
 #pragma unroll
-            for (int c = 0; c < GRAD_NC; ++c)
-                if (colof(c) < m) atomicAdd(&myQ[lv[c]], (double)pv[c] * (double)al[c]);
+            for (int c = 0; c < GRAD_NC; ++c) asm("" : "+v"(pv[c]), "+v"(wv[c]), "+v"(sv[c]));      // (not converted to doubles until used: registers)
+#pragma unroll
+            for (int c = 0; c < GRAD_NC; ++c) {
+                const double dw = (double)wv[c] - (double)al[c] * csh[lv[c]];
+                pd[c] = fma(dw, (double)hds[c][tid], (double)pv[c]);
+                lacc = fma(pd[c], dw, lacc);        // (columns past the row: all zero)
+                if (colof(c) < m) atomicAdd(&myQ[lv[c]], pd[c] * (double)al[c]);
+            }
         } else {
-            for (long long j = tid; j < m; j += PREP_THREADS)
-                atomicAdd(&myQ[Lr[j] & 15], (double)Pr[j] * (double)alpha[j]);
+            for (long long j = tid; j < m; j += PREP_THREADS) {
+                const int k = Lr[j] & 15;
+                const double a = (double)alpha[j], dw = (double)Wr[j] - a * csh[k], p = fma(dw, (double)hdiag[j], (double)Pr[j]);
+                lacc = fma(p, dw, lacc);
+                atomicAdd(&myQ[k], p * a);
+            }
         }
         __syncthreads();
         if (tid < 16) {
             const double q = bin_total(binQ, tid), d = den_k;
             rsh[tid] = d > 0.0 ? q / d : 0.0;
-            csh[tid] = cen_k;
         }
         __syncthreads();
         if (REG) {
 #pragma unroll
             for (int c = 0; c < GRAD_NC; ++c) {
                 const double a = (double)al[c], cc = csh[lv[c]];
-                const double term = (double)pv[c] * cc + rsh[lv[c]] * (double)sv[c] * ((double)wv[c] - 2.0 * a * cc);
+                const double term = pd[c] * cc + rsh[lv[c]] * (double)sv[c] * ((double)wv[c] - 2.0 * a * cc);
                 gacc[c] += -2.0 * term;
-                lacc += (double)pv[c] * (double)(float)((double)wv[c] - a * cc);       // (columns past the row: P = 0)
             }
         } else {
             for (long long l = tid; l < m; l += PREP_THREADS) {
                 const int k = Lr[l] & 15;
                 const double a = (double)alpha[l], cc = csh[k];
-                const double term = (double)Pr[l] * cc + rsh[k] * (double)Sr[l] * ((double)Wr[l] - 2.0 * a * cc);
-                lacc += (double)Pr[l] * (double)(float)((double)Wr[l] - a * cc);
+                const double p = fma((double)Wr[l] - a * cc, (double)hdiag[l], (double)Pr[l]);
+                const double term = p * cc + rsh[k] * (double)Sr[l] * ((double)Wr[l] - 2.0 * a * cc);
                 gp[l] += -2.0 * term;   // the same thread owns column l for every row of the strip
             }
         }
@@ -1023,9 +1050,9 @@ __global__ void __launch_bounds__(ADAM_COLS * ADAM_GROUPS) adam_kernel(const dou
 }
 
 struct LossWs {
-    float *P;
+    float *P;                // dW H without the diagonal of H
     uint16_t *dWp, *Hp;      // pieces of dW and of H
-    uint32_t *hmax;          // largest magnitudes of H (their scales)
+    uint32_t *hmax;          // largest couplings of H (the channels' scales)
     float *hdiag;            // the diagonal of H
     int *rexp;               // exponents of the rows of dW
     double *rdiag;           // the rows' losses on the diagonal
@@ -1240,14 +1267,14 @@ skim_status scale_step_impl(skim_ctx *ctx, const float *W, const float *S, const
     }
     // rows of W, S, P start 16-byte aligned and the labels of a row 4-byte aligned (m is a multiple of 16)
     const bool vec4 = rows_vec4(W, S, alpha, labels, ld) && ((uintptr_t)w.P & 15) == 0;
-    if (m <= (int64_t)GRAD_NC * PREP_THREADS)
-        hipLaunchKernelGGL(grad_rows_kernel<true>, dim3(w.nstrip), dim3(PREP_THREADS), 0, ctx->stream, W, S,
-                           (const float *)alpha, (long long)n, (long long)m, (long long)ld, labels, w.P, w.cent, w.Den,
-                           w.gpart, w.lossp, vec4);
-    else
-        hipLaunchKernelGGL(grad_rows_kernel<false>, dim3(w.nstrip), dim3(PREP_THREADS), 0, ctx->stream, W, S,
-                           (const float *)alpha, (long long)n, (long long)m, (long long)ld, labels, w.P, w.cent, w.Den,
-                           w.gpart, w.lossp, false);
+    auto grad = [&](auto reg, auto vec) {
+        hipLaunchKernelGGL((grad_rows_kernel<decltype(reg)::value, decltype(vec)::value>), dim3(w.nstrip), dim3(PREP_THREADS), 0, ctx->stream, W, S,
+                           (const float *)alpha, (long long)n, (long long)m, (long long)ld, labels, (const float *)w.P, (const float *)w.hdiag,
+                           (const double *)w.cent, (const double *)w.Den, w.gpart, w.lossp);
+    };
+    if (m > (int64_t)GRAD_NC * PREP_THREADS) grad(std::false_type{}, std::false_type{});
+    else if (vec4) grad(std::true_type{}, std::true_type{});
+    else grad(std::true_type{}, std::false_type{});
     const double lr = (double)opts->lr0 * pow((double)opts->decay, (double)((t - 1) / opts->decay_every));
     const double bc1 = 1.0 - pow((double)opts->beta1, (double)t), bc2 = 1.0 - pow((double)opts->beta2, (double)t);
     hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((m + ADAM_COLS - 1) / ADAM_COLS) + 1u), dim3(ADAM_COLS * ADAM_GROUPS), 0, ctx->stream, w.gpart, w.nstrip,
