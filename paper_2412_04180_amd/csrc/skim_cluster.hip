@@ -297,6 +297,9 @@ __device__ __forceinline__ double lane_below(double x) {
 __device__ __forceinline__ double lane_above(double x) {
     return __hiloint2double(lane_above(__double2hiint(x)), lane_above(__double2loint(x)));
 }
+__device__ __forceinline__ double read_lane63(double x) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63), __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
 // Sum over the four lanes of a quad; every lane of the quad gets the same bits.
 __device__ __forceinline__ double quad_sum(double x) {
     x += dpp_move_d<0xB1>(x);  // quad_perm [1,0,3,2]
@@ -1317,9 +1320,11 @@ __global__ void __launch_bounds__(MG_THREADS) merge_tile_kernel(ClusterParams pr
 // Sums over whole 16-key chunks.  Level 0 = chunk sums (global memory, written by the sort); level 1 = groups of
 // 4 chunks (64 keys).  For sum s and sum s*w a workgroup keeps, per row, the running sums ahead of every group in
 // LDS as double-double numbers (an unevaluated pair hi + lo, about 106 bits): the sum over a range of groups is the
-// difference of two of them, exact to about 2^-104 of the row total, so a cluster of tiny mass next to a heavy
-// element keeps full relative precision (a difference of plain float64 running sums would not).  The second
+// difference of two of them, exact to about 2^-104 of the row total, so a cluster of small mass next to a heavy
+// element keeps full relative precision (a difference of plain float64 running sums would not).  A range of less than 2^-40 of the
+// total (THIN_SHARE) is added up directly.  The second
 // moments (sum s*w*w), needed once at the end, form a radix-4 tree: level 1 in global memory, levels >= 2 in LDS.
+constexpr double THIN_SHARE = 0x1p-40;
 struct LevelMap {
     int nlev;        // levels 0 .. nlev-1 of the second-moment tree
     int n[8];        // entries per level
@@ -1377,7 +1382,7 @@ __host__ __device__ inline LevelMap level_map_resident(int m, int G) {
     L.t3_off = n3 > 1 ? o : 0;
     if (n3 > 1) o += 32;
     L.ppd_off = o = (o + 15) & ~15;
-    o += (L.np + 1) * 16;
+    o += (L.np + 2) * 16;                   // (one more: nonzero where a piece has less than THIN_SHARE of the row's mass, but some)
     L.ppn_off = o;
     o += (L.np + 1) * 16;
     for (int k = 2; k < 8; ++k) {
@@ -1502,6 +1507,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     const int ng = LM.n[1];
     // groups of 4 chunks per lane: at most 8 (rows of up to 32768 keys); whole groups of 16 chunks where those count
     const int per = WIDE ? 4 * ((LM.np + ITER_THREADS - 1) / ITER_THREADS) : (ng + ITER_THREADS - 1) / ITER_THREADS;
+    bool thin_groups[2] = {false, false};      // G == 0: the row has groups of less than THIN_SHARE of its mass, but some
     double2 qv[2][8];
     float t8[2][8];
     double rq4[2][4];
@@ -1574,6 +1580,10 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                         mn = dd_add(mn, make_double2(qv[hh][k].y, 0.0));
                     }
                     const double2 id = dd_wave_scan_incl(md), in = dd_wave_scan_incl(mn);
+                    uint32_t least = ~0u;      // (as below for pieces)
+#pragma unroll
+                    for (int k = 0; k < N; ++k) least = min(least, (uint32_t)__double2hiint(qv[hh][k].x) - 1u);
+                    thin_groups[hh] = __ballot(least < (uint32_t)__double2hiint(THIN_SHARE * read_lane63(id.x))) != 0;
                     // sums of the lanes below: the inclusive sums shifted up by one lane
                     double2 rd = make_double2(lane_below(id.x), lane_below(id.y));
                     double2 rn = make_double2(lane_below(in.x), lane_below(in.y));
@@ -1633,6 +1643,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             // own sums wait in its place of ppd.
             const int each = ((np + 63) / 64) | 1, c0 = lane * each;
             double2 rd = make_double2(0.0, 0.0), rn = rd;
+            uint32_t least = ~0u;                    // upper word less one of the least of its pieces' sums, those without mass last
             for (int k = 0; k < each; ++k) {
                 const int c = c0 + k;
                 const u64x2 *kp = (const u64x2 *)(kw + (size_t)min(c, np - 1) * G);
@@ -1648,11 +1659,14 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 }
                 if (c < np) {
                     ppdw[c] = make_double2(d, nn);
+                    least = min(least, (uint32_t)__double2hiint(d) - 1u);
                     rd = dd_add(rd, make_double2(d, 0.0));
                     rn = dd_add(rn, make_double2(nn, 0.0));
                 }
             }
             const double2 id = dd_wave_scan_incl(rd), in = dd_wave_scan_incl(rn);
+            const u64 thin_piece = __ballot(least < (uint32_t)__double2hiint(THIN_SHARE * read_lane63(id.x)));
+            if (lane == 0) ppdw[np + 1] = make_double2(thin_piece ? 1.0 : 0.0, 0.0);
             // sums of the lanes below: the inclusive sums shifted up by one lane
             rd = make_double2(lane_below(id.x), lane_below(id.y));
             rn = make_double2(lane_below(in.x), lane_below(in.y));
@@ -1856,6 +1870,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     // ranks, inside the same 16 keys, and then the lane asks the memory system for nothing
     u64 el[CH];
     int cl_held = -2;
+    const u64 thin_rows = __ballot(G > 0 ? ppd[LM.np + 1].x != 0.0 : (h ? thin_groups[1] : thin_groups[0]));      // (nearly always none)
     // so do the sums over the whole chunks between the boundary chunks [a0_held, b0_held)
     int a0_held = 0, b0_held = 0;
     double midD = 0.0, midN = 0.0;
@@ -2002,6 +2017,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             const double2 da = ppd[a0], db = ppd[b0], na = ppn[a0], nb = ppn[b0];
             midD = dd_diff(db, da);
             midN = dd_diff(nb, na);
+            if (__builtin_expect(thin_rows != 0, 0)) {
+                const bool thin = ((thin_rows >> lane) & 1) && b0 > a0 && midD < THIN_SHARE * ppd[b0].x;
+                double d = 0.0, nn = 0.0;
+                for (int j = thin ? a0 * CH : m; j < min(b0 * CH, m); ++j) {
+                    const u64 e = lkeys[j];
+                    d += (double)plain_s(e);
+                    nn = fma((double)plain_s(e), (double)elem_w(e), nn);
+                }
+                if (thin) {
+                    midD = d;
+                    midN = nn;
+                }
+            }
         } else {
             reload = cl_want != cl_held;
         }
@@ -2049,6 +2077,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 if (WIDE) {
                     sD += pq[k].x;
                     sN += pq[k].y;
+                }
+            }
+            if (__builtin_expect(thin_rows != 0, 0)) {
+                const bool thin = ((thin_rows >> lane) & 1) && resum && gb > ga && sD < THIN_SHARE * ppd[gb].x;
+                double d = 0.0, nn = 0.0;
+                for (int c = thin ? a0 : b0; c < b0; ++c) {
+                    const double2 x = L1[c];
+                    d += x.x;
+                    nn += x.y;
+                }
+                if (thin) {
+                    sD = d;
+                    sN = nn;
                 }
             }
             if (resum) {

@@ -770,3 +770,35 @@ def test_rows_shared_out_by_claims_or_in_fixed_shares(ctx, n, m):
     k = min(n, 64)
     assert torch.equal(first["upper_all"][:k], alone["upper_all"][:k])
     assert torch.equal(first["upper_all"], first["upper_all"][:300].repeat(reps, 1)[:n])
+
+
+# (pieces of 4 keys with three and four levels of the search tree, pieces of 8; even and odd rows of a workgroup)
+@pytest.mark.parametrize("n,m,tiled", [(41, 512, 41), (40, 1003, 6600), (7, 3000, 1100), (5, 6007, 600), (5, 13001, 5)])
+def test_clusters_of_tiny_mass_beside_a_heavy_element(ctx, n, m, tiled):
+    """Rows whose sensitivities differ by up to 1e34, kept in LDS and (with more of them, or longer ones) not: the light clusters are
+    smaller than the last digit of the running sums' low word where that holds something in between, and their sums must not come from
+    a difference of two of those.  Against the oracle."""
+    rng = np.random.default_rng(m)
+    W, S = skim_synth.make_ws_small(77 + m, n, m)
+    S = S + np.float32(0.01)
+    order = np.argsort(W, axis=1)
+    for i in range(n):
+        heavy = order[i, rng.integers(m // 4, 3 * m // 4)]
+        if i % 4 == 0:                      # heavy, in between, light
+            S[i, heavy] = 1e32
+            S[i, order[i, : 32]] *= np.float32(1e17)
+        elif i % 4 == 1:
+            S[i] *= np.float32(1e-12)
+            S[i, order[i, m // 2: m // 2 + 16]] = rng.uniform(1e20, 2e20, 16)
+            S[i, order[i, : m // 8]] *= np.float32(1e16)
+        elif i % 4 == 2:                    # everything below the median light, the rest of many magnitudes
+            S[i, order[i, : m // 2]] *= np.float32(1e-34)
+            S[i, order[i, m // 2:]] = np.float32(10.0) ** rng.uniform(-24, 6, m - m // 2)
+        else:                               # 1e-6 of everything, and keys without mass
+            S[i, heavy] = 1e9
+            S[i, rng.random(m) < 0.3] = 0.0
+    _, _, excused = check_table(ctx, W, S)
+    assert excused <= n // 8
+    check_rows(ctx, W, S, rng.integers(1, 5, n).astype(np.uint8))
+    reps = -(-tiled // n)
+    check_table(ctx, np.tile(W, (reps, 1)), np.tile(S, (reps, 1)))
