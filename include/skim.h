@@ -24,6 +24,11 @@
  *     There is no CPU fallback: without a usable GPU, skim_create fails.
  *   - Inputs must be finite, S >= 0, alpha > 0.  Violations are not detected.
  *   - Calls on one context must not overlap in time (they share the workspace).
+ *   - The same call on the same inputs gives the same bits.  The clustering of a
+ *     row does not depend on the other rows, but how its sums are ordered depends
+ *     on their number: centroids and errors of a row that is clustered among
+ *     others, or in blocks of rows, may differ in their last digits (1e-13), and
+ *     with them a codebook entry or an allocation that is a tie to that precision.
  *
  * Labels and cluster order.  Cluster k of a row (k = 0 .. 2^b - 1) is the k-th
  * starting centroid, taken at ascending weighted quantiles of the row; a

@@ -1488,8 +1488,7 @@ __device__ __forceinline__ int count_below(const float4 &x, const float4 &y, flo
 // keys per row 4 workgroups fitted a compute unit and the kernel waited on latency with one wavefront per SIMD; now 8
 // fit (8192 x 22016: 456 -> 379 us).  Rows of which 8 workgroups fit anyway do without the extra loads.
 // G > 0: the rows are kept in LDS as a whole, keys and running sums ahead of every G of them: no trip to memory inside the iterations, no
-// chunk sums, and only G keys to add up at a boundary (none with G = 1: a cluster is the difference of two running sums).  For matrices
-// of which the LDS holds enough rows at a time: see launch_cluster.
+// chunk sums, and only G keys to add up at a boundary.  For matrices of which the LDS holds enough rows at a time: see resident_plan.
 template <bool RAGGED, bool WIDE, int G>
 __global__ void __launch_bounds__(G > 0 ? RESIDENT_THREADS : ITER_THREADS) __attribute__((amdgpu_waves_per_eu(G > 0 ? 4 : WIDE ? 2 : 3, G > 0 ? 4 : WIDE ? 2 : 3)))
 lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
@@ -2863,6 +2862,24 @@ size_t lloyd_lds_bytes(const LevelMap &lm) {
     return tables > errors ? tables : errors;
 }
 
+// Rows kept in LDS, in pieces of G = 4 keys or else of 8 (less LDS), where all workgroups of the iteration kernel are resident at once, or at most
+// twice as many as are and these at least 4 a compute unit, or 8 a compute unit are; otherwise G = 0.  Iterations and errors of a table in us,
+// kept in LDS / over global memory: 512 x 512 38 / 61, 1021 x 2999 54 / 83, 4096 x 512 51 / 86, 11008 x 512 110 / 152, 4096 x 1024 84 / 101.
+// Beyond: 2048 x 2048 (2 of 4 resident) 84 / 78, 11008 x 1024 (6 of 22) 179 / 179, 4096 x 2048 (3 of 8) 144 / 112.
+struct ResidentPlan {
+    int G;
+    LevelMap lm;
+};
+ResidentPlan resident_plan(const skim_ctx *ctx, int64_t n, int m) {
+    const long long each = ((n + 1) / 2 + ctx->num_cu - 1) / ctx->num_cu;
+    for (int g = 4; g <= 8; g *= 2) {
+        const LevelMap t = level_map_resident(m, g);
+        const long long fit = min((long long)ctx->lds_limit / (long long)(lloyd_lds_bytes(t) + 256), 8ll);
+        if (t.np <= RESIDENT_MAX_PIECES && (each <= fit || (fit >= 4 && each <= 2 * fit) || fit >= 8)) return {g, t};
+    }
+    return {0, LevelMap{}};
+}
+
 // Scratch layout of one call (inside the caller's workspace).
 skim_status carve_cluster_ws(skim_ctx *ctx, ClusterParams &prm, int64_t n, double **cent_scratch) {
     prm.nseg = 1;
@@ -2980,6 +2997,7 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     // 2000 x 3001: 61 / 58; many, 11008 x 4096: 235 / 251; 1024 threads, 4096 x 11008: 221 / 224).
     const bool claims = prm.bk_bpt > 0 && (threads > 512 || (threads > 256 && prm.nwork > 4 * sort_grid));
     prm.work_counters = claims ? ctx->sort_counters : nullptr;
+    const ResidentPlan resident = resident_plan(ctx, n, prm.m);
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
     hipLaunchKernelGGL(variants[variant], dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
     if (prm.nseg > 1) {
@@ -2998,32 +3016,18 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     {
         const long long wgs = (n + 1) / 2;
         const dim3 grid((unsigned)wgs), block(ITER_THREADS);
-        // Rows kept in LDS, in pieces of 4 keys or else of 8 (less LDS), where all workgroups are resident at once, or at most twice as many as
-        // are and these at least 4 a compute unit, or 8 a compute unit are.  Iterations and errors of a table in us, kept in LDS / over
-        // global memory: 512 x 512 38 / 61, 1021 x 2999 54 / 83, 4096 x 512 51 / 86, 11008 x 512 110 / 152, 4096 x 1024 84 / 101.  Beyond:
-        // 2048 x 2048 (2 of 4 resident) 84 / 78, 11008 x 1024 (6 of 22) 179 / 179, 4096 x 2048 (3 of 8) 144 / 112.
-        int G = 0;
-        LevelMap lm{};
-        for (int g = 4; g <= 8 && G == 0; g *= 2) {
-            const LevelMap t = level_map_resident(prm.m, g);
-            const long long fit = min((long long)ctx->lds_limit / (long long)(lloyd_lds_bytes(t) + 256), 8ll);
-            const long long each = (wgs + ctx->num_cu - 1) / ctx->num_cu;
-            if (t.np <= RESIDENT_MAX_PIECES && (each <= fit || (fit >= 4 && each <= 2 * fit) || fit >= 8)) {
-                G = g;
-                lm = t;
-            }
-        }
-        if (G > 0) {
-            const size_t llds = lloyd_lds_bytes(lm);
+        if (resident.G > 0) {
+            const size_t llds = lloyd_lds_bytes(resident.lm);
+            const int G = resident.G;
             const void *kern = G == 4 ? (const void *)lloyd_iter_kernel<false, false, 4> : (const void *)lloyd_iter_kernel<false, false, 8>;
             if (llds > 65536 && llds > ctx->lloyd_lds_enabled[G / 8]) {
                 SKIM_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)llds));
                 ctx->lloyd_lds_enabled[G / 8] = llds;
             }
-            if (G == 4) hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 4>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, lm);
-            else hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 8>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, lm);
+            if (G == 4) hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 4>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, resident.lm);
+            else hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 8>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, resident.lm);
         } else {
-            lm = level_map((prm.m + 15) >> 4, false);
+            LevelMap lm = level_map((prm.m + 15) >> 4, false);
             // Running sums at every 4 chunks as long as they leave the LDS room for 8 workgroups a compute unit (two wavefronts
             // per SIMD; registers allow three).
             const bool wide = 8 * (lloyd_lds_bytes(lm) + 256) > (size_t)ctx->lds_limit;
@@ -3051,6 +3055,8 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
 }
 
 }  // namespace
+
+extern "C" int skim_cluster_pieces(const skim_ctx *ctx, int64_t n, int64_t m) { return resident_plan(ctx, n, (int)m).G; }
 
 extern "C" skim_status skim_error_table(skim_ctx *ctx, const float *W, const float *S, const float *alpha,
                                         int64_t n, int64_t m, int64_t ld, int bmin, int bmax, int iters,

@@ -70,6 +70,10 @@ static inline int skim_block_offset(int bmin, int b) {  // start of block b insi
 // Looks up this device's address of the static scratch of skim_pack_static (the device must be current).
 skim_status skim_pack_static_setup(skim_ctx *ctx);
 
+// How the iterations of skim_error_table and skim_cluster_rows take a matrix of n rows of m columns: keys per piece (4 or 8) of rows that
+// are kept in LDS, 0 for rows in global memory.  The labels are the same either way, centroids and errors to the last digits.  For tests.
+extern "C" int skim_cluster_pieces(const skim_ctx *ctx, int64_t n, int64_t m);
+
 // Labels that are worked out from the clusters' upper bounds instead of read: 2^bits bounds per row at upper + i *
 // upper_stride (bits = 0: labels are read), with the clusters' centroids at centroids + i * centroid_stride; labels_out (may be
 // NULL) receives them.

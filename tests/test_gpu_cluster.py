@@ -8,6 +8,8 @@ those entries are excused from the exact comparison, and they are still checked
 for self-consistency through the oracle's functions (tests/parity_util.py).
 On config 0 the count must be zero.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -718,8 +720,9 @@ def test_random_shapes_and_flavours(ctx, seed):
 
 # (the last piece of 4 or 8 keys partly filled; 251, 256, 513 and 750 pieces: the search tree with and without a fourth level; two rows a
 # workgroup, the last one alone; rows in pieces of 4 and of 8 keys)
-@pytest.mark.parametrize("m,n,tiled", [(1003, 41, 6600), (1024, 40, 6600), (2050, 41, 1700), (3000, 900, 1100), (4100, 37, 600)])
-def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n, tiled):
+@pytest.mark.parametrize("m,n,tiled,piece", [(1003, 41, 6600, 4), (1024, 40, 6600, 4), (2050, 41, 1700, 4), (3000, 900, 1100, 8),
+                                             (4100, 37, 600, 4)])
+def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n, tiled, piece):
     """A small matrix has its rows in LDS while they iterate, a larger one does not: the same rows in either.  Bounds
     (assignments) are equal; sums are taken in another order: centroids within 1e-13 of the row's largest weight times the number
     of iterations, errors within 1e-13 of the row's second moment."""
@@ -740,6 +743,7 @@ def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n
     S[9] = np.float32(10.0) ** rng.integers(-18, 6, m)
     Wd, Sd = dev(W), dev(S)
     reps = -(-tiled // n)
+    assert [ctx.lib.skim_cluster_pieces(ctx.h, ctypes.c_int64(k), ctypes.c_int64(m)) for k in (n, reps * n)] == [piece, 0]
     Wt, St = Wd.repeat(reps, 1), Sd.repeat(reps, 1)
     bits = torch.from_numpy(rng.integers(1, 5, n).astype(np.uint8)).cuda()
     few, many = ctx.error_table(Wd, Sd), ctx.error_table(Wt, St)
@@ -758,7 +762,8 @@ def test_rows_kept_in_lds_agree_with_the_iterations_over_global_memory(ctx, m, n
 @pytest.mark.parametrize("n,m", [(2100, 4096), (2100, 4095), (700, 8200), (5000, 520), (600, 12287), (3, 4000)])
 def test_rows_shared_out_by_claims_or_in_fixed_shares(ctx, n, m):
     """Many and few rows a workgroup, 16-byte and 4-byte loads with 8, 12 and 16 slots: every call after the first
-    finds the counter of the units as the first did, and a row's result does not depend on the others."""
+    finds the counter of the units as the first did, and a row's thresholds do not depend on the others.  Its centroids and errors do in
+    their last digits, where the number of rows decides how the iterations add up (bounds as in the test above)."""
     W, S = skim_synth.make_ws_small(n, min(n, 300), m)
     reps = -(-n // len(W))
     Wd, Sd = dev(W).repeat(reps, 1)[:n].contiguous(), dev(S).repeat(reps, 1)[:n].contiguous()
@@ -770,6 +775,10 @@ def test_rows_shared_out_by_claims_or_in_fixed_shares(ctx, n, m):
     k = min(n, 64)
     assert torch.equal(first["upper_all"][:k], alone["upper_all"][:k])
     assert torch.equal(first["upper_all"], first["upper_all"][:300].repeat(reps, 1)[:n])
+    w, s = Wd[:k].double(), Sd[:k].double()
+    scale, moment = w.abs().amax(1, keepdim=True), (s * w * w).sum(1, keepdim=True)
+    assert bool(((first["centroids_all"][:k] - alone["centroids_all"][:k]).abs() <= 3e-12 * scale).all())
+    assert bool(((first["E"][:k] - alone["E"][:k]).abs() <= 1e-13 * moment).all())
 
 
 # (pieces of 4 keys with three and four levels of the search tree, pieces of 8; even and odd rows of a workgroup)
