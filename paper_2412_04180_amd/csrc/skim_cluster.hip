@@ -68,6 +68,7 @@ struct ClusterParams {
     int *segmass;         // per segment of a long row: nonzero when it holds sensitivity mass
     long long nwork;      // rows x segments: the units of work sort_kernel's workgroups share out
     int *work_counters;   // units handed out beyond every workgroup's first two (zero at launch); null: fixed shares
+    bool chunk_sums;      // the chunks' first weights and sums of s and s*w are wanted (not by iterations that keep the rows in LDS)
     int *vflag;           // validation result (one word of scratch)
     // bucket path of sort_kernel: value bins per thread (0: always the bitonic network) and the byte
     // offsets of its tables inside the dynamic LDS
@@ -1145,13 +1146,15 @@ __global__ void __launch_bounds__(1024) sort_kernel(ClusterParams prm) {
             for (int e = 0; e < EPT; ++e) add_key((tid * EPT + e < m) ? mine[e] : NEUTRAL_KEY, e);
         }
         if (mine_ok) {
-            prm.L1[row * prm.n1 + tid] = make_double2(c, q);
             prm.R1[row * prm.n1 + tid] = r2;
-            prm.w16[row * prm.n1 + tid] = w0;
+            if (prm.chunk_sums) {
+                prm.L1[row * prm.n1 + tid] = make_double2(c, q);
+                prm.w16[row * prm.n1 + tid] = w0;
+            }
         }
         const double c4 = quad_sum(c), q4 = quad_sum(q), r4 = quad_sum(r2);   // threads past the row add zeros
         if (mine_ok && (tid & 3) == 0) {
-            prm.Q[row * prm.nq + (tid >> 2)] = make_double2(c4, q4);
+            if (prm.chunk_sums) prm.Q[row * prm.nq + (tid >> 2)] = make_double2(c4, q4);
             prm.RQ[row * prm.nq + (tid >> 2)] = r4;
         }
     }
@@ -2998,6 +3001,7 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     const bool claims = prm.bk_bpt > 0 && (threads > 512 || (threads > 256 && prm.nwork > 4 * sort_grid));
     prm.work_counters = claims ? ctx->sort_counters : nullptr;
     const ResidentPlan resident = resident_plan(ctx, n, prm.m);
+    prm.chunk_sums = resident.G == 0;
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
     hipLaunchKernelGGL(variants[variant], dim3((unsigned)sort_grid), dim3(threads), lds, ctx->stream, prm);
     if (prm.nseg > 1) {
