@@ -1960,6 +1960,31 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         const bool anyhard = __ballot(hard) != 0;
         if (!finite) u = 0.0f;       // (the searches below rely on it)
 
+        // Between centroids an ulp apart the exact question has no single answer along the sorted keys: to a key far away both are equally far, and
+        // the lower cluster index wins on either side.  Such a boundary is looked for between the nearest ones that are not hard, at
+        // the first key that says no, and hard ones are kept in order: every boundary stays between different values, and no key
+        // is counted twice.  (Three values, one of them the centroid of 13 clusters to within an ulp: a cluster got the keys of the one below it too.)
+        int least = 0, most = 0;
+        auto neighbours = [&](int x, int top) {      // x of the nearest searching lanes that are not hard (0, top where there is none)
+            least = searching && !hard ? x : 0;
+            most = searching && !hard ? x : top;
+#pragma unroll
+            for (int d = 1; d < 16; d <<= 1) {
+                const int b1 = __shfl_up(least, d, 64), a1 = __shfl_down(most, d, 64);
+                if (p >= d) least = max(least, b1);
+                if (p + d < K) most = min(most, a1);
+            }
+        };
+        auto in_order = [&](int x) -> int {
+            int y = searching ? x : 0;
+#pragma unroll
+            for (int d = 1; d < 16; d <<= 1) {
+                const int b1 = __shfl_up(y, d, 64);
+                if (p >= d) y = max(y, b1);
+            }
+            return searching ? y : x;
+        };
+
         // ---- chunk of the boundary: lo = number of chunks whose first key is nearer to the lower centroid (a prefix of
         // the chunks): three levels of a search tree, 8 first weights per node (one trip to the LDS each)
         int lo = 0;
@@ -1981,7 +2006,8 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             lo = 8 * b0 + node(w16q + 2 * b0);
         }
         if (__builtin_expect(anyhard, 0)) {
-            int l2 = 0, h2 = hard ? n1u : 0;
+            neighbours(lo, n1u);
+            int l2 = least, h2 = hard ? most : least;
             while (__ballot(l2 < h2) != 0) {
                 const int md = min((l2 + h2) >> 1, n1u - 1);
                 const bool nl = nearer_lo(w16[md]);
@@ -1990,6 +2016,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 }
             }
             if (hard) lo = l2;
+            lo = in_order(lo);
         }
         int cl = searching ? lo - 1 : -1;          // chunk that holds the boundary (-1: boundary at rank 0)
         // what the cluster below sees of this position: its chunk, boundary and the sums of the
@@ -2122,18 +2149,22 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 #pragma unroll
             for (int j = CH - 1; j >= 0; --j) lowbits = shift_sign_in(lowbits, __fsub_rn(elem_w(el[j]), u));
         }
-        int tc = __builtin_popcount(lowbits);
-        if (__builtin_expect(anyhard, 0)) {
-            int te = 0;
-#pragma unroll
-            for (int j = 0; j < CH; ++j) te += (j < nvalid && nearer_lo(elem_w(el[j]))) ? 1 : 0;
-            if (hard) {
-                tc = te;
-                lowbits = (1u << te) - 1u;
-            }
-        }
-        if (cl < 0) tc = 0;
+        const int tc = __builtin_popcount(lowbits);
         Bcur = (searching && cl >= 0) ? rbase + tc : 0;  // p == 0 or no chunk below the boundary: 0
+        if (__builtin_expect(anyhard, 0)) {
+            neighbours(Bcur, m);
+            int te = min(max(least - rbase, 0), CH);
+            const int from = te;
+            bool open = true;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                open = open && (j < from || (j < nvalid && nearer_lo(elem_w(el[j]))));
+                te += j >= from && open ? 1 : 0;
+            }
+            if (hard && cl >= 0) Bcur = min(rbase + te, most);
+            Bcur = in_order(Bcur);
+            if (hard && cl >= 0) lowbits = (1u << (Bcur - rbase)) - 1u;
+        }
         if (__builtin_expect(anydup, 0)) {
             // a position sharing its value with the one before it owns nothing:
             // its range starts where the next distinct value's range starts

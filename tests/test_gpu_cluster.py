@@ -811,3 +811,31 @@ def test_clusters_of_tiny_mass_beside_a_heavy_element(ctx, n, m, tiled):
     check_rows(ctx, W, S, rng.integers(1, 5, n).astype(np.uint8))
     reps = -(-tiled // n)
     check_table(ctx, np.tile(W, (reps, 1)), np.tile(S, (reps, 1)))
+
+
+# (rows in LDS in pieces of 4 and of 8 keys, over global memory with running sums of 4 and of 16 chunks: with four wavefronts for the errors, the
+# last of them without keys; one wavefront; an odd number of rows; widths that are flagged and widths that are not)
+@pytest.mark.parametrize("n,m", [(5, 520), (41, 2050), (900, 3000), (3, 9001), (5, 20000), (2601, 4700), (1601, 17000)])
+def test_errors_of_rows_of_few_values(ctx, n, m):
+    """Rows of 3 or 12 distinct values, whose errors drown in the cancellation of the second moments at some widths or all: every entry is the sum of
+    s (w - c)^2 over the row with the centroids and thresholds of the same call, to 1e-12."""
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    values = torch.randn((n, 12), device="cuda", generator=gen)
+    values[::2, 3:] = values[::2, :1]
+    W = values.gather(1, torch.randint(0, 12, (n, m), device="cuda", generator=gen))
+    W[1] += torch.randn(m, device="cuda", generator=gen)           # one ordinary row
+    S = torch.randn((n, m), device="cuda", generator=gen).square()
+    out = ctx.error_table(W, S)
+    w, s = W.double(), S.double()
+    for b in range(1, 5):
+        sl = slice((1 << b) - 2, (2 << b) - 2)
+        best = torch.full_like(W, float("inf"))
+        c = torch.zeros_like(w)
+        for up, ck in zip(out["upper_all"][:, sl].T, out["centroids_all"][:, sl].T):
+            closer = (up[:, None] >= W) & (up[:, None] < best)
+            best = torch.where(closer, up[:, None], best)
+            c = torch.where(closer, ck[:, None], c)
+        ref = (s * (w - c) ** 2).sum(1)
+        # (the second moments serve from 1e-9 of them up and are good to 1e-16 of themselves, a few times over)
+        ok = (out["E"][:, b - 1] - ref).abs() <= torch.where(ref >= 0.99e-9 * (s * w * w).sum(1), 1e-6 * ref, 1e-12 * ref)
+        assert bool(ok.all()), f"b={b}: rows {torch.nonzero(~ok).flatten()[:5].tolist()}"
