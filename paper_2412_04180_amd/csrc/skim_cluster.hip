@@ -1441,7 +1441,6 @@ __device__ __forceinline__ double2 dd_wave_scan_incl(double2 x) {
 }
 
 constexpr int ITER_THREADS = 64;   // one wavefront serves two rows
-constexpr int RESIDENT_THREADS = 128;      // ... of which each has a wavefront while rows kept in LDS are laid out
 constexpr int MAX_LEVELS = 8;
 
 // One lane per cluster.  A row takes 30 lanes of a half wavefront: bit width 1 on lanes 0-1, 2 on
@@ -1485,6 +1484,68 @@ __device__ __forceinline__ int count_below(const float4 &x, const float4 &y, flo
     return __builtin_popcount(a) + __builtin_popcount(b);
 }
 
+// Errors evaluated key by key: s (w - c)^2 over the sorted rows of a workgroup, all flagged widths of a row in one pass; a wavefront takes every
+// `waves`-th stretch of 512 keys.  (Rows of few distinct values, as a dequantised matrix has, need it in all widths.)  A stretch nearly always lies
+// inside one cluster and asks nothing per key.  Whole table of such rows in us, one wavefront that asks at every 64 keys / this / a kernel with a
+// workgroup per row: 16 x 32768 285 / 121 / 126, 256 x 11008 152 / 90 / 94, 4096 x 11008 798 / 767 / 801, 1021 x 2999 108 / 93 / 113.
+// (Kept small: with this unrolled over 64-key steps the iterations ahead of it were 1 % slower.)
+constexpr int EVAL_WAVES = 4;
+struct EvalScratch {
+    double cpos[64];                          // centroids and first ranks by lane
+    int bpos[64];
+    double part[2][EVAL_WAVES][4];            // a wavefront's sums by row and width
+    u64 todo;                                 // the lanes of position 0 whose widths are flagged: 0, 2, 6 and 14 of the row's half
+};
+__device__ __forceinline__ void evaluate_errors(const ClusterParams &prm, EvalScratch &ev, u64 todo, int wave, int waves, int lane) {
+    const int m = prm.m;
+    for (int hh = 0; hh < 2; ++hh) {
+        const uint32_t flags = (uint32_t)(todo >> (32 * hh));
+        if (flags == 0u) continue;
+        const u64 *__restrict__ kr = prm.keys + (2ll * blockIdx.x + hh) * (long long)m;
+        // per width, the same in every lane: the cluster that the last stretch ended in, its centroid, the rank where the next one starts
+        double e[4] = {0.0, 0.0, 0.0, 0.0}, c[4];
+        int at[4], nxt[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            at[w] = 32 * hh + (2 << w) - 2;
+            c[w] = ev.cpos[at[w]];
+            nxt[w] = __builtin_amdgcn_readfirstlane(ev.bpos[at[w] + 1]);
+        }
+        constexpr int EU = 8;       // loads in flight
+        for (int base0 = wave * EU * 64; base0 < m; base0 += waves * EU * 64) {
+            u64 ke[EU];
+#pragma unroll
+            for (int q = 0; q < EU; ++q) ke[q] = base0 + 64 * q + lane < m ? kr[base0 + 64 * q + lane] : NEUTRAL_KEY;      // (past the row: no mass)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (!((flags >> ((2 << w) - 2)) & 1u)) continue;
+                const int last = 32 * hh + (4 << w) - 3;
+                double cc[EU];
+#pragma unroll
+                for (int q = 0; q < EU; ++q) cc[q] = c[w];
+                while (nxt[w] < base0 + EU * 64 && at[w] < last) {       // (nearly always the stretch lies inside one cluster)
+                    ++at[w];
+                    c[w] = ev.cpos[at[w]];
+#pragma unroll
+                    for (int q = 0; q < EU; ++q) cc[q] = base0 + 64 * q + lane >= nxt[w] ? c[w] : cc[q];
+                    nxt[w] = at[w] < last ? __builtin_amdgcn_readfirstlane(ev.bpos[at[w] + 1]) : 0x7fffffff;
+                }
+#pragma unroll
+                for (int q = 0; q < EU; ++q) {
+                    const double d = (double)elem_w(ke[q]) - cc[q];
+                    e[w] = fma((double)plain_s(ke[q]) * d, d, e[w]);
+                }
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) e[w] += __shfl_xor(e[w], o, 64);
+            if (lane == 0) ev.part[hh][wave][w] = e[w];
+        }
+    }
+}
+
 // RAGGED: the row length is not a multiple of 16, so the last chunk holds fewer than 16 keys.
 // WIDE: the running sums are kept ahead of every 16 chunks instead of every 4, and a range takes up to 3 + 3 sums of
 // 4 chunks more from global memory, requested with the chunk sums.  The LDS of a long row is mostly running sums: at 22016
@@ -1492,14 +1553,16 @@ __device__ __forceinline__ int count_below(const float4 &x, const float4 &y, flo
 // fit (8192 x 22016: 456 -> 379 us).  Rows of which 8 workgroups fit anyway do without the extra loads.
 // G > 0: the rows are kept in LDS as a whole, keys and running sums ahead of every G of them: no trip to memory inside the iterations, no
 // chunk sums, and only G keys to add up at a boundary.  For matrices of which the LDS holds enough rows at a time: see resident_plan.
-template <bool RAGGED, bool WIDE, int G>
-__global__ void __launch_bounds__(G > 0 ? RESIDENT_THREADS : ITER_THREADS) __attribute__((amdgpu_waves_per_eu(G > 0 ? 4 : WIDE ? 2 : 3, G > 0 ? 4 : WIDE ? 2 : 3)))
+// WAVES: wavefronts of a workgroup.  One serves its two rows (two lay out rows that are kept in LDS); four where they have room, for errors
+// that have to be evaluated.
+template <bool RAGGED, bool WIDE, int G, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(G > 0 ? 4 : WIDE ? 2 : 3, G > 0 ? 4 : WIDE ? 2 : 3)))
 lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int m = prm.m;
     constexpr int CH = G > 0 ? G : 16;      // keys of a piece
     const int n1u = (m + CH - 1) / CH;      // LM = level_map(n1u, WIDE) or level_map_resident(m, G), worked out by the host
-    const int lane = threadIdx.x & 63, mine = G > 0 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int lane = threadIdx.x & 63, mine = WAVES > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;      // wavefront
     const int h = lane >> 5, l5 = lane & 31;
 
     // ---- prologue: both rows' first weights, running sums and second-moment levels into LDS -------
@@ -1515,7 +1578,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     double rq4[2][4];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-        if (G > 0 && hh != mine) continue;
+        if (WAVES > 1 && mine != (G > 0 ? hh : 0)) continue;
         const long long rr = 2ll * blockIdx.x + (hh < nhalf ? hh : 0);
         const double *grq = prm.RQ + rr * prm.nq;
         if constexpr (G == 0) {
@@ -1544,7 +1607,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
         if (hh >= nhalf) break;
-        if (G > 0 && hh != mine) continue;
+        if (WAVES > 1 && mine != (G > 0 ? hh : 0)) continue;
         const long long rr = 2ll * blockIdx.x + hh;
         unsigned char *blkw = smem + (size_t)hh * LM.bytes;
         if constexpr (G == 0) {
@@ -1705,7 +1768,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
     for (int lv = 3; lv < MAX_LEVELS; ++lv) {
         if (lv < LM.nlev) {
             for (int hh = 0; hh < nhalf; ++hh) {
-                if (G > 0 && hh != mine) continue;
+                if (WAVES > 1 && mine != (G > 0 ? hh : 0)) continue;
                 unsigned char *blkw = smem + (size_t)hh * LM.bytes;
                 const double *rsrc = (const double *)(blkw + LM.roff[lv - 1]);
                 double *rdst = (double *)(blkw + LM.roff[lv]);
@@ -1721,7 +1784,19 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         }
     }
 
-    if (G > 0 && mine > 0) return;       // one wavefront for the rest: no barrier follows
+    if (mine > 0) {          // one wavefront for the rest, but for errors to evaluate
+        if constexpr (WAVES == EVAL_WAVES) {
+            if (prm.bits) return;
+            EvalScratch &ev = *(EvalScratch *)((double *)smem + 128);
+            __syncthreads();
+            const u64 todo = ev.todo;
+            if (todo != 0) {
+                evaluate_errors(prm, ev, todo, mine, WAVES, lane);
+                __syncthreads();
+            }
+        }
+        return;
+    }
 
     // ---- lane -> (row, bit width, position) ------------------------------------------------------
     const long long row = 2ll * blockIdx.x + h;
@@ -2035,6 +2110,30 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         int a0 = summing ? cl + 1 : 0, b0 = summing ? cl_next : 0;
         b0 = max(b0, a0);
 
+        auto add_thin_ranges = [&]() {
+            const bool thin = ((thin_rows >> lane) & 1) && b0 > a0 && midD < THIN_SHARE * ppd[LM.np].x;
+            double d = 0.0, nn = 0.0;
+            if constexpr (G > 0) {
+#pragma unroll 1
+                for (int j = thin ? a0 * CH : m; j < min(b0 * CH, m); ++j) {
+                    const u64 e = lkeys[j];
+                    d += (double)plain_s(e);
+                    nn = fma((double)plain_s(e), (double)elem_w(e), nn);
+                }
+            } else {
+#pragma unroll 1
+                for (int c = thin ? a0 : b0; c < b0; ++c) {
+                    const double2 x = L1[c];
+                    d += x.x;
+                    nn += x.y;
+                }
+            }
+            if (thin) {
+                midD = d;
+                midN = nn;
+            }
+        };
+
         // ---- one round of global loads: the boundary chunk's keys and the level-0 pieces ----------
         // (lanes without a boundary chunk read the row's first chunk and ignore it)
         const int rbase = cl * CH;
@@ -2046,19 +2145,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
             const double2 da = ppd[a0], db = ppd[b0], na = ppn[a0], nb = ppn[b0];
             midD = dd_diff(db, da);
             midN = dd_diff(nb, na);
-            if (__builtin_expect(thin_rows != 0, 0)) {
-                const bool thin = ((thin_rows >> lane) & 1) && b0 > a0 && midD < THIN_SHARE * ppd[b0].x;
-                double d = 0.0, nn = 0.0;
-                for (int j = thin ? a0 * CH : m; j < min(b0 * CH, m); ++j) {
-                    const u64 e = lkeys[j];
-                    d += (double)plain_s(e);
-                    nn = fma((double)plain_s(e), (double)elem_w(e), nn);
-                }
-                if (thin) {
-                    midD = d;
-                    midN = nn;
-                }
-            }
+            if (__builtin_expect(thin_rows != 0, 0)) add_thin_ranges();
         } else {
             reload = cl_want != cl_held;
         }
@@ -2106,19 +2193,6 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
                 if (WIDE) {
                     sD += pq[k].x;
                     sN += pq[k].y;
-                }
-            }
-            if (__builtin_expect(thin_rows != 0, 0)) {
-                const bool thin = ((thin_rows >> lane) & 1) && resum && gb > ga && sD < THIN_SHARE * ppd[gb].x;
-                double d = 0.0, nn = 0.0;
-                for (int c = thin ? a0 : b0; c < b0; ++c) {
-                    const double2 x = L1[c];
-                    d += x.x;
-                    nn += x.y;
-                }
-                if (thin) {
-                    sD = d;
-                    sN = nn;
                 }
             }
             if (resum) {
@@ -2213,6 +2287,7 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         if (p == K - 1 || cl_next <= cl) { nD = 0.0; nN = 0.0; }
         D += nD;
         N += nN;
+        if (G == 0 && __builtin_expect(thin_rows != 0, 0)) add_thin_ranges();      // (here: next to the sums it replaces it costs the loads their place)
         D += midD;
         N += midN;
         if (summing) {
@@ -2324,61 +2399,29 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         // not a number) the error is evaluated key by key instead
         exact_b = !(err_b >= 1e-9 * rtot) || !(err_b > 0.0);
     }
-    // table mode: an error that drowned in cancellation is summed up key by key here, s (w - c)^2 over the sorted row by the whole
-    // wavefront (rows of few distinct values; iterations with all four widths of every row: 4096 x 4096 115 us, 4096 x 20000 294; with a kernel
-    // of its own for this 120 and 260).  That kernel, launched
-    // over all rows of every table, took 4 us to find nothing to do.
-    u64 todo = prm.bits ? 0ull : __ballot(exact_b);
-    if (__builtin_expect(todo != 0, 0)) {
-        double *cpos = escr + 128;               // centroids and first ranks by lane
-        int *bpos = (int *)(cpos + 64);
-        cpos[lane] = v;
-        bpos[lane] = Bold;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        for (int hh = 0; hh < 2; ++hh) {         // a row's widths in one pass
-            // (the lanes of position 0: 0, 2, 6 and 14 of the row's half)
-            const uint32_t flags = (uint32_t)(todo >> (32 * hh));
-            if (flags == 0u) continue;
-            const u64 *__restrict__ kr = prm.keys + (2ll * blockIdx.x + hh) * (long long)m;
-            // per width, the same in every lane: the cluster of the first rank of the current 64, the rank where it ends, its centroid
-            double e[4] = {0.0, 0.0, 0.0, 0.0}, c[4] = {0.0, 0.0, 0.0, 0.0};
-            int at[4], nxt[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int w = 0; w < 4; ++w) at[w] = 32 * hh + (2 << w) - 2;
-            constexpr int EU = 8;       // loads in flight
-            for (int base0 = 0; base0 < m; base0 += EU * 64) {
-                u64 ke[EU];
-#pragma unroll
-                for (int q = 0; q < EU; ++q) ke[q] = base0 + 64 * q + lane < m ? kr[base0 + 64 * q + lane] : NEUTRAL_KEY;      // (past the row: no mass)
-#pragma unroll
-                for (int q = 0; q < EU; ++q) {
-                    const int base = base0 + 64 * q;
-                    const double wd = (double)elem_w(ke[q]), sd = (double)plain_s(ke[q]);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        if (!((flags >> ((2 << w) - 2)) & 1u)) continue;
-                        const int last = 32 * hh + (4 << w) - 3;
-                        if (base >= nxt[w]) {
-                            while (at[w] < last && __builtin_amdgcn_readfirstlane(bpos[at[w] + 1]) <= base) ++at[w];
-                            nxt[w] = at[w] < last ? __builtin_amdgcn_readfirstlane(bpos[at[w] + 1]) : 0x7fffffff;
-                            c[w] = cpos[at[w]];
-                        }
-                        double cc = c[w];
-                        if (base + 64 > nxt[w]) {       // a boundary inside this stretch: looked up lane by lane
-                            int pp = at[w];
-                            while (pp < last && bpos[pp + 1] <= base + lane) ++pp;
-                            cc = cpos[pp];
-                        }
-                        const double d = wd - cc;
-                        e[w] += sd * d * d;
-                    }
-                }
-            }
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) e[w] += __shfl_xor(e[w], o, 64);
-                if (exact_b && lane == 32 * hh + (2 << w) - 2) err_b = e[w];
+    // table mode: an error that drowned in cancellation is summed up key by key here, by all wavefronts of the workgroup.  (A kernel of its own
+    // for this, launched over all rows of every table, took 4 us to find nothing to do.)
+    if (!prm.bits) {
+        const u64 todo = __ballot(exact_b);
+        constexpr int waves = WAVES == EVAL_WAVES ? WAVES : 1;
+        EvalScratch &ev = *(EvalScratch *)(escr + 128);
+        if (todo != 0) {
+            ev.cpos[lane] = v;
+            ev.bpos[lane] = Bold;
+        }
+        if (waves > 1) {
+            if (lane == 0) ev.todo = todo;
+            __syncthreads();
+        }
+        if (__builtin_expect(todo != 0, 0)) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            evaluate_errors(prm, ev, todo, 0, waves, lane);
+            if (waves > 1) __syncthreads();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (exact_b) {
+                const int wi = 31 - __builtin_clz((unsigned)l5 + 2) - 1;      // (positions 0 of the widths: lanes 0, 2, 6, 14 of the half)
+                err_b = ev.part[h][0][wi];
+                for (int q = 1; q < waves; ++q) err_b += ev.part[h][q][wi];
             }
         }
     }
@@ -2892,7 +2935,7 @@ skim_status validate_inputs(skim_ctx *ctx, const ClusterParams &prm, int64_t n) 
 size_t sort_lds_bytes(int P) { return (size_t)(P + P / 16) * 8; }
 
 size_t lloyd_lds_bytes(const LevelMap &lm) {
-    const size_t tables = 2 * (size_t)lm.bytes, errors = (128 + 64 + 32) * sizeof(double);     // what the end needs lies over the tables
+    const size_t tables = 2 * (size_t)lm.bytes, errors = 128 * sizeof(double) + sizeof(EvalScratch);     // what the end needs lies over the tables
     return tables > errors ? tables : errors;
 }
 
@@ -3050,17 +3093,26 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
     if (ctx->profiling) SKIM_HIP(ctx, hipEventRecord(ctx->ev[1], ctx->stream));
     {
         const long long wgs = (n + 1) / 2;
-        const dim3 grid((unsigned)wgs), block(ITER_THREADS);
+        const dim3 grid((unsigned)wgs);
+        // Four wavefronts for errors to evaluate, where one would be long at it (2048 keys) and there is room: all wavefronts are resident at
+        // once (`slots` a compute unit), so those that wait at the barrier take nothing from anybody.
+        auto helped = [&](int slots) { return !prm.bits && prm.m >= 2048 && EVAL_WAVES * ((wgs + ctx->num_cu - 1) / ctx->num_cu) <= slots; };
+        using four = std::integral_constant<int, EVAL_WAVES>;
         if (resident.G > 0) {
             const size_t llds = lloyd_lds_bytes(resident.lm);
-            const int G = resident.G;
-            const void *kern = G == 4 ? (const void *)lloyd_iter_kernel<false, false, 4> : (const void *)lloyd_iter_kernel<false, false, 8>;
-            if (llds > 65536 && llds > ctx->lloyd_lds_enabled[G / 8]) {
-                SKIM_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)llds));
-                ctx->lloyd_lds_enabled[G / 8] = llds;
-            }
-            if (G == 4) hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 4>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, resident.lm);
-            else hipLaunchKernelGGL((lloyd_iter_kernel<false, false, 8>), grid, dim3(RESIDENT_THREADS), llds, ctx->stream, prm, (long long)n, resident.lm);
+            auto launch = [&](auto g, auto waves) -> skim_status {
+                constexpr int G = decltype(g)::value, WAVES = decltype(waves)::value;
+                size_t &enabled = ctx->lloyd_lds_enabled[(G == 8) + 2 * (WAVES == EVAL_WAVES)];
+                if (llds > 65536 && llds > enabled) {
+                    SKIM_HIP(ctx, hipFuncSetAttribute((const void *)lloyd_iter_kernel<false, false, G, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)llds));
+                    enabled = llds;
+                }
+                hipLaunchKernelGGL((lloyd_iter_kernel<false, false, G, WAVES>), grid, dim3(64 * WAVES), llds, ctx->stream, prm, (long long)n, resident.lm);
+                return SKIM_OK;
+            };
+            auto pick = [&](auto g) { return helped(16) ? launch(g, four{}) : launch(g, std::integral_constant<int, 2>{}); };
+            const skim_status st = resident.G == 4 ? pick(std::integral_constant<int, 4>{}) : pick(std::integral_constant<int, 8>{});
+            if (st != SKIM_OK) return st;
         } else {
             LevelMap lm = level_map((prm.m + 15) >> 4, false);
             // Running sums at every 4 chunks as long as they leave the LDS room for 8 workgroups a compute unit (two wavefronts
@@ -3068,13 +3120,18 @@ skim_status launch_cluster(skim_ctx *ctx, ClusterParams &prm, int64_t n, bool so
             const bool wide = 8 * (lloyd_lds_bytes(lm) + 256) > (size_t)ctx->lds_limit;
             if (wide) lm = level_map((prm.m + 15) >> 4, true);
             const size_t llds = lloyd_lds_bytes(lm);
-            auto launch = [&](auto ragged, auto w) {
-                hipLaunchKernelGGL((lloyd_iter_kernel<decltype(ragged)::value, decltype(w)::value, 0>), grid, block,
+            auto launch = [&](auto ragged, auto w, auto waves) {
+                constexpr int WAVES = decltype(waves)::value;
+                hipLaunchKernelGGL((lloyd_iter_kernel<decltype(ragged)::value, decltype(w)::value, 0, WAVES>), grid, dim3(64 * WAVES),
                                    llds, ctx->stream, prm, (long long)n, lm);
             };
+            auto pick_waves = [&](auto ragged, auto w) {
+                if (helped(decltype(w)::value ? 8 : 12)) launch(ragged, w, four{});
+                else launch(ragged, w, std::integral_constant<int, 1>{});
+            };
             auto pick = [&](auto ragged) {
-                if (wide) launch(ragged, std::true_type{});
-                else launch(ragged, std::false_type{});
+                if (wide) pick_waves(ragged, std::true_type{});
+                else pick_waves(ragged, std::false_type{});
             };
             if (prm.m & 15) pick(std::true_type{});
             else pick(std::false_type{});
