@@ -47,15 +47,20 @@ __device__ __forceinline__ RowPlace place_row(const long long *gwo, long long m,
 // neighbouring columns at a time into one 16-byte store.  The columns ahead of the first 16-byte border of the segment (any m, any
 // address of Wq) and behind the last whole four go one by one.  ALIGNED: m is a multiple of 4, so the borders are the same in every row
 // and alpha stays in registers.
-// 4096 x 11008 with alpha, codes from memory: 37 us, 5.3 TB/s (67 with one workgroup per row; 49 with stores that stay in
-// the caches, which serve a reader that follows at once and everything else not: with a library product behind it 121, 126 and 110).
+// STREAM: stores that pass the caches by.  A matrix that the 256 MB of the last cache hold stays there for whoever reads it next, which costs a
+// call whose outputs are not read 12 us at 180 MB (each evicts an older one) and saves the reader more; a larger one would only
+// drive itself out.  us with alpha, codes of four layers in turn, alone / with torch.mv behind it, streamed and not: 4096 x 4096 18 / 43 and
+// 18 / 36, 4096 x 11008 40 / 96 and 37 / 78 (every output in memory of its own: 37 and 48), 5120 x 11008 49 / 131 and 57 / 106, 5632 x 11008
+// 53 / 140 and 63 / 132, 6144 x 11008 58 / 149 and 69 / 155, 8192 x 22016 164 / 376 and 188 / 414.  One workgroup per row, 4096 x 11008: 43 / 78, in
+// memory of its own 68.
+constexpr int64_t UNPACK_CACHED_BYTES = 240ll << 20;
 constexpr uint32_t UNPACK_SEGMENT = 4096;
 constexpr int UNPACK_QUADS = UNPACK_SEGMENT / (4 * UNPACK_THREADS);       // of a thread, at most
 constexpr int UNPACK_WORDS = UNPACK_SEGMENT * 4 / 32 / UNPACK_THREADS;    // of a thread, at 4 bits
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-template <int B, bool ALPHA, bool ALIGNED>
+template <int B, bool ALPHA, bool ALIGNED, bool STREAM>
 __device__ __forceinline__ void unpack_segment(const uint32_t *words, const float *cbf, uint32_t cols, uint32_t head, bool alpha_vec,
                                                const float *__restrict__ alpha, const float4 (&al)[UNPACK_QUADS], float *__restrict__ out) {
     const uint32_t tid = threadIdx.x;
@@ -73,7 +78,8 @@ __device__ __forceinline__ void unpack_segment(const uint32_t *words, const floa
                 if (!ALIGNED) a = alpha_vec ? *(const float4 *)(alpha + j) : make_float4(alpha[j], alpha[j + 1], alpha[j + 2], alpha[j + 3]);
                 c = make_float4(__fmul_rn(a.x, c.x), __fmul_rn(a.y, c.y), __fmul_rn(a.z, c.z), __fmul_rn(a.w, c.w));
             }
-            __builtin_nontemporal_store(float4v{c.x, c.y, c.z, c.w}, (float4v *)(out + j));      // (the caches are left to the codes)
+            if (STREAM) __builtin_nontemporal_store(float4v{c.x, c.y, c.z, c.w}, (float4v *)(out + j));
+            else *(float4 *)(out + j) = c;
         }
     }
     // at most three columns at either end
@@ -87,7 +93,7 @@ __device__ __forceinline__ void unpack_segment(const uint32_t *words, const floa
     }
 }
 
-template <bool ALPHA, bool ALIGNED>
+template <bool ALPHA, bool ALIGNED, bool STREAM>
 __global__ void __launch_bounds__(UNPACK_THREADS) unpack_kernel(const uint32_t *__restrict__ codes, const long long *__restrict__ gwo,
                                                                const int *__restrict__ row_perm, const uint16_t *__restrict__ codebooks,
                                                                const float *__restrict__ alpha, long long n, long long m, uint32_t seglen,
@@ -147,10 +153,10 @@ __global__ void __launch_bounds__(UNPACK_THREADS) unpack_kernel(const uint32_t *
         fetch(p);
         const bool vec = ALPHA && !ALIGNED && (((uintptr_t)(alpha + head)) & 15) == 0;
         switch (b) {
-            case 1: unpack_segment<1, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
-            case 2: unpack_segment<2, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
-            case 3: unpack_segment<3, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
-            default: unpack_segment<4, ALPHA, ALIGNED>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            case 1: unpack_segment<1, ALPHA, ALIGNED, STREAM>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            case 2: unpack_segment<2, ALPHA, ALIGNED, STREAM>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            case 3: unpack_segment<3, ALPHA, ALIGNED, STREAM>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
+            default: unpack_segment<4, ALPHA, ALIGNED, STREAM>(words[buf], cbf[buf], cols, head, vec, alpha, al, out); break;
         }
     }
 }
@@ -163,13 +169,17 @@ void launch_unpack(skim_ctx *ctx, const uint32_t *codes, const int64_t *gwo, con
     nseg = (m + seglen - 1) / seglen;
     const int64_t resident = 6ll * ctx->num_cu, rounds = (n * nseg + resident - 1) / resident;
     const int64_t stride = (n + rounds - 1) / rounds;
-    auto launch = [&](auto al, auto aligned) {
-        hipLaunchKernelGGL((unpack_kernel<decltype(al)::value, decltype(aligned)::value>), dim3((unsigned)nseg, (unsigned)stride), dim3(UNPACK_THREADS), 0,
+    auto launch = [&](auto al, auto aligned, auto stream) {
+        hipLaunchKernelGGL((unpack_kernel<decltype(al)::value, decltype(aligned)::value, decltype(stream)::value>), dim3((unsigned)nseg, (unsigned)stride), dim3(UNPACK_THREADS), 0,
                            ctx->stream, codes, (const long long *)gwo, row_perm, codebooks, alpha, (long long)n, (long long)m, (uint32_t)seglen, Wq);
     };
+    auto pick_stores = [&](auto al, auto aligned) {
+        if (n * m > UNPACK_CACHED_BYTES / (int64_t)sizeof(float)) launch(al, aligned, std::true_type{});
+        else launch(al, aligned, std::false_type{});
+    };
     auto pick = [&](auto al) {
-        if (m % 4 == 0) launch(al, std::true_type{});
-        else launch(al, std::false_type{});
+        if (m % 4 == 0) pick_stores(al, std::true_type{});
+        else pick_stores(al, std::false_type{});
     };
     if (alpha) pick(std::true_type{});
     else pick(std::false_type{});

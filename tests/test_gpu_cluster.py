@@ -458,7 +458,8 @@ def test_unpack_at_any_alignment(ctx, gpu_lib, m, offset):
         assert np.all(got[:offset] == 7.0) and np.all(got[offset + n * m:] == 7.0)
 
 
-@pytest.mark.parametrize("n,m", [(3200, 64), (1537, 1001), (900, 4097), (700, 8224), (2, 40000)])
+@pytest.mark.parametrize("n,m", [(3200, 64), (1537, 1001), (900, 4097), (700, 8224), (2, 40000),
+                                 (15376, 4096), (16000, 4001)])      # (stores that pass the caches by)
 def test_unpack_of_several_rows_and_segments_a_workgroup(ctx, n, m):
     """One to three rows a workgroup (the last round part-filled), one to ten segments of a row: bit-exact against the codes looked up one
     by one on the device."""
