@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(256) hmax_direct_kernel(const float *__restric
         hdiag[j0 + threadIdx.x] = H[(long long)(j0 + threadIdx.x) * (m + 1)];
     }
 }
-// Longer ones: H is read once, 64 rows x 256 columns a workgroup, into a cleared hmax.
+// Longer ones: H is read once, 64 rows x 256 columns a workgroup, into a cleared hmax (12288 columns 115 us, 604 MB).
 constexpr int HMAX_ROWS = 64, HMAX_COLS = 256;
 __global__ void __launch_bounds__(256) hmax_clear_kernel(const float *__restrict__ H, long long m, uint32_t *__restrict__ hmax, float *__restrict__ hdiag) {
     const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -193,24 +193,28 @@ __global__ void __launch_bounds__(256) hmax_kernel(const float *__restrict__ H, 
     __shared__ uint32_t cols[4][HMAX_COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long j0 = (long long)(blockIdx.x / tiles_x) * HMAX_ROWS + 16 * wave, k = (long long)(blockIdx.x % tiles_x) * HMAX_COLS + 4 * lane;
-    float4 x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = (j0 + i < m && k < m) ? *(const float4 *)(H + (j0 + i) * m + k) : make_float4(0.f, 0.f, 0.f, 0.f);
     uint32_t c[4] = {0u, 0u, 0u, 0u};
     uint32_t mine = 0u;          // lane i < 16: the largest of row j0 + i
+#pragma unroll 1
+    for (int i0 = 0; i0 < 16; i0 += 8) {       // (eight rows at a time: 16 at once leave room for half as many wavefronts)
+        float4 x[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint32_t b[4] = {coupling_bits(x[i].x, k == j0 + i), coupling_bits(x[i].y, k + 1 == j0 + i), coupling_bits(x[i].z, k + 2 == j0 + i),
-                               coupling_bits(x[i].w, k + 3 == j0 + i)};
-        uint32_t r = 0u;
+        for (int i = 0; i < 8; ++i) x[i] = (j0 + i0 + i < m && k < m) ? *(const float4 *)(H + (j0 + i0 + i) * m + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int d = (int)min(max(j0 + i0 - k, -64ll), 64ll);      // column k + d is the diagonal of row j0 + i0
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c[q] = max(c[q], b[q]);
-            r = max(r, b[q]);
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t b[4] = {coupling_bits(x[i].x, d + i == 0), coupling_bits(x[i].y, d + i == 1), coupling_bits(x[i].z, d + i == 2),
+                                   coupling_bits(x[i].w, d + i == 3)};
+            uint32_t r = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                c[q] = max(c[q], b[q]);
+                r = max(r, b[q]);
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) r = max(r, (uint32_t)__shfl_xor((int)r, o, 64));
+            if (lane == i0 + i) mine = r;
         }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) r = max(r, (uint32_t)__shfl_xor((int)r, o, 64));
-        if (lane == i) mine = r;
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) cols[wave][4 * lane + q] = c[q];
@@ -750,6 +754,7 @@ struct LossLine {
 };
 constexpr int LOSS_MAX_WG = 256;
 constexpr int LOSS_MIN_STAGES = 4;      // a piece is this long, or a whole tile where that is shorter (256 x 256: 20 us, 31 with 16 stages)
+constexpr long long LOSS_SMALL = 40000;
 inline LossLine loss_line(int64_t n, int64_t m, int num_cu) {
     LossLine l;
     l.tj = (int)((m + TILE - 1) / TILE);
@@ -830,19 +835,51 @@ dwh_loss_kernel(const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Hp
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// row_loss[i] = the share of the diagonal and the pieces of the tiles of its row, in the order of the line; left in rows[i] for the total.
-__global__ void __launch_bounds__(256) loss_rows_kernel(const double *__restrict__ partial, const double *__restrict__ rdiag, LossLine line, long long n, double *rows,
-                                                        double *row_loss, long long row_stride) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int I = blockIdx.x;
+// row_loss[i] = the share of the diagonal and the pieces of the tiles of its row; left in rows[i] for the total.  Four threads a row take every
+// fourth piece each (one, 256 x 12288, 304 pieces a row: 27 us).
+__global__ void __launch_bounds__(4 * TILE) loss_rows_kernel(const double *__restrict__ partial, const double *__restrict__ rdiag, LossLine line, long long n, double *rows,
+                                                             double *row_loss, long long row_stride) {
+    __shared__ double share[3][TILE];
+    const int r = threadIdx.x % TILE, part = threadIdx.x / TILE, I = blockIdx.x;
+    const long long i = (long long)I * TILE + r;
     const long long first = (long long)I * line.per_row;
     const long long p0 = (long long)I * line.tj + line.owner(first), p1 = (long long)I * line.tj + line.tj - 1 + line.owner(first + line.per_row - 1);
-    double tot = rdiag[i];
+    double tot = part == 0 && i < n ? rdiag[i] : 0.0;
 #pragma unroll 8
-    for (long long p = p0; p <= p1; ++p) tot += partial[p * TILE + threadIdx.x];
+    for (long long p = p0 + part; p <= p1; p += 4) tot += partial[p * TILE + r];       // (there are numbers for whole tiles of rows)
+    if (part > 0) share[part - 1][r] = tot;
+    __syncthreads();
+    if (part > 0 || i >= n) return;
+    tot = ((tot + share[0][r]) + share[1][r]) + share[2][r];
     if (row_loss) row_loss[i * row_stride] = tot;
     rows[i] = tot;
+}
+
+// That and the total in one workgroup, for few and short rows: such a layer's call is mostly launches (4096 x 32 34 -> 32 us; 11008 rows
+// take it 9 us, the two kernels 4 + 4.5 and the gap between them).
+__global__ void __launch_bounds__(1024) loss_small_kernel(const double *__restrict__ partial, const double *__restrict__ rdiag, LossLine line, int n,
+                                                          double *row_loss, double *loss) {
+    __shared__ double sh[16];
+    double acc = 0.0;
+    const uint32_t per_row = (uint32_t)line.per_row, total = (uint32_t)line.total, G = (uint32_t)line.G, tj = (uint32_t)line.tj;
+#pragma unroll 2
+    for (int i = threadIdx.x; i < n; i += 1024) {
+        const uint32_t I = (uint32_t)i >> 8, first = I * per_row;
+        const uint32_t p0 = I * tj + ((first + 1) * G - 1) / total, p1 = I * tj + tj - 1 + ((first + per_row) * G - 1) / total;
+        double tot = rdiag[i];
+#pragma unroll 4
+        for (uint32_t p = p0; p <= p1; ++p) tot += partial[(size_t)p * TILE + (i & 255)];
+        if (row_loss) row_loss[i] = tot;
+        acc += tot;
+    }
+    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_down(acc, d, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < 16; ++w) s += sh[w];
+        *loss = s;
+    }
 }
 
 // loss = sum_i rows[i] (single workgroup, fixed order).
@@ -867,6 +904,8 @@ __global__ void __launch_bounds__(1024) loss_total_kernel(const double *rows, lo
 // their sums, alpha and the row's P and labels stay in registers, so a row is read from HBM once;
 // otherwise the sums live in gpart and the row is read twice.  gpart[strip][l] is reduced over the strips
 // afterwards.  The strip's share of the loss, sum P_ij dW_ij, falls out on the way.
+// Column groups that lie outside the row cost nothing, and alpha and the diagonal are requested together: 11008 x 32 62 -> 46 us; 4096 x 4096 58,
+// bound by the 13 bytes per weight; 256 x 12288 (not REG) 349 -> 294 with four columns in flight.
 constexpr int GRAD_NC = 16;
 
 template <bool REG, bool VEC>
@@ -891,13 +930,32 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
     auto colof = [&](int c) -> long long {
         return VEC ? 4ll * (tid + (long long)(c >> 2) * PREP_THREADS) + (c & 3) : tid + (long long)c * PREP_THREADS;
     };
+    auto any = [&](int c) { return (VEC ? 4 * PREP_THREADS * (c >> 2) : PREP_THREADS * c) < (int)m; };      // whether any thread has a column there
     if (REG) {
+        float hd[GRAD_NC];         // (all requested before the first is used)
+        if constexpr (VEC) {
+#pragma unroll
+            for (int q = 0; q < GRAD_NC / 4; ++q) {
+                const long long l = min(colof(4 * q), m - 4);
+                const float4 a4 = *(const float4 *)(alpha + l), h4 = *(const float4 *)(hdiag + l);
+                al[4 * q] = a4.x; al[4 * q + 1] = a4.y; al[4 * q + 2] = a4.z; al[4 * q + 3] = a4.w;
+                hd[4 * q] = h4.x; hd[4 * q + 1] = h4.y; hd[4 * q + 2] = h4.z; hd[4 * q + 3] = h4.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < GRAD_NC; ++c) {
+                const long long l = min(colof(c), m - 1);
+                al[c] = alpha[l];
+                hd[c] = hdiag[l];
+            }
+        }
 #pragma unroll
         for (int c = 0; c < GRAD_NC; ++c) {
-            const long long l = colof(c);
+            const bool in = colof(c) < m;
             gacc[c] = 0.0;
-            al[c] = l < m ? alpha[l] : 0.0f;
-            hds[c][tid] = l < m ? hdiag[l] : 0.0f;
+            al[c] = in ? al[c] : 0.0f;
+            asm("" : "+v"(al[c]));
+            hds[c][tid] = in ? hd[c] : 0.0f;
         }
     } else {
         for (long long l = tid; l < m; l += PREP_THREADS) gp[l] = 0.0;
@@ -957,12 +1015,14 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
             for (int c = 0; c < GRAD_NC; ++c) asm("" : "+v"(pv[c]), "+v"(wv[c]), "+v"(sv[c]));      // (not converted to doubles until used: registers)
 #pragma unroll
             for (int c = 0; c < GRAD_NC; ++c) {
+                if (!any(c)) continue;
                 const double dw = (double)wv[c] - (double)al[c] * csh[lv[c]];
                 pd[c] = fma(dw, (double)hds[c][tid], (double)pv[c]);
                 lacc = fma(pd[c], dw, lacc);        // (columns past the row: all zero)
                 if (colof(c) < m) atomicAdd(&myQ[lv[c]], pd[c] * (double)al[c]);
             }
         } else {
+#pragma unroll 4
             for (long long j = tid; j < m; j += PREP_THREADS) {
                 const int k = Lr[j] & 15;
                 const double a = (double)alpha[j], dw = (double)Wr[j] - a * csh[k], p = fma(dw, (double)hdiag[j], (double)Pr[j]);
@@ -979,11 +1039,13 @@ __global__ void __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_
         if (REG) {
 #pragma unroll
             for (int c = 0; c < GRAD_NC; ++c) {
+                if (!any(c)) continue;
                 const double a = (double)al[c], cc = csh[lv[c]];
                 const double term = pd[c] * cc + rsh[lv[c]] * (double)sv[c] * ((double)wv[c] - 2.0 * a * cc);
                 gacc[c] += -2.0 * term;
             }
         } else {
+#pragma unroll 4
             for (long long l = tid; l < m; l += PREP_THREADS) {
                 const int k = Lr[l] & 15;
                 const double a = (double)alpha[l], cc = csh[k];
@@ -1219,7 +1281,15 @@ skim_status skim_layer_loss_strided(skim_ctx *ctx, const float *W, const float *
     launch_row_prep(ctx, W, S, alpha, n, m, ld, labels, bounds, w, H, !h_ready, SPLIT_LOWER);
     hipLaunchKernelGGL(dwh_loss_kernel, dim3((unsigned)w.line.G), dim3(G_THREADS), G_LDS_BYTES, ctx->stream, w.dWp, w.Hp, (const int *)w.rexp,
                        (long long)n, (long long)m, w.line, w.partial);
-    hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(TILE), 0, ctx->stream, (const double *)w.partial,
+    // one launch for what takes hardly longer than that (numbers to add up: those of the tiles, and a row of tiles is cut into up to cuts + 1)
+    const long long cuts = (w.line.G * (long long)TILE + n - 1) / n + 1;
+    if (loss && row_stride == 1 && n * (w.line.tj + cuts) <= LOSS_SMALL && w.line.total * w.line.G <= 0x7fffffff) {
+        hipLaunchKernelGGL(loss_small_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double *)w.partial, (const double *)w.rdiag, w.line, (int)n, row_loss,
+                           loss);
+        SKIM_HIP(ctx, hipGetLastError());
+        return SKIM_OK;
+    }
+    hipLaunchKernelGGL(loss_rows_kernel, dim3((unsigned)((n + TILE - 1) / TILE)), dim3(4 * TILE), 0, ctx->stream, (const double *)w.partial,
                        (const double *)w.rdiag, w.line, (long long)n, w.rows, row_loss, (long long)row_stride);
     if (loss) hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(1024), 0, ctx->stream, (const double *)w.rows, (long long)n, loss);
     SKIM_HIP(ctx, hipGetLastError());

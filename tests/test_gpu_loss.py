@@ -565,3 +565,23 @@ def test_gradient_of_correlated_channels(ctx, m, bound):
         ref = -2 * (P * ck + R * S.double() * (W.double() - 2 * a * ck)).sum(0)
         total += float((g - ref).norm() / ref.norm()) ** 2
     assert (total / 6) ** 0.5 <= bound, f"{(total / 6) ** 0.5:.3e}"
+
+
+@pytest.mark.parametrize("n,m", [(1, 16), (255, 48), (1025, 64), (2049, 272), (5000, 32), (20100, 16), (300, 4112)])
+def test_total_of_the_row_losses(ctx, n, m):
+    """Row losses added up in one workgroup with their pieces, or in a kernel of their own with four threads a row: the total is the sum of the
+    rows' losses, which agree with float64 (5e-7 of the sum of the products' magnitudes, as above)."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((64, m), device="cuda", generator=gen)
+    H = (X.T.contiguous() @ X).contiguous()
+    H = ((H + H.T) / 2).contiguous()
+    W = torch.randn((n, m), device="cuda", generator=gen)
+    labels = torch.randint(0, 4, (n, m), device="cuda", generator=gen, dtype=torch.uint8)
+    out = ctx.layer_loss(W, torch.ones_like(W), H, labels)
+    L = labels.long()
+    D = torch.zeros(n, 16, device="cuda", dtype=torch.float64).scatter_add_(1, L, torch.ones_like(W).double())
+    dW = W.double() - (torch.zeros_like(D).scatter_add_(1, L, W.double()) / D.clamp_min(1.0)).gather(1, L)
+    ref, mag = ((dW @ H.double()) * dW).sum(1), ((dW.abs() @ H.double().abs()) * dW.abs()).sum(1)
+    assert bool(((out["row_loss"] - ref).abs() <= 5e-7 * mag).all())
+    total = float(out["row_loss"].sum())
+    assert abs(out["loss"].item() - total) <= 1e-13 * float(out["row_loss"].abs().sum())
