@@ -28,7 +28,7 @@ def resource_remarks(source):
 def test_sort_kernel_variants_for_rows_up_to_12288_keep_their_keys_in_registers():
     r = resource_remarks("skim_cluster.hip")
     found = 0
-    for variant in ("sort_kernelILi8ELb1E", "sort_kernelILi12ELb1E"):
+    for variant in ("sort_kernelILi8ELb1E", "sort_kernelILi12ELb1E", "sort_kernelILi8ELb0E", "sort_kernelILi12ELb0E"):
         m = re.search(r"Function Name: \S*" + variant + r".*?LDS Size", r.stdout, re.S)
         assert m, f"no resource remarks for {variant}"
         scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1))
@@ -36,7 +36,15 @@ def test_sort_kernel_variants_for_rows_up_to_12288_keep_their_keys_in_registers(
         assert scratch == 0, f"{variant} spills {scratch} bytes per lane into scratch memory"
         assert vgprs <= 128
         found += 1
-    assert found == 2
+    assert found == 4
+    # the iterations: at most three doubles a lane, parked around what only rare rows execute, and the wavefronts they are written for
+    found = list(re.finditer(r"Function Name: \S*lloyd_iter_kernelILb[01]ELb([01])ELi([048])ELi[124]E.*?LDS Size", r.stdout, re.S))
+    assert len(found) == 12
+    for m in found:
+        scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1))
+        occupancy = int(re.search(r"Occupancy \[waves/SIMD\]: (\d+)", m.group(0)).group(1))
+        assert scratch <= 24, m.group(0)[:120]
+        assert occupancy == (4 if m.group(2) != "0" else 2 if m.group(1) == "1" else 3)
 
 
 def scratch_inside_mfma_loops(source, kernel):
@@ -73,10 +81,15 @@ def test_hessian_kernel_for_wide_layers_does_not_spill():
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_contraction_kernels_do_not_spill_in_their_stage_loops():
-    """The same holds for the contraction with H.  dwh_loss_kernel parks 11 registers of its epilogue's addresses in scratch
-    memory ahead of the loop and reads them behind it, which is no harm."""
+    """The same holds for the contraction with H.  The kernels around it: the gradient kernel keeps a row in registers, the row kernel
+    is held to 64 of them where two of its workgroups share a compute unit (three for labels from bounds do not fit)."""
     r = resource_remarks("skim_loss.hip")
-    for kernel, limit in (("dwh_kernel", 0), ("dwh_loss_kernel", 64)):
+    for kernel, limit, count in (("grad_rows_kernel", 0, 3), ("row_prep_kernel", 12, 24), ("hmax_kernel", 0, 1)):
+        found = list(re.finditer(r"Function Name: \S*\d" + kernel + r".*?LDS Size", r.stdout, re.S))
+        assert len(found) == count, kernel
+        for m in found:
+            assert int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1)) <= limit, m.group(0)[:120]
+    for kernel, limit in (("dwh_kernel", 0), ("dwh_loss_kernel", 0)):
         m = re.search(r"Function Name: \S*\d" + kernel + r".*?LDS Size", r.stdout, re.S)
         assert m, f"no resource remarks for {kernel}"
         assert int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", m.group(0)).group(1)) <= limit
