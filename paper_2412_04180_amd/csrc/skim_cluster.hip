@@ -2227,15 +2227,11 @@ lloyd_iter_kernel(ClusterParams prm, long long nrows, LevelMap LM) {
         Bcur = (searching && cl >= 0) ? rbase + tc : 0;  // p == 0 or no chunk below the boundary: 0
         if (__builtin_expect(anyhard, 0)) {
             neighbours(Bcur, m);
-            int te = min(max(least - rbase, 0), CH);
-            const int from = te;
-            bool open = true;
+            uint32_t yes = 0u;
 #pragma unroll
-            for (int j = 0; j < CH; ++j) {
-                open = open && (j < from || (j < nvalid && nearer_lo(elem_w(el[j]))));
-                te += j >= from && open ? 1 : 0;
-            }
-            if (hard && cl >= 0) Bcur = min(rbase + te, most);
+            for (int j = 0; j < CH; ++j) yes |= (j < nvalid && nearer_lo(elem_w(el[j]))) ? 1u << j : 0u;
+            yes |= (1u << min(max(least - rbase, 0), CH)) - 1u;           // (ahead of the boundary before it: below it)
+            if (hard && cl >= 0) Bcur = min(rbase + __builtin_ctz(~yes), most);
             Bcur = in_order(Bcur);
             if (hard && cl >= 0) lowbits = (1u << (Bcur - rbase)) - 1u;
         }
