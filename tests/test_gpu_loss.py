@@ -2,7 +2,7 @@
 
 Bar: loss, per-row loss, gradient and updated alpha within 1e-5
 relative.  The contraction runs on the matrix cores with every float32
-operand scaled and cut into two binary16 pieces and float32 accumulation; the
+operand scaled and cut into two binary16 pieces and float32 accumulation, the diagonal of H in float64; the
 oracle is float64 throughout.  Parity is per call on identical inputs: the
 oracle is fed the same W, S, H, labels and alpha as the GPU.
 """
@@ -237,7 +237,7 @@ def test_hessian_plans_match_oracle(gpu_lib, N, m, workspace):
 
 
 @pytest.mark.parametrize("n,m,K", [
-    (3, 4112, 16), (9, 11280, 8),       # rows of 5 .. 11 steps kept in registers, longer ones read twice; row groups part empty
+    (3, 4112, 16), (9, 11280, 8),       # rows of 5 .. 11 steps kept in registers, longer ones read again; row groups part empty
     (7, 256, 16), (1030, 32, 8),        # one wavefront a row, H cut in the same launch; a workgroup of the loss for every tile
     (70, 2064, 4),                      # few tiles: every one split; a last stage of 16 columns past a multiple of 32
     (8200, 2080, 16)])                  # more tiles than workgroups: one round of whole tiles, then split ones
